@@ -112,7 +112,8 @@ void xmgn_ctx_destroy(xmgn_ctx* ctx);
  * (at most 64-row edge tiles), at H = 256 (32-row node tiles; 32-row edge
  * tiles unless, in the BF16 form, 64 are asked for, or 128 for the gathered
  * edge forward's wide kernel, 8 waves, whose edge adjoint then runs 64-row
- * tiles unless set otherwise) and at H = 512 (16-row node tiles; 32-row edge
+ * tiles unless set otherwise; the BF16 gathered edge forward at H = 128 has
+ * one configuration, whatever is asked) and at H = 512 (16-row node tiles; 32-row edge
  * tiles unless 64 are asked for the BF16 gathered forward's wide kernel,
  * whose adjoint stays on 32) whatever is asked.  Changing it invalidates
  * cached batch plans. */

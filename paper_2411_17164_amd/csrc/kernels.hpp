@@ -78,6 +78,10 @@ void launch_enc_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, cons
 void launch_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h,
                      const void* e, void* e_out, float* m, void* z_out, void* a_out, const float* pr,
                      const float* ps, hipStream_t st);
+// The BF16 gathered forward at H = 128 runs as wave-private chains.
+bool edge_fwd_chain(const Shape& s);
+void launch_edge_fwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
+                           void* e_out, float* m, void* z_out, void* a_out, hipStream_t st);
 // pr = W1_r h + b1, ps = W1_s h for every node (FP32 [n][H] each).
 void launch_node_proj(const Shape& s, const BatchView& b, const MlpW& w, const void* h, float* pr, float* ps,
                       hipStream_t st);

@@ -865,7 +865,7 @@ static void edge_fwd_nw(const Shape& s, const BatchView& b, const MlpW& w, const
       using I1 = std::integral_constant<int, 1>;
       if (pr) {
         if (s.agg) go(I1{}, I1{}); else go(I0{}, I1{});
-      } else {
+      } else if constexpr (sizeof(T) == 4 || H != 128) {  // (BF16 at H = 128 runs k_edge_fwd_chain)
         if (s.agg) go(I1{}, I0{}); else go(I0{}, I0{});
       }
     } else {
@@ -884,6 +884,12 @@ void launch_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
                      void* e_out, float* m, void* z_out, void* a_out, const float* pr, const float* ps,
                      hipStream_t st) {
   if (b.n_etiles == 0) return;
+  // the BF16 gathered form at H = 128, at every size: both its weights fit in
+  // LDS beside the waves' buffers (at H = 256 W1 alone is 384 KiB)
+  if (edge_fwd_chain(s) && !pr) {
+    launch_edge_fwd_chain(s, b, w, h, e, e_out, m, z_out, a_out, st);
+    return;
+  }
   if (edge_fwd_wide(s) && !pr) {  // the split form runs k_edge_fwd (128-row tiles never reach it)
     auto go = [&](auto hh, auto mt, auto act, auto agg) {
       constexpr int NWW = decltype(hh)::value == 256 && decltype(mt)::value == 64 ? 4 : 8;

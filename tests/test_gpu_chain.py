@@ -1,0 +1,77 @@
+"""The H = 128 BF16 edge kernels where their work split can go wrong: a wave
+takes whole receiver segments 16 edges at a time, so segments that straddle
+16-edge groups and tile ends, receivers without in-edges, and edge counts
+around one group and one workgroup's share are held against the oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from cases import Case, log, oracle_refs, rel_l2
+from oracle import graph as og
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def api():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2411_17164_amd import api as a
+    return a
+
+
+def degree_graph(n, degrees, seed):
+    """Graph on n nodes whose receiver i has degrees[i % len(degrees)] random senders."""
+    rng = np.random.default_rng(seed)
+    recv, send = [], []
+    for i in range(n):
+        d = min(degrees[i % len(degrees)], n - 1)
+        s = rng.choice(n - 1, size=d, replace=False)
+        s = np.sort(np.where(s >= i, s + 1, s))
+        recv.append(np.full(d, i, dtype=np.int64))
+        send.append(s.astype(np.int64))
+    return og.Graph(n, np.concatenate(recv), np.concatenate(send))
+
+
+@pytest.mark.parametrize("act,agg", [("silu", "message"), ("silu", "edge"), ("relu", "message"), ("relu", "edge")])
+@pytest.mark.parametrize("n,degrees", [
+    (8, [1, 0]),                # less than one group
+    (40, [16]),                 # every group exactly one segment
+    (33, [15, 1, 17]),          # segments around a group's end
+    (70, [31, 0, 0, 2, 32]),    # segments over three groups, runs of empty receivers
+    (130, [1]),                 # a receiver per edge
+    (515, [0, 9, 7, 0, 12]),    # a ragged last group in many workgroups
+])
+def test_chain_edges(api, n, degrees, act, agg):
+    """Outputs within 2e-2 of the oracle at the BF16-cast weights (the bar of
+    the BF16 form), and under SiLU the whole gradient too (under ReLU a
+    cloud this small has single kinks that BF16 rounding flips)."""
+    case = Case(1, levels=(n,), layers=2, precision="bf16", activation=act, aggregate=agg)
+    G = degree_graph(n, degrees, 7)
+    case._graph = G
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    ctx = api.Context(0)
+    ps = api.Partset.halo(api.Graph.from_csr(G.row_ptr, G.col), case.inp.pos, None, case.L)
+    p, node_in, pos, target = dev(case.params), dev(case.inp.node_in), dev(case.inp.pos), dev(case.inp.targets)
+    out = torch.full((n, 4), float("nan"), device="cuda")
+    d_out, loss, grad = torch.zeros_like(out), torch.zeros(1, device="cuda"), torch.full_like(p, float("nan"))
+    log(f"chain n={n} E={len(G.col)} {act} {agg}")
+    ctx.forward(case.model(api), p, ps, [0], node_in, pos, case.inp.edge_norm, out)
+    ctx.mse_grad(out, target, n, d_out, loss)
+    ctx.backward(case.model(api), p, d_out, grad)
+    torch.cuda.synchronize()
+    _, (_, y, g) = oracle_refs(case)
+    e_out, e_grad = rel_l2(out.cpu().numpy(), y), rel_l2(grad.cpu().numpy(), g)
+    log(f"  out {e_out:.2e} grad {e_grad:.2e}")
+    assert np.isfinite(grad.cpu().numpy()).all()
+    assert e_out <= 2e-2
+    if act == "silu":
+        assert e_grad <= 2e-2
+    # a forward without a tape gives the same bits
+    free = torch.zeros_like(out)
+    ctx.forward(case.model(api), p, ps, [0], node_in, pos, case.inp.edge_norm, free, keep_tape=False)
+    torch.cuda.synchronize()
+    assert torch.equal(free, out)
