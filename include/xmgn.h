@@ -122,11 +122,10 @@ xmgn_status xmgn_ctx_set_tiles(xmgn_ctx* ctx, int32_t edge_rows, int32_t node_ro
 
 /* Tiles of the edge adjoint, which tiles the same edges on its own (whole
  * receiver segments per tile).  edge_rows: 32 or 64 in the BF16 form at
- * H = 128 and 256 (at H = 128, 32-row tiles with the z tape run a variant
- * that keeps half the weight-gradient accumulators and two workgroups per
- * compute unit), else the forward's; 0 = the forward's.  edge_waves: 4 or 8
- * waves per workgroup, any form; 0 = the forward's.  Invalidates the last
- * forward. */
+ * H = 128 and 256, else the forward's; 0 = the forward's.  edge_waves: 4 or 8
+ * waves per workgroup, any form; 0 = the forward's.  (With z on the tape the
+ * BF16 adjoint at H = 128 has one configuration, whatever is asked.)
+ * Invalidates the last forward. */
 xmgn_status xmgn_ctx_set_bwd_tiles(xmgn_ctx* ctx, int32_t edge_rows, int32_t edge_waves);
 xmgn_status xmgn_ctx_get_bwd_tiles(const xmgn_ctx* ctx, int32_t* edge_rows, int32_t* edge_waves);
 

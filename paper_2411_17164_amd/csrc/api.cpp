@@ -1345,8 +1345,10 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
   se.mt_edge = s.mt_edge_bwd;
   se.nw_edge = s.nw_edge_bwd;
   const bool fw = edge_bwd_fuses_wgrad(se);
-  const bool fw1e = edge_bwd_fuses_dw1e(se, c->tape_z);  // else the e-block of dW1 is a separate product
-  if (fw) se.grid = std::min(s.grid, 512);
+  if (edge_bwd_chain(se, c->tape_z))
+    se.grid = edge_bwd_chain_grid((int)E);
+  else if (fw)
+    se.grid = std::min(s.grid, 512);
   const bool fnode = node_bwd_fuses_wgrad(s);
   if (enc_bwd_fuses_wgrad(s) || fnode) {
     // encoders: [<=256][2][H][H]; node adjoint: [<=512][H][H]
@@ -1434,9 +1436,8 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     rb.add_vec(c->part_e.as<float>(), se.grid, 4 * (int)H, es, 4);
     if (fw) {
       rb.add(c->wfused_e.as<float>(), se.grid, 2 * (int)(H * H), (int)H, (int)H, P(2, l, 2), (int)H);
-      if (fw1e)
-        rb.add(c->wfused_e.as<float>() + H * H, se.grid, 2 * (int)(H * H), (int)H, (int)H, P(2, l, 0) + 2 * H,
-               3 * (int)H);
+      rb.add(c->wfused_e.as<float>() + H * H, se.grid, 2 * (int)(H * H), (int)H, (int)H, P(2, l, 0) + 2 * H,
+             3 * (int)H);
     }
     { KT("sender_sum"); launch_sender_sum(s, b, c->fa.p, c->Ss.as<float>(), st); }
     { KT("node_dh"); launch_node_dh(s, b, we, c->dhMid.as<float>(), c->Sr.as<float>(), c->Ss.as<float>(), c->dhA.as<float>(), st); }
@@ -1444,12 +1445,12 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
            3 * (int)H));
     wg(wop(c->Ss.p, 1, (int)H, 0, nullptr, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(2, l, 0) + H,
            3 * (int)H));
-    if (!fw1e)
+    if (!fw) {
       wg(wop(c->fa.p, 0, (int)H, 0, nullptr, eslot(c, d, l), 0, (int)H, 0, nullptr, (int)E, (int)H, (int)H,
              P(2, l, 0) + 2 * H, 3 * (int)H));
-    if (!fw)
       wg(wop(c->fb.p, 0, (int)H, 0, nullptr, zt ? zt : c->fc.p, 0, (int)H, 0, nullptr, (int)E, (int)H, (int)H,
              P(2, l, 2), (int)H));
+    }
     if ((size_t)rb.tmp_floats > reduce_tmp_floats((int)red_cols))
       throw std::logic_error("a layer's reduction batch exceeds its scratch");
     { KT("wgrad"); launch_reduce_batch(rb, rt, st); }

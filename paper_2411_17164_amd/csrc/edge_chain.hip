@@ -328,4 +328,381 @@ void launch_edge_fwd_chain(const Shape& s, const BatchView& b, const MlpW& w, co
   }
 }
 
+// ---------------------------------------------------------------------------
+// Edge adjoint with z (and a) from the tape, BF16 H = 128.
+// ---------------------------------------------------------------------------
+// Eight waves, each 16 edges of its own range at a time, go through the three
+// products (u = W2 z, dz = W2^T du, de = W1e^T da) as private chains; dW2 and
+// the e-block of dW1 are sums over edges, so the waves lay [du | z], then
+// [da | e], in LDS as one 128-row tile and each accumulates a 32 x 64 block of
+// either matrix from all of it: four barriers per 128 edges.  W2, W2^T and the
+// e-block of W1^T stay in LDS (96 KiB); z comes a step ahead, de' and dm_r
+// during u and its statistics.  Column sums over edges (db2, dgamma, dbeta)
+// are taken across the 16 lanes of a DPP row; db1 is the total of the receiver
+// sums.  On 3.55M edges and 400k nodes 1,819 us (6.8 GB algorithmic, 3.7 TB/s;
+// a large copy reaches 4.9); the 64-row workgroup-tile kernel it replaces took
+// 3,345 us, and its 32-row form 2,430 us plus a product of 300 us for the
+// e-block.  Bound by HBM and, between its barriers, by LDS reads of the weight
+// fragments (1 KiB per MFMA).  Sums keep that kernel's order: da, de and S_r
+// are the same bits.
+struct EdgeBwdChain {
+  static constexpr int NW = 8;
+  static constexpr size_t WS = 32 * 1024;  // one matrix of fragments
+  static constexpr size_t REG = 8192;      // per wave: 16 rows of two 128-wide BF16 tiles
+  static constexpr size_t bytes = 3 * WS + NW * REG;
+};
+
+// A wave's share of the 128-row tile: 16 rows x 128 BF16 in 256-byte rows,
+// 32-byte units swizzled by row so that neither the row writes nor the
+// transposing reads meet in a bank.
+__device__ __forceinline__ int tile_off(int row, int unit16) {  // in bytes
+  return row * 256 + ((((unit16 >> 1) ^ row) & 7) << 5) + ((unit16 & 1) << 4);
+}
+__device__ __forceinline__ void tile_put(unsigned char* reg, const bf16x8 (&x)[4], int l) {
+  const int li = l & 15, lg = l >> 4;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) *(bf16x8*)(reg + tile_off(li, 4 * c + lg)) = x[c];
+}
+// Fragment [features c0 .. + 15][rows 32 c .. + 31] of the tile at byte offset
+// `off` of every wave's region (k order: rows 4 g + r, 16 + 4 g + r).
+__device__ __forceinline__ bf16x8 tile_frag(const unsigned char* regs, int off, int c, int c0, int l) {
+  const int L = l & 15, lg = l >> 4;
+  const int row = 4 * lg + (L >> 2);
+  const int f = c0 + 4 * (L & 3);
+  const unsigned char* p = regs + (size_t)(2 * c) * EdgeBwdChain::REG + off + tile_off(row, f >> 3) + (f & 7) * 2;
+  const bf16x4_lds lo = lds_read_tr4((const bf16*)p), hi = lds_read_tr4((const bf16*)(p + EdgeBwdChain::REG));
+  return bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+}
+// acc[i][j] += block (32 wm + 16 i, 64 wn + 16 j) of the sum over the tile's
+// 128 rows of (row of the tile at offA)^T (row of the tile at offB).
+__device__ __forceinline__ void tile_wgrad(f32x4 (&acc)[2][4], const unsigned char* regs, int offA, int offB, int wm,
+                                           int wn, int l) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 a[2], b[4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a[i] = tile_frag(regs, offA, c, 32 * wm + 16 * i, l);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = tile_frag(regs, offB, c, 64 * wn + 16 * j, l);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = mma(a[i], b[j], acc[i][j]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Sum over the 16 lanes of a DPP row of each of a lane's 32 values (x in the
+// accumulator layout: value 4 mb + r), halving the values a lane keeps at each
+// exchange: lane li ends with the totals of two values, 2 k and 2 k + 1 with
+// k = colsum_slot(li).
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float s) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL, int N>
+__device__ __forceinline__ void half_reduce(const float (&x)[2 * N], float (&y)[N], bool up) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const float keep = up ? x[N + k] : x[k], send = up ? x[k] : x[N + k];
+    y[k] = keep + dpp_mov<CTRL>(send);
+  }
+}
+// value index of the first of lane li's two totals
+__device__ __forceinline__ int colsum_slot(int li) {
+  return ((li >> 3) & 1) * 16 + ((li >> 2) & 1) * 8 + ((li >> 1) & 1) * 4 + (li & 1) * 2;
+}
+__device__ __forceinline__ void colsum16(const f32x4 (&x)[8], double (&tot)[2]) {
+  const int li = lane_id() & 15;
+  float v[32], a[16], b[8], c[4], d[2];
+#pragma unroll
+  for (int k = 0; k < 32; ++k) v[k] = x[k >> 2][k & 3];
+  half_reduce<0x140, 16>(v, a, li & 8);   // row_mirror: lane 15 - li
+  half_reduce<0x141, 8>(a, b, li & 4);    // row_half_mirror: lane 7 - li of its half
+  half_reduce<0x4E, 4>(b, c, li & 2);     // quad_perm [2,3,0,1]
+  half_reduce<0xB1, 2>(c, d, li & 1);     // quad_perm [1,0,3,2]
+  tot[0] += (double)d[0];
+  tot[1] += (double)d[1];
+}
+
+template <int ACT, int AGG>
+__global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, const bf16* __restrict__ e,
+                                                           const bf16* __restrict__ zt, const bf16* __restrict__ at,
+                                                           const float* __restrict__ de_in,
+                                                           const float* __restrict__ dm, EdgeBwdOut o, float eps) {
+  constexpr int H = 128, NW = EdgeBwdChain::NW;
+  using L = EdgeBwdChain;
+  __shared__ __align__(16) unsigned char smem[L::bytes];
+  bf16x8* F2 = (bf16x8*)smem;                  // W2: rows u, k = z
+  bf16x8* F2T = (bf16x8*)(smem + L::WS);       // W2^T: rows z, k = u
+  bf16x8* F1T = (bf16x8*)(smem + 2 * L::WS);   // e-block of W1, transposed: rows e, k = a
+  unsigned char* regs = smem + 3 * L::WS;
+  unsigned char* reg = regs + wave_id() * L::REG;
+  float* fr = (float*)reg;
+  const int l = lane_id(), li = l & 15, lg = l >> 4;
+  const int nw = gridDim.x * NW, wv = wave_rank(NW);
+  const int wm = wave_id() & 3, wn = wave_id() >> 2;
+
+  stage_frags<8, 4, 512>(F2, (const bf16*)w.W2, H);
+  stage_frags<8, 4, 512>(F2T, (const bf16*)w.W2T, H);
+  stage_frags<8, 4, 512>(F1T, (const bf16*)w.W1T, H);
+  // b2 and gamma: lane l holds 4 of the 256 floats
+  const f32x4 vec = *(const f32x4*)((l < 32 ? w.b2 : w.gamma) + 4 * (l & 31));
+  const WaveEdges we(b, wv, nw);
+  // every wave of the workgroup takes as many steps as its longest range needs
+  if (l == 0) *(int*)reg = we.end - we.begin;
+  __syncthreads();
+  int longest = 0;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) longest = max(longest, *(const int*)(regs + k * L::REG));
+  const int steps = (__builtin_amdgcn_readfirstlane(longest) + 15) >> 4;
+  __syncthreads();
+
+  const int last = max(we.end - 1, 0);  // rows past the range repeat its last edge and count as zero
+  int rv = 0, rn = 0;
+  auto load_idx = [&](int e0) {
+    const int k = min(e0 + li, last);
+    rv = b.recv[k];
+    rn = k + 1 < b.E ? b.recv[k + 1] : -1;
+  };
+  bf16x8 z[4], av[4];
+  auto load_rows = [&](int e0) {
+    const int k = min(e0 + li, last);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      z[c] = *(const bf16x8*)(zt + (size_t)k * H + 32 * c + 8 * lg);
+      if constexpr (ACT != 0) av[c] = *(const bf16x8*)(at + (size_t)k * H + 32 * c + 8 * lg);
+    }
+  };
+  f32x4 accW2[2][4], accW1[2][4];
+  zero_acc(accW2);
+  zero_acc(accW1);
+  double cb2[2] = {}, cg[2] = {}, cbt[2] = {}, cb1[2] = {};
+  float s0 = 0.f, s1 = 0.f;  // running receiver sum (lane l: features 2 l, 2 l + 1)
+  if (steps) {
+    load_idx(we.begin);
+    load_rows(we.begin);
+  }
+  for (int it = 0; it < steps; ++it) {
+    // lane numbers the compiler cannot see through: the LDS addresses made of
+    // them are formed again in every step instead of spilled
+    const int l = opaque(lane_id()), li = l & 15, lg = l >> 4;
+    const int e0 = we.begin + 16 * it;
+    const int ne = min(16, we.end - e0);  // may be <= 0
+    const bool ok = li < ne;
+    const int rc = rv;
+    const unsigned ends = (unsigned)__ballot(rv != rn) & 0xffffu;
+    const bool more = it + 1 < steps;
+    f32x4 dve[8];  // de', in flight during u and its statistics
+    if (de_in) {
+      const float* p = de_in + (size_t)min(e0 + li, last) * H + 4 * lg;
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) dve[mb] = *(const f32x4*)(p + 16 * mb);
+    } else {
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) dve[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    if (more) load_idx(e0 + 16);
+    wave_sync();
+    *(f32x4*)(fr + 4 * l) = vec;
+    wave_sync();
+    auto vget = [&](int v, int mb) { return *(const f32x4*)(fr + 128 * v + 16 * mb + 4 * lg); };
+    // u = W2 z + b2, xhat
+    f32x4 x[1][8];
+    zero_acc(x);
+    {
+      const bf16x8 zz[1][4] = {{z[0], z[1], z[2], z[3]}};
+      chain_gemm<1, 8, 4, 0, 4, 4, true>(x, F2, zz, 0);
+    }
+    f32x4 dvm[8];  // dm_r, in flight during the statistics
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) dvm[mb] = *(const f32x4*)(dm + (size_t)rc * H + 16 * mb + 4 * lg);
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) x[0][mb] += vget(0, mb);
+    const float inv = ln128(x[0], eps);
+    // dv = dm_r + de'
+    f32x4 g[8];
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) g[mb][r] = ok ? dvm[mb][r] + dve[mb][r] : 0.f;
+    // LayerNorm adjoint: g = du
+    {
+      f32x4 t[8];
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) t[mb] = g[mb] * x[0][mb];
+      colsum16(t, cg);
+    }
+    colsum16(g, cbt);
+    float sg = 0.f, sgx = 0.f;  // row sums of dv gamma and of dv gamma xhat
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 g0 = vget(1, 2 * q), g1 = vget(1, 2 * q + 1);
+      f32x4 &lo = g[2 * q], &hi = g[2 * q + 1];
+      const f32x4 &xl = x[0][2 * q], &xu = x[0][2 * q + 1];
+      float a[4], d[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float dv1 = hi[r];
+        lo[r] *= g0[r];
+        hi[r] = dv1 * g1[r];
+        a[r] = __builtin_fmaf(dv1, g1[r], lo[r]);
+        d[r] = __builtin_fmaf(xu[r], hi[r], xl[r] * lo[r]);
+      }
+      sg += add_xor32(add_xor16((a[0] + a[1]) + (a[2] + a[3])));
+      sgx += add_xor32(add_xor16((d[0] + d[1]) + (d[2] + d[3])));
+    }
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        g[mb][r] = __builtin_fmaf(sgx * (-1.f / H), x[0][mb][r], __builtin_fmaf(sg, -1.f / H, g[mb][r])) * inv;
+    colsum16(g, cb2);
+    bf16x8 du[1][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) du[0][c] = to_natural(g[2 * c], g[2 * c + 1]);
+    // [du | z] of the 128 edges; act'(a) from z (ReLU: a > 0 exactly where z > 0) or a
+    wave_sync();
+    tile_put(reg, du[0], l);
+    tile_put(reg + 4096, z, l);
+    bf16x8 az[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) az[c] = ACT ? av[c] : z[c];
+    bf16x8 er[4];
+    {
+      const int k = min(e0 + li, last);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) er[c] = *(const bf16x8*)(e + (size_t)max(k, 0) * H + 32 * c + 8 * lg);
+    }
+    lds_sync();
+    tile_wgrad(accW2, regs, 0, 4096, wm, wn, l);  // dW2 += du^T z
+    // dz = W2^T du ; da = dz * act'(a)
+    zero_acc(x);
+    chain_gemm<1, 8, 4, 0, 4, 4, true>(x, F2T, du, 0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      f32x4 lo, hi;
+      from_natural(az[c], lo, hi);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        x[0][2 * c][r] *= act_d<ACT>(lo[r]);
+        x[0][2 * c + 1][r] *= act_d<ACT>(hi[r]);
+      }
+    }
+    bf16x8 da[1][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      da[0][c] = to_natural(x[0][2 * c], x[0][2 * c + 1]);
+      if (ok) *(bf16x8*)((bf16*)o.da + (size_t)(e0 + li) * H + 32 * c + 8 * lg) = da[0][c];
+    }
+    lds_sync();  // every wave is done with [du | z]
+    // S_r: receiver sums of da in edge order; their total is db1
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) *(f32x4*)(fr + li * 128 + (((4 * mb + lg) ^ li) << 2)) = x[0][mb];
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (i < ne) {
+        const float2 v = *(const float2*)(fr + i * 128 + ((((l >> 1) ^ i) << 2) | ((l & 1) << 1)));
+        s0 += v.x;
+        s1 += v.y;
+        if (ends >> i & 1) {
+          const int r = __builtin_amdgcn_readlane(rc, i);
+          *(float2*)(o.S_r + (size_t)r * H + 2 * l) = float2{s0, s1};
+          cb1[0] += (double)s0;
+          cb1[1] += (double)s1;
+          s0 = 0.f;
+          s1 = 0.f;
+        }
+      }
+    }
+    wave_sync();
+    tile_put(reg, da[0], l);
+    tile_put(reg + 4096, er, l);
+    if (more) load_rows(e0 + 16);  // the next step's rows, in flight from here
+    lds_sync();
+    tile_wgrad(accW1, regs, 0, 4096, wm, wn, l);  // dW1[:, 2H:3H] += da^T e
+    // de = de' (+ dm_r) + (W1^T da)[2H:3H]
+    zero_acc(x);
+    chain_gemm<1, 8, 4, 0, 4, 4, true>(x, F1T, da, 0);
+    if (ok) {
+      const size_t at_ = (size_t)(e0 + li) * H + 4 * lg;
+      f32x4 v[8];
+      if (de_in) {
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) v[mb] = *(const f32x4*)(de_in + at_ + 16 * mb);
+      } else {
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) v[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) {
+        if (AGG) v[mb] += *(const f32x4*)(dm + (size_t)rc * H + 16 * mb + 4 * lg);
+        *(f32x4*)(o.de_out + at_ + 16 * mb) = x[0][mb] + v[mb];
+      }
+    }
+    lds_sync();  // every wave is done with [da | e]
+  }
+  zero_empty_rows(b, o.S_r, H, wv, nw);
+  // column sums of the workgroup's eight waves: lane li of group lg holds
+  // values 2k, 2k + 1 of block layout (feature 16 (v / 4) + 4 lg + v % 4)
+  double* ds = (double*)smem;  // [8 waves][4][128]; the weights are done with
+  __syncthreads();
+  {
+    double* d = ds + wave_id() * 512;
+    const int v = colsum_slot(li), f = 16 * (v >> 2) + 4 * lg + (v & 3);
+    d[2 * l] = cb1[0];
+    d[2 * l + 1] = cb1[1];
+    d[128 + f] = cb2[0];
+    d[128 + f + 1] = cb2[1];
+    d[256 + f] = cg[0];
+    d[256 + f + 1] = cg[1];
+    d[384 + f] = cbt[0];
+    d[384 + f + 1] = cbt[1];
+  }
+  __syncthreads();
+  {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) s += ds[k * 512 + threadIdx.x];
+    o.partial[(size_t)blockIdx.x * 512 + threadIdx.x] = (float)s;
+  }
+  float* q2 = o.wpart + (size_t)blockIdx.x * 2 * H * H;
+  float* q1 = q2 + H * H;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int at_ = (32 * wm + 16 * i + 4 * lg + r) * H + 64 * wn + 16 * j + li;
+        q2[at_] = accW2[i][j][r];
+        q1[at_] = accW1[i][j][r];
+      }
+}
+
+bool edge_bwd_chain(const Shape& s, bool ztape) { return s.prec == 1 && s.H == 128 && ztape; }
+
+int edge_bwd_chain_grid(int E) { return std::max(1, std::min(256, (E + 127) / 128)); }
+
+void launch_edge_bwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* e, const void* zt,
+                           const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o, hipStream_t st) {
+  if (s.act != 0 && !at) {
+    g_config_error = 1;
+    return;
+  }
+  auto go = [&](auto act, auto agg) {
+    k_edge_bwd_chain<decltype(act)::value, decltype(agg)::value><<<edge_bwd_chain_grid(b.E), 512, 0, st>>>(
+        b, w, (const bf16*)e, (const bf16*)zt, (const bf16*)at, de_in, dm, o, s.eps);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  if (s.act) {
+    if (s.agg) go(I1{}, I1{}); else go(I1{}, I0{});
+  } else {
+    if (s.agg) go(I0{}, I1{}); else go(I0{}, I0{});
+  }
+}
+
 }  // namespace xmgn

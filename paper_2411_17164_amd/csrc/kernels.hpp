@@ -103,9 +103,6 @@ struct EdgeBwdOut {
 // True when the edge adjoint accumulates dW2 and the e-block of dW1 itself
 // (then du and z are not written and wpart must be given).
 bool edge_bwd_fuses_wgrad(const Shape& s);
-// True when it also accumulates the e-block of dW1 (else that block is a
-// separate product over da and e); s.mt_edge is the adjoint's tile rows.
-bool edge_bwd_fuses_dw1e(const Shape& s, bool ztape);
 // Fixed-order sums over the rows of partial matrices use a two-stage
 // reduction with caller scratch of reduce_tmp_floats(columns) floats.
 size_t reduce_tmp_floats(int max_cols);
@@ -121,6 +118,14 @@ bool edge_a_tape(const Shape& s);
 void launch_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                      const void* zt, const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o,
                      hipStream_t st);
+
+// The BF16 adjoint at H = 128 with z on the tape runs as wave-private chains
+// that accumulate dW2 and the e-block of dW1; its partials have
+// edge_bwd_chain_grid(E) rows.
+bool edge_bwd_chain(const Shape& s, bool ztape);
+int edge_bwd_chain_grid(int E);
+void launch_edge_bwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* e, const void* zt,
+                           const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o, hipStream_t st);
 
 struct NodeBwdOut {
   float* dh_mid;   // [n][H]

@@ -142,13 +142,8 @@ __device__ __forceinline__ void write_partial(float* p, int n0, const double (&v
 // W1 then live in LDS for the whole kernel and serve both their products and
 // (read transposed) the adjoint products dz = du W2 and de = da W1e; the FP32
 // staging tile takes the first 2H columns of the gathered tile's rows so that
-// its e columns stay intact.  One workgroup per compute unit.
-// FW = 2 (BF16, H = 128, z from the tape, 32-row tiles): dW2 only, W2 alone
-// in LDS, the e-block of W1 read from L2 for de = da W1e, and the e-block of
-// dW1 left to a separate product over da (which is written anyway) and the e
-// tape.  Half the accumulator registers and under 80 KB of LDS: two
-// workgroups per compute unit, so one's loads and barriers overlap the
-// other's arithmetic.
+// its e columns stay intact.  One workgroup per compute unit.  Only the
+// recomputing adjoint uses it: with z on the tape k_edge_bwd_chain runs.
 template <typename T, int H, int MT, int FW, int NW>
 struct EdgeBwdLds {
   using D = BD<T, H, NW>;
@@ -156,13 +151,13 @@ struct EdgeBwdLds {
   static constexpr size_t ZS = (size_t)MT * D::LDH * sizeof(T);
   static constexpr int LDW = H + 8;  // LDS-resident weights (BF16)
   static constexpr size_t WS = FW ? (size_t)H * LDW * 2 : 0;
-  static constexpr int NWS = FW == 1 ? 2 : FW == 2 ? 1 : 0;  // LDS-resident weight matrices
+  static constexpr int NWS = FW ? 2 : 0;             // LDS-resident weight matrices
   static constexpr int LDF = FW ? D::LD3 * (int)sizeof(T) / 4 : D::LDF;  // FP32 staging row stride
   // receivers, senders, segment starts (MT + 1, padded)
   static constexpr size_t bytes = XS + ZS + NWS * WS + 2 * NW * MT * 4 + (3 * MT + 4) * 4;
 };
 
-// ZT (BF16): z of every edge comes from the forward's tape (zt) instead of
+// ZT: z of every edge comes from the forward's tape (zt) instead of
 // being recomputed -- no gather of h_r, h_s and no first product.  ReLU's
 // derivative is [z > 0], exactly [a > 0]; SiLU's takes a from the tape of
 // pre-activations (at, BF16).  Unfused (H = 256, 512), the dW2 product then
@@ -178,18 +173,15 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
   constexpr size_t XS = L::XS, ZS = L::ZS, WS = L::WS;
   constexpr int LDW = L::LDW, LDF = L::LDF;
   static_assert(!FW || (sizeof(T) == 2 && H == 128), "fused weight gradients: BF16, H = 128");
-  static_assert(FW != 2 || ZT, "dW2-only fusion reads z from the tape");
+  static_assert(!FW || !ZT, "fused weight gradients with z from the tape: k_edge_bwd_chain");
   static_assert((size_t)MT * LDF * 4 <= XS, "FP32 tile must fit in the staging tile");
   static_assert(!FW || (size_t)H * 4 <= 2 * H * sizeof(T), "FP32 rows must leave the e columns intact");
-  // z from the tape, fused weight gradients, ReLU: the FP32 tile's columns
-  // are free from the start of a tile, so dv is loaded with z and e
-  constexpr bool EARLY_DV = ZT && FW && ACT == 0;
   __shared__ __align__(16) unsigned char smem[L::bytes];
   T* xs = (T*)smem;
   float* ft = (float*)smem;
   T* zs = (T*)(smem + XS);
   bf16* W2s = (bf16*)(smem + XS + ZS);       // W2 [out][in]
-  bf16* W1es = (bf16*)(smem + XS + ZS + WS);  // W1[:, 2H:3H] [out][in] (FW = 1)
+  bf16* W1es = (bf16*)(smem + XS + ZS + WS);  // W1[:, 2H:3H] [out][in]
   float* red = (float*)(smem + XS + ZS + L::NWS * WS);
   int* rs = (int*)(red + 2 * NW * MT);
   const T* W1 = (const T*)w.W1;
@@ -202,13 +194,12 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
   f32x4 accW2[NB][H / 16], accW1[NB][H / 16];
   if constexpr (FW) {
     zero_acc(accW2);
-    if constexpr (FW == 1) zero_acc(accW1);
+    zero_acc(accW1);
     // weights resident in LDS (visible after the first barrier of the tile loop)
     for (int c = threadIdx.x; c < H * (H / 8); c += 64 * NW) {
       const int r = c / (H / 8), q = c - r * (H / 8);
       *(uint4*)(W2s + r * LDW + 8 * q) = *(const uint4*)(W2 + (size_t)r * H + 8 * q);
-      if constexpr (FW == 1)
-        *(uint4*)(W1es + r * LDW + 8 * q) = *(const uint4*)(W1 + (size_t)r * 3 * H + 2 * H + 8 * q);
+      *(uint4*)(W1es + r * LDW + 8 * q) = *(const uint4*)(W1 + (size_t)r * 3 * H + 2 * H + 8 * q);
     }
   }
 
@@ -227,15 +218,14 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
     lds_sync();
     tile_segments(sg, rs, r0, r1, ne);  // read after the next barrier
     if constexpr (ZT) {
-      // z rows into zs, (fused: for dW1's e-block) e rows into the e columns
-      // of xs and (SiLU) a rows into its first H columns, one batch of loads
-      constexpr int NPART = 1 + (FW == 1 ? 1 : 0) + (ACT != 0 ? 1 : 0);
+      // z rows into zs and (SiLU) a rows into the first H columns of xs, one
+      // batch of loads
+      constexpr int NPART = 1 + (ACT != 0 ? 1 : 0);
       constexpr int E8 = 16 / sizeof(T), CPR = H / E8, TOT = NPART * MT * CPR, IT = TOT / (64 * NW);
       static_assert(TOT % (64 * NW) == 0, "whole steps of the workgroup");
-      auto src = [&](int p) -> const T* { return p == 0 ? zt : (FW == 1 && p == 1) ? e : at; };
+      auto src = [&](int p) -> const T* { return p == 0 ? zt : at; };
       auto dst = [&](int p, int i, int q) -> T* {
-        return p == 0 ? zs + i * D::LDH + q * E8 : (FW == 1 && p == 1) ? xs + i * D::LD3 + 2 * H + q * E8
-                                                                  : xs + i * D::LD3 + q * E8;
+        return p == 0 ? zs + i * D::LDH + q * E8 : xs + i * D::LD3 + q * E8;
       };
       uint4 v[IT];
 #pragma unroll
@@ -245,11 +235,6 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
         v[k] = uint4{0u, 0u, 0u, 0u};
         if (i < ne) v[k] = *(const uint4*)(src(p) + (size_t)(e0 + i) * H + q * E8);
       }
-      if constexpr (EARLY_DV)  // dv = dm_r + de' in the same round trip, into the FP32 tile
-        f32_tile<MT, H, 64 * NW>(
-            ne, de_in != nullptr, [&](int i, int q) { return *(const float4*)(dm + (size_t)rs[i] * H + 4 * q); },
-            [&](int i, int q) { return *(const float4*)(de_in + (size_t)(e0 + i) * H + 4 * q); },
-            [&](int i, int q, const float4& w4) { *(float4*)(ft + i * LDF + 4 * q) = w4; });
 #pragma unroll
       for (int k = 0; k < IT; ++k) {
         const int c = (int)threadIdx.x + k * 64 * NW, p = c / (MT * CPR), rem = c - p * (MT * CPR);
@@ -278,7 +263,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
           for (int r = 0; r < 4; ++r)
             a[mb][nb][r] = ACT == 0 ? to_f(zs[acc_row(mb, r) * D::LDH + acc_col(n0, nb)])
                                     : to_f(xs[acc_row(mb, r) * D::LD3 + acc_col(n0, nb)]);
-    } else if constexpr (FW == 1) {
+    } else if constexpr (FW) {
       wave_gemm<T, MB, NB, 2 * H, D::LD3>(a, xs, W1, 3 * H, n0);  // [h_r ; h_s] blocks from global
       wave_gemm_lds<MB, NB, H, D::LD3>(a, (const bf16*)xs + 2 * H, [&](int k, int nb) {
         return *(const bf16x8*)(W1es + (n0 + 16 * nb + li) * LDW + k + 8 * lg);
@@ -321,11 +306,10 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
     ln_normalize<MB, NB, MT, H, NW>(x, red, eps, inv);  // x = xhat
 
     // upstream gradient dv = dm_r + de'_k  (FP32 tile over the dead gather)
-    if constexpr (!EARLY_DV)
-      f32_tile<MT, H, 64 * NW>(
-          ne, de_in != nullptr, [&](int i, int q) { return *(const float4*)(dm + (size_t)rs[i] * H + 4 * q); },
-          [&](int i, int q) { return *(const float4*)(de_in + (size_t)(e0 + i) * H + 4 * q); },
-          [&](int i, int q, const float4& v) { *(float4*)(ft + i * LDF + 4 * q) = v; });
+    f32_tile<MT, H, 64 * NW>(
+        ne, de_in != nullptr, [&](int i, int q) { return *(const float4*)(dm + (size_t)rs[i] * H + 4 * q); },
+        [&](int i, int q) { return *(const float4*)(de_in + (size_t)(e0 + i) * H + 4 * q); },
+        [&](int i, int q, const float4& v) { *(float4*)(ft + i * LDF + 4 * q) = v; });
     if constexpr (!FW && !ZT) lds_rows_to_global<T, D::LDH>(zs, ne, H, (T*)o.z + (size_t)e0 * H, H, [](int i) { return i; });
     lds_sync();
     f32x4 g[MB][NB];
@@ -360,7 +344,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
 #pragma unroll
         for (int r = 0; r < 4; ++r) x[mb][nb][r] *= act_d<ACT>(a[mb][nb][r]);
     col_accumulate(x, cb1);
-    if constexpr (FW == 1) wave_wgrad<MB, NB, H, D::LD3>(accW1, x, (const bf16*)xs + 2 * H);  // dW1[:, 2H:3H] += da^T e
+    if constexpr (FW) wave_wgrad<MB, NB, H, D::LD3>(accW1, x, (const bf16*)xs + 2 * H);  // dW1[:, 2H:3H] += da^T e
     lds_sync();
     acc_to_ldsf<MB, NB, LDF>(x, ft, n0);
     acc_to_lds<T, MB, NB, D::LDH>(x, zs, n0);
@@ -399,7 +383,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
     lds_rows_to_global<T, D::LDH>(zs, ne, H, (T*)o.da + (size_t)e0 * H, H, [](int i) { return i; });
     // de = de' (+ dm_r) + (W1^T da)[2H:3H]
     zero_acc(g);
-    if constexpr (FW == 1) {
+    if constexpr (FW) {
       wave_gemm_lds<MB, NB, H, D::LDH>(g, (const bf16*)zs, [&](int k, int nb) {
         return lds_bfrag_tr(W1es, LDW, k + 8 * lg, n0 + 16 * nb, 4);
       });
@@ -447,7 +431,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
         for (int r = 0; r < 4; ++r) {
           const int m = n0 + nb * 16 + lg * 4 + r, n = jb * 16 + li;
           q2[m * H + n] = accW2[nb][jb][r];
-          if constexpr (FW == 1) q1[m * H + n] = accW1[nb][jb][r];
+          q1[m * H + n] = accW1[nb][jb][r];
         }
   }
 }
@@ -1168,37 +1152,26 @@ constexpr bool node_fits() {
 }
 
 bool edge_bwd_fuses_wgrad(const Shape& s) { return s.prec == 1 && s.H == 128; }
-bool edge_bwd_fuses_dw1e(const Shape& s, bool ztape) {
-  return edge_bwd_fuses_wgrad(s) && !(ztape && s.mt_edge == 32);
-}
 
 template <int NW>
 static void edge_bwd_nw(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                         const void* zt, const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o,
                         hipStream_t st) {
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT_EDGE(s.mt_edge, {
-    // z from the tape: dW2-only fusion on 32-row tiles (two workgroups per
-    // CU), both blocks fused on 64-row tiles; recompute: both fused
-    constexpr int FW = (sizeof(T) == 2 && H == 128) ? (MT == 32 ? 2 : 1) : 0;
-    constexpr int FWR = (sizeof(T) == 2 && H == 128) ? 1 : 0;
-    constexpr int ZT = 1;
+    constexpr int FW = (sizeof(T) == 2 && H == 128) ? 1 : 0;
     if constexpr (edge_bwd_fits<T, H, MT>()) {
+      auto go = [&](auto agg, auto zz, const T* z, const T* av) {
+        k_edge_bwd<T, H, MT, ACT, decltype(agg)::value, FW, NW, decltype(zz)::value><<<s.grid, 64 * NW, 0, st>>>(
+            b, w, (const T*)h, (const T*)e, z, av, de_in, dm, o, s.eps);
+      };
+      using I0 = std::integral_constant<int, 0>;
+      using I1 = std::integral_constant<int, 1>;
       if (zt && ACT != 0 && !at) {
         g_config_error = 1;
-      } else if (zt) {
-        if (s.agg)
-          k_edge_bwd<T, H, MT, ACT, 1, FW, NW, ZT><<<s.grid, 64 * NW, 0, st>>>(
-              b, w, (const T*)h, (const T*)e, (const T*)zt, (const T*)at, de_in, dm, o, s.eps);
-        else
-          k_edge_bwd<T, H, MT, ACT, 0, FW, NW, ZT><<<s.grid, 64 * NW, 0, st>>>(
-              b, w, (const T*)h, (const T*)e, (const T*)zt, (const T*)at, de_in, dm, o, s.eps);
-      } else {
-        if (s.agg)
-          k_edge_bwd<T, H, MT, ACT, 1, FWR, NW, 0><<<s.grid, 64 * NW, 0, st>>>(b, w, (const T*)h, (const T*)e, nullptr,
-                                                                              nullptr, de_in, dm, o, s.eps);
-        else
-          k_edge_bwd<T, H, MT, ACT, 0, FWR, NW, 0><<<s.grid, 64 * NW, 0, st>>>(b, w, (const T*)h, (const T*)e, nullptr,
-                                                                              nullptr, de_in, dm, o, s.eps);
+      } else if (!zt) {
+        if (s.agg) go(I1{}, I0{}, nullptr, nullptr); else go(I0{}, I0{}, nullptr, nullptr);
+      } else if constexpr (!FW) {  // (else k_edge_bwd_chain)
+        if (s.agg) go(I1{}, I1{}, (const T*)zt, (const T*)at); else go(I0{}, I1{}, (const T*)zt, (const T*)at);
       }
     } else {
       g_config_error = 1;
@@ -1212,6 +1185,12 @@ bool edge_a_tape(const Shape& s) { return s.act != 0; }
 void launch_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                      const void* zt, const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o,
                      hipStream_t st) {
+  // z from the tape at H = 128 (BF16), at every size: W2, W2^T and the
+  // transposed e-block of W1 fit in LDS beside the waves' shares of the tile
+  if (edge_bwd_chain(s, zt != nullptr)) {
+    launch_edge_bwd_chain(s, b, w, e, zt, at, de_in, dm, o, st);
+    return;
+  }
   if (s.nw_edge == 8)
     edge_bwd_nw<8>(s, b, w, h, e, zt, at, de_in, dm, o, st);
   else
