@@ -1537,9 +1537,8 @@ extern "C" xmgn_status xmgn_adam_step(xmgn_ctx* c, float* params, const float* g
   AdamArgs a{};
   if (xmgn_status r = adam_args(params, grad, m, v, n, step, lr, beta1, beta2, eps, clip_norm, &a)) return r;
   HIPCHK(hipSetDevice(c->device));
-  const int G = kAdamScratchPartials;
-  if (xmgn_status r = c->optp.ensure(G * sizeof(double), (hipStream_t)stream)) return r;
-  launch_adam(params, grad, m, v, n, c->optp.as<double>(), G, a, grad_norm, (hipStream_t)stream);
+  if (xmgn_status r = c->optp.ensure(kAdamScratchPartials * sizeof(double), (hipStream_t)stream)) return r;
+  launch_adam(params, grad, m, v, n, c->optp.as<double>(), a, grad_norm, (hipStream_t)stream);
   HIPCHK(hipGetLastError());
   return XMGN_OK;
   GUARD_END
@@ -1555,15 +1554,14 @@ extern "C" xmgn_status xmgn_adam_step_noalloc(int32_t device, float* params, con
   HIPCHK(hipGetDeviceCount(&n_dev));
   if (device < 0 || device >= n_dev || device >= kMaxDevices) return fail(XMGN_ERR_INVALID, "device out of range");
   // the partial count is fixed (the array's size), so no n needs more
-  const int G = kAdamScratchPartials;
   HIPCHK(hipSetDevice(device));
   double* partial = nullptr;
   const char* err = "";
   if (const int rc = adam_noalloc_scratch(device, &partial, &err))
     return fail(rc == -1 ? XMGN_ERR_INVALID : XMGN_ERR_HIP, std::string("optimizer scratch: ") + err);
-  // k_sumsq writes all G partials before k_adam reads them (stream order),
+  // k_sumsq writes all the partials before k_adam reads them (stream order),
   // so nothing of a previous call needs clearing
-  launch_adam(params, grad, m, v, n, partial, G, a, grad_norm, (hipStream_t)stream);
+  launch_adam(params, grad, m, v, n, partial, a, grad_norm, (hipStream_t)stream);
   HIPCHK(hipGetLastError());
   return XMGN_OK;
   GUARD_END

@@ -255,12 +255,12 @@ struct AdamArgs {
   float lr, b1, b2, c1, c2, eps, bc1, bc2;
   double clip;
 };
-// partial: dev double [G] scratch; norm_out: dev float [1] or NULL.
-void launch_adam(float* p, const float* g, float* m, float* v, int64_t n, double* partial, int G,
-                 const AdamArgs& a, float* norm_out, hipStream_t st);
-// Partials of the allocation-free optimizer step: the count launch_adam is
-// given by both optimizer entry points, and the capacity of the library's
-// fixed per-device array that the allocation-free one uses.
+// partial: dev double [kAdamScratchPartials] scratch; norm_out: dev float [1] or NULL.
+void launch_adam(float* p, const float* g, float* m, float* v, int64_t n, double* partial, const AdamArgs& a,
+                 float* norm_out, hipStream_t st);
+// Partials of the clipping norm: what launch_adam writes and reads, and the
+// capacity of the library's fixed per-device array that the allocation-free
+// entry point uses.
 constexpr int kAdamScratchPartials = 256;
 constexpr int kMaxDevices = 64;
 // Device address (on `device`, which must be current) of that array; looked
