@@ -514,7 +514,7 @@ struct Batch {
 };
 
 struct BlockW {
-  int64_t W1 = -1, W2 = -1, W3 = -1, W1T = -1, W2T = -1, W3T = -1, Brs = -1;
+  int64_t W1 = -1, W2 = -1, W3 = -1, W1T = -1, W2T = -1, W3T = -1, Brs = -1, FS = -1;
 };
 
 struct xmgn_ctx {
@@ -621,16 +621,16 @@ static Shape make_shape(const xmgn_ctx* c, const xmgn_model_desc* d) {
   s.eps = d->ln_eps;
   int me = c->mt_edge > 0 ? std::min(c->mt_edge, 64) : 64, mn = c->mt_node > 0 ? c->mt_node : 64;
   // LDS budget: H = 256 runs 32-row node tiles and 32-row edge tiles, or in
-  // the BF16 form 64-row edge tiles, or 128-row ones in the wide gathered
-  // forward (not in the split form); H = 512 16-row node tiles and 32-row
-  // edge tiles (a tile holds whole receiver segments), or 64-row ones in the
-  // wide gathered forward.  The edge adjoint stays on 32 or 64 rows.
+  // the BF16 form 64-row edge tiles; H = 512 16-row node tiles and 32-row edge
+  // tiles (a tile holds whole receiver segments).  The gathered BF16 forward
+  // takes no tiles; its rows (also 128 at H = 256 and 64 at H = 512) only
+  // bound the in-degree together with the adjoint's 32 or 64.
   const bool wide = d->precision == 1 && !c->edge_split;
   if (d->hidden == 256) {
     me = (d->precision == 1 && c->mt_edge == 64) || (wide && c->mt_edge == 128) ? c->mt_edge : 32;
     mn = 32;
   }
-  if (d->hidden == 512) {  // the wide gathered forward by default (1.8x the 32-row kernel on C6)
+  if (d->hidden == 512) {
     me = (wide && (c->mt_edge == 64 || c->mt_edge == 0)) ? 64 : 32;
     mn = 16;
   }
@@ -867,6 +867,15 @@ static void add_job(xmgn_ctx* c, int64_t src, int src_ld, int col0, int transpos
   c->jobs.push_back(j);
 }
 
+// The same matrix in MFMA fragment order, placed right behind the last job's
+// (rows a multiple of 16, cols of 32); returns its offset.
+static int64_t add_frag_job(xmgn_ctx* c, int64_t src, int src_ld, int col0, int transpose, int rows, int cols) {
+  int64_t dst = -1;
+  add_job(c, src, src_ld, col0, transpose, rows, cols, dst);
+  c->jobs.back().frag = 1;
+  return dst;
+}
+
 static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream_t st) {
   if (c->have_wplan && std::memcmp(&c->wdesc, d, sizeof(*d)) == 0) return XMGN_OK;
   // the job table and the blob may still be read by enqueued kernels
@@ -892,6 +901,10 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
     add_job(c, W1e, 3 * H, 2 * H, 1, H, H, we.W1T);  // [c][j] = W1[j][2H + c]
     add_job(c, W1e, 3 * H, 0, 1, H, H, we.Brs, 2 * H, 0);
     add_job(c, W1e, 3 * H, H, 1, H, H, we.Brs, 2 * H, H, false);
+    if (d->precision == 1 && H > 128) {  // the streaming edge kernels' slabs
+      we.FS = add_frag_job(c, W1e, 3 * H, 0, 0, H, 3 * H);
+      add_frag_job(c, W2e, H, 0, 0, H, H);
+    }
     BlockW& wn = c->bw[3 + 2 * l];
     const int64_t W1n = poff(d, 3, l, 0), W2n = poff(d, 3, l, 2);
     add_job(c, W1n, 2 * H, 0, 0, H, 2 * H, wn.W1);
@@ -924,6 +937,7 @@ static MlpW weights(const xmgn_ctx* c, const xmgn_model_desc* d, const float* pa
   w.W2T = ptr(b.W2T);
   w.W3T = ptr(b.W3T);
   w.Brs = ptr(b.Brs);
+  w.FS = ptr(b.FS);
   auto P = [&](int t) { return params + poff(d, block, layer, t); };
   if (block == 0 || block == 1) {
     w.W1f = P(0);

@@ -28,6 +28,13 @@ __device__ __forceinline__ int opaque(int v) {
   return v;
 }
 
+// Has the compiler wait for a loaded value here.
+__device__ __forceinline__ void arrived(bf16x8& v) {
+  u32x4 u = __builtin_bit_cast(u32x4, v);
+  asm volatile("" : "+v"(u));
+  v = __builtin_bit_cast(bf16x8, u);
+}
+
 // Swap of the odd 16-lane rows of a with the even rows of b.
 __device__ __forceinline__ void swap16(unsigned& a, unsigned& b) {
   const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);

@@ -4,59 +4,9 @@
 
 #include "chain.hpp"
 #include "kernels.hpp"
+#include "segsum.hpp"
 
 namespace xmgn {
-
-// The range of edges of wave `wv` of `nw`: E wv / nw and E (wv + 1) / nw, each
-// moved on to the next segment start, so a wave holds whole receiver segments.
-struct WaveEdges {
-  int begin, end;
-  __device__ static int align(const int* __restrict__ recv, int E, int t) {
-    if (t <= 0) return 0;
-    for (; t < E; t += 64) {
-      const int i = t + lane_id();
-      const bool start = i < E && recv[i] != recv[i - 1];
-      const unsigned long long m = __ballot(start);
-      if (m) return t + __builtin_ctzll(m);
-    }
-    return E;
-  }
-  __device__ WaveEdges(const BatchView& b, int wv, int nw) {
-    begin = align(b.recv, b.E, (int)((long long)b.E * wv / nw));
-    end = align(b.recv, b.E, (int)((long long)b.E * (wv + 1) / nw));
-  }
-};
-
-// Position of this wave among the grid's waves: workgroup b runs on XCD b % 8,
-// and each XCD takes a contiguous part of the edges.
-__device__ __forceinline__ int wave_rank(int nw_wg) {
-  const int G = gridDim.x, b = blockIdx.x;
-  const int per = (G + 7) >> 3, full = G - 8 * (per - 1);  // XCDs with `per` workgroups
-  const int x = b & 7, j = b >> 3;
-  const int base = x < full ? x * per : full * per + (x - full) * (per - 1);
-  return (base + j) * nw_wg + __builtin_amdgcn_readfirstlane(wave_id());
-}
-
-// Ordering of LDS accesses between the lanes of one wave (a wave's LDS
-// instructions execute in order; this holds the compiler to it).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
-// Rows without in-edges: their sums are zero.
-__device__ __forceinline__ void zero_empty_rows(const BatchView& b, float* __restrict__ m, int H, int wv, int nw) {
-  for (int r0 = wv * 64; r0 < b.n; r0 += nw * 64) {
-    const int r = r0 + lane_id();
-    unsigned long long em = __ballot(r < b.n && b.row_ptr[r] == b.row_ptr[r + 1]);
-    while (em) {
-      const int i = __builtin_ctzll(em);
-      em &= em - 1;
-      for (int c = lane_id(); c < H; c += 64) m[(size_t)(r0 + i) * H + c] = 0.f;
-    }
-  }
-}
 
 // Receiver sums of rows held in the accumulator layout, added one edge after
 // the other in edge order (ascending sender), through a wave-private LDS

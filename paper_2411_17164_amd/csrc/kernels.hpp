@@ -43,6 +43,9 @@ struct MlpW {
   const float* b3;
   const float* gamma;
   const float* beta;
+  // BF16 edge MLPs at H = 256 and 512: weights in MFMA fragment order, k chunk
+  // by k chunk, as the streaming kernels walk them
+  const void* FS;   // forward: W1, W2
 };
 
 struct Shape {
@@ -82,6 +85,10 @@ void launch_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
 bool edge_fwd_chain(const Shape& s);
 void launch_edge_fwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                            void* e_out, float* m, void* z_out, void* a_out, hipStream_t st);
+// The BF16 gathered forward at H = 256 and 512 streams its weights (w.FS).
+bool edge_fwd_stream(const Shape& s);
+void launch_edge_fwd_stream(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
+                            void* e_out, float* m, void* z_out, void* a_out, hipStream_t st);
 // pr = W1_r h + b1, ps = W1_s h for every node (FP32 [n][H] each).
 void launch_node_proj(const Shape& s, const BatchView& b, const MlpW& w, const void* h, float* pr, float* ps,
                       hipStream_t st);
@@ -243,6 +250,7 @@ struct PrepJob {
   int dst_ld;
   int dst_col0;
   int rows, cols;
+  int frag;          // 1: dst in MFMA fragment order (rows, cols multiples of 16 and 32): k chunk, block, lane
 };
 void launch_prep(const float* params, void* blob, int prec, const PrepJob* jobs_dev, int n_jobs,
                  hipStream_t st);

@@ -1,4 +1,4 @@
-"""The H = 128 BF16 edge kernels where their work split can go wrong: a wave
+"""The BF16 edge kernels where their work split can go wrong: a wave
 takes whole receiver segments 16 edges at a time, so segments that straddle
 16-edge groups and tile ends, receivers without in-edges, and edge counts
 around one group and one workgroup's share are held against the oracle."""
@@ -45,11 +45,12 @@ def degree_graph(n, degrees, seed):
     (130, [1]),                 # a receiver per edge
     (515, [0, 9, 7, 0, 12]),    # a ragged last group in many workgroups
 ])
-def test_chain_edges(api, n, degrees, act, agg):
+@pytest.mark.parametrize("hidden", [128, 256, 512])
+def test_chain_edges(api, hidden, n, degrees, act, agg):
     """Outputs within 2e-2 of the oracle at the BF16-cast weights (the bar of
     the BF16 form), and under SiLU the whole gradient too (under ReLU a
     cloud this small has single kinks that BF16 rounding flips)."""
-    case = Case(1, levels=(n,), layers=2, precision="bf16", activation=act, aggregate=agg)
+    case = Case(1, levels=(n,), hidden=hidden, layers=2, precision="bf16", activation=act, aggregate=agg)
     G = degree_graph(n, degrees, 7)
     case._graph = G
     dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
@@ -58,7 +59,7 @@ def test_chain_edges(api, n, degrees, act, agg):
     p, node_in, pos, target = dev(case.params), dev(case.inp.node_in), dev(case.inp.pos), dev(case.inp.targets)
     out = torch.full((n, 4), float("nan"), device="cuda")
     d_out, loss, grad = torch.zeros_like(out), torch.zeros(1, device="cuda"), torch.full_like(p, float("nan"))
-    log(f"chain n={n} E={len(G.col)} {act} {agg}")
+    log(f"chain H={hidden} n={n} E={len(G.col)} {act} {agg}")
     ctx.forward(case.model(api), p, ps, [0], node_in, pos, case.inp.edge_norm, out)
     ctx.mse_grad(out, target, n, d_out, loss)
     ctx.backward(case.model(api), p, d_out, grad)
