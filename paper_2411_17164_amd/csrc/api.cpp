@@ -514,7 +514,7 @@ struct Batch {
 };
 
 struct BlockW {
-  int64_t W1 = -1, W2 = -1, W3 = -1, W1T = -1, W2T = -1, W3T = -1, Brs = -1, FS = -1;
+  int64_t W1 = -1, W2 = -1, W3 = -1, W1T = -1, W2T = -1, W3T = -1, Brs = -1, FS = -1, BS = -1;
 };
 
 struct xmgn_ctx {
@@ -904,6 +904,9 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
     if (d->precision == 1 && H > 128) {  // the streaming edge kernels' slabs
       we.FS = add_frag_job(c, W1e, 3 * H, 0, 0, H, 3 * H);
       add_frag_job(c, W2e, H, 0, 0, H, H);
+      we.BS = add_frag_job(c, W2e, H, 0, 0, H, H);
+      add_frag_job(c, W2e, H, 0, 1, H, H);
+      add_frag_job(c, W1e, 3 * H, 2 * H, 1, H, H);
     }
     BlockW& wn = c->bw[3 + 2 * l];
     const int64_t W1n = poff(d, 3, l, 0), W2n = poff(d, 3, l, 2);
@@ -938,6 +941,7 @@ static MlpW weights(const xmgn_ctx* c, const xmgn_model_desc* d, const float* pa
   w.W3T = ptr(b.W3T);
   w.Brs = ptr(b.Brs);
   w.FS = ptr(b.FS);
+  w.BS = ptr(b.BS);
   auto P = [&](int t) { return params + poff(d, block, layer, t); };
   if (block == 0 || block == 1) {
     w.W1f = P(0);
@@ -1360,7 +1364,7 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
   se.nw_edge = s.nw_edge_bwd;
   const bool fw = edge_bwd_fuses_wgrad(se);
   if (edge_bwd_chain(se, c->tape_z))
-    se.grid = edge_bwd_chain_grid((int)E);
+    se.grid = edge_bwd_chain_grid((int)H, (int)E);
   else if (fw)
     se.grid = std::min(s.grid, 512);
   const bool fnode = node_bwd_fuses_wgrad(s);

@@ -125,6 +125,21 @@ __device__ __forceinline__ void chain_gemm(f32x4 (&acc)[ET][MBS], const bf16x8* 
   if constexpr (BOUND) __builtin_amdgcn_sched_barrier(0);
 }
 
+// One exchange of a sum across lanes that halves the values a lane keeps: of
+// x[0 .. 2N), the lanes with `up` keep the upper half and send the lower to
+// their DPP partner, the others the reverse.
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float s) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL, int N>
+__device__ __forceinline__ void half_reduce(const float (&x)[2 * N], float (&y)[N], bool up) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const float keep = up ? x[N + k] : x[k], send = up ? x[k] : x[N + k];
+    y[k] = keep + dpp_mov<CTRL>(send);
+  }
+}
 // Sum over the 16 columns (features 32 w .. 32 w + 31 taken as li and
 // li + 16) of one 32-feature span, in the pairwise order of sum16 on a row
 // held one feature per lane: features li and li + 16 first, then pairs, quads,

@@ -347,18 +347,6 @@ __device__ __forceinline__ void tile_wgrad(f32x4 (&acc)[2][4], const unsigned ch
 // accumulator layout: value 4 mb + r), halving the values a lane keeps at each
 // exchange: lane li ends with the totals of two values, 2 k and 2 k + 1 with
 // k = colsum_slot(li).
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float s) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), CTRL, 0xF, 0xF, false));
-}
-template <int CTRL, int N>
-__device__ __forceinline__ void half_reduce(const float (&x)[2 * N], float (&y)[N], bool up) {
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const float keep = up ? x[N + k] : x[k], send = up ? x[k] : x[N + k];
-    y[k] = keep + dpp_mov<CTRL>(send);
-  }
-}
 // value index of the first of lane li's two totals
 __device__ __forceinline__ int colsum_slot(int li) {
   return ((li >> 3) & 1) * 16 + ((li >> 2) & 1) * 8 + ((li >> 1) & 1) * 4 + (li & 1) * 2;
@@ -632,9 +620,11 @@ __global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, 
       }
 }
 
-bool edge_bwd_chain(const Shape& s, bool ztape) { return s.prec == 1 && s.H == 128 && ztape; }
+bool edge_bwd_chain(const Shape& s, bool ztape) { return s.prec == 1 && ztape; }
 
-int edge_bwd_chain_grid(int E) { return std::max(1, std::min(256, (E + 127) / 128)); }
+int edge_bwd_chain_grid(int H, int E) {
+  return H == 128 ? std::max(1, std::min(256, (E + 127) / 128)) : edge_bwd_stream_grid(H, E);
+}
 
 void launch_edge_bwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* e, const void* zt,
                            const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o, hipStream_t st) {
@@ -643,7 +633,7 @@ void launch_edge_bwd_chain(const Shape& s, const BatchView& b, const MlpW& w, co
     return;
   }
   auto go = [&](auto act, auto agg) {
-    k_edge_bwd_chain<decltype(act)::value, decltype(agg)::value><<<edge_bwd_chain_grid(b.E), 512, 0, st>>>(
+    k_edge_bwd_chain<decltype(act)::value, decltype(agg)::value><<<edge_bwd_chain_grid(128, b.E), 512, 0, st>>>(
         b, w, (const bf16*)e, (const bf16*)zt, (const bf16*)at, de_in, dm, o, s.eps);
   };
   using I0 = std::integral_constant<int, 0>;

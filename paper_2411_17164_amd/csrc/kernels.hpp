@@ -46,6 +46,7 @@ struct MlpW {
   // BF16 edge MLPs at H = 256 and 512: weights in MFMA fragment order, k chunk
   // by k chunk, as the streaming kernels walk them
   const void* FS;   // forward: W1, W2
+  const void* BS;   // adjoint: W2, W2^T, e-block of W1^T
 };
 
 struct Shape {
@@ -126,11 +127,15 @@ void launch_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
                      const void* zt, const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o,
                      hipStream_t st);
 
-// The BF16 adjoint at H = 128 with z on the tape runs as wave-private chains
-// that accumulate dW2 and the e-block of dW1; its partials have
-// edge_bwd_chain_grid(E) rows.
+// The BF16 adjoint with z on the tape runs as wave-private chains: at H = 128
+// they accumulate dW2 and the e-block of dW1, at H = 256 and 512 they stream
+// their weights (w.BS) and write du.  Their partials have
+// edge_bwd_chain_grid(H, E) rows.
 bool edge_bwd_chain(const Shape& s, bool ztape);
-int edge_bwd_chain_grid(int E);
+int edge_bwd_chain_grid(int H, int E);
+int edge_bwd_stream_grid(int H, int E);
+void launch_edge_bwd_stream(const Shape& s, const BatchView& b, const MlpW& w, const void* zt, const void* at,
+                            const float* de_in, const float* dm, const EdgeBwdOut& o, hipStream_t st);
 void launch_edge_bwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* e, const void* zt,
                            const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o, hipStream_t st);
 

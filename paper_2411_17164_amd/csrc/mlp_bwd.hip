@@ -1170,7 +1170,7 @@ static void edge_bwd_nw(const Shape& s, const BatchView& b, const MlpW& w, const
         g_config_error = 1;
       } else if (!zt) {
         if (s.agg) go(I1{}, I0{}, nullptr, nullptr); else go(I0{}, I0{}, nullptr, nullptr);
-      } else if constexpr (!FW) {  // (else k_edge_bwd_chain)
+      } else if constexpr (sizeof(T) == 4) {  // (BF16: k_edge_bwd_chain, k_edge_bwd_stream)
         if (s.agg) go(I1{}, I1{}, (const T*)zt, (const T*)at); else go(I0{}, I1{}, (const T*)zt, (const T*)at);
       }
     } else {
@@ -1185,10 +1185,13 @@ bool edge_a_tape(const Shape& s) { return s.act != 0; }
 void launch_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                      const void* zt, const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o,
                      hipStream_t st) {
-  // z from the tape at H = 128 (BF16), at every size: W2, W2^T and the
+  // z from the tape (BF16), at every size; at H = 128 W2, W2^T and the
   // transposed e-block of W1 fit in LDS beside the waves' shares of the tile
   if (edge_bwd_chain(s, zt != nullptr)) {
-    launch_edge_bwd_chain(s, b, w, e, zt, at, de_in, dm, o, st);
+    if (s.H == 128)
+      launch_edge_bwd_chain(s, b, w, e, zt, at, de_in, dm, o, st);
+    else
+      launch_edge_bwd_stream(s, b, w, zt, at, de_in, dm, o, st);
     return;
   }
   if (s.nw_edge == 8)
