@@ -887,6 +887,13 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
   c->bw.assign(3 + 2 * L, BlockW{});
   for (int b = 0; b < 2; ++b) {
     BlockW& w = c->bw[b];
+    if (d->precision == 1 && H > 128) {  // the streaming encoders' slabs
+      w.FS = add_frag_job(c, poff(d, b, 0, 2), H, 0, 0, H, H);
+      add_frag_job(c, poff(d, b, 0, 4), H, 0, 0, H, H);
+      w.BS = add_frag_job(c, poff(d, b, 0, 4), H, 0, 1, H, H);
+      add_frag_job(c, poff(d, b, 0, 2), H, 0, 1, H, H);
+      continue;
+    }
     add_job(c, poff(d, b, 0, 2), H, 0, 0, H, H, w.W2);
     add_job(c, poff(d, b, 0, 4), H, 0, 0, H, H, w.W3);
     add_job(c, poff(d, b, 0, 2), H, 0, 1, H, H, w.W2T);
@@ -1345,7 +1352,7 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
   for (DBuf* p : {&c->fa, &c->fb, &c->fc, &c->fd})
     if (xmgn_status r = p->ensure(rows * H * ts, st)) return r;
   if (xmgn_status r = c->dy.ensure((size_t)c->cur->n_inner * 16 * 4, st)) return r;
-  if (xmgn_status r = c->part.ensure((size_t)G * 13 * H * 4, st)) return r;
+  if (xmgn_status r = c->part.ensure((size_t)std::max(G, 256) * 13 * H * 4, st)) return r;
   {
     size_t need = 0;
     const int Rs[3] = {(int)n, (int)E, c->cur->n_inner};
@@ -1486,16 +1493,15 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     const bool wide = blk == 0 && d->node_in > 8;
     EncBwdOut o{c->fa.p, c->fb.p, c->fc.p, c->fd.p, part, fe ? c->wfused.as<float>() : nullptr,
                 wide ? c->Sr.as<float>() : nullptr};
-    int R;
-    int in_dim;
+    const int R = blk == 1 ? (int)E : (int)n, in_dim = blk == 1 ? 4 : d->node_in;
+    if (enc_stream(s)) sn.grid = enc_stream_grid((int)H, R);
+    // (the streaming form's FP32 scratch: the adjoint buffers the layers are done with)
     if (blk == 1) {
-      { KT("enc_edge_bwd"); launch_enc_edge_bwd(sn, b, w, c->xe.as<float>(), de_in, o, st); }
-      R = (int)E;
-      in_dim = 4;
+      KT("enc_edge_bwd");
+      launch_enc_edge_bwd(sn, b, w, c->xe.as<float>(), de_in, o, de_out->as<float>(), st);
     } else {
-      { KT("enc_node_bwd"); launch_enc_node_bwd(sn, b, w, c->f_node_in, d->node_in, c->dhA.as<float>(), o, st); }
-      R = (int)n;
-      in_dim = d->node_in;
+      KT("enc_node_bwd");
+      launch_enc_node_bwd(sn, b, w, c->f_node_in, in_dim, c->dhA.as<float>(), o, c->dhMid.as<float>(), st);
     }
     VecSeg vs[5] = {{0, (int)H, P(blk, 0, 1)}, {(int)H, (int)H, P(blk, 0, 3)}, {2 * (int)H, (int)H, P(blk, 0, 5)},
                     {3 * (int)H, (int)H, P(blk, 0, 6)}, {4 * (int)H, (int)H, P(blk, 0, 7)}};

@@ -35,6 +35,14 @@ __device__ __forceinline__ void arrived(bf16x8& v) {
   v = __builtin_bit_cast(bf16x8, u);
 }
 
+// Ordering of LDS accesses between the lanes of one wave (a wave's LDS
+// instructions execute in order; this holds the compiler to it).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Swap of the odd 16-lane rows of a with the even rows of b.
 __device__ __forceinline__ void swap16(unsigned& a, unsigned& b) {
   const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
@@ -140,6 +148,20 @@ __device__ __forceinline__ void half_reduce(const float (&x)[2 * N], float (&y)[
     y[k] = keep + dpp_mov<CTRL>(send);
   }
 }
+// Column sums over the 16 rows of 64 features (four blocks): each lane ends
+// with one total, of feature 16 (li / 4) + 4 lg + li % 4 (li = lane % 16).
+__device__ __forceinline__ float colsum64(const f32x4 (&x)[4]) {
+  const int li = lane_id() & 15;
+  float v[16], a[8], b[4], c[2], d[1];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v[k] = x[k >> 2][k & 3];
+  half_reduce<0x140, 8>(v, a, li & 8);  // row_mirror: lane 15 - li
+  half_reduce<0x141, 4>(a, b, li & 4);  // row_half_mirror: lane 7 - li of its half
+  half_reduce<0x4E, 2>(b, c, li & 2);   // quad_perm [2,3,0,1]
+  half_reduce<0xB1, 1>(c, d, li & 1);   // quad_perm [1,0,3,2]
+  return d[0];
+}
+
 // Sum over the 16 columns (features 32 w .. 32 w + 31 taken as li and
 // li + 16) of one 32-feature span, in the pairwise order of sum16 on a row
 // held one feature per lane: features li and li + 16 first, then pairs, quads,

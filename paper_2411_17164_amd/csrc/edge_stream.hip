@@ -263,20 +263,6 @@ struct EdgeBwdStream {
   static_assert(NW * 4 * H * 8 <= RING, "the column sums fit in the ring");
 };
 
-// Column sums over the 16 rows of 64 features (four blocks): each lane ends
-// with one total, of feature 16 (li / 4) + 4 lg + li % 4 (li = lane % 16).
-__device__ __forceinline__ float colsum64(const f32x4 (&x)[4]) {
-  const int li = lane_id() & 15;
-  float v[16], a[8], b[4], c[2], d[1];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) v[k] = x[k >> 2][k & 3];
-  half_reduce<0x140, 8>(v, a, li & 8);  // row_mirror: lane 15 - li
-  half_reduce<0x141, 4>(a, b, li & 4);  // row_half_mirror: lane 7 - li of its half
-  half_reduce<0x4E, 2>(b, c, li & 2);   // quad_perm [2,3,0,1]
-  half_reduce<0xB1, 1>(c, d, li & 1);   // quad_perm [1,0,3,2]
-  return d[0];
-}
-
 template <int H, int ACT, int AGG>
 __global__ __launch_bounds__(EdgeBwdStream<H>::NT, EdgeBwdStream<H>::NW / 4) void k_edge_bwd_stream(
     BatchView b, MlpW w, const bf16* __restrict__ zt, const bf16* __restrict__ at, const float* __restrict__ de_in,

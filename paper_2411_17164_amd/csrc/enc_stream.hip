@@ -1,0 +1,531 @@
+// Encoders with streamed weights (BF16, H = 256 and 512; see stream.hpp):
+// y = LN(W3 act(W2 act(W1 x + b1) + b2) + b3), the input layer (at most 32
+// inputs) as FMA in the accumulator layout.  The workgroup-tile kernels they
+// replace loaded each H x H matrix from L2 for every 32 (16 at H = 512) rows
+// and spilled in the adjoint.  Edge encoder, 886k rows at H = 256: forward
+// 1,353 -> 322 us, adjoint 3,359 -> 1,121 us (its two kernels and their
+// reductions; FP32 dout in, z1, z2, du3, da2 out: bound by HBM); 442k rows at
+// H = 512, SiLU: 3,462 -> 866 us and 14,703 -> 2,604 us (bound by the weight
+// fragments, as the edge kernels).  The adjoint is two kernels because xhat,
+// the upstream gradient and both FP32 pre-activations of a row do not fit in a
+// wave's registers together.
+#include <algorithm>
+#include <type_traits>
+
+#include "kernels.hpp"
+#include "stream.hpp"
+
+namespace xmgn {
+
+template <int H>
+struct EncStream {
+  static constexpr int NW = H == 256 ? 8 : 4, NT = 64 * NW;
+  static constexpr int MBS = H / 16, KC = H / 32, S = 2 * KC;  // two H x H matrices
+  static constexpr size_t RING = 4 * MBS * 1024;
+  static constexpr size_t VEC = 5 * H * 4;  // b1, b2, b3, gamma, beta
+  static constexpr size_t BUF = 8192;       // per wave (second adjoint kernel): 16 rows x 128 FP32
+  static constexpr int SW = H / 4;          // LayerNorm span: the sums of four waves
+};
+// Input weights in LDS, [k][H]: 4 or 8 inputs; more are read from global memory.
+template <int H, int KIN>
+constexpr size_t enc_w1_bytes() {
+  return KIN <= 8 ? (size_t)KIN * H * 4 : 0;
+}
+
+// The rows of one wave: [begin, end) of R, and the workgroup's common number
+// of 16-row steps.
+struct WaveRows {
+  int begin, end, steps;
+  __device__ WaveRows(int R, int nw_wg) {
+    const int nw = gridDim.x * nw_wg, w0 = blockIdx.x * nw_wg, wv = w0 + __builtin_amdgcn_readfirstlane(wave_id());
+    begin = (int)((long long)R * wv / nw);
+    end = (int)((long long)R * (wv + 1) / nw);
+    steps = R > 0 ? (R / nw + 1 + 15) >> 4 : 0;  // (no range is longer than R / nw + 1)
+  }
+};
+
+// The input layer and its data: KIN = 4 (edge features), 8 (up to 8 node
+// inputs) or 32.
+template <int H, int KIN, int KIND>
+struct EncIn {
+  static constexpr int MBS = H / 16;
+  const float* src;
+  const int* gid;
+  const float* W1f;  // [H][in_dim]
+  const float* w1s;  // LDS [KIN][H] (KIN <= 8)
+  int in_dim;
+  float x[KIN];
+  // stage W1 (a barrier follows)
+  __device__ __forceinline__ void stage(float* dst, int nt) {
+    w1s = dst;
+    if constexpr (KIN <= 8)
+      for (int c = threadIdx.x; c < KIN * H; c += nt) {
+        const int k = c / H, f = c - k * H;
+        dst[c] = k < in_dim ? W1f[f * in_dim + k] : 0.f;
+      }
+  }
+  __device__ __forceinline__ void load(int row) {
+    if constexpr (KIND == 1) {
+      const float4 f = ((const float4*)src)[row];
+      x[0] = f.x;
+      x[1] = f.y;
+      x[2] = f.z;
+      x[3] = f.w;
+    } else {
+      const float* p = src + (size_t)gid[row] * in_dim;
+#pragma unroll
+      for (int k = 0; k < KIN; ++k) x[k] = k < in_dim ? p[k] : 0.f;
+    }
+  }
+  // block mb of a1 = b1 + W1 x
+  __device__ __forceinline__ f32x4 layer(const float* b1, int mb, int lg) const {
+    f32x4 a = *(const f32x4*)(b1 + 16 * mb + 4 * lg);
+    if constexpr (KIN <= 8) {
+#pragma unroll
+      for (int k = 0; k < KIN; ++k) {
+        const f32x4 wk = *(const f32x4*)(w1s + k * H + 16 * mb + 4 * lg);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[r] = __builtin_fmaf(wk[r], x[k], a[r]);
+      }
+    } else {
+      const float* p = W1f + (size_t)(16 * mb + 4 * lg) * in_dim;
+#pragma unroll
+      for (int k = 0; k < KIN; k += 4)
+        if (k < in_dim) {  // (a multiple of 4)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[r] = __builtin_fmaf(p[r * in_dim + k + j], x[k + j], a[r]);
+        }
+    }
+    return a;
+  }
+};
+
+// x = W xs over the KC chunks of slabs [s0, s0 + KC).
+template <int NW, int S, int MBS, int KC>
+__device__ __forceinline__ void stream_product(const WStream<NW, S, MBS>& ws, int s0, f32x4 (&x)[1][MBS],
+                                               const bf16x8 (&xs)[KC]) {
+  zero_acc(x);
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    const bf16x8 xc[1] = {xs[c]};
+    ws.begin(s0 + c);
+    slab_gemm(x, ws.frags(s0 + c), xc);
+    ws.end(s0 + c, s0, s0 + KC);
+  }
+}
+
+template <int H>
+__device__ __forceinline__ void stage_vecs(float* vec, const MlpW& w, int nt) {
+  for (int c = threadIdx.x; c < H; c += nt) {
+    vec[c] = w.b1[c];
+    vec[H + c] = w.b2[c];
+    vec[2 * H + c] = w.b3[c];
+    vec[3 * H + c] = w.gamma[c];
+    vec[4 * H + c] = w.beta[c];
+  }
+}
+
+// Adds the NW waves' column sums of one vector (each lane gives its values
+// through put(double* row of H)) and writes them to dst[f * stride].
+template <int H, int NW, typename PutFn>
+__device__ __forceinline__ void wg_colsum(double* ds, float* dst, int stride, PutFn put) {
+  __syncthreads();
+  put(ds + wave_id() * H);
+  __syncthreads();
+  for (int f = threadIdx.x; f < H; f += 64 * NW) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) s += ds[k * H + f];
+    dst[(size_t)f * stride] = (float)s;
+  }
+}
+// ... of totals in colsum64's layout, one per 64 features
+template <int H, int NW>
+__device__ __forceinline__ void wg_colsum64(double* ds, float* dst, const double (&v)[H / 64]) {
+  wg_colsum<H, NW>(ds, dst, 1, [&](double* d) {
+    const int l = lane_id(), li = l & 15, lg = l >> 4;
+#pragma unroll
+    for (int gr = 0; gr < H / 64; ++gr) d[64 * gr + 16 * (li >> 2) + 4 * lg + (li & 3)] = v[gr];
+  });
+}
+
+template <int H, int ACT, int KIN, int KIND>
+__global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_fwd_stream(
+    int rows, const int* __restrict__ gid, MlpW w, const float* __restrict__ src, int in_dim, bf16* __restrict__ out,
+    float eps) {
+  using L = EncStream<H>;
+  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC;
+  __shared__ __align__(16) unsigned char smem[L::RING + L::VEC + enc_w1_bytes<H, KIN>()];
+  float* vec = (float*)(smem + L::RING);
+  const WStream<NW, L::S, MBS> ws{(const unsigned char*)w.FS, smem};
+  EncIn<H, KIN, KIND> in{src, gid, w.W1f, nullptr, in_dim};
+  in.stage(vec + 5 * H, NT);
+  stage_vecs<H>(vec, w, NT);
+  const WaveRows wr(rows, NW);
+  const int last = max(wr.end - 1, 0);
+  if (wr.steps) in.load(min(wr.begin + (lane_id() & 15), last));
+  ws.start();
+  lds_sync();
+  for (int it = 0; it < wr.steps; ++it) {
+    const int l = opaque(lane_id()), li = l & 15, lg = l >> 4;
+    const int r0 = wr.begin + 16 * it;
+    const bool ok = r0 + li < wr.end;
+    auto vget = [&](int v, int mb) { return *(const f32x4*)(vec + v * H + 16 * mb + 4 * lg); };
+    f32x4 x[1][MBS];
+    bf16x8 z[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      f32x4 a0 = in.layer(vec, 2 * c, lg), a1 = in.layer(vec, 2 * c + 1, lg);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        a0[r] = act_f<ACT>(a0[r]);
+        a1[r] = act_f<ACT>(a1[r]);
+      }
+      z[c] = to_natural(a0, a1);
+    }
+    in.load(min(r0 + 16 + li, last));
+    stream_product(ws, 0, x, z);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      f32x4 a0 = x[0][2 * c] + vget(1, 2 * c), a1 = x[0][2 * c + 1] + vget(1, 2 * c + 1);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        a0[r] = act_f<ACT>(a0[r]);
+        a1[r] = act_f<ACT>(a1[r]);
+      }
+      z[c] = to_natural(a0, a1);
+    }
+    stream_product(ws, KC, x, z);
+#pragma unroll
+    for (int mb = 0; mb < MBS; ++mb) x[0][mb] += vget(2, mb);
+    ln_chain<H, L::SW>(x[0], eps);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      f32x4 y[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const f32x4 gm = vget(3, 2 * c + k), be = vget(4, 2 * c + k);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[k][r] = __builtin_fmaf(gm[r], x[0][2 * c + k][r], be[r]);
+      }
+      const bf16x8 v = to_natural(y[0], y[1]);
+      if (ok) *(bf16x8*)(out + (size_t)(r0 + li) * H + 32 * c + 8 * lg) = v;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Adjoint, first kernel: recomputes the chain to xhat, takes the LayerNorm
+// adjoint of dout and writes z1, z2 and du3 (and, under SiLU, a2 in FP32 for
+// the second kernel's derivative).
+// ---------------------------------------------------------------------------
+template <int H, int ACT, int KIN, int KIND>
+__global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_bwd1_stream(
+    int rows, const int* __restrict__ gid, MlpW w, const float* __restrict__ src, int in_dim,
+    const float* __restrict__ dout, EncBwdOut o, float* __restrict__ a2_out, float eps) {
+  using L = EncStream<H>;
+  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC, SW = L::SW, NB = SW / 16;
+  __shared__ __align__(16) unsigned char smem[L::RING + L::VEC + enc_w1_bytes<H, KIN>()];
+  float* vec = (float*)(smem + L::RING);
+  const WStream<NW, L::S, MBS> ws{(const unsigned char*)w.FS, smem};
+  EncIn<H, KIN, KIND> in{src, gid, w.W1f, nullptr, in_dim};
+  in.stage(vec + 5 * H, NT);
+  stage_vecs<H>(vec, w, NT);
+  const WaveRows wr(rows, NW);
+  const int last = max(wr.end - 1, 0);
+  if (wr.steps) in.load(min(wr.begin + (lane_id() & 15), last));
+  ws.start();
+  lds_sync();
+  double cb3[H / 64] = {}, cg[H / 64] = {}, cbt[H / 64] = {};
+  for (int it = 0; it < wr.steps; ++it) {
+    const int l = opaque(lane_id()), li = l & 15, lg = l >> 4;
+    const int r0 = wr.begin + 16 * it;
+    const bool ok = r0 + li < wr.end;
+    const size_t row = (size_t)min(r0 + li, last) * H;
+    auto vget = [&](int v, int mb) { return *(const f32x4*)(vec + v * H + 16 * mb + 4 * lg); };
+    auto put = [&](void* dst, const bf16x8(&v)[KC]) {
+      if (ok) {
+#pragma unroll
+        for (int c = 0; c < KC; ++c) *(bf16x8*)((bf16*)dst + row + 32 * c + 8 * lg) = v[c];
+      }
+    };
+    f32x4 x[1][MBS];
+    bf16x8 z[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      f32x4 a0 = in.layer(vec, 2 * c, lg), a1 = in.layer(vec, 2 * c + 1, lg);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        a0[r] = act_f<ACT>(a0[r]);
+        a1[r] = act_f<ACT>(a1[r]);
+      }
+      z[c] = to_natural(a0, a1);
+    }
+    in.load(min(r0 + 16 + li, last));
+    stream_product(ws, 0, x, z);
+    put(o.z1, z);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      f32x4 a[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        a[k] = x[0][2 * c + k] + vget(1, 2 * c + k);
+        if (ACT != 0 && ok) *(f32x4*)(a2_out + row + 16 * (2 * c + k) + 4 * lg) = a[k];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[k][r] = act_f<ACT>(a[k][r]);
+      }
+      z[c] = to_natural(a[0], a[1]);
+    }
+    stream_product(ws, KC, x, z);
+    put(o.z2, z);
+    // dout, one group of four blocks ahead
+    f32x4 pd[2][4];
+    auto load_dv = [&](int s, int gr) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) pd[s][k] = *(const f32x4*)(dout + row + 64 * gr + 16 * k + 4 * lg);
+    };
+    load_dv(0, 0);
+    load_dv(1, 1);
+#pragma unroll
+    for (int mb = 0; mb < MBS; ++mb) x[0][mb] += vget(2, mb);
+    const float inv = ln_chain<H, SW>(x[0], eps);
+    f32x4 g[MBS];
+    float sg = 0.f, sgx = 0.f, a[4], d[4];
+#pragma unroll
+    for (int gr = 0; gr < H / 64; ++gr) {
+      f32x4 dv[4], t[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dv[k][r] = ok ? pd[gr & 1][k][r] : 0.f;
+      if (gr + 2 < H / 64) load_dv(gr & 1, gr + 2);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) t[k] = dv[k] * x[0][4 * gr + k];
+      cg[gr] += (double)colsum64(t);
+      cbt[gr] += (double)colsum64(dv);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int mb = 4 * gr + k;
+        const f32x4 gm = vget(3, mb);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float p = dv[k][r] * gm[r];
+          a[r] = mb % NB ? __builtin_fmaf(dv[k][r], gm[r], a[r]) : p;
+          d[r] = mb % NB ? __builtin_fmaf(x[0][mb][r], p, d[r]) : x[0][mb][r] * p;
+          g[mb][r] = p;
+        }
+        if (mb % NB == NB - 1) {  // a span is whole
+          sg += add_xor32(add_xor16((a[0] + a[1]) + (a[2] + a[3])));
+          sgx += add_xor32(add_xor16((d[0] + d[1]) + (d[2] + d[3])));
+        }
+      }
+    }
+#pragma unroll
+    for (int gr = 0; gr < H / 64; ++gr) {
+      f32x4 t[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          t[k][r] = __builtin_fmaf(sgx * (-1.f / H), x[0][4 * gr + k][r], __builtin_fmaf(sg, -1.f / H, g[4 * gr + k][r])) * inv;
+      cb3[gr] += (double)colsum64(t);
+      z[2 * gr] = to_natural(t[0], t[1]);
+      z[2 * gr + 1] = to_natural(t[2], t[3]);
+    }
+    put(o.du3, z);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no weights on their way into the ring)
+  float* p = o.partial + (size_t)blockIdx.x * 13 * H;
+  wg_colsum64<H, NW>((double*)smem, p + 2 * H, cb3);
+  wg_colsum64<H, NW>((double*)smem, p + 3 * H, cg);
+  wg_colsum64<H, NW>((double*)smem, p + 4 * H, cbt);
+}
+
+// Adjoint, second kernel: dz2 = W3^T du3, da2, dz1 = W2^T da2, da1; writes da2,
+// and the input layer's gradient as column sums (KIN <= 8) or da1 in FP32.
+template <int H, int ACT, int KIN, int KIND>
+__global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_bwd2_stream(
+    int rows, const int* __restrict__ gid, MlpW w, const float* __restrict__ src, int in_dim, EncBwdOut o,
+    const float* __restrict__ a2) {
+  using L = EncStream<H>;
+  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC;
+  constexpr int NP = H / 128, KW = KIN <= 8 ? KIN : 0;
+  constexpr size_t HEAD = L::RING + L::VEC + enc_w1_bytes<H, KIN>();
+  // H = 512: the waves' buffers lie in the slot of the cycle's last slab, free
+  // from its products to the next step
+  constexpr bool ALIAS = HEAD + NW * L::BUF > 160 * 1024;
+  static_assert(!ALIAS || NW * L::BUF <= L::RING / 4, "the buffers fit in one slot");
+  __shared__ __align__(16) unsigned char smem[HEAD + (ALIAS ? 0 : NW * L::BUF)];
+  float* vec = (float*)(smem + L::RING);
+  float* buf = (float*)(smem + (ALIAS ? L::RING / 4 * 3 : HEAD) + wave_id() * L::BUF);
+  const WStream<NW, L::S, MBS> ws{(const unsigned char*)w.BS, smem};
+  EncIn<H, KIN, KIND> in{src, gid, w.W1f, nullptr, in_dim};
+  in.stage(vec + 5 * H, NT);
+  stage_vecs<H>(vec, w, NT);
+  const WaveRows wr(rows, NW);
+  const int last = max(wr.end - 1, 0);
+  bf16x8 du[KC];
+  auto load_du = [&](int r0) {
+    const int l = lane_id(), k = min(r0 + (l & 15), last);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) du[c] = *(const bf16x8*)((const bf16*)o.du3 + (size_t)k * H + 32 * c + 8 * (l >> 4));
+  };
+  if (wr.steps) load_du(wr.begin);
+  ws.start();
+  lds_sync();
+  double cb2[H / 64] = {}, cb1[NP][2] = {}, cw[NP][KW > 0 ? KW : 1][2] = {};
+  for (int it = 0; it < wr.steps; ++it) {
+    const int l = opaque(lane_id()), li = l & 15, lg = l >> 4;
+    const int r0 = wr.begin + 16 * it;
+    const bool ok = r0 + li < wr.end;
+    const size_t row = (size_t)min(r0 + li, last) * H;
+    if constexpr (ALIAS) lds_sync();  // every wave is done with its buffer
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      arrived(du[c]);
+      if (!ok) du[c] = bf16x8{};
+    }
+    in.load(min(r0 + li, last));
+    f32x4 x[1][MBS];
+    stream_product(ws, 0, x, du);
+    bf16x8 da[KC];
+#pragma unroll
+    for (int gr = 0; gr < H / 64; ++gr) {
+      f32x4 t[4];
+      if constexpr (ACT == 0) {  // a2 > 0 exactly where z2 > 0
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          from_natural(*(const bf16x8*)((const bf16*)o.z2 + row + 32 * (2 * gr + k) + 8 * lg), t[2 * k], t[2 * k + 1]);
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = *(const f32x4*)(a2 + row + 64 * gr + 16 * k + 4 * lg);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) t[k][r] = x[0][4 * gr + k][r] * act_d<ACT>(t[k][r]);
+      cb2[gr] += (double)colsum64(t);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        da[2 * gr + k] = to_natural(t[2 * k], t[2 * k + 1]);
+        if (ok) *(bf16x8*)((bf16*)o.da2 + row + 32 * (2 * gr + k) + 8 * lg) = da[2 * gr + k];
+      }
+    }
+    stream_product(ws, KC, x, da);
+    if (it + 1 < wr.steps) load_du(r0 + 16);  // in flight during the sums
+#pragma unroll
+    for (int mb = 0; mb < MBS; ++mb) {
+      const f32x4 a = in.layer(vec, mb, lg);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[0][mb][r] *= act_d<ACT>(a[r]);
+      if (KIN > 8 && ok) *(f32x4*)(o.da1 + row + 16 * mb + 4 * lg) = x[0][mb];
+    }
+    // sums over the rows of da1 and da1 x^T, row by row through the wave's
+    // buffer (lane l: features 2 l, 2 l + 1 of every 128)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      wave_sync();
+#pragma unroll
+      for (int k = 0; k < 8; ++k) *(f32x4*)(buf + li * 128 + (((4 * k + lg) ^ li) << 2)) = x[0][8 * p + k];
+      wave_sync();
+      float2 s = {0.f, 0.f}, sw[KW > 0 ? KW : 1];
+#pragma unroll
+      for (int k = 0; k < KW; ++k) sw[k] = float2{0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float2 v = *(const float2*)(buf + i * 128 + ((((l >> 1) ^ i) << 2) | ((l & 1) << 1)));
+        s.x += v.x;
+        s.y += v.y;
+#pragma unroll
+        for (int k = 0; k < KW; ++k) {
+          const float xi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, in.x[k]), i));
+          sw[k].x = __builtin_fmaf(v.x, xi, sw[k].x);
+          sw[k].y = __builtin_fmaf(v.y, xi, sw[k].y);
+        }
+      }
+      cb1[p][0] += (double)s.x;
+      cb1[p][1] += (double)s.y;
+#pragma unroll
+      for (int k = 0; k < KW; ++k) {
+        cw[p][k][0] += (double)sw[k].x;
+        cw[p][k][1] += (double)sw[k].y;
+      }
+    }
+    wave_sync();
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no weights on their way into the ring)
+  float* p = o.partial + (size_t)blockIdx.x * 13 * H;
+  double* ds = (double*)smem;
+  wg_colsum64<H, NW>(ds, p + H, cb2);
+  wg_colsum<H, NW>(ds, p, 1, [&](double* d) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      d[128 * q + 2 * lane_id()] = cb1[q][0];
+      d[128 * q + 2 * lane_id() + 1] = cb1[q][1];
+    }
+  });
+#pragma unroll
+  for (int k = 0; k < KW; ++k)
+    wg_colsum<H, NW>(ds, p + 5 * H + k, 8, [&](double* d) {
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        d[128 * q + 2 * lane_id()] = cw[q][k][0];
+        d[128 * q + 2 * lane_id() + 1] = cw[q][k][1];
+      }
+    });
+}
+
+// ---------------------------------------------------------------------------
+bool enc_stream(const Shape& s) { return s.prec == 1 && (s.H == 256 || s.H == 512); }
+
+int enc_stream_grid(int H, int R) {
+  const int rows = H == 256 ? 128 : 64;
+  return std::max(1, std::min(256, (R + rows - 1) / rows));
+}
+
+// f(H, ACT, KIN, KIND) as constants
+template <typename F>
+static void enc_dispatch(const Shape& s, int kind, int in_dim, F f) {
+  auto by = [&](auto hh, auto act) {
+    if (kind == 1)
+      f(hh, act, std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
+    else if (in_dim <= 8)
+      f(hh, act, std::integral_constant<int, 8>{}, std::integral_constant<int, 0>{});
+    else
+      f(hh, act, std::integral_constant<int, 32>{}, std::integral_constant<int, 0>{});
+  };
+  auto by_act = [&](auto hh) {
+    if (s.act)
+      by(hh, std::integral_constant<int, 1>{});
+    else
+      by(hh, std::integral_constant<int, 0>{});
+  };
+  if (s.H == 256)
+    by_act(std::integral_constant<int, 256>{});
+  else
+    by_act(std::integral_constant<int, 512>{});
+}
+
+void launch_enc_fwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
+                           void* out, hipStream_t st) {
+  enc_dispatch(s, kind, in_dim, [&](auto hh, auto act, auto kin, auto kd) {
+    constexpr int H = decltype(hh)::value;
+    k_enc_fwd_stream<H, decltype(act)::value, decltype(kin)::value, decltype(kd)::value>
+        <<<enc_stream_grid(H, R), EncStream<H>::NT, 0, st>>>(R, gid, w, src, in_dim, (bf16*)out, s.eps);
+  });
+}
+
+void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
+                           const float* dout, const EncBwdOut& o, float* a2, hipStream_t st) {
+  enc_dispatch(s, kind, in_dim, [&](auto hh, auto act, auto kin, auto kd) {
+    constexpr int H = decltype(hh)::value, A = decltype(act)::value, KIN = decltype(kin)::value, KD = decltype(kd)::value;
+    const int grid = enc_stream_grid(H, R);
+    k_enc_bwd1_stream<H, A, KIN, KD>
+        <<<grid, EncStream<H>::NT, 0, st>>>(R, gid, w, src, in_dim, dout, o, a2, s.eps);
+    k_enc_bwd2_stream<H, A, KIN, KD><<<grid, EncStream<H>::NT, 0, st>>>(R, gid, w, src, in_dim, o, a2);
+  });
+}
+
+}  // namespace xmgn

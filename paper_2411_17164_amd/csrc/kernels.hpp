@@ -43,10 +43,10 @@ struct MlpW {
   const float* b3;
   const float* gamma;
   const float* beta;
-  // BF16 edge MLPs at H = 256 and 512: weights in MFMA fragment order, k chunk
-  // by k chunk, as the streaming kernels walk them
-  const void* FS;   // forward: W1, W2
-  const void* BS;   // adjoint: W2, W2^T, e-block of W1^T
+  // BF16 edge MLPs and encoders at H = 256 and 512: weights in MFMA fragment
+  // order, k chunk by k chunk, as the streaming kernels walk them
+  const void* FS;   // forward: W1, W2 (edge MLP); W2, W3 (encoder)
+  const void* BS;   // adjoint: W2, W2^T, e-block of W1^T (edge MLP); W3^T, W2^T (encoder)
 };
 
 struct Shape {
@@ -186,9 +186,19 @@ inline int enc_edge_rows(const Shape& s) { return s.H == 128 ? s.mt_edge : s.mt_
 // z2, da2 and du3 are not written and wpart must be given).
 bool enc_bwd_fuses_wgrad(const Shape& s);
 void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, const float* node_in,
-                         int in_dim, const float* dh0, const EncBwdOut& o, hipStream_t st);
+                         int in_dim, const float* dh0, const EncBwdOut& o, float* a2, hipStream_t st);
 void launch_enc_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, const float* de0,
-                         const EncBwdOut& o, hipStream_t st);
+                         const EncBwdOut& o, float* a2, hipStream_t st);
+
+// The BF16 encoders at H = 256 and 512 stream their weights (w.FS, w.BS);
+// kind 0: node inputs src[gid[row]], 1: edge features src[row].  The adjoint's
+// partials have enc_stream_grid(H, R) rows; a2: FP32 [R][H] scratch (SiLU).
+bool enc_stream(const Shape& s);
+int enc_stream_grid(int H, int R);
+void launch_enc_fwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
+                           void* out, hipStream_t st);
+void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
+                           const float* dout, const EncBwdOut& o, float* a2, hipStream_t st);
 
 // ---- auxiliary ----
 // C[m][n] = sum_r A[ia(r)][a0 + m] * B[ib(r)][b0 + n] over r < R; partial

@@ -1237,9 +1237,13 @@ void launch_dec_bwd(const Shape& s, const BatchView& b, const MlpW& w, const voi
 }
 
 void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, const float* node_in, int in_dim,
-                         const float* dh0, const EncBwdOut& o, hipStream_t st) {
+                         const float* dh0, const EncBwdOut& o, float* a2, hipStream_t st) {
+  if (enc_stream(s)) {
+    launch_enc_bwd_stream(s, 0, b.n, b.gid, w, node_in, in_dim, dh0, o, a2, st);
+    return;
+  }
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
-    if constexpr (node_fits<T, H, MT>()) {
+    if constexpr (node_fits<T, H, MT>() && (sizeof(T) == 4 || H == 128)) {
       if (in_dim <= 8)
         k_enc_bwd<T, H, MT, ACT, 0, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
       else if (o.da1)
@@ -1253,9 +1257,13 @@ void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, cons
 }
 
 void launch_enc_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, const float* de0,
-                         const EncBwdOut& o, hipStream_t st) {
+                         const EncBwdOut& o, float* a2, hipStream_t st) {
+  if (enc_stream(s)) {
+    launch_enc_bwd_stream(s, 1, b.E, nullptr, w, xe, 4, de0, o, a2, st);
+    return;
+  }
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(enc_edge_rows(s), {
-    if constexpr (node_fits<T, H, MT>())
+    if constexpr (node_fits<T, H, MT>() && (sizeof(T) == 4 || H == 128))
       k_enc_bwd<T, H, MT, ACT, 1, 8><<<s.grid, NTHR, 0, st>>>(b.E, b, w, xe, 4, de0, o, s.eps);
     else
       g_config_error = 1;

@@ -721,19 +721,30 @@ void launch_node_fwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
 void launch_enc_node_fwd(const Shape& s, const BatchView& b, const MlpW& w, const float* node_in, int in_dim,
                          void* h0, hipStream_t st) {
   if (b.n == 0) return;
+  if (enc_stream(s)) {
+    launch_enc_fwd_stream(s, 0, b.n, b.gid, w, node_in, in_dim, h0, st);
+    return;
+  }
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
-    if (in_dim <= 8)
-      k_enc_fwd<T, H, MT, ACT, 0, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, (T*)h0, s.eps);
-    else
-      k_enc_fwd<T, H, MT, ACT, 0, 32><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, (T*)h0, s.eps);
+    if constexpr (sizeof(T) == 4 || H == 128) {
+      if (in_dim <= 8)
+        k_enc_fwd<T, H, MT, ACT, 0, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, (T*)h0, s.eps);
+      else
+        k_enc_fwd<T, H, MT, ACT, 0, 32><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, (T*)h0, s.eps);
+    }
   }))));
 }
 
 void launch_enc_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, void* e0,
                          hipStream_t st) {
   if (b.E == 0) return;
+  if (enc_stream(s)) {
+    launch_enc_fwd_stream(s, 1, b.E, nullptr, w, xe, 4, e0, st);
+    return;
+  }
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(enc_edge_rows(s), {
-    k_enc_fwd<T, H, MT, ACT, 1, 8><<<s.grid, NTHR, 0, st>>>(b.E, b, w, xe, 4, (T*)e0, s.eps);
+    if constexpr (sizeof(T) == 4 || H == 128)
+      k_enc_fwd<T, H, MT, ACT, 1, 8><<<s.grid, NTHR, 0, st>>>(b.E, b, w, xe, 4, (T*)e0, s.eps);
   }))));
 }
 

@@ -36,14 +36,6 @@ __device__ __forceinline__ int wave_rank(int nw_wg) {
   return (base + j) * nw_wg + __builtin_amdgcn_readfirstlane(wave_id());
 }
 
-// Ordering of LDS accesses between the lanes of one wave (a wave's LDS
-// instructions execute in order; this holds the compiler to it).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
 // Rows without in-edges: their sums are zero.
 __device__ __forceinline__ void zero_empty_rows(const BatchView& b, float* __restrict__ m, int H, int wv, int nw) {
   for (int r0 = wv * 64; r0 < b.n; r0 += nw * 64) {

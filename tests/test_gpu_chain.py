@@ -9,6 +9,8 @@ import pytest
 
 from cases import Case, log, oracle_refs, rel_l2
 from oracle import graph as og
+from oracle import model as om
+from synth import init_params
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +78,35 @@ def test_chain_edges(api, hidden, n, degrees, act, agg):
     ctx.forward(case.model(api), p, ps, [0], node_in, pos, case.inp.edge_norm, free, keep_tape=False)
     torch.cuda.synchronize()
     assert torch.equal(free, out)
+
+
+@pytest.mark.parametrize("hidden", [256, 512])
+@pytest.mark.parametrize("node_in", [1, 8, 12, 32])
+def test_stream_encoder_inputs(api, hidden, node_in):
+    """The streamed encoders at every way they take the node inputs (1 and 8 in
+    LDS, 12 and 32 from memory) and a ragged last group of rows, SiLU, held to
+    the bar of the BF16 form (outputs and whole gradient 2e-2)."""
+    n = 77
+    rng = np.random.default_rng(node_in)
+    G = degree_graph(n, [3, 5, 1], 3)
+    pos = rng.standard_normal((n, 3)).astype(np.float32)
+    x = rng.standard_normal((n, node_in)).astype(np.float32)
+    target = rng.standard_normal((n, 4)).astype(np.float32)
+    norm = np.array([[0, 0, 0, 1], [1, 1, 1, 0.5]], dtype=np.float32)
+    desc = om.Desc(hidden=hidden, layers=1, node_in=node_in, activation="silu")
+    params = init_params(om.param_entries(desc), 5)
+    model = api.Model(hidden, 1, node_in=node_in, activation="silu", precision="bf16")
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    ctx = api.Context(0)
+    ps = api.Partset.halo(api.Graph.from_csr(G.row_ptr, G.col), pos, None, 1)
+    p, out = dev(params), torch.zeros(n, 4, device="cuda")
+    d_out, loss, grad = torch.zeros_like(out), torch.zeros(1, device="cuda"), torch.zeros_like(p)
+    xd, pd = dev(x), dev(pos)
+    ctx.forward(model, p, ps, [0], xd, pd, norm, out)
+    ctx.mse_grad(out, dev(target), n, d_out, loss)
+    ctx.backward(model, p, d_out, grad)
+    torch.cuda.synchronize()
+    _, y, g = om.step_full(desc, om.amp_cast(desc, params), G, x, pos, norm, target)
+    e_out, e_grad = rel_l2(out.cpu().numpy(), y), rel_l2(grad.cpu().numpy(), g)
+    log(f"encoder H={hidden} node_in={node_in}: out {e_out:.2e} grad {e_grad:.2e}")
+    assert e_out <= 2e-2 and e_grad <= 2e-2
