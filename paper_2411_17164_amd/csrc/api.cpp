@@ -884,10 +884,11 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
   c->jobs.clear();
   c->blob_elems = 0;
   const int H = d->hidden, L = d->n_layers;
+  const bool stream = edge_stream(make_shape(c, d));
   c->bw.assign(3 + 2 * L, BlockW{});
   for (int b = 0; b < 2; ++b) {
     BlockW& w = c->bw[b];
-    if (d->precision == 1 && H > 128) {  // the streaming encoders' slabs
+    if (stream) {  // the streaming encoders' slabs
       w.FS = add_frag_job(c, poff(d, b, 0, 2), H, 0, 0, H, H);
       add_frag_job(c, poff(d, b, 0, 4), H, 0, 0, H, H);
       w.BS = add_frag_job(c, poff(d, b, 0, 4), H, 0, 1, H, H);
@@ -908,7 +909,7 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
     add_job(c, W1e, 3 * H, 2 * H, 1, H, H, we.W1T);  // [c][j] = W1[j][2H + c]
     add_job(c, W1e, 3 * H, 0, 1, H, H, we.Brs, 2 * H, 0);
     add_job(c, W1e, 3 * H, H, 1, H, H, we.Brs, 2 * H, H, false);
-    if (d->precision == 1 && H > 128) {  // the streaming edge kernels' slabs
+    if (stream) {  // the streaming edge kernels' slabs
       we.FS = add_frag_job(c, W1e, 3 * H, 0, 0, H, 3 * H);
       add_frag_job(c, W2e, H, 0, 0, H, H);
       we.BS = add_frag_job(c, W2e, H, 0, 0, H, H);
@@ -1219,7 +1220,7 @@ extern "C" xmgn_status xmgn_forward(xmgn_ctx* c, const xmgn_model_desc* d, const
   c->fwd_valid = false;
   if (xmgn_status r = ensure_batch(c, ps, part_ids, n_batch, s.mt_edge, s.mt_edge_bwd, st)) return r;
   if (xmgn_status r = ensure_wplan(c, d, st)) return r;
-  const bool keep_z = c->tape_hidden && edge_z_tape(s);
+  const bool keep_z = c->tape_hidden;
   if (xmgn_status r = ensure_tape(c, d, keep_tape != 0, keep_z, keep_z && edge_a_tape(s), st)) return r;
   const BatchView& b = c->cur->view;
   const int L = d->n_layers;
@@ -1370,10 +1371,10 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
   se.mt_edge = s.mt_edge_bwd;
   se.nw_edge = s.nw_edge_bwd;
   const bool fw = edge_bwd_fuses_wgrad(se);
-  if (edge_bwd_chain(se, c->tape_z))
-    se.grid = edge_bwd_chain_grid((int)H, (int)E);
-  else if (fw)
-    se.grid = std::min(s.grid, 512);
+  if (fw) se.grid = std::min(s.grid, 512);
+  // (the buffers take either policy's grid: a change of it allocates nothing)
+  const size_t ge = std::max(se.grid, edge_bwd_chain_grid(se, (int)E));
+  if (c->tape_z) se.grid = edge_bwd_chain_grid(se, (int)E);
   const bool fnode = node_bwd_fuses_wgrad(s);
   if (enc_bwd_fuses_wgrad(s) || fnode) {
     // encoders: [<=256][2][H][H]; node adjoint: [<=512][H][H]
@@ -1381,8 +1382,8 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     if (xmgn_status r = c->wfused.ensure(mats * H * H * 4, st)) return r;
   }
   if (fw)  // edge adjoint: [se.grid][2][H][H]
-    if (xmgn_status r = c->wfused_e.ensure((size_t)se.grid * 2 * H * H * 4, st)) return r;
-  if (xmgn_status r = c->part_e.ensure((size_t)se.grid * 4 * H * 4, st)) return r;
+    if (xmgn_status r = c->wfused_e.ensure(ge * 2 * H * H * 4, st)) return r;
+  if (xmgn_status r = c->part_e.ensure(ge * 4 * H * 4, st)) return r;
   // one layer's batch of reductions: at most 9 H x H matrices and 8 H-vectors
   const size_t red_cols = std::max<size_t>(std::max<size_t>(H * H, 16 * H), 9 * H * H + 8 * H);
   if (xmgn_status r = c->redtmp.ensure(reduce_tmp_floats((int)red_cols) * 4, st)) return r;
@@ -1453,7 +1454,7 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     const MlpW we = weights(c, d, params, 2 + 2 * l, 2, l);
     EdgeBwdOut eo{de_out->as<float>(), c->Sr.as<float>(), c->fa.p, c->fb.p, c->fc.p, c->part_e.as<float>(),
                   fw ? c->wfused_e.as<float>() : nullptr};
-    const void* zt = edge_z_tape(se) ? zslot(c, d, l) : nullptr;  // the forward's z, when it kept it
+    const void* zt = zslot(c, d, l);  // the forward's z, when it kept it
     const void* at = edge_a_tape(se) ? aslot(c, d, l) : nullptr;  // ... and a (SiLU)
     { KT("edge_bwd"); launch_edge_bwd(se, c->cur->view_b, we, hl(l), eslot(c, d, l), zt, at, de_in, c->dm.as<float>(), eo, st); }
     VecSeg es[4] = {{0, (int)H, P(2, l, 1)}, {(int)H, (int)H, P(2, l, 3)}, {2 * (int)H, (int)H, P(2, l, 4)},
@@ -1494,7 +1495,7 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     EncBwdOut o{c->fa.p, c->fb.p, c->fc.p, c->fd.p, part, fe ? c->wfused.as<float>() : nullptr,
                 wide ? c->Sr.as<float>() : nullptr};
     const int R = blk == 1 ? (int)E : (int)n, in_dim = blk == 1 ? 4 : d->node_in;
-    if (enc_stream(s)) sn.grid = enc_stream_grid((int)H, R);
+    if (enc_stream(s)) sn.grid = edge_stream_grid(s, R);
     // (the streaming form's FP32 scratch: the adjoint buffers the layers are done with)
     if (blk == 1) {
       KT("enc_edge_bwd");

@@ -375,9 +375,10 @@ __global__ void k_prep(const float* __restrict__ params, T* __restrict__ blob, c
     const float v = j.transpose ? params[j.src_off + (int64_t)k * j.src_ld + j.src_col0 + i]
                                 : params[j.src_off + (int64_t)i * j.src_ld + j.src_col0 + k];
     int64_t at = j.dst_off;
-    if (j.frag)  // k chunk, block of 16 rows, then lane (k / 8 % 4, row % 16) with 8 k each
-      at += ((int64_t)(k >> 5) * (j.rows >> 4) + (i >> 4)) * 512 + ((k >> 3 & 3) * 16 + (i & 15)) * 8 + (k & 7);
-    else
+    if (j.frag) {  // k chunk (4 E wide), block of 16 rows, then lane (k / E % 4, row % 16) with E k each
+      constexpr int E = 16 / sizeof(T);
+      at += (((int64_t)(k / (4 * E)) * (j.rows >> 4) + (i >> 4)) * 64 + (k / E % 4) * 16 + (i & 15)) * E + k % E;
+    } else
       at += (int64_t)i * j.dst_ld + j.dst_col0 + k;
     blob[at] = from_f<T>(v);
   }

@@ -29,10 +29,11 @@ __device__ __forceinline__ int opaque(int v) {
 }
 
 // Has the compiler wait for a loaded value here.
-__device__ __forceinline__ void arrived(bf16x8& v) {
+template <typename V>
+__device__ __forceinline__ void arrived(V& v) {
   u32x4 u = __builtin_bit_cast(u32x4, v);
   asm volatile("" : "+v"(u));
-  v = __builtin_bit_cast(bf16x8, u);
+  v = __builtin_bit_cast(V, u);
 }
 
 // Ordering of LDS accesses between the lanes of one wave (a wave's LDS

@@ -264,7 +264,7 @@ bool edge_fwd_chain(const Shape& s) { return s.prec == 1 && s.H == 128; }
 void launch_edge_fwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e, void* e_out,
                            float* m, void* z_out, void* a_out, hipStream_t st) {
   constexpr int NW = 8, ET = 1;
-  const int grid = std::max(1, std::min(256, (b.E + NW * 16 * ET - 1) / (NW * 16 * ET)));
+  const int grid = edge_bwd_chain_grid(s, b.E);
   auto go = [&](auto act, auto agg) {
     k_edge_fwd_chain<decltype(act)::value, decltype(agg)::value, NW, ET><<<grid, 64 * NW, 0, st>>>(
         b, w, (const bf16*)h, (const bf16*)e, (bf16*)e_out, m, (bf16*)z_out, (bf16*)a_out, s.eps);
@@ -620,10 +620,8 @@ __global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, 
       }
 }
 
-bool edge_bwd_chain(const Shape& s, bool ztape) { return s.prec == 1 && ztape; }
-
-int edge_bwd_chain_grid(int H, int E) {
-  return H == 128 ? std::max(1, std::min(256, (E + 127) / 128)) : edge_bwd_stream_grid(H, E);
+int edge_bwd_chain_grid(const Shape& s, int E) {
+  return edge_stream(s) ? edge_stream_grid(s, E) : std::max(1, std::min(256, (E + 47) / 48));
 }
 
 void launch_edge_bwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* e, const void* zt,
@@ -633,7 +631,7 @@ void launch_edge_bwd_chain(const Shape& s, const BatchView& b, const MlpW& w, co
     return;
   }
   auto go = [&](auto act, auto agg) {
-    k_edge_bwd_chain<decltype(act)::value, decltype(agg)::value><<<edge_bwd_chain_grid(128, b.E), 512, 0, st>>>(
+    k_edge_bwd_chain<decltype(act)::value, decltype(agg)::value><<<edge_bwd_chain_grid(s, b.E), 512, 0, st>>>(
         b, w, (const bf16*)e, (const bf16*)zt, (const bf16*)at, de_in, dm, o, s.eps);
   };
   using I0 = std::integral_constant<int, 0>;

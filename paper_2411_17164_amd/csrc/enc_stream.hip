@@ -1,4 +1,4 @@
-// Encoders with streamed weights (BF16, H = 256 and 512; see stream.hpp):
+// Encoders with streamed weights (see stream.hpp):
 // y = LN(W3 act(W2 act(W1 x + b1) + b2) + b3), the input layer (at most 32
 // inputs) as FMA in the accumulator layout.  The workgroup-tile kernels they
 // replace loaded each H x H matrix from L2 for every 32 (16 at H = 512) rows
@@ -6,7 +6,8 @@
 // 1,353 -> 322 us, adjoint 3,359 -> 1,121 us (its two kernels and their
 // reductions; FP32 dout in, z1, z2, du3, da2 out: bound by HBM); 442k rows at
 // H = 512, SiLU: 3,462 -> 866 us and 14,703 -> 2,604 us (bound by the weight
-// fragments, as the edge kernels).  The adjoint is two kernels because xhat,
+// fragments, as the edge kernels); FP32, 443k rows at H = 128: 345 -> 269 us and
+// 1,015 -> 687 us.  The adjoint is two kernels because xhat,
 // the upstream gradient and both FP32 pre-activations of a row do not fit in a
 // wave's registers together.
 #include <algorithm>
@@ -17,11 +18,9 @@
 
 namespace xmgn {
 
-template <int H>
-struct EncStream {
-  static constexpr int NW = H == 256 ? 8 : 4, NT = 64 * NW;
-  static constexpr int MBS = H / 16, KC = H / 32, S = 2 * KC;  // two H x H matrices
-  static constexpr size_t RING = 4 * MBS * 1024;
+template <typename T, int H, int W>
+struct EncStream : StreamDims<T, H, W> {
+  static constexpr int S = 2 * StreamDims<T, H>::SP;  // two H x H matrices
   static constexpr size_t VEC = 5 * H * 4;  // b1, b2, b3, gamma, beta
   static constexpr size_t BUF = 8192;       // per wave (second adjoint kernel): 16 rows x 128 FP32
   static constexpr int SW = H / 4;          // LayerNorm span: the sums of four waves
@@ -102,20 +101,6 @@ struct EncIn {
   }
 };
 
-// x = W xs over the KC chunks of slabs [s0, s0 + KC).
-template <int NW, int S, int MBS, int KC>
-__device__ __forceinline__ void stream_product(const WStream<NW, S, MBS>& ws, int s0, f32x4 (&x)[1][MBS],
-                                               const bf16x8 (&xs)[KC]) {
-  zero_acc(x);
-#pragma unroll
-  for (int c = 0; c < KC; ++c) {
-    const bf16x8 xc[1] = {xs[c]};
-    ws.begin(s0 + c);
-    slab_gemm(x, ws.frags(s0 + c), xc);
-    ws.end(s0 + c, s0, s0 + KC);
-  }
-}
-
 template <int H>
 __device__ __forceinline__ void stage_vecs(float* vec, const MlpW& w, int nt) {
   for (int c = threadIdx.x; c < H; c += nt) {
@@ -151,15 +136,17 @@ __device__ __forceinline__ void wg_colsum64(double* ds, float* dst, const double
   });
 }
 
-template <int H, int ACT, int KIN, int KIND>
-__global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_fwd_stream(
-    int rows, const int* __restrict__ gid, MlpW w, const float* __restrict__ src, int in_dim, bf16* __restrict__ out,
+template <typename T, int H, int W, int ACT, int KIN, int KIND>
+__global__ __launch_bounds__((StreamDims<T, H, W>::NT), (StreamDims<T, H, W>::NW / 4)) void k_enc_fwd_stream(
+    int rows, const int* __restrict__ gid, MlpW w, const float* __restrict__ src, int in_dim, T* __restrict__ out,
     float eps) {
-  using L = EncStream<H>;
-  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC;
+  using L = EncStream<T, H, W>;
+  using C = Chunk<T>;
+  using V = typename C::V;
+  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC, BLK = C::BLK;
   __shared__ __align__(16) unsigned char smem[L::RING + L::VEC + enc_w1_bytes<H, KIN>()];
   float* vec = (float*)(smem + L::RING);
-  const WStream<NW, L::S, MBS> ws{(const unsigned char*)w.FS, smem};
+  const WStream<NW, L::S, L::FR> ws{(const unsigned char*)w.FS, smem};
   EncIn<H, KIN, KIND> in{src, gid, w.W1f, nullptr, in_dim};
   in.stage(vec + 5 * H, NT);
   stage_vecs<H>(vec, w, NT);
@@ -173,45 +160,46 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
     const int r0 = wr.begin + 16 * it;
     const bool ok = r0 + li < wr.end;
     auto vget = [&](int v, int mb) { return *(const f32x4*)(vec + v * H + 16 * mb + 4 * lg); };
-    f32x4 x[1][MBS];
-    bf16x8 z[KC];
+    f32x4 x[MBS];
+    V z[KC];
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      f32x4 a0 = in.layer(vec, 2 * c, lg), a1 = in.layer(vec, 2 * c + 1, lg);
+      f32x4 a[BLK];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        a0[r] = act_f<ACT>(a0[r]);
-        a1[r] = act_f<ACT>(a1[r]);
+      for (int k = 0; k < BLK; ++k) {
+        a[k] = in.layer(vec, BLK * c + k, lg);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[k][r] = act_f<ACT>(a[k][r]);
       }
-      z[c] = to_natural(a0, a1);
+      z[c] = C::of(a);
     }
     in.load(min(r0 + 16 + li, last));
-    stream_product(ws, 0, x, z);
+    stream_product<T, H>(ws, 0, x, z);
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      f32x4 a0 = x[0][2 * c] + vget(1, 2 * c), a1 = x[0][2 * c + 1] + vget(1, 2 * c + 1);
+      f32x4 a[BLK];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        a0[r] = act_f<ACT>(a0[r]);
-        a1[r] = act_f<ACT>(a1[r]);
+      for (int k = 0; k < BLK; ++k) {
+        a[k] = x[BLK * c + k] + vget(1, BLK * c + k);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[k][r] = act_f<ACT>(a[k][r]);
       }
-      z[c] = to_natural(a0, a1);
+      z[c] = C::of(a);
     }
-    stream_product(ws, KC, x, z);
+    stream_product<T, H>(ws, L::SP, x, z);
 #pragma unroll
-    for (int mb = 0; mb < MBS; ++mb) x[0][mb] += vget(2, mb);
-    ln_chain<H, L::SW>(x[0], eps);
+    for (int mb = 0; mb < MBS; ++mb) x[mb] += vget(2, mb);
+    ln_chain<H, L::SW>(x, eps);
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      f32x4 y[2];
+      f32x4 y[BLK];
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const f32x4 gm = vget(3, 2 * c + k), be = vget(4, 2 * c + k);
+      for (int k = 0; k < BLK; ++k) {
+        const f32x4 gm = vget(3, BLK * c + k), be = vget(4, BLK * c + k);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) y[k][r] = __builtin_fmaf(gm[r], x[0][2 * c + k][r], be[r]);
+        for (int r = 0; r < 4; ++r) y[k][r] = __builtin_fmaf(gm[r], x[BLK * c + k][r], be[r]);
       }
-      const bf16x8 v = to_natural(y[0], y[1]);
-      if (ok) *(bf16x8*)(out + (size_t)(r0 + li) * H + 32 * c + 8 * lg) = v;
+      if (ok) *(V*)(out + (size_t)(r0 + li) * H + C::KW * c + C::E * lg) = C::of(y);
     }
   }
 }
@@ -221,15 +209,17 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
 // adjoint of dout and writes z1, z2 and du3 (and, under SiLU, a2 in FP32 for
 // the second kernel's derivative).
 // ---------------------------------------------------------------------------
-template <int H, int ACT, int KIN, int KIND>
-__global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_bwd1_stream(
+template <typename T, int H, int W, int ACT, int KIN, int KIND>
+__global__ __launch_bounds__((StreamDims<T, H, W>::NT), (StreamDims<T, H, W>::NW / 4)) void k_enc_bwd1_stream(
     int rows, const int* __restrict__ gid, MlpW w, const float* __restrict__ src, int in_dim,
     const float* __restrict__ dout, EncBwdOut o, float* __restrict__ a2_out, float eps) {
-  using L = EncStream<H>;
-  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC, SW = L::SW, NB = SW / 16;
+  using L = EncStream<T, H, W>;
+  using C = Chunk<T>;
+  using V = typename C::V;
+  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC, BLK = C::BLK, SW = L::SW, NB = SW / 16;
   __shared__ __align__(16) unsigned char smem[L::RING + L::VEC + enc_w1_bytes<H, KIN>()];
   float* vec = (float*)(smem + L::RING);
-  const WStream<NW, L::S, MBS> ws{(const unsigned char*)w.FS, smem};
+  const WStream<NW, L::S, L::FR> ws{(const unsigned char*)w.FS, smem};
   EncIn<H, KIN, KIND> in{src, gid, w.W1f, nullptr, in_dim};
   in.stage(vec + 5 * H, NT);
   stage_vecs<H>(vec, w, NT);
@@ -245,41 +235,36 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
     const bool ok = r0 + li < wr.end;
     const size_t row = (size_t)min(r0 + li, last) * H;
     auto vget = [&](int v, int mb) { return *(const f32x4*)(vec + v * H + 16 * mb + 4 * lg); };
-    auto put = [&](void* dst, const bf16x8(&v)[KC]) {
-      if (ok) {
-#pragma unroll
-        for (int c = 0; c < KC; ++c) *(bf16x8*)((bf16*)dst + row + 32 * c + 8 * lg) = v[c];
-      }
-    };
-    f32x4 x[1][MBS];
-    bf16x8 z[KC];
+    f32x4 x[MBS];
+    V z[KC];
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      f32x4 a0 = in.layer(vec, 2 * c, lg), a1 = in.layer(vec, 2 * c + 1, lg);
+      f32x4 a[BLK];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        a0[r] = act_f<ACT>(a0[r]);
-        a1[r] = act_f<ACT>(a1[r]);
-      }
-      z[c] = to_natural(a0, a1);
-    }
-    in.load(min(r0 + 16 + li, last));
-    stream_product(ws, 0, x, z);
-    put(o.z1, z);
-#pragma unroll
-    for (int c = 0; c < KC; ++c) {
-      f32x4 a[2];
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        a[k] = x[0][2 * c + k] + vget(1, 2 * c + k);
-        if (ACT != 0 && ok) *(f32x4*)(a2_out + row + 16 * (2 * c + k) + 4 * lg) = a[k];
+      for (int k = 0; k < BLK; ++k) {
+        a[k] = in.layer(vec, BLK * c + k, lg);
 #pragma unroll
         for (int r = 0; r < 4; ++r) a[k][r] = act_f<ACT>(a[k][r]);
       }
-      z[c] = to_natural(a[0], a[1]);
+      z[c] = C::of(a);
     }
-    stream_product(ws, KC, x, z);
-    put(o.z2, z);
+    in.load(min(r0 + 16 + li, last));
+    stream_product<T, H>(ws, 0, x, z);
+    if (ok) store_row((T*)o.z1 + row, z, lg);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      f32x4 a[BLK];
+#pragma unroll
+      for (int k = 0; k < BLK; ++k) {
+        a[k] = x[BLK * c + k] + vget(1, BLK * c + k);
+        if (ACT != 0 && ok) *(f32x4*)(a2_out + row + 16 * (BLK * c + k) + 4 * lg) = a[k];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[k][r] = act_f<ACT>(a[k][r]);
+      }
+      z[c] = C::of(a);
+    }
+    stream_product<T, H>(ws, L::SP, x, z);
+    if (ok) store_row((T*)o.z2 + row, z, lg);
     // dout, one group of four blocks ahead
     f32x4 pd[2][4];
     auto load_dv = [&](int s, int gr) {
@@ -289,8 +274,8 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
     load_dv(0, 0);
     load_dv(1, 1);
 #pragma unroll
-    for (int mb = 0; mb < MBS; ++mb) x[0][mb] += vget(2, mb);
-    const float inv = ln_chain<H, SW>(x[0], eps);
+    for (int mb = 0; mb < MBS; ++mb) x[mb] += vget(2, mb);
+    const float inv = ln_chain<H, SW>(x, eps);
     f32x4 g[MBS];
     float sg = 0.f, sgx = 0.f, a[4], d[4];
 #pragma unroll
@@ -302,7 +287,7 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
         for (int r = 0; r < 4; ++r) dv[k][r] = ok ? pd[gr & 1][k][r] : 0.f;
       if (gr + 2 < H / 64) load_dv(gr & 1, gr + 2);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) t[k] = dv[k] * x[0][4 * gr + k];
+      for (int k = 0; k < 4; ++k) t[k] = dv[k] * x[4 * gr + k];
       cg[gr] += (double)colsum64(t);
       cbt[gr] += (double)colsum64(dv);
 #pragma unroll
@@ -313,7 +298,7 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
         for (int r = 0; r < 4; ++r) {
           const float p = dv[k][r] * gm[r];
           a[r] = mb % NB ? __builtin_fmaf(dv[k][r], gm[r], a[r]) : p;
-          d[r] = mb % NB ? __builtin_fmaf(x[0][mb][r], p, d[r]) : x[0][mb][r] * p;
+          d[r] = mb % NB ? __builtin_fmaf(x[mb][r], p, d[r]) : x[mb][r] * p;
           g[mb][r] = p;
         }
         if (mb % NB == NB - 1) {  // a span is whole
@@ -329,12 +314,12 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
       for (int k = 0; k < 4; ++k)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          t[k][r] = __builtin_fmaf(sgx * (-1.f / H), x[0][4 * gr + k][r], __builtin_fmaf(sg, -1.f / H, g[4 * gr + k][r])) * inv;
+          t[k][r] = __builtin_fmaf(sgx * (-1.f / H), x[4 * gr + k][r], __builtin_fmaf(sg, -1.f / H, g[4 * gr + k][r])) * inv;
       cb3[gr] += (double)colsum64(t);
-      z[2 * gr] = to_natural(t[0], t[1]);
-      z[2 * gr + 1] = to_natural(t[2], t[3]);
+#pragma unroll
+      for (int k = 0; k < 4 / BLK; ++k) z[4 / BLK * gr + k] = C::of(*(const f32x4(*)[BLK])(t + BLK * k));
     }
-    put(o.du3, z);
+    if (ok) store_row((T*)o.du3 + row, z, lg);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no weights on their way into the ring)
   float* p = o.partial + (size_t)blockIdx.x * 13 * H;
@@ -345,12 +330,14 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
 
 // Adjoint, second kernel: dz2 = W3^T du3, da2, dz1 = W2^T da2, da1; writes da2,
 // and the input layer's gradient as column sums (KIN <= 8) or da1 in FP32.
-template <int H, int ACT, int KIN, int KIND>
-__global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_bwd2_stream(
+template <typename T, int H, int W, int ACT, int KIN, int KIND>
+__global__ __launch_bounds__((StreamDims<T, H, W>::NT), (StreamDims<T, H, W>::NW / 4)) void k_enc_bwd2_stream(
     int rows, const int* __restrict__ gid, MlpW w, const float* __restrict__ src, int in_dim, EncBwdOut o,
     const float* __restrict__ a2) {
-  using L = EncStream<H>;
-  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC;
+  using L = EncStream<T, H, W>;
+  using C = Chunk<T>;
+  using V = typename C::V;
+  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC, BLK = C::BLK;
   constexpr int NP = H / 128, KW = KIN <= 8 ? KIN : 0;
   constexpr size_t HEAD = L::RING + L::VEC + enc_w1_bytes<H, KIN>();
   // H = 512: the waves' buffers lie in the slot of the cycle's last slab, free
@@ -360,17 +347,16 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
   __shared__ __align__(16) unsigned char smem[HEAD + (ALIAS ? 0 : NW * L::BUF)];
   float* vec = (float*)(smem + L::RING);
   float* buf = (float*)(smem + (ALIAS ? L::RING / 4 * 3 : HEAD) + wave_id() * L::BUF);
-  const WStream<NW, L::S, MBS> ws{(const unsigned char*)w.BS, smem};
+  const WStream<NW, L::S, L::FR> ws{(const unsigned char*)w.BS, smem};
   EncIn<H, KIN, KIND> in{src, gid, w.W1f, nullptr, in_dim};
   in.stage(vec + 5 * H, NT);
   stage_vecs<H>(vec, w, NT);
   const WaveRows wr(rows, NW);
   const int last = max(wr.end - 1, 0);
-  bf16x8 du[KC];
+  V du[KC];
   auto load_du = [&](int r0) {
     const int l = lane_id(), k = min(r0 + (l & 15), last);
-#pragma unroll
-    for (int c = 0; c < KC; ++c) du[c] = *(const bf16x8*)((const bf16*)o.du3 + (size_t)k * H + 32 * c + 8 * (l >> 4));
+    load_row(du, (const T*)o.du3 + (size_t)k * H, l >> 4);
   };
   if (wr.steps) load_du(wr.begin);
   ws.start();
@@ -385,19 +371,19 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
       arrived(du[c]);
-      if (!ok) du[c] = bf16x8{};
+      if (!ok) du[c] = V{};
     }
     in.load(min(r0 + li, last));
-    f32x4 x[1][MBS];
-    stream_product(ws, 0, x, du);
-    bf16x8 da[KC];
+    f32x4 x[MBS];
+    stream_product<T, H>(ws, 0, x, du);
+    V da[KC];
 #pragma unroll
     for (int gr = 0; gr < H / 64; ++gr) {
       f32x4 t[4];
       if constexpr (ACT == 0) {  // a2 > 0 exactly where z2 > 0
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-          from_natural(*(const bf16x8*)((const bf16*)o.z2 + row + 32 * (2 * gr + k) + 8 * lg), t[2 * k], t[2 * k + 1]);
+        for (int k = 0; k < 4 / BLK; ++k)
+          C::to(*(const V*)((const T*)o.z2 + row + C::KW * (4 / BLK * gr + k) + C::E * lg), *(f32x4(*)[BLK])(t + BLK * k));
       } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k) t[k] = *(const f32x4*)(a2 + row + 64 * gr + 16 * k + 4 * lg);
@@ -405,22 +391,20 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
 #pragma unroll
       for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) t[k][r] = x[0][4 * gr + k][r] * act_d<ACT>(t[k][r]);
+        for (int r = 0; r < 4; ++r) t[k][r] = x[4 * gr + k][r] * act_d<ACT>(t[k][r]);
       cb2[gr] += (double)colsum64(t);
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        da[2 * gr + k] = to_natural(t[2 * k], t[2 * k + 1]);
-        if (ok) *(bf16x8*)((bf16*)o.da2 + row + 32 * (2 * gr + k) + 8 * lg) = da[2 * gr + k];
-      }
+      for (int k = 0; k < 4 / BLK; ++k) da[4 / BLK * gr + k] = C::of(*(const f32x4(*)[BLK])(t + BLK * k));
     }
-    stream_product(ws, KC, x, da);
+    if (ok) store_row((T*)o.da2 + row, da, lg);
+    stream_product<T, H>(ws, L::SP, x, da);
     if (it + 1 < wr.steps) load_du(r0 + 16);  // in flight during the sums
 #pragma unroll
     for (int mb = 0; mb < MBS; ++mb) {
       const f32x4 a = in.layer(vec, mb, lg);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) x[0][mb][r] *= act_d<ACT>(a[r]);
-      if (KIN > 8 && ok) *(f32x4*)(o.da1 + row + 16 * mb + 4 * lg) = x[0][mb];
+      for (int r = 0; r < 4; ++r) x[mb][r] *= act_d<ACT>(a[r]);
+      if (KIN > 8 && ok) *(f32x4*)(o.da1 + row + 16 * mb + 4 * lg) = x[mb];
     }
     // sums over the rows of da1 and da1 x^T, row by row through the wave's
     // buffer (lane l: features 2 l, 2 l + 1 of every 128)
@@ -428,7 +412,7 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
     for (int p = 0; p < NP; ++p) {
       wave_sync();
 #pragma unroll
-      for (int k = 0; k < 8; ++k) *(f32x4*)(buf + li * 128 + (((4 * k + lg) ^ li) << 2)) = x[0][8 * p + k];
+      for (int k = 0; k < 8; ++k) *(f32x4*)(buf + li * 128 + (((4 * k + lg) ^ li) << 2)) = x[8 * p + k];
       wave_sync();
       float2 s = {0.f, 0.f}, sw[KW > 0 ? KW : 1];
 #pragma unroll
@@ -478,53 +462,63 @@ __global__ __launch_bounds__(EncStream<H>::NT, EncStream<H>::NW / 4) void k_enc_
 }
 
 // ---------------------------------------------------------------------------
-bool enc_stream(const Shape& s) { return s.prec == 1 && (s.H == 256 || s.H == 512); }
+bool enc_stream(const Shape& s) { return edge_stream(s); }
 
-int enc_stream_grid(int H, int R) {
-  const int rows = H == 256 ? 128 : 64;
-  return std::max(1, std::min(256, (R + rows - 1) / rows));
-}
-
-// f(H, ACT, KIN, KIND) as constants
+// f(T{}, H, W, ACT, KIN, KIND) as constants
 template <typename F>
-static void enc_dispatch(const Shape& s, int kind, int in_dim, F f) {
-  auto by = [&](auto hh, auto act) {
+static void enc_dispatch(const Shape& s, int R, int kind, int in_dim, F f) {
+  using std::integral_constant;
+  using I0 = integral_constant<int, 0>;
+  using I1 = integral_constant<int, 1>;
+  auto by = [&](auto t, auto hh, auto ww, auto act) {
     if (kind == 1)
-      f(hh, act, std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
+      f(t, hh, ww, act, integral_constant<int, 4>{}, I1{});
     else if (in_dim <= 8)
-      f(hh, act, std::integral_constant<int, 8>{}, std::integral_constant<int, 0>{});
+      f(t, hh, ww, act, integral_constant<int, 8>{}, I0{});
     else
-      f(hh, act, std::integral_constant<int, 32>{}, std::integral_constant<int, 0>{});
+      f(t, hh, ww, act, integral_constant<int, 32>{}, I0{});
   };
-  auto by_act = [&](auto hh) {
+  auto by_act = [&](auto t, auto hh, auto ww) {
     if (s.act)
-      by(hh, std::integral_constant<int, 1>{});
+      by(t, hh, ww, I1{});
     else
-      by(hh, std::integral_constant<int, 0>{});
+      by(t, hh, ww, I0{});
   };
-  if (s.H == 256)
-    by_act(std::integral_constant<int, 256>{});
-  else
-    by_act(std::integral_constant<int, 512>{});
+  if (s.prec == 1) {
+    if (s.H == 256)
+      by_act(bf16{}, integral_constant<int, 256>{}, I0{});
+    else
+      by_act(bf16{}, integral_constant<int, 512>{}, I0{});
+  } else {
+    if (s.H == 128 && stream_small(s, R))
+      by_act(float{}, integral_constant<int, 128>{}, integral_constant<int, 4>{});
+    else if (s.H == 128)
+      by_act(float{}, integral_constant<int, 128>{}, I0{});
+    else
+      by_act(float{}, integral_constant<int, 256>{}, I0{});
+  }
 }
 
 void launch_enc_fwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
                            void* out, hipStream_t st) {
-  enc_dispatch(s, kind, in_dim, [&](auto hh, auto act, auto kin, auto kd) {
-    constexpr int H = decltype(hh)::value;
-    k_enc_fwd_stream<H, decltype(act)::value, decltype(kin)::value, decltype(kd)::value>
-        <<<enc_stream_grid(H, R), EncStream<H>::NT, 0, st>>>(R, gid, w, src, in_dim, (bf16*)out, s.eps);
+  enc_dispatch(s, R, kind, in_dim, [&](auto t, auto hh, auto ww, auto act, auto kin, auto kd) {
+    using T = decltype(t);
+    constexpr int H = decltype(hh)::value, W = decltype(ww)::value;
+    k_enc_fwd_stream<T, H, W, decltype(act)::value, decltype(kin)::value, decltype(kd)::value>
+        <<<edge_stream_grid(s, R), StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, (T*)out, s.eps);
   });
 }
 
 void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
                            const float* dout, const EncBwdOut& o, float* a2, hipStream_t st) {
-  enc_dispatch(s, kind, in_dim, [&](auto hh, auto act, auto kin, auto kd) {
-    constexpr int H = decltype(hh)::value, A = decltype(act)::value, KIN = decltype(kin)::value, KD = decltype(kd)::value;
-    const int grid = enc_stream_grid(H, R);
-    k_enc_bwd1_stream<H, A, KIN, KD>
-        <<<grid, EncStream<H>::NT, 0, st>>>(R, gid, w, src, in_dim, dout, o, a2, s.eps);
-    k_enc_bwd2_stream<H, A, KIN, KD><<<grid, EncStream<H>::NT, 0, st>>>(R, gid, w, src, in_dim, o, a2);
+  enc_dispatch(s, R, kind, in_dim, [&](auto t, auto hh, auto ww, auto act, auto kin, auto kd) {
+    using T = decltype(t);
+    constexpr int H = decltype(hh)::value, W = decltype(ww)::value, A = decltype(act)::value, KIN = decltype(kin)::value,
+                  KD = decltype(kd)::value;
+    const int grid = edge_stream_grid(s, R);
+    k_enc_bwd1_stream<T, H, W, A, KIN, KD>
+        <<<grid, StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, dout, o, a2, s.eps);
+    k_enc_bwd2_stream<T, H, W, A, KIN, KD><<<grid, StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, o, a2);
   });
 }
 

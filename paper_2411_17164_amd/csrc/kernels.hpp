@@ -43,8 +43,8 @@ struct MlpW {
   const float* b3;
   const float* gamma;
   const float* beta;
-  // BF16 edge MLPs and encoders at H = 256 and 512: weights in MFMA fragment
-  // order, k chunk by k chunk, as the streaming kernels walk them
+  // forms with streamed weights (edge_stream): MFMA fragment order, k chunk by
+  // k chunk, as the kernels walk them
   const void* FS;   // forward: W1, W2 (edge MLP); W2, W3 (encoder)
   const void* BS;   // adjoint: W2, W2^T, e-block of W1^T (edge MLP); W3^T, W2^T (encoder)
 };
@@ -75,7 +75,7 @@ void launch_enc_node_fwd(const Shape& s, const BatchView& b, const MlpW& w, cons
 void launch_edge_feat(const BatchView& b, const float* pos, EdgeNorm en, float* xe, hipStream_t st);
 void launch_enc_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, void* e0,
                          hipStream_t st);
-// z_out (or NULL): the hidden activation of every edge, for edge_z_tape forms;
+// z_out (or NULL): the hidden activation of every edge;
 // a_out (or NULL): its pre-activation, for edge_a_tape forms.
 // pr, ps (or NULL for the gathered form): the node projections of
 // launch_node_proj for this layer's edge MLP.
@@ -86,8 +86,10 @@ void launch_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
 bool edge_fwd_chain(const Shape& s);
 void launch_edge_fwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                            void* e_out, float* m, void* z_out, void* a_out, hipStream_t st);
-// The BF16 gathered forward at H = 256 and 512 streams its weights (w.FS).
-bool edge_fwd_stream(const Shape& s);
+// Every other form streams its weights (w.FS) through LDS.
+bool edge_stream(const Shape& s);
+bool stream_small(const Shape& s, int rows);     // so few rows that it runs four waves per workgroup
+int edge_stream_grid(const Shape& s, int rows);  // workgroups of a streaming kernel over so many rows
 void launch_edge_fwd_stream(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                             void* e_out, float* m, void* z_out, void* a_out, hipStream_t st);
 // pr = W1_r h + b1, ps = W1_s h for every node (FP32 [n][H] each).
@@ -119,7 +121,6 @@ void launch_wgrad_reduce(const float* partial, int n_chunks, int M_valid, int N,
 // True when the edge adjoint can read z from the forward's tape instead of
 // recomputing it (every form); zt is then that tape (else NULL: recompute),
 // and the unfused form does not write o.z (its dW2 product reads the tape).
-bool edge_z_tape(const Shape& s);
 // True when the forms that read z from the tape also need a (SiLU); at is
 // then the tape of pre-activations (else NULL).
 bool edge_a_tape(const Shape& s);
@@ -127,13 +128,11 @@ void launch_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
                      const void* zt, const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o,
                      hipStream_t st);
 
-// The BF16 adjoint with z on the tape runs as wave-private chains: at H = 128
-// they accumulate dW2 and the e-block of dW1, at H = 256 and 512 they stream
+// With z on the tape the adjoint runs as wave-private chains: in the BF16 form
+// at H = 128 they accumulate dW2 and the e-block of dW1, elsewhere they stream
 // their weights (w.BS) and write du.  Their partials have
-// edge_bwd_chain_grid(H, E) rows.
-bool edge_bwd_chain(const Shape& s, bool ztape);
-int edge_bwd_chain_grid(int H, int E);
-int edge_bwd_stream_grid(int H, int E);
+// edge_bwd_chain_grid(s, E) rows.
+int edge_bwd_chain_grid(const Shape& s, int E);
 void launch_edge_bwd_stream(const Shape& s, const BatchView& b, const MlpW& w, const void* zt, const void* at,
                             const float* de_in, const float* dm, const EdgeBwdOut& o, hipStream_t st);
 void launch_edge_bwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* e, const void* zt,
@@ -190,11 +189,10 @@ void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, cons
 void launch_enc_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, const float* de0,
                          const EncBwdOut& o, float* a2, hipStream_t st);
 
-// The BF16 encoders at H = 256 and 512 stream their weights (w.FS, w.BS);
-// kind 0: node inputs src[gid[row]], 1: edge features src[row].  The adjoint's
-// partials have enc_stream_grid(H, R) rows; a2: FP32 [R][H] scratch (SiLU).
+// The encoders of the same forms stream their weights (w.FS, w.BS); kind 0:
+// node inputs src[gid[row]], 1: edge features src[row].  The adjoint's partials
+// have edge_stream_grid(s, R) rows; a2: FP32 [R][H] scratch (SiLU).
 bool enc_stream(const Shape& s);
-int enc_stream_grid(int H, int R);
 void launch_enc_fwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
                            void* out, hipStream_t st);
 void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,

@@ -157,23 +157,16 @@ struct EdgeBwdLds {
   static constexpr size_t bytes = XS + ZS + NWS * WS + 2 * NW * MT * 4 + (3 * MT + 4) * 4;
 };
 
-// ZT: z of every edge comes from the forward's tape (zt) instead of
-// being recomputed -- no gather of h_r, h_s and no first product.  ReLU's
-// derivative is [z > 0], exactly [a > 0]; SiLU's takes a from the tape of
-// pre-activations (at, BF16).  Unfused (H = 256, 512), the dW2 product then
-// reads z from the tape too.
-template <typename T, int H, int MT, int ACT, int AGG, int FW, int NW, int ZT>
+template <typename T, int H, int MT, int ACT, int AGG, int FW, int NW>
 __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW>::bytes, NW)) void k_edge_bwd(
-    BatchView b, MlpW w, const T* __restrict__ h, const T* __restrict__ e, const T* __restrict__ zt,
-    const T* __restrict__ at, const float* __restrict__ de_in, const float* __restrict__ dm, EdgeBwdOut o,
-    float eps) {
+    BatchView b, MlpW w, const T* __restrict__ h, const T* __restrict__ e, const float* __restrict__ de_in,
+    const float* __restrict__ dm, EdgeBwdOut o, float eps) {
   using D = BD<T, H, NW>;
   using L = EdgeBwdLds<T, H, MT, FW, NW>;
   constexpr int MB = MT / 16, NB = D::NB;
   constexpr size_t XS = L::XS, ZS = L::ZS, WS = L::WS;
   constexpr int LDW = L::LDW, LDF = L::LDF;
   static_assert(!FW || (sizeof(T) == 2 && H == 128), "fused weight gradients: BF16, H = 128");
-  static_assert(!FW || !ZT, "fused weight gradients with z from the tape: k_edge_bwd_chain");
   static_assert((size_t)MT * LDF * 4 <= XS, "FP32 tile must fit in the staging tile");
   static_assert(!FW || (size_t)H * 4 <= 2 * H * sizeof(T), "FP32 rows must leave the e columns intact");
   __shared__ __align__(16) unsigned char smem[L::bytes];
@@ -217,53 +210,18 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
     }
     lds_sync();
     tile_segments(sg, rs, r0, r1, ne);  // read after the next barrier
-    if constexpr (ZT) {
-      // z rows into zs and (SiLU) a rows into the first H columns of xs, one
-      // batch of loads
-      constexpr int NPART = 1 + (ACT != 0 ? 1 : 0);
-      constexpr int E8 = 16 / sizeof(T), CPR = H / E8, TOT = NPART * MT * CPR, IT = TOT / (64 * NW);
-      static_assert(TOT % (64 * NW) == 0, "whole steps of the workgroup");
-      auto src = [&](int p) -> const T* { return p == 0 ? zt : at; };
-      auto dst = [&](int p, int i, int q) -> T* {
-        return p == 0 ? zs + i * D::LDH + q * E8 : xs + i * D::LD3 + q * E8;
-      };
-      uint4 v[IT];
-#pragma unroll
-      for (int k = 0; k < IT; ++k) {
-        const int c = (int)threadIdx.x + k * 64 * NW, p = c / (MT * CPR), rem = c - p * (MT * CPR);
-        const int i = rem / CPR, q = rem - i * CPR;
-        v[k] = uint4{0u, 0u, 0u, 0u};
-        if (i < ne) v[k] = *(const uint4*)(src(p) + (size_t)(e0 + i) * H + q * E8);
-      }
-#pragma unroll
-      for (int k = 0; k < IT; ++k) {
-        const int c = (int)threadIdx.x + k * 64 * NW, p = c / (MT * CPR), rem = c - p * (MT * CPR);
-        const int i = rem / CPR, q = rem - i * CPR;
-        *(uint4*)dst(p, i, q) = v[k];
-      }
-    } else {
-      gather_tile<T, D::LD3, MT, 3, H, 64 * NW>(
-          xs, ne,
-          [&](int p, int i) { return p == 0 ? h + (size_t)rs[i] * H : p == 1 ? h + (size_t)ss[i] * H : e + (size_t)(e0 + i) * H; },
-          [](int, int, int, const uint4&) {});
-    }
+    gather_tile<T, D::LD3, MT, 3, H, 64 * NW>(
+        xs, ne,
+        [&](int p, int i) { return p == 0 ? h + (size_t)rs[i] * H : p == 1 ? h + (size_t)ss[i] * H : e + (size_t)(e0 + i) * H; },
+        [](int, int, int, const uint4&) {});
     if (t + sch.step < sch.end) nx.load(b, t + sch.step);  // next tile's indices, in flight from here
     lds_sync();
 
-    // recompute: a, z, u, xhat (ZT, ReLU: a holds z, whose sign is a's)
+    // recompute: a, z, u, xhat
     f32x4 a[MB][NB];
     f32x4 x[MB][NB];
     zero_acc(a);
-    if constexpr (ZT) {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            a[mb][nb][r] = ACT == 0 ? to_f(zs[acc_row(mb, r) * D::LDH + acc_col(n0, nb)])
-                                    : to_f(xs[acc_row(mb, r) * D::LD3 + acc_col(n0, nb)]);
-    } else if constexpr (FW) {
+    if constexpr (FW) {
       wave_gemm<T, MB, NB, 2 * H, D::LD3>(a, xs, W1, 3 * H, n0);  // [h_r ; h_s] blocks from global
       wave_gemm_lds<MB, NB, H, D::LD3>(a, (const bf16*)xs + 2 * H, [&](int k, int nb) {
         return *(const bf16x8*)(W1es + (n0 + 16 * nb + li) * LDW + k + 8 * lg);
@@ -271,21 +229,19 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
     } else {
       wave_gemm<T, MB, NB, 3 * H, D::LD3>(a, xs, W1, 3 * H, n0);
     }
-    if constexpr (!ZT) {
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const float bb = w.b1[acc_col(n0, nb)];
+      for (int nb = 0; nb < NB; ++nb) {
+        const float bb = w.b1[acc_col(n0, nb)];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            a[mb][nb][r] += bb;
-            x[mb][nb][r] = act_f<ACT>(a[mb][nb][r]);
-          }
+        for (int r = 0; r < 4; ++r) {
+          a[mb][nb][r] += bb;
+          x[mb][nb][r] = act_f<ACT>(a[mb][nb][r]);
         }
-      acc_to_lds<T, MB, NB, D::LDH>(x, zs, n0);
-      lds_sync();
-    }
+      }
+    acc_to_lds<T, MB, NB, D::LDH>(x, zs, n0);
+    lds_sync();
     zero_acc(x);
     if constexpr (FW) {
       wave_gemm_lds<MB, NB, H, D::LDH>(x, (const bf16*)zs, [&](int k, int nb) {
@@ -310,7 +266,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
         ne, de_in != nullptr, [&](int i, int q) { return *(const float4*)(dm + (size_t)rs[i] * H + 4 * q); },
         [&](int i, int q) { return *(const float4*)(de_in + (size_t)(e0 + i) * H + 4 * q); },
         [&](int i, int q, const float4& v) { *(float4*)(ft + i * LDF + 4 * q) = v; });
-    if constexpr (!FW && !ZT) lds_rows_to_global<T, D::LDH>(zs, ne, H, (T*)o.z + (size_t)e0 * H, H, [](int i) { return i; });
+    if constexpr (!FW) lds_rows_to_global<T, D::LDH>(zs, ne, H, (T*)o.z + (size_t)e0 * H, H, [](int i) { return i; });
     lds_sync();
     f32x4 g[MB][NB];
 #pragma unroll
@@ -1155,49 +1111,41 @@ bool edge_bwd_fuses_wgrad(const Shape& s) { return s.prec == 1 && s.H == 128; }
 
 template <int NW>
 static void edge_bwd_nw(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
-                        const void* zt, const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o,
-                        hipStream_t st) {
+                        const float* de_in, const float* dm, const EdgeBwdOut& o, hipStream_t st) {
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT_EDGE(s.mt_edge, {
     constexpr int FW = (sizeof(T) == 2 && H == 128) ? 1 : 0;
     if constexpr (edge_bwd_fits<T, H, MT>()) {
-      auto go = [&](auto agg, auto zz, const T* z, const T* av) {
-        k_edge_bwd<T, H, MT, ACT, decltype(agg)::value, FW, NW, decltype(zz)::value><<<s.grid, 64 * NW, 0, st>>>(
-            b, w, (const T*)h, (const T*)e, z, av, de_in, dm, o, s.eps);
+      auto go = [&](auto agg) {
+        k_edge_bwd<T, H, MT, ACT, decltype(agg)::value, FW, NW><<<s.grid, 64 * NW, 0, st>>>(
+            b, w, (const T*)h, (const T*)e, de_in, dm, o, s.eps);
       };
       using I0 = std::integral_constant<int, 0>;
       using I1 = std::integral_constant<int, 1>;
-      if (zt && ACT != 0 && !at) {
-        g_config_error = 1;
-      } else if (!zt) {
-        if (s.agg) go(I1{}, I0{}, nullptr, nullptr); else go(I0{}, I0{}, nullptr, nullptr);
-      } else if constexpr (sizeof(T) == 4) {  // (BF16: k_edge_bwd_chain, k_edge_bwd_stream)
-        if (s.agg) go(I1{}, I1{}, (const T*)zt, (const T*)at); else go(I0{}, I1{}, (const T*)zt, (const T*)at);
-      }
+      if (s.agg) go(I1{}); else go(I0{});
     } else {
       g_config_error = 1;
     }
   }))));
 }
 
-bool edge_z_tape(const Shape&) { return true; }
 bool edge_a_tape(const Shape& s) { return s.act != 0; }
 
 void launch_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                      const void* zt, const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o,
                      hipStream_t st) {
-  // z from the tape (BF16), at every size; at H = 128 W2, W2^T and the
-  // transposed e-block of W1 fit in LDS beside the waves' shares of the tile
-  if (edge_bwd_chain(s, zt != nullptr)) {
-    if (s.H == 128)
-      launch_edge_bwd_chain(s, b, w, e, zt, at, de_in, dm, o, st);
-    else
+  // z from the tape; BF16 at H = 128: W2, W2^T and the transposed e-block of W1
+  // fit in LDS beside the waves' shares of the tile
+  if (zt) {
+    if (edge_stream(s))
       launch_edge_bwd_stream(s, b, w, zt, at, de_in, dm, o, st);
+    else
+      launch_edge_bwd_chain(s, b, w, e, zt, at, de_in, dm, o, st);
     return;
   }
   if (s.nw_edge == 8)
-    edge_bwd_nw<8>(s, b, w, h, e, zt, at, de_in, dm, o, st);
+    edge_bwd_nw<8>(s, b, w, h, e, de_in, dm, o, st);
   else
-    edge_bwd_nw<4>(s, b, w, h, e, zt, at, de_in, dm, o, st);
+    edge_bwd_nw<4>(s, b, w, h, e, de_in, dm, o, st);
 }
 
 void launch_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const float* m,
@@ -1243,7 +1191,7 @@ void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, cons
     return;
   }
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
-    if constexpr (node_fits<T, H, MT>() && (sizeof(T) == 4 || H == 128)) {
+    if constexpr (sizeof(T) == 2 && H == 128) {
       if (in_dim <= 8)
         k_enc_bwd<T, H, MT, ACT, 0, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
       else if (o.da1)
@@ -1263,7 +1211,7 @@ void launch_enc_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, cons
     return;
   }
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(enc_edge_rows(s), {
-    if constexpr (node_fits<T, H, MT>() && (sizeof(T) == 4 || H == 128))
+    if constexpr (sizeof(T) == 2 && H == 128)
       k_enc_bwd<T, H, MT, ACT, 1, 8><<<s.grid, NTHR, 0, st>>>(b.E, b, w, xe, 4, de0, o, s.eps);
     else
       g_config_error = 1;

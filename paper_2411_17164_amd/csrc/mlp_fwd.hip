@@ -22,64 +22,52 @@ struct Dims {
 };
 
 // ---------------------------------------------------------------------------
-// Fused edge processor, forward (Eq. 1-2):
+// Fused edge processor, forward (Eq. 1-2), split form:
 //   x = [h_r ; h_s ; e],  v = LN(W2 act(W1 x + b1) + b2),  e' = e + v,
-//   m_r = sum over the tile-local segment of r of v (or of e').
+//   m_r = sum over the tile-local segment of r of v (or of e'),
+// with W1 x + b1 = W1_e e + (W1_r h_r + b1) + W1_s h_s, the last two read per
+// edge from the FP32 node projections pr and ps (k_node_proj): the value of
+// the gathered form up to the rounding order of the sum.
 // A tile holds whole receiver segments, so m_r is summed in one workgroup in
 // ascending sender order (the CSR order) -- deterministic, no atomics.
 // ---------------------------------------------------------------------------
 // NW waves per workgroup; each wave owns H / NW output columns of every GEMM.
-// Gathered form: [h_s ; e] per edge (stride LD2) and h_r once per receiver
-// of the tile (the tile's receivers are consecutive rows of h; MT rows at
-// most), the first product reading each edge's h_r row through its
-// receiver's tile-local index.
-// SPLIT: the first layer's node blocks come precomputed per node (see
-// k_node_proj), so only the e rows are gathered.  The FP32 tile of the
-// segment sums aliases the staging tile; where it would be the larger (the
-// split form), it holds one half of the columns at a time (NH = 2).
-template <typename T, int H, int MT, int NW, int SPLIT = 0>
-struct EdgeFwdLds {
+// The FP32 tile of the segment sums aliases the staging tile and holds one
+// half of the columns at a time.
+template <typename T, int H, int MT, int NW>
+struct EdgeSplitLds {
   using D = Dims<T, H, NW>;
-  static constexpr size_t ES = (size_t)MT * (SPLIT ? D::LDH : D::LD2) * sizeof(T);  // per-edge rows
-  static constexpr size_t GS = ES + (SPLIT ? 0 : (size_t)MT * D::LDH * sizeof(T));  // + receiver rows
+  static constexpr size_t GS = (size_t)MT * D::LDH * sizeof(T);  // e rows
   static constexpr int NH = (size_t)MT * D::LDF * 4 > GS ? 2 : 1;
   static constexpr int LDFH = H / NH + 4;
   static constexpr size_t FS = (size_t)MT * LDFH * 4;
   static constexpr size_t XS = FS > GS ? FS : GS;
   static constexpr size_t ZS = (size_t)MT * D::LDH * sizeof(T);
-  // receivers, senders, segment starts (MT + 1, padded)
-  static constexpr size_t bytes = XS + ZS + 2 * NW * MT * 4 + (3 * MT + 4) * 4;
+  static constexpr size_t bytes = XS + ZS + 2 * NW * MT * 4 + 2 * MT * 4;  // + receivers, senders
 };
 
 // z_out (or NULL): the hidden activation z = act(W1 x + b1) of every edge,
 // kept for the adjoint; a_out (or NULL): its pre-activation a = W1 x + b1
 // (SiLU's derivative needs a).
-// SPLIT = 1: W1 x + b1 = W1_e e + (W1_r h_r + b1) + W1_s h_s, the last two
-// read per edge from the FP32 node projections pr and ps (same value as the
-// gathered form up to the rounding order of the sum).
-template <typename T, int H, int MT, int ACT, int AGG, int NW, int SPLIT>
-__global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeFwdLds<T, H, MT, NW, SPLIT>::bytes, NW)) void k_edge_fwd(
+template <typename T, int H, int MT, int ACT, int AGG, int NW>
+__global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeSplitLds<T, H, MT, NW>::bytes, NW)) void k_edge_fwd_split(
     BatchView b, MlpW w, const T* __restrict__ h, const T* __restrict__ e, T* __restrict__ e_out,
     float* __restrict__ m, T* __restrict__ z_out, T* __restrict__ a_out, const float* __restrict__ pr,
     const float* __restrict__ ps, float eps) {
   using D = Dims<T, H, NW>;
-  using L = EdgeFwdLds<T, H, MT, NW, SPLIT>;
-  constexpr int LDX = SPLIT ? D::LDH : D::LD2;  // staging row stride
-  constexpr int EC = SPLIT ? 0 : H;              // column of e in a staged row
+  using L = EdgeSplitLds<T, H, MT, NW>;
+  constexpr int LDX = D::LDH;
   constexpr int MB = MT / 16, NB = D::NB;
   constexpr size_t XS = L::XS, ZS = L::ZS;
   constexpr int NH = L::NH, HH = H / NH, LDFH = L::LDFH;
-  static_assert(NH == 1 || !SPLIT || D::CPW <= HH, "a wave's columns lie in one half");
-  static_assert(SPLIT || NH == 1, "the gathered tile holds the whole FP32 tile");
+  static_assert(NH == 1 || D::CPW <= HH, "a wave's columns lie in one half");
   __shared__ __align__(16) unsigned char smem[L::bytes];
   T* xs = (T*)smem;
-  T* hr = (T*)(smem + L::ES);  // gathered form: h_r of the tile's receivers
-  float* ft = (float*)smem;  // aliases xs once the gathered tile is dead
+  float* ft = (float*)smem;  // aliases xs once the staged tile is dead
   T* zs = (T*)(smem + XS);
   float* red = (float*)(smem + XS + ZS);
   int* rs = (int*)(red + 2 * NW * MT);
   int* ss = rs + MT;
-  int* sg = rs + 2 * MT;
   const T* W1 = (const T*)w.W1;
   const T* W2 = (const T*)w.W2;
   const int n0 = wave_id() * D::CPW;
@@ -95,84 +83,42 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeFwdLds<T, H, MT, NW, SP
       ss[threadIdx.x] = cur.cv;
     }
     lds_sync();
-    if constexpr (!SPLIT) tile_segments(sg, rs, r0, r1, ne);  // read after the next barrier
     f32x4 acc[MB][NB];
-    if constexpr (SPLIT) {
-      gather_tile<T, D::LDH, MT, 1, H, 64 * NW>(
-          xs, ne, [&](int, int i) { return e + (size_t)(e0 + i) * H; }, [](int, int, int, const uint4&) {});
-      // the node blocks of the first product, in the accumulator layout:
-      // acc = P_r[receiver] + P_s[sender], in flight during the barrier
-      f32x4 sv[MB][NB];
+    gather_tile<T, D::LDH, MT, 1, H, 64 * NW>(
+        xs, ne, [&](int, int i) { return e + (size_t)(e0 + i) * H; }, [](int, int, int, const uint4&) {});
+    // the node blocks of the first product, in the accumulator layout:
+    // acc = P_r[receiver] + P_s[sender], in flight during the barrier
+    f32x4 sv[MB][NB];
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = acc_row(mb, r);
-          const float* prow = pr + (size_t)rs[row] * H + n0 + (lane_id() & 15);
-          const float* srow = ps + (size_t)ss[row] * H + n0 + (lane_id() & 15);
+      for (int r = 0; r < 4; ++r) {
+        const int row = acc_row(mb, r);
+        const float* prow = pr + (size_t)rs[row] * H + n0 + (lane_id() & 15);
+        const float* srow = ps + (size_t)ss[row] * H + n0 + (lane_id() & 15);
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) {
-            acc[mb][nb][r] = prow[16 * nb];
-            sv[mb][nb][r] = srow[16 * nb];
-          }
+        for (int nb = 0; nb < NB; ++nb) {
+          acc[mb][nb][r] = prow[16 * nb];
+          sv[mb][nb][r] = srow[16 * nb];
         }
-      ip.advance(b, sch, t);  // next tile's indices and the bounds after, in flight from here
-      lds_sync();
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[mb][nb][r] += sv[mb][nb][r];
-      wave_gemm<T, MB, NB, H, D::LDH>(acc, xs, W1 + 2 * H, 3 * H, n0);  // + W1_e e
-    } else {
-      // one batch of loads: h_r of the nr receivers (consecutive rows of h),
-      // then h_s and e of the ne edges
-      const int nr = r1 - r0;
-      constexpr int E8 = 16 / sizeof(T), CPR = H / E8, TOT = 3 * MT * CPR, IT = TOT / (64 * NW);
-      static_assert(TOT % (64 * NW) == 0, "whole steps of the workgroup");
-      uint4 v[IT];
-#pragma unroll
-      for (int k = 0; k < IT; ++k) {
-        const int c = (int)threadIdx.x + k * 64 * NW, p = c / (MT * CPR), rem = c - p * (MT * CPR);
-        const int i = rem / CPR, q = rem - i * CPR;
-        const T* src = p == 0 ? h + (size_t)(r0 + i) * H : p == 1 ? h + (size_t)ss[i] * H : e + (size_t)(e0 + i) * H;
-        v[k] = uint4{0u, 0u, 0u, 0u};
-        if (i < (p == 0 ? nr : ne)) v[k] = *(const uint4*)(src + q * E8);
       }
+    ip.advance(b, sch, t);  // next tile's indices and the bounds after, in flight from here
+    lds_sync();
 #pragma unroll
-      for (int k = 0; k < IT; ++k) {
-        const int c = (int)threadIdx.x + k * 64 * NW, p = c / (MT * CPR), rem = c - p * (MT * CPR);
-        const int i = rem / CPR, q = rem - i * CPR;
-        *(uint4*)(p == 0 ? hr + i * D::LDH + q * E8 : xs + i * D::LD2 + (p - 1) * H + q * E8) = v[k];
-      }
-      ip.advance(b, sch, t);  // next tile's indices and the bounds after, in flight from here
-      // each lane's h_r row (its row of every 16-row block): the receiver's tile-local index
-      int roff[MB];
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const int row = mb * 16 + (lane_id() & 15);
-        roff[mb] = (row < ne ? rs[row] - r0 : 0) * D::LDH;
-      }
-      WFrag<T, NB, H> fr;
-      fr.load(W1, 3 * H, n0);
-      lds_sync();
-      zero_acc(acc);
-      wave_gemm_rows<T, MB, NB, H>(acc, hr, roff, fr);                // W1_r h_r
-      wave_gemm<T, MB, NB, 2 * H, D::LD2>(acc, xs, W1 + H, 3 * H, n0);  // + W1_s h_s + W1_e e
-    }
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mb][nb][r] += sv[mb][nb][r];
+    wave_gemm<T, MB, NB, H, D::LDH>(acc, xs, W1 + 2 * H, 3 * H, n0);  // + W1_e e
     f32x4 ev[MB][NB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         const int c = acc_col(n0, nb);
-        const float bb = SPLIT ? 0.f : w.b1[c];  // SPLIT: b1 is in P_r
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          acc[mb][nb][r] += bb;
-          ev[mb][nb][r] = to_f(xs[acc_row(mb, r) * LDX + EC + c]);
-        }
+        for (int r = 0; r < 4; ++r) ev[mb][nb][r] = to_f(xs[acc_row(mb, r) * LDX + c]);  // (b1 is in P_r)
       }
     if (a_out) {  // uniform: the pre-activation goes out through zs first
       acc_to_lds<T, MB, NB, D::LDH>(acc, zs, n0);
@@ -233,9 +179,8 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeFwdLds<T, H, MT, NW, SP
       lds_sync();
       for (int task = threadIdx.x; task < nr * (HH / 4); task += 64 * NW) {
         const int rl = task / (HH / 4), q = task - rl * (HH / 4);
-        // (the split form reads the row pointers: the LDS starts cost it registers)
-        const int lo = SPLIT ? b.row_ptr[r0 + rl] - e0 : sg[rl];
-        const int hi = SPLIT ? b.row_ptr[r0 + rl + 1] - e0 : sg[rl + 1];
+        // (row pointers: segment starts kept in LDS cost registers)
+        const int lo = b.row_ptr[r0 + rl] - e0, hi = b.row_ptr[r0 + rl + 1] - e0;
         float4 s = {0.f, 0.f, 0.f, 0.f};
         for (int i = lo; i < hi; ++i) {
           const float4 v = *(const float4*)(ft + i * LDFH + 4 * q);
@@ -659,21 +604,17 @@ constexpr bool edge_fits() {
 }
 
 template <int NW>
-static void edge_fwd_nw(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e, void* e_out,
+static void edge_split_nw(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e, void* e_out,
                         float* m, void* z_out, void* a_out, const float* pr, const float* ps, hipStream_t st) {
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT_EDGE(s.mt_edge, {
     if constexpr (edge_fits<T, H, MT>()) {
-      auto go = [&](auto agg, auto split) {
-        k_edge_fwd<T, H, MT, ACT, decltype(agg)::value, NW, decltype(split)::value><<<s.grid, 64 * NW, 0, st>>>(
+      auto go = [&](auto agg) {
+        k_edge_fwd_split<T, H, MT, ACT, decltype(agg)::value, NW><<<s.grid, 64 * NW, 0, st>>>(
             b, w, (const T*)h, (const T*)e, (T*)e_out, m, (T*)z_out, (T*)a_out, pr, ps, s.eps);
       };
       using I0 = std::integral_constant<int, 0>;
       using I1 = std::integral_constant<int, 1>;
-      if (pr) {
-        if (s.agg) go(I1{}, I1{}); else go(I0{}, I1{});
-      } else if constexpr (sizeof(T) == 4) {  // (BF16: launch_edge_fwd_chain, launch_edge_fwd_stream)
-        if (s.agg) go(I1{}, I0{}); else go(I0{}, I0{});
-      }
+      if (s.agg) go(I1{}); else go(I0{});
     } else {
       g_config_error = 1;
     }
@@ -684,21 +625,20 @@ void launch_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
                      void* e_out, float* m, void* z_out, void* a_out, const float* pr, const float* ps,
                      hipStream_t st) {
   if (b.n_etiles == 0) return;
-  // the BF16 gathered form at H = 128, at every size: both its weights fit in
-  // LDS beside the waves' buffers (at H = 256 W1 alone takes 384 KiB)
-  if (edge_fwd_chain(s) && !pr) {
-    launch_edge_fwd_chain(s, b, w, h, e, e_out, m, z_out, a_out, st);
-    return;
-  }
-  // the BF16 gathered form at H = 256 and 512, at every size
-  if (edge_fwd_stream(s) && !pr) {
-    launch_edge_fwd_stream(s, b, w, h, e, e_out, m, z_out, a_out, st);
+  // gathered form: BF16 at H = 128 keeps both weights in LDS beside the waves'
+  // buffers (at H = 256 W1 alone takes 384 KiB, in FP32 at H = 128 192), the
+  // others stream them
+  if (!pr) {
+    if (edge_fwd_chain(s))
+      launch_edge_fwd_chain(s, b, w, h, e, e_out, m, z_out, a_out, st);
+    else
+      launch_edge_fwd_stream(s, b, w, h, e, e_out, m, z_out, a_out, st);
     return;
   }
   if (s.nw_edge == 8)
-    edge_fwd_nw<8>(s, b, w, h, e, e_out, m, z_out, a_out, pr, ps, st);
+    edge_split_nw<8>(s, b, w, h, e, e_out, m, z_out, a_out, pr, ps, st);
   else
-    edge_fwd_nw<4>(s, b, w, h, e, e_out, m, z_out, a_out, pr, ps, st);
+    edge_split_nw<4>(s, b, w, h, e, e_out, m, z_out, a_out, pr, ps, st);
 }
 
 void launch_node_proj(const Shape& s, const BatchView& b, const MlpW& w, const void* h, float* pr, float* ps,
@@ -726,7 +666,7 @@ void launch_enc_node_fwd(const Shape& s, const BatchView& b, const MlpW& w, cons
     return;
   }
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
-    if constexpr (sizeof(T) == 4 || H == 128) {
+    if constexpr (sizeof(T) == 2 && H == 128) {
       if (in_dim <= 8)
         k_enc_fwd<T, H, MT, ACT, 0, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, (T*)h0, s.eps);
       else
@@ -743,7 +683,7 @@ void launch_enc_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, cons
     return;
   }
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(enc_edge_rows(s), {
-    if constexpr (sizeof(T) == 4 || H == 128)
+    if constexpr (sizeof(T) == 2 && H == 128)
       k_enc_fwd<T, H, MT, ACT, 1, 8><<<s.grid, NTHR, 0, st>>>(b.E, b, w, xe, 4, (T*)e0, s.eps);
   }))));
 }

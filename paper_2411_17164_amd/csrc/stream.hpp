@@ -1,8 +1,8 @@
-// Wave-private chains with streamed weights (BF16, H = 256 and 512; see
-// chain.hpp).
+// Wave-private chains with streamed weights (see chain.hpp): BF16 at H = 256
+// and 512, FP32 at H = 128 and 256.
 //
-// At these widths the weights do not fit in LDS.  The workgroup's waves walk
-// the same sequence of weight slabs (the MFMA fragments of one 32-wide k chunk,
+// In these forms the weights do not fit in LDS.  The workgroup's waves walk
+// the same sequence of weight slabs (the MFMA fragments of one or two k chunks,
 // 16 or 32 KiB), which travel from L2 straight into a ring of four LDS slots,
 // three slabs ahead of their use; one barrier per slab.  A wave's rows,
 // accumulators and LayerNorm stay in its registers.
@@ -11,6 +11,39 @@
 #include "chain.hpp"
 
 namespace xmgn {
+
+// One k chunk of a row's operand: 16 bytes per lane, features KW c + E g .. + E
+// - 1 (g = lane / 16).  BF16: a 32-feature chunk, two accumulator blocks; FP32:
+// 16 features, where the operand is the accumulator block itself.
+template <typename T>
+struct Chunk;
+template <>
+struct Chunk<bf16> {
+  using V = bf16x8;
+  static constexpr int KW = 32, E = 8, BLK = 2, MF = 1;  // MF: MFMAs per fragment
+  static __device__ __forceinline__ V of(const f32x4 (&a)[2]) { return to_natural(a[0], a[1]); }
+  static __device__ __forceinline__ void to(const V& v, f32x4 (&a)[2]) { from_natural(v, a[0], a[1]); }
+};
+template <>
+struct Chunk<float> {
+  using V = f32x4;
+  static constexpr int KW = 16, E = 4, BLK = 1, MF = 4;
+  static __device__ __forceinline__ V of(const f32x4 (&a)[1]) { return a[0]; }
+  static __device__ __forceinline__ void to(const V& v, f32x4 (&a)[1]) { a[0] = v; }
+};
+
+// Shape of a streamed chain of width H: eight waves of 256 registers where a
+// row's operand takes at most 32 of them, else four of 512.  W: so many waves
+// instead.
+template <typename T, int H, int W = 0>
+struct StreamDims {
+  using C = Chunk<T>;
+  static constexpr int NW = W ? W : H * (int)sizeof(T) <= 512 ? 8 : 4, NT = 64 * NW;
+  static constexpr int MBS = H / 16, KC = H / C::KW;       // output blocks; k chunks of an H-wide operand
+  static constexpr int CPS = MBS < 16 ? 16 / MBS : 1;      // chunks per slab (16 or 32 KiB)
+  static constexpr int FR = MBS * CPS, SP = KC / CPS;      // fragments per slab; slabs of an H x H matrix
+  static constexpr size_t RING = 4 * FR * 1024;
+};
 
 // A sequence of S weight slabs in global memory, in fragment order (k chunk by
 // k chunk, block by block, 1 KiB each), cycled through by a workgroup of NW
@@ -26,9 +59,9 @@ namespace xmgn {
 // make it wait for more.  At the end of a product (slabs [s0, s1), back to
 // back) it waits for everything, so that the first two slabs of the next need
 // no wait behind the loads and stores between the products.
-template <int NW, int S, int MBS>
+template <int NW, int S, int FR>
 struct WStream {
-  static constexpr int SLAB = MBS * 1024, K = MBS / NW;  // K loads of 1 KiB per wave and slab
+  static constexpr int SLAB = FR * 1024, K = FR / NW;  // K loads of 1 KiB per wave and slab
   static_assert(S % 4 == 0, "a slab's slot is s % 4");
   const unsigned char* base;  // (uniform)
   unsigned char* ring;        // LDS, 4 SLAB bytes
@@ -59,39 +92,93 @@ struct WStream {
     else if (s >= s0 + 2) {
       if constexpr (K == 2)
         asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      else if constexpr (K == 4)
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
       else
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
     }
     lds_sync();
   }
-  __device__ __forceinline__ const bf16x8* frags(int s) const { return (const bf16x8*)(ring + (s & 3) * SLAB); }
-  static_assert(K == 2 || K == 8, "waits are written for these counts");
+  // fragment f of slab s
+  template <typename V>
+  __device__ __forceinline__ const V* frag(int s, int f) const {
+    return (const V*)(ring + (s & 3) * SLAB) + f * 64;
+  }
+  static_assert(K == 2 || K == 4 || K == 8, "waits are written for these counts");
 };
 
-// acc[t][mb] += W x over one k chunk; fragments are read D ahead of their
+// acc[mb] += W x over one k chunk; fragments are read D ahead of their
 // products.
-template <int ET, int MBS>
-__device__ __forceinline__ void slab_gemm(f32x4 (&acc)[ET][MBS], const bf16x8* f, const bf16x8 (&x)[ET]) {
-  constexpr int D = 6, N = MBS;
+template <typename T, int MBS>
+__device__ __forceinline__ void chunk_gemm(f32x4 (&acc)[MBS], const typename Chunk<T>::V* f,
+                                           const typename Chunk<T>::V& x) {
+  using V = typename Chunk<T>::V;
+  constexpr int D = 6, MF = Chunk<T>::MF;
   f += lane_id();
-  bf16x8 a[D];
+  V a[D];
 #pragma unroll
   for (int i = 0; i < D; ++i) a[i] = f[i * 64];
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const bf16x8 cur = a[i % D];
-    if (i + D < N) a[i % D] = f[(i + D) * 64];
-#pragma unroll
-    for (int t = 0; t < ET; ++t) acc[t][i] = mma(cur, x[t], acc[t][i]);
+  for (int i = 0; i < MBS; ++i) {
+    const V cur = a[i % D];
+    if (i + D < MBS) a[i % D] = f[(i + D) * 64];
+    acc[i] = mma(cur, x, acc[i]);
   }
   __builtin_amdgcn_sched_group_barrier(0x100, D, 0);  // DS reads
 #pragma unroll
-  for (int i = 0; i < N - D; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, ET, 0);  // MFMA
+  for (int i = 0; i < MBS - D; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, MF, 0);  // MFMA
     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
   }
-  __builtin_amdgcn_sched_group_barrier(0x008, D * ET, 0);
+  __builtin_amdgcn_sched_group_barrier(0x008, D * MF, 0);
   __builtin_amdgcn_sched_barrier(0);
+}
+
+// x += W xs for an H-wide operand, its weights in slabs [s, s + SP) of a
+// product over slabs [s0, s1).
+template <typename T, int H, int NW, int S>
+__device__ __forceinline__ void stream_gemm(const WStream<NW, S, StreamDims<T, H>::FR>& ws, int s,
+                                            int s0, int s1, f32x4 (&x)[H / 16],
+                                            const typename Chunk<T>::V (&xs)[StreamDims<T, H>::KC]) {
+  using L = StreamDims<T, H>;
+#pragma unroll
+  for (int c = 0; c < L::SP; ++c) {
+    ws.begin(s + c);
+#pragma unroll
+    for (int j = 0; j < L::CPS; ++j)
+      chunk_gemm<T>(x, ws.template frag<typename Chunk<T>::V>(s + c, j * L::MBS), xs[c * L::CPS + j]);
+    ws.end(s + c, s0, s1);
+  }
+}
+template <int N>
+__device__ __forceinline__ void zero_blocks(f32x4 (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+// a product of one operand: x = W xs, slabs [s0, s0 + SP)
+template <typename T, int H, int NW, int S>
+__device__ __forceinline__ void stream_product(const WStream<NW, S, StreamDims<T, H>::FR>& ws, int s0,
+                                               f32x4 (&x)[H / 16],
+                                               const typename Chunk<T>::V (&xs)[StreamDims<T, H>::KC]) {
+  zero_blocks(x);
+  stream_gemm<T, H>(ws, s0, s0, s0 + StreamDims<T, H>::SP, x, xs);
+}
+
+// A row's operand from and to global memory (p: the row's first element).
+template <typename T, int KC>
+__device__ __forceinline__ void load_row(typename Chunk<T>::V (&v)[KC], const T* p, int lg) {
+#pragma unroll
+  for (int c = 0; c < KC; ++c) v[c] = *(const typename Chunk<T>::V*)(p + Chunk<T>::KW * c + Chunk<T>::E * lg);
+}
+template <typename T, int KC>
+__device__ __forceinline__ void store_row(T* p, const typename Chunk<T>::V (&v)[KC], int lg) {
+#pragma unroll
+  for (int c = 0; c < KC; ++c) *(typename Chunk<T>::V*)(p + Chunk<T>::KW * c + Chunk<T>::E * lg) = v[c];
+}
+template <typename V, int KC>
+__device__ __forceinline__ void arrived_row(V (&v)[KC]) {
+#pragma unroll
+  for (int c = 0; c < KC; ++c) arrived(v[c]);
 }
 
 // LayerNorm of a row of H in the accumulator layout (in place -> xhat),

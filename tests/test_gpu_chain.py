@@ -1,4 +1,4 @@
-"""The BF16 edge kernels where their work split can go wrong: a wave
+"""The edge and encoder kernels where their work split can go wrong: a wave
 takes whole receiver segments 16 edges at a time, so segments that straddle
 16-edge groups and tile ends, receivers without in-edges, and edge counts
 around one group and one workgroup's share are held against the oracle."""
@@ -78,6 +78,37 @@ def test_chain_edges(api, hidden, n, degrees, act, agg):
     ctx.forward(case.model(api), p, ps, [0], node_in, pos, case.inp.edge_norm, free, keep_tape=False)
     torch.cuda.synchronize()
     assert torch.equal(free, out)
+
+
+@pytest.mark.parametrize("agg", ["message", "edge"])
+@pytest.mark.parametrize("n,degrees", [
+    (8, [1, 0]),                # less than one group
+    (70, [31, 0, 0, 2, 32]),    # segments over three groups, runs of empty receivers
+    (1024, [12]),               # the most edges that four-wave workgroups take at H = 128
+    (1025, [12]),               # and the first that eight waves take
+])
+@pytest.mark.parametrize("hidden", [128, 256])
+def test_fp32_edges(api, hidden, n, degrees, agg):
+    """The FP32 form under SiLU at its bar: outputs and whole gradient within
+    1e-4 of the oracle."""
+    case = Case(1, levels=(n,), hidden=hidden, layers=2, precision="fp32", activation="silu", aggregate=agg)
+    G = degree_graph(n, degrees, 7)
+    case._graph = G
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    ctx = api.Context(0)
+    ps = api.Partset.halo(api.Graph.from_csr(G.row_ptr, G.col), case.inp.pos, None, case.L)
+    p, node_in, pos, target = dev(case.params), dev(case.inp.node_in), dev(case.inp.pos), dev(case.inp.targets)
+    out = torch.full((n, 4), float("nan"), device="cuda")
+    d_out, loss, grad = torch.zeros_like(out), torch.zeros(1, device="cuda"), torch.full_like(p, float("nan"))
+    log(f"fp32 H={hidden} n={n} E={len(G.col)} {agg}")
+    ctx.forward(case.model(api), p, ps, [0], node_in, pos, case.inp.edge_norm, out)
+    ctx.mse_grad(out, target, n, d_out, loss)
+    ctx.backward(case.model(api), p, d_out, grad)
+    torch.cuda.synchronize()
+    (_, y, g), _ = oracle_refs(case)
+    e_out, e_grad = rel_l2(out.cpu().numpy(), y), rel_l2(grad.cpu().numpy(), g)
+    log(f"  out {e_out:.2e} grad {e_grad:.2e}")
+    assert e_out <= 1e-4 and e_grad <= 1e-4
 
 
 @pytest.mark.parametrize("hidden", [256, 512])
