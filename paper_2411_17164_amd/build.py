@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libxmgn.so")
 BUILD = os.path.join(ROOT, "_build")
 ARCH = "gfx950"
-SOURCES = ["edge_chain.hip", "edge_stream.hip", "enc_stream.hip", "mlp_fwd.hip", "mlp_bwd.hip", "aux.hip", "knn.hip", "api.cpp"]
+SOURCES = ["edge_chain.hip", "edge_stream.hip", "enc_stream.hip", "node_stream.hip", "mlp_fwd.hip", "mlp_bwd.hip", "aux.hip", "knn.hip", "api.cpp"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I" + os.path.join(ROOT, "include"),
          "-Wno-unused-result"]
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

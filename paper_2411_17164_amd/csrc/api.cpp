@@ -907,8 +907,10 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
     add_job(c, W2e, H, 0, 0, H, H, we.W2);
     add_job(c, W2e, H, 0, 1, H, H, we.W2T);
     add_job(c, W1e, 3 * H, 2 * H, 1, H, H, we.W1T);  // [c][j] = W1[j][2H + c]
-    add_job(c, W1e, 3 * H, 0, 1, H, H, we.Brs, 2 * H, 0);
-    add_job(c, W1e, 3 * H, H, 1, H, H, we.Brs, 2 * H, H, false);
+    if (l == 0) {  // (the other layers': in the node adjoint's slabs)
+      add_job(c, W1e, 3 * H, 0, 1, H, H, we.Brs, 2 * H, 0);
+      add_job(c, W1e, 3 * H, H, 1, H, H, we.Brs, 2 * H, H, false);
+    }
     if (stream) {  // the streaming edge kernels' slabs
       we.FS = add_frag_job(c, W1e, 3 * H, 0, 0, H, 3 * H);
       add_frag_job(c, W2e, H, 0, 0, H, H);
@@ -918,10 +920,23 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
     }
     BlockW& wn = c->bw[3 + 2 * l];
     const int64_t W1n = poff(d, 3, l, 0), W2n = poff(d, 3, l, 2);
-    add_job(c, W1n, 2 * H, 0, 0, H, 2 * H, wn.W1);
-    add_job(c, W2n, H, 0, 0, H, H, wn.W2);
-    add_job(c, W2n, H, 0, 1, H, H, wn.W2T);
-    add_job(c, W1n, 2 * H, 0, 1, 2 * H, H, wn.W1T);
+    wn.FS = add_frag_job(c, W1n, 2 * H, 0, 0, H, 2 * H);
+    add_frag_job(c, W2n, H, 0, 0, H, H);
+    int64_t* first = &wn.BS;
+    auto bs = [&](int64_t src, int ld, int col0, int transpose, int cols) {
+      const int64_t at = add_frag_job(c, src, ld, col0, transpose, H, cols);
+      if (first) *first = at;
+      first = nullptr;
+    };
+    if (l + 1 < L) {
+      bs(poff(d, 2, l + 1, 0), 3 * H, 0, 1, H);
+      bs(poff(d, 2, l + 1, 0), 3 * H, H, 1, H);
+    }
+    bs(W1n, 2 * H, 0, 0, 2 * H);
+    bs(W2n, H, 0, 0, H);
+    bs(W2n, H, 0, 1, H);
+    bs(W1n, 2 * H, 0, 1, H);
+    bs(W1n, 2 * H, H, 1, H);
   }
   BlockW& wd = c->bw[2 + 2 * L];
   add_job(c, poff(d, 4, 0, 0), H, 0, 0, H, H, wd.W1);
@@ -1375,12 +1390,8 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
   // (the buffers take either policy's grid: a change of it allocates nothing)
   const size_t ge = std::max(se.grid, edge_bwd_chain_grid(se, (int)E));
   if (c->tape_z) se.grid = edge_bwd_chain_grid(se, (int)E);
-  const bool fnode = node_bwd_fuses_wgrad(s);
-  if (enc_bwd_fuses_wgrad(s) || fnode) {
-    // encoders: [<=256][2][H][H]; node adjoint: [<=512][H][H]
-    const size_t mats = std::max((size_t)std::min(s.grid, 256) * 2, (size_t)std::min(s.grid, 512));
-    if (xmgn_status r = c->wfused.ensure(mats * H * H * 4, st)) return r;
-  }
+  if (enc_bwd_fuses_wgrad(s))  // encoders: [<=256][2][H][H]
+    if (xmgn_status r = c->wfused.ensure((size_t)std::min(s.grid, 256) * 2 * H * H * 4, st)) return r;
   if (fw)  // edge adjoint: [se.grid][2][H][H]
     if (xmgn_status r = c->wfused_e.ensure(ge * 2 * H * H * 4, st)) return r;
   if (xmgn_status r = c->part_e.ensure(ge * 4 * H * 4, st)) return r;
@@ -1409,8 +1420,6 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
           c->wpart, st);
   }
   // processor layers, last to first
-  Shape snode = s;  // node adjoint with W2 resident in LDS: two workgroups per CU
-  if (fnode) snode.grid = std::min(s.grid, 512);
   const float* de_in = nullptr;
   DBuf* de_out = &c->deA;
   DBuf* de_other = &c->deB;
@@ -1426,9 +1435,15 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
       if (xmgn_status r = tape_in(c, d, st, l - 1, true, em, em, &back[l - 1])) return r;
     }
     const MlpW wn = weights(c, d, params, 3 + 2 * l, 3, l);
-    NodeBwdOut no{c->dhMid.as<float>(), c->dm.as<float>(), c->fa.p, c->fb.p, c->fc.p, part,
-                  fnode ? c->wfused.as<float>() : nullptr};
-    { KT("node_bwd"); launch_node_bwd(snode, b, wn, hl(l), mslot(c, d, l), c->dhA.as<float>(), no, st); }
+    NodeBwdOut no{c->dhMid.as<float>(), c->dm.as<float>(), c->fa.p, c->fb.p, c->fc.p, part};
+    {
+      KT("node_bwd");
+      if (l == L - 1)  // below the decoder
+        launch_node_bwd(s, b, wn, hl(l), mslot(c, d, l), c->dhA.as<float>(), nullptr, nullptr, no, st);
+      else
+        launch_node_bwd(s, b, wn, hl(l), mslot(c, d, l), c->dhMid.as<float>(), c->Sr.as<float>(), c->Ss.as<float>(), no,
+                        st);
+    }
     // the layer's reductions of partial sums run as one batch at its end
     RedBatch rb;
     int n_wg = 0;
@@ -1439,17 +1454,14 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     };
     VecSeg ns[4] = {{0, (int)H, P(3, l, 1)}, {(int)H, (int)H, P(3, l, 3)}, {2 * (int)H, (int)H, P(3, l, 4)},
                     {3 * (int)H, (int)H, P(3, l, 5)}};
-    rb.add_vec(part, snode.grid, 4 * (int)H, ns, 4);
-    // dW1 = sum da [h ; m]^T (two products); dW2 = sum du z^T, fused or a product
+    rb.add_vec(part, edge_stream_grid(s, (int)n), 4 * (int)H, ns, 4);
+    // dW1 = sum da [h ; m]^T (two products); dW2 = sum du z^T
     wg(wop(c->fa.p, 0, (int)H, 0, nullptr, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 0),
            2 * (int)H));
     wg(wop(c->fa.p, 0, (int)H, 0, nullptr, mslot(c, d, l), 1, (int)H, 0, nullptr, (int)n, (int)H, (int)H,
            P(3, l, 0) + H, 2 * (int)H));
-    if (fnode)
-      rb.add(c->wfused.as<float>(), snode.grid, (int)(H * H), (int)H, (int)H, P(3, l, 2), (int)H);
-    else
-      wg(wop(c->fb.p, 0, (int)H, 0, nullptr, c->fc.p, 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 2),
-             (int)H));
+    wg(wop(c->fb.p, 0, (int)H, 0, nullptr, c->fc.p, 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 2),
+           (int)H));
 
     const MlpW we = weights(c, d, params, 2 + 2 * l, 2, l);
     EdgeBwdOut eo{de_out->as<float>(), c->Sr.as<float>(), c->fa.p, c->fb.p, c->fc.p, c->part_e.as<float>(),
@@ -1466,7 +1478,10 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
              3 * (int)H);
     }
     { KT("sender_sum"); launch_sender_sum(s, b, c->fa.p, c->Ss.as<float>(), st); }
-    { KT("node_dh"); launch_node_dh(s, b, we, c->dhMid.as<float>(), c->Sr.as<float>(), c->Ss.as<float>(), c->dhA.as<float>(), st); }
+    if (l == 0) {  // (the other layers' node adjoints take this in)
+      KT("node_dh");
+      launch_node_dh(s, b, we, c->dhMid.as<float>(), c->Sr.as<float>(), c->Ss.as<float>(), c->dhA.as<float>(), st);
+    }
     wg(wop(c->Sr.p, 1, (int)H, 0, nullptr, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(2, l, 0),
            3 * (int)H));
     wg(wop(c->Ss.p, 1, (int)H, 0, nullptr, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(2, l, 0) + H,

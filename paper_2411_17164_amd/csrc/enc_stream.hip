@@ -31,18 +31,6 @@ constexpr size_t enc_w1_bytes() {
   return KIN <= 8 ? (size_t)KIN * H * 4 : 0;
 }
 
-// The rows of one wave: [begin, end) of R, and the workgroup's common number
-// of 16-row steps.
-struct WaveRows {
-  int begin, end, steps;
-  __device__ WaveRows(int R, int nw_wg) {
-    const int nw = gridDim.x * nw_wg, w0 = blockIdx.x * nw_wg, wv = w0 + __builtin_amdgcn_readfirstlane(wave_id());
-    begin = (int)((long long)R * wv / nw);
-    end = (int)((long long)R * (wv + 1) / nw);
-    steps = R > 0 ? (R / nw + 1 + 15) >> 4 : 0;  // (no range is longer than R / nw + 1)
-  }
-};
-
 // The input layer and its data: KIN = 4 (edge features), 8 (up to 8 node
 // inputs) or 32.
 template <int H, int KIN, int KIND>
@@ -110,30 +98,6 @@ __device__ __forceinline__ void stage_vecs(float* vec, const MlpW& w, int nt) {
     vec[3 * H + c] = w.gamma[c];
     vec[4 * H + c] = w.beta[c];
   }
-}
-
-// Adds the NW waves' column sums of one vector (each lane gives its values
-// through put(double* row of H)) and writes them to dst[f * stride].
-template <int H, int NW, typename PutFn>
-__device__ __forceinline__ void wg_colsum(double* ds, float* dst, int stride, PutFn put) {
-  __syncthreads();
-  put(ds + wave_id() * H);
-  __syncthreads();
-  for (int f = threadIdx.x; f < H; f += 64 * NW) {
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < NW; ++k) s += ds[k * H + f];
-    dst[(size_t)f * stride] = (float)s;
-  }
-}
-// ... of totals in colsum64's layout, one per 64 features
-template <int H, int NW>
-__device__ __forceinline__ void wg_colsum64(double* ds, float* dst, const double (&v)[H / 64]) {
-  wg_colsum<H, NW>(ds, dst, 1, [&](double* d) {
-    const int l = lane_id(), li = l & 15, lg = l >> 4;
-#pragma unroll
-    for (int gr = 0; gr < H / 64; ++gr) d[64 * gr + 16 * (li >> 2) + 4 * lg + (li & 3)] = v[gr];
-  });
 }
 
 template <typename T, int H, int W, int ACT, int KIN, int KIND>

@@ -43,10 +43,11 @@ struct MlpW {
   const float* b3;
   const float* gamma;
   const float* beta;
-  // forms with streamed weights (edge_stream): MFMA fragment order, k chunk by
-  // k chunk, as the kernels walk them
-  const void* FS;   // forward: W1, W2 (edge MLP); W2, W3 (encoder)
-  const void* BS;   // adjoint: W2, W2^T, e-block of W1^T (edge MLP); W3^T, W2^T (encoder)
+  // kernels with streamed weights (the node MLP's; edge_stream): MFMA fragment
+  // order, k chunk by k chunk, as the kernels walk them
+  const void* FS;   // forward: W1, W2 (edge, node MLP); W2, W3 (encoder)
+  const void* BS;   // adjoint: W2, W2^T, e-block of W1^T (edge MLP); W3^T, W2^T (encoder);
+                    // B_rs of the edge layer above (if any), W1, W2, W2^T, W1^T (node MLP)
 };
 
 struct Shape {
@@ -144,14 +145,13 @@ struct NodeBwdOut {
   void* da;        // [n][H] T
   void* du;        // [n][H] T
   void* z;         // [n][H] T
-  float* partial;  // [grid][4H]
-  float* wpart;    // fused dW2 partials [grid][H][H] (or NULL)
+  float* partial;  // [grid][4H]: db1, db2, dgamma, dbeta
 };
-// True when the node adjoint accumulates dW2 itself (then z and du are not
-// written and wpart must be given); da is always written.
-bool node_bwd_fuses_wgrad(const Shape& s);
-void launch_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h,
-                     const float* m, const float* dh_in, const NodeBwdOut& o, hipStream_t st);
+// Upstream gradient dh_in, or with S_r and S_s dh_in + [S_r | S_s] * [W1_r ;
+// W1_s] of the edge layer above (dh_in may be o.dh_mid then).  Partials have
+// edge_stream_grid(s, b.n) rows.
+void launch_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const float* m,
+                     const float* dh_in, const float* S_r, const float* S_s, const NodeBwdOut& o, hipStream_t st);
 // dh_out = dh_mid + [S_r | S_s] * [W1_r ; W1_s]  (edge-layer input gradients)
 void launch_node_dh(const Shape& s, const BatchView& b, const MlpW& w, const float* dh_mid,
                     const float* S_r, const float* S_s, float* dh_out, hipStream_t st);

@@ -392,203 +392,6 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeBwdLds<T, H, MT, FW, NW
   }
 }
 
-// ---------------------------------------------------------------------------
-// Node adjoint (with recompute).  dh_mid = dh' + (W1^T da)[0:H], dm = (W1^T da)[H:2H].
-// FM (BF16, H = 128, 32-row tiles): W2 lives in LDS for the whole kernel
-// and serves both its product and, read transposed, dz = du W2; dW2 is
-// accumulated per workgroup on MFMA (du from the accumulators, z read
-// transposed from its tile; partials to o.wpart [grid][H][H]), so z and du
-// are not written.  78 KB of LDS: two workgroups per CU.  W1 and W1^T come
-// from L2, and da is written for the two dW1 blocks, which are separate
-// products over da, h and m.  (Keeping W1 in LDS too and fusing both dW1
-// blocks takes 146 KB, one workgroup per CU, and measured slower.)
-// ---------------------------------------------------------------------------
-bool node_bwd_fuses_wgrad(const Shape& s) { return s.prec == 1 && s.H == 128 && s.mt_node == 32; }
-
-template <typename T, int H, int MT, int ACT>
-__global__ __launch_bounds__(NTHR, (MT == 32 && H == 128 ? 2 : 1)) void k_node_bwd(
-    int n, MlpW w, const T* __restrict__ h, const float* __restrict__ m, const float* __restrict__ dh_in,
-    NodeBwdOut o, float eps) {
-  using D = BD<T, H>;
-  constexpr bool FM = sizeof(T) == 2 && H == 128 && MT == 32;
-  constexpr int MB = MT / 16, NB = D::NB;
-  constexpr int LDW2 = H + 8;
-  constexpr size_t XS = (size_t)MT * D::LD2 * sizeof(T);
-  constexpr size_t ZS = (size_t)MT * D::LDH * sizeof(T);
-  constexpr size_t W2S = FM ? (size_t)H * LDW2 * 2 : 0;
-  static_assert((size_t)MT * D::LDF * 4 <= XS, "FP32 tile must fit in the staging tile");
-  static_assert(!FM || MB % 2 == 0, "fused weight gradients: k chunks of 32 rows");
-  __shared__ __align__(16) unsigned char smem[XS + ZS + 2 * NWAVE * MT * 4 + W2S];
-  T* xs = (T*)smem;
-  T* zs = (T*)(smem + XS);
-  float* red = (float*)(smem + XS + ZS);
-  bf16* W2s = (bf16*)(red + 2 * NWAVE * MT);  // FM: W2 [out][in]
-  float* ft = (float*)smem;                   // aliases [h ; m] once the first product is done
-  const T* W1 = (const T*)w.W1;
-  const T* W2 = (const T*)w.W2;
-  const T* W2T = (const T*)w.W2T;
-  const T* W1T = (const T*)w.W1T;
-  const int n0 = wave_id() * D::CPW;
-  const int li = lane_id() & 15, lg = lane_id() >> 4;
-  double cb1[NB] = {}, cb2[NB] = {}, cg[NB] = {}, cbt[NB] = {};
-  f32x4 accW2[NB][H / 16];
-  if constexpr (FM) {
-    zero_acc(accW2);
-    for (int c = threadIdx.x; c < H * (H / 8); c += NTHR) {
-      const int r = c / (H / 8), q = c - r * (H / 8);
-      *(uint4*)(W2s + r * LDW2 + 8 * q) = *(const uint4*)(W2 + (size_t)r * H + 8 * q);
-    }
-  }
-  const int n_tiles = (n + MT - 1) / MT;
-  // fused form, ReLU: the next tile's h and m rows travel in registers while
-  // this tile computes, and this tile's dh_in rows are issued at its start,
-  // so no HBM round trip waits on a tile's critical path (SiLU and the
-  // unfused forms have no registers to spare: they would spill)
-  constexpr bool PF = FM && ACT == 0;
-  constexpr int CPF = H / 4, IF = PF ? MT * CPF / NTHR : 1;
-  NodeRowsPre<T, H, MT, D::LD2> pre;  // (unused by the unfused forms)
-  float4 pd[IF];
-
-  TileSched sch(n_tiles);
-  if constexpr (PF)
-    if (sch.begin < sch.end) pre.load(h, m, sch.begin * MT, min(MT, n - sch.begin * MT));
-  for (int t = sch.begin; t < sch.end; t += sch.step) {
-    const int row0 = t * MT, nr = min(MT, n - row0);
-    if constexpr (PF) {
-#pragma unroll
-      for (int k = 0; k < IF; ++k) {
-        const int c = (int)threadIdx.x + k * NTHR, i = c / CPF, q = c - i * CPF;
-        pd[k] = float4{0.f, 0.f, 0.f, 0.f};
-        if (i < nr) pd[k] = *(const float4*)(dh_in + (size_t)(row0 + i) * H + 4 * q);
-      }
-      pre.store(xs);
-      if (t + sch.step < sch.end) pre.load(h, m, (t + sch.step) * MT, min(MT, n - (t + sch.step) * MT));
-    } else {
-      global_rows_to_lds<T, D::LD2, MT, H>(xs, nr, 0, [&](int i) { return h + (size_t)(row0 + i) * H; });
-      global_f32_rows_to_lds<T, D::LD2, MT, H>(xs, nr, H, [&](int i) { return m + (size_t)(row0 + i) * H; });
-    }
-    lds_sync();
-    f32x4 a[MB][NB], x[MB][NB];
-    zero_acc(a);
-    wave_gemm<T, MB, NB, 2 * H, D::LD2>(a, xs, W1, 2 * H, n0);
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const float bb = w.b1[acc_col(n0, nb)];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          a[mb][nb][r] += bb;
-          x[mb][nb][r] = act_f<ACT>(a[mb][nb][r]);
-        }
-      }
-    acc_to_lds<T, MB, NB, D::LDH>(x, zs, n0);
-    lds_sync();
-    zero_acc(x);
-    if constexpr (FM) {
-      wave_gemm_lds<MB, NB, H, D::LDH>(x, (const bf16*)zs, [&](int k, int nb) {
-        return *(const bf16x8*)(W2s + (n0 + 16 * nb + li) * LDW2 + k + 8 * lg);
-      });
-    } else {
-      wave_gemm<T, MB, NB, H, D::LDH>(x, zs, W2, H, n0);
-    }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const float bb = w.b2[acc_col(n0, nb)];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) x[mb][nb][r] += bb;
-      }
-    float inv[MB][4];
-    ln_normalize<MB, NB, MT, H>(x, red, eps, inv);
-    if constexpr (PF) {
-#pragma unroll
-      for (int k = 0; k < IF; ++k) {
-        const int c = (int)threadIdx.x + k * NTHR, i = c / CPF, q = c - i * CPF;
-        *(float4*)(ft + i * D::LDF + 4 * q) = pd[k];
-      }
-    } else {
-      f32_rows_to_lds<H, D::LDF, MT>(ft, nr, [&](int i, int q) { return *(const float4*)(dh_in + (size_t)(row0 + i) * H + 4 * q); });
-    }
-    if constexpr (!FM) lds_rows_to_global<T, D::LDH>(zs, nr, H, (T*)o.z + (size_t)row0 * H, H, [](int i) { return i; });
-    lds_sync();
-    f32x4 g[MB][NB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) g[mb][nb][r] = ft[acc_row(mb, r) * D::LDF + acc_col(n0, nb)];
-    ln_backward<MB, NB, MT, H>(x, g, inv, w.gamma, n0, red, cg, cbt);
-    col_accumulate(g, cb2);
-    if constexpr (FM) {
-      wave_wgrad<MB, NB, H, D::LDH>(accW2, g, (const bf16*)zs);  // dW2 += du^T z
-      lds_sync();  // every wave is done reading z before du replaces it
-    }
-    acc_to_lds<T, MB, NB, D::LDH>(g, zs, n0);
-    lds_sync();
-    zero_acc(x);
-    if constexpr (FM) {
-      wave_gemm_lds<MB, NB, H, D::LDH>(x, (const bf16*)zs, [&](int k, int nb) {
-        return lds_bfrag_tr(W2s, LDW2, k + 8 * lg, n0 + 16 * nb, 4);
-      });
-    } else {
-      lds_rows_to_global<T, D::LDH>(zs, nr, H, (T*)o.du + (size_t)row0 * H, H, [](int i) { return i; });
-      wave_gemm<T, MB, NB, H, D::LDH>(x, zs, W2T, H, n0);
-    }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) x[mb][nb][r] *= act_d<ACT>(a[mb][nb][r]);
-    col_accumulate(x, cb1);
-    lds_sync();
-    acc_to_lds<T, MB, NB, D::LDH>(x, zs, n0);
-    lds_sync();
-    // da for the dW1 products
-    lds_rows_to_global<T, D::LDH>(zs, nr, H, (T*)o.da + (size_t)row0 * H, H, [](int i) { return i; });
-    zero_acc(g);
-    zero_acc(x);
-    wave_gemm<T, MB, NB, H, D::LDH>(g, zs, W1T, H, n0);                  // -> dh part
-    wave_gemm<T, MB, NB, H, D::LDH>(x, zs, W1T + (size_t)H * H, H, n0);  // -> dm
-    acc_to_ldsf<MB, NB, D::LDF>(g, ft, n0);
-    lds_sync();
-    f32_tile<MT, H, NTHR>(
-        nr, false, [&](int i, int q) { return *(const float4*)(dh_in + (size_t)(row0 + i) * H + 4 * q); },
-        [](int, int) { return float4{0.f, 0.f, 0.f, 0.f}; },
-        [&](int i, int q, const float4& d) {
-          if (i < nr) {
-            const float4 v = *(const float4*)(ft + i * D::LDF + 4 * q);
-            *(float4*)(o.dh_mid + (size_t)(row0 + i) * H + 4 * q) = float4{v.x + d.x, v.y + d.y, v.z + d.z, v.w + d.w};
-          }
-        });
-    lds_sync();
-    acc_to_ldsf<MB, NB, D::LDF>(x, ft, n0);
-    lds_sync();
-    for (int c = threadIdx.x; c < nr * (H / 4); c += NTHR) {
-      const int i = c / (H / 4), q = c - i * (H / 4);
-      *(float4*)(o.dm + (size_t)(row0 + i) * H + 4 * q) = *(const float4*)(ft + i * D::LDF + 4 * q);
-    }
-    lds_sync();
-  }
-  float* p = o.partial + (size_t)blockIdx.x * 4 * H;
-  write_partial<NB>(p, n0, cb1);
-  write_partial<NB>(p + H, n0, cb2);
-  write_partial<NB>(p + 2 * H, n0, cg);
-  write_partial<NB>(p + 3 * H, n0, cbt);
-  if constexpr (FM) {
-    float* q2 = o.wpart + (size_t)blockIdx.x * H * H;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int jb = 0; jb < H / 16; ++jb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) q2[(n0 + nb * 16 + lg * 4 + r) * H + jb * 16 + li] = accW2[nb][jb][r];
-  }
-}
-
 // dh_out = dh_mid + [S_r | S_s] B_rs^T, B_rs = [W1_r^T | W1_s^T] ([H][2H]).
 template <typename T, int H, int MT>
 __global__ __launch_bounds__(NTHR, H == 128 ? 2 : 1) void k_node_dh(int n, const T* __restrict__ Brs, const float* __restrict__ dh_mid,
@@ -1146,16 +949,6 @@ void launch_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
     edge_bwd_nw<8>(s, b, w, h, e, de_in, dm, o, st);
   else
     edge_bwd_nw<4>(s, b, w, h, e, de_in, dm, o, st);
-}
-
-void launch_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const float* m,
-                     const float* dh_in, const NodeBwdOut& o, hipStream_t st) {
-  XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
-    if constexpr (node_fits<T, H, MT>())
-      k_node_bwd<T, H, MT, ACT><<<s.grid, NTHR, 0, st>>>(b.n, w, (const T*)h, m, dh_in, o, s.eps);
-    else
-      g_config_error = 1;
-  }))));
 }
 
 void launch_node_dh(const Shape& s, const BatchView& b, const MlpW& w, const float* dh_mid, const float* S_r,

@@ -248,90 +248,6 @@ __global__ __launch_bounds__(NTHR, 2) void k_node_proj(int n, MlpW w, const T* _
 }
 
 // ---------------------------------------------------------------------------
-// Node processor, forward (Eq. 3): h' = h + LN(W2 act(W1 [h ; m] + b1) + b2)
-// ---------------------------------------------------------------------------
-template <typename T, int H, int MT, int ACT>
-__global__ __launch_bounds__(NTHR, H == 128 ? 2 : 1) void k_node_fwd(int n, MlpW w, const T* __restrict__ h,
-                                                   const float* __restrict__ m, T* __restrict__ h_out,
-                                                   float eps) {
-  using D = Dims<T, H>;
-  constexpr int MB = MT / 16, NB = D::NB;
-  constexpr size_t XS = (size_t)MT * D::LD2 * sizeof(T);
-  constexpr size_t ZS = (size_t)MT * D::LDH * sizeof(T);
-  __shared__ __align__(16) unsigned char smem[XS + ZS + 2 * NWAVE * MT * 4];
-  T* xs = (T*)smem;
-  T* zs = (T*)(smem + XS);
-  float* red = (float*)(smem + XS + ZS);
-  const T* W1 = (const T*)w.W1;
-  const T* W2 = (const T*)w.W2;
-  const int n0 = wave_id() * D::CPW;
-  const int n_tiles = (n + MT - 1) / MT;
-
-  // H = 128: the next tile's h and m rows travel in registers while this
-  // tile computes, so their HBM round trip is off the tile's critical path
-  // (wider forms have no registers to spare)
-  constexpr bool PF = H == 128;
-  TileSched sch(n_tiles);
-  NodeRowsPre<T, H, MT, D::LD2> pre;
-  if constexpr (PF)
-    if (sch.begin < sch.end) pre.load(h, m, sch.begin * MT, min(MT, n - sch.begin * MT));
-  for (int t = sch.begin; t < sch.end; t += sch.step) {
-    const int row0 = t * MT, nr = min(MT, n - row0);
-    if constexpr (PF) {
-      pre.store(xs);
-      if (t + sch.step < sch.end) pre.load(h, m, (t + sch.step) * MT, min(MT, n - (t + sch.step) * MT));
-    } else {
-      global_rows_to_lds<T, D::LD2, MT, H>(xs, nr, 0, [&](int i) { return h + (size_t)(row0 + i) * H; });
-      global_f32_rows_to_lds<T, D::LD2, MT, H>(xs, nr, H, [&](int i) { return m + (size_t)(row0 + i) * H; });
-    }
-    lds_sync();
-    f32x4 acc[MB][NB];
-    zero_acc(acc);
-    wave_gemm<T, MB, NB, 2 * H, D::LD2>(acc, xs, W1, 2 * H, n0);
-    f32x4 hv[MB][NB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int c = acc_col(n0, nb);
-        const float bb = w.b1[c];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          acc[mb][nb][r] = act_f<ACT>(acc[mb][nb][r] + bb);
-          hv[mb][nb][r] = to_f(xs[acc_row(mb, r) * D::LD2 + c]);
-        }
-      }
-    acc_to_lds<T, MB, NB, D::LDH>(acc, zs, n0);
-    lds_sync();
-    zero_acc(acc);
-    wave_gemm<T, MB, NB, H, D::LDH>(acc, zs, W2, H, n0);
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const float bb = w.b2[acc_col(n0, nb)];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[mb][nb][r] += bb;
-      }
-    float inv[MB][4];
-    ln_normalize<MB, NB, MT, H>(acc, red, eps, inv);
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int c = acc_col(n0, nb);
-        const float g = w.gamma[c], be = w.beta[c];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          zs[acc_row(mb, r) * D::LDH + c] = from_f<T>(hv[mb][nb][r] + g * acc[mb][nb][r] + be);
-      }
-    lds_sync();
-    lds_rows_to_global<T, D::LDH>(zs, nr, H, h_out + (size_t)row0 * H, H, [](int i) { return i; });
-    lds_sync();
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Encoders: in -> H -> H -> H, LN.  The first layer (in <= 8) is a plain FMA
 // product in the accumulator layout; the other two run on MFMA.
 // Node input: node_in[gid]; edge input: the edge features of k_edge_feat.
@@ -648,14 +564,6 @@ void launch_node_proj(const Shape& s, const BatchView& b, const MlpW& w, const v
     constexpr int MT = H == 512 ? 16 : 32;
     k_node_proj<T, H, MT><<<s.grid, NTHR, 0, st>>>(b.n, w, (const T*)h, pr, ps);
   }));
-}
-
-void launch_node_fwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const float* m,
-                     void* h_out, hipStream_t st) {
-  if (b.n == 0) return;
-  XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
-    k_node_fwd<T, H, MT, ACT><<<s.grid, NTHR, 0, st>>>(b.n, w, (const T*)h, m, (T*)h_out, s.eps);
-  }))));
 }
 
 void launch_enc_node_fwd(const Shape& s, const BatchView& b, const MlpW& w, const float* node_in, int in_dim,

@@ -59,16 +59,18 @@ struct StreamDims {
 // make it wait for more.  At the end of a product (slabs [s0, s1), back to
 // back) it waits for everything, so that the first two slabs of the next need
 // no wait behind the loads and stores between the products.
-template <int NW, int S, int FR>
+// SLOTS == S: the sequence stays in LDS, and none of this is needed.
+template <int NW, int S, int FR, int SLOTS = 4>
 struct WStream {
   static constexpr int SLAB = FR * 1024, K = FR / NW;  // K loads of 1 KiB per wave and slab
-  static_assert(S % 4 == 0, "a slab's slot is s % 4");
+  static constexpr bool STAY = SLOTS == S;
+  static_assert(STAY || (SLOTS == 4 && S % 4 == 0), "a slab's slot is s % 4");
   const unsigned char* base;  // (uniform)
   unsigned char* ring;        // LDS, 4 SLAB bytes
   __device__ __forceinline__ void send(int s) const {
     const int w = __builtin_amdgcn_readfirstlane(wave_id()) * K;
     const unsigned char* g = base + (size_t)(s % S) * SLAB + w * 1024;
-    const unsigned dst = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)(ring) + (s & 3) * SLAB + w * 1024;
+    const unsigned dst = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)(ring) + s % SLOTS * SLAB + w * 1024;
 #pragma unroll
     for (int k = 0; k < K; ++k)
       asm volatile(
@@ -79,14 +81,16 @@ struct WStream {
           : "s"(dst + k * 1024), "v"(lane_id() * 16), "s"(g + k * 1024)
           : "memory", "m0");
   }
-  __device__ __forceinline__ void start() const {  // slabs 0, 1 and 2, whole at the next barrier
-    send(0);
-    send(1);
-    send(2);
+  __device__ __forceinline__ void start() const {  // slabs 0, 1 and 2 (or all), whole at the next barrier
+#pragma unroll
+    for (int s = 0; s < (STAY ? S : 3); ++s) send(s);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
-  __device__ __forceinline__ void begin(int s) const { send(s + 3); }
+  __device__ __forceinline__ void begin(int s) const {
+    if constexpr (!STAY) send(s + 3);
+  }
   __device__ __forceinline__ void end(int s, int s0, int s1) const {
+    if constexpr (STAY) return;
     if (s == s1 - 1)
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else if (s >= s0 + 2) {
@@ -102,7 +106,7 @@ struct WStream {
   // fragment f of slab s
   template <typename V>
   __device__ __forceinline__ const V* frag(int s, int f) const {
-    return (const V*)(ring + (s & 3) * SLAB) + f * 64;
+    return (const V*)(ring + s % SLOTS * SLAB) + f * 64;
   }
   static_assert(K == 2 || K == 4 || K == 8, "waits are written for these counts");
 };
@@ -136,8 +140,8 @@ __device__ __forceinline__ void chunk_gemm(f32x4 (&acc)[MBS], const typename Chu
 
 // x += W xs for an H-wide operand, its weights in slabs [s, s + SP) of a
 // product over slabs [s0, s1).
-template <typename T, int H, int NW, int S>
-__device__ __forceinline__ void stream_gemm(const WStream<NW, S, StreamDims<T, H>::FR>& ws, int s,
+template <typename T, int H, int NW, int S, int SLOTS>
+__device__ __forceinline__ void stream_gemm(const WStream<NW, S, StreamDims<T, H>::FR, SLOTS>& ws, int s,
                                             int s0, int s1, f32x4 (&x)[H / 16],
                                             const typename Chunk<T>::V (&xs)[StreamDims<T, H>::KC]) {
   using L = StreamDims<T, H>;
@@ -156,8 +160,8 @@ __device__ __forceinline__ void zero_blocks(f32x4 (&x)[N]) {
   for (int i = 0; i < N; ++i) x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 // a product of one operand: x = W xs, slabs [s0, s0 + SP)
-template <typename T, int H, int NW, int S>
-__device__ __forceinline__ void stream_product(const WStream<NW, S, StreamDims<T, H>::FR>& ws, int s0,
+template <typename T, int H, int NW, int S, int SLOTS>
+__device__ __forceinline__ void stream_product(const WStream<NW, S, StreamDims<T, H>::FR, SLOTS>& ws, int s0,
                                                f32x4 (&x)[H / 16],
                                                const typename Chunk<T>::V (&xs)[StreamDims<T, H>::KC]) {
   zero_blocks(x);
@@ -180,6 +184,36 @@ __device__ __forceinline__ void arrived_row(V (&v)[KC]) {
 #pragma unroll
   for (int c = 0; c < KC; ++c) arrived(v[c]);
 }
+
+// A row held in FP32 as an operand: load, then get once it is needed (rounded to
+// T, waiting for it at once: the compiler's counted waits do not know of the
+// weight loads behind it).
+template <typename T, int H>
+struct F32Row {
+  using C = Chunk<T>;
+  static constexpr int KC = H / C::KW, N = C::E / 4;
+  f32x4 v[KC][N];
+  __device__ __forceinline__ void load(const float* p, int lg) {
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int k = 0; k < N; ++k) v[c][k] = *(const f32x4*)(p + C::KW * c + C::E * lg + 4 * k);
+  }
+  __device__ __forceinline__ void get(typename C::V (&x)[KC]) {
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) arrived(v[c][k]);
+      if constexpr (N == 1) {
+        x[c] = v[c][0];
+      } else {
+        const u32x4 u = {pack2(v[c][0][0], v[c][0][1]), pack2(v[c][0][2], v[c][0][3]), pack2(v[c][1][0], v[c][1][1]),
+                         pack2(v[c][1][2], v[c][1][3])};
+        x[c] = __builtin_bit_cast(bf16x8, u);
+      }
+    }
+  }
+};
 
 // LayerNorm of a row of H in the accumulator layout (in place -> xhat),
 // returning 1 / std: (mean, M2) of each span of SW features, merged pairwise;
@@ -226,6 +260,42 @@ __device__ __forceinline__ float ln_chain(f32x4 (&u)[H / 16], float eps) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) u[mb][r] = (u[mb][r] - mean) * inv;
   return inv;
+}
+
+// The rows of one wave: [begin, end) of R, and the workgroup's common number
+// of 16-row steps.
+struct WaveRows {
+  int begin, end, steps;
+  __device__ WaveRows(int R, int nw_wg) {
+    const int nw = gridDim.x * nw_wg, w0 = blockIdx.x * nw_wg, wv = w0 + __builtin_amdgcn_readfirstlane(wave_id());
+    begin = (int)((long long)R * wv / nw);
+    end = (int)((long long)R * (wv + 1) / nw);
+    steps = R > 0 ? (R / nw + 1 + 15) >> 4 : 0;  // (no range is longer than R / nw + 1)
+  }
+};
+
+// Adds the NW waves' column sums of one vector (each lane gives its values
+// through put(double* row of H)) and writes them to dst[f * stride].
+template <int H, int NW, typename PutFn>
+__device__ __forceinline__ void wg_colsum(double* ds, float* dst, int stride, PutFn put) {
+  __syncthreads();
+  put(ds + wave_id() * H);
+  __syncthreads();
+  for (int f = threadIdx.x; f < H; f += 64 * NW) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) s += ds[k * H + f];
+    dst[(size_t)f * stride] = (float)s;
+  }
+}
+// ... of totals in colsum64's layout, one per 64 features
+template <int H, int NW>
+__device__ __forceinline__ void wg_colsum64(double* ds, float* dst, const double (&v)[H / 64]) {
+  wg_colsum<H, NW>(ds, dst, 1, [&](double* d) {
+    const int l = lane_id(), li = l & 15, lg = l >> 4;
+#pragma unroll
+    for (int gr = 0; gr < H / 64; ++gr) d[64 * gr + 16 * (li >> 2) + 4 * lg + (li & 3)] = v[gr];
+  });
 }
 
 }  // namespace xmgn

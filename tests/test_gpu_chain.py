@@ -111,6 +111,34 @@ def test_fp32_edges(api, hidden, n, degrees, agg):
     assert e_out <= 1e-4 and e_grad <= 1e-4
 
 
+@pytest.mark.parametrize("precision,hidden", [("bf16", 128), ("bf16", 256), ("bf16", 512), ("fp32", 128), ("fp32", 256)])
+def test_rows_in_several_steps(api, precision, hidden):
+    """So many nodes that every wave takes its rows in two or more 16-row steps,
+    the last one ragged, two layers (the lower layer's node adjoint starts from
+    the sums of the upper layer's edges), SiLU, at the form's bar (outputs and
+    whole gradient 2e-2 or 1e-4)."""
+    n = 33001
+    case = Case(1, levels=(n,), hidden=hidden, layers=2, precision=precision, activation="silu")
+    rng = np.random.default_rng(2)
+    case._graph = G = og.Graph(n, np.arange(n, dtype=np.int64), (np.arange(n) + rng.integers(1, n, n)) % n)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    ctx = api.Context(0)
+    ps = api.Partset.halo(api.Graph.from_csr(G.row_ptr, G.col), case.inp.pos, None, case.L)
+    p, out = dev(case.params), torch.full((n, 4), float("nan"), device="cuda")
+    d_out, loss, grad = torch.zeros_like(out), torch.zeros(1, device="cuda"), torch.full_like(p, float("nan"))
+    ctx.forward(case.model(api), p, ps, [0], dev(case.inp.node_in), dev(case.inp.pos), case.inp.edge_norm, out)
+    ctx.mse_grad(out, dev(case.inp.targets), n, d_out, loss)
+    ctx.backward(case.model(api), p, d_out, grad)
+    torch.cuda.synchronize()
+    log(f"steps {precision} H={hidden}: the oracle")
+    base, amp = oracle_refs(case)
+    _, y, g = amp or base
+    e_out, e_grad = rel_l2(out.cpu().numpy(), y), rel_l2(grad.cpu().numpy(), g)
+    log(f"  out {e_out:.2e} grad {e_grad:.2e}")
+    bar = 2e-2 if precision == "bf16" else 1e-4
+    assert e_out <= bar and e_grad <= bar
+
+
 @pytest.mark.parametrize("hidden", [256, 512])
 @pytest.mark.parametrize("node_in", [1, 8, 12, 32])
 def test_stream_encoder_inputs(api, hidden, node_in):
