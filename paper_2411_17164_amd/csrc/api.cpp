@@ -548,7 +548,7 @@ struct xmgn_ctx {
   std::vector<hipEvent_t> sev;       // ordering events between st and cs
   size_t sev_used = 0;
   // backward workspace
-  DBuf dhA, dhMid, dm, Sr, Ss, deA, deB, fa, fb, fc, fd, dy, part, wpart, wfused, redtmp, lossp;
+  DBuf dhA, dhMid, dm, Sr, Ss, deA, deB, fa, fb, fc, fd, na, nb, nc, dy, part, wpart, wfused, redtmp, lossp;
   DBuf part_e, wfused_e;  // the edge adjoint's partials, reduced with the node adjoint's at the end of a layer
   DBuf xe;    // edge features of the forward [E][4]
   DBuf optp;  // optimizer: per-workgroup squared-norm partials (FP64)
@@ -757,7 +757,7 @@ extern "C" xmgn_status xmgn_ctx_memory(const xmgn_ctx* c, int64_t* bytes) {
   int64_t t = 0;
   for (const auto& P : c->plans) t += (int64_t)P->ints.bytes;
   const DBuf* bufs[] = {&c->jobs_dev, &c->blob, &c->h, &c->e, &c->m, &c->dhA, &c->dhMid,
-                        &c->dm, &c->Sr, &c->Ss, &c->deA, &c->deB, &c->fa, &c->fb, &c->fc, &c->fd,
+                        &c->dm, &c->Sr, &c->Ss, &c->deA, &c->deB, &c->fa, &c->fb, &c->fc, &c->fd, &c->na, &c->nb, &c->nc,
                         &c->dy, &c->part, &c->wpart, &c->wfused, &c->redtmp, &c->lossp, &c->xe, &c->zt,
                         &c->part_e, &c->wfused_e, &c->proj,
                         &c->at, &c->optp};
@@ -1315,20 +1315,13 @@ extern "C" xmgn_status xmgn_mse_grad(xmgn_ctx* c, const float* out, const float*
   GUARD_END
 }
 
-static void wgrad_run(xmgn_ctx* c, const Shape& s, WgradOp op, DBuf& wpart, hipStream_t st) {
-  KT("wgrad");
-  launch_wgrad(s, op, wpart.as<float>(), c->redtmp.as<float>(), st);
-}
-#define wgrad(s_, op_, wp_, st_) wgrad_run(c, s_, op_, wp_, st_)
-
-static WgradOp wop(const void* A, int a_f32, int lda, int a0, const int* ia, const void* B, int b_f32, int ldb, int b0,
+static WgradOp wop(const void* A, int a_f32, int lda, int a0, const void* B, int b_f32, int ldb, int b0,
                    const int* ib, int R, int M, int N, float* dst, int ldd, int M_valid = -1) {
   WgradOp o{};
   o.A = A;
   o.a_f32 = a_f32;
   o.lda = lda;
   o.a0 = a0;
-  o.ia = ia;
   o.B = B;
   o.b_f32 = b_f32;
   o.ldb = ldb;
@@ -1359,8 +1352,6 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
   const size_t H = d->hidden, n = c->cur->n, E = c->cur->E, ts = tsize(d);
   const int L = d->n_layers, G = s.grid;
   const size_t rows = std::max(n, E);
-  constexpr int kLayerWgrads = 7;
-  size_t wpart_stride = 0;
   for (DBuf* p : {&c->dhA, &c->dhMid, &c->dm, &c->Sr, &c->Ss})
     if (xmgn_status r = p->ensure(n * H * 4, st)) return r;
   for (DBuf* p : {&c->deA, &c->deB})
@@ -1369,17 +1360,9 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     if (xmgn_status r = p->ensure(rows * H * ts, st)) return r;
   if (xmgn_status r = c->dy.ensure((size_t)c->cur->n_inner * 16 * 4, st)) return r;
   if (xmgn_status r = c->part.ensure((size_t)std::max(G, 256) * 13 * H * 4, st)) return r;
-  {
-    size_t need = 0;
-    const int Rs[3] = {(int)n, (int)E, c->cur->n_inner};
-    for (int R : Rs)
-      need = std::max(need, wgrad_partial_floats(s, wop(nullptr, 0, 0, 0, nullptr, nullptr, 0, 0, 0, nullptr, R,
-                                                        (int)H, (int)H, nullptr, 0)));
-    // a layer's separate weight-gradient products (at most 3 node-side, 4
-    // edge-side) each keep their partials until the layer's reductions run
-    wpart_stride = need;
-    if (xmgn_status r = c->wpart.ensure(kLayerWgrads * need * 4, st)) return r;
-  }
+  for (DBuf* p : {&c->na, &c->nb, &c->nc})  // the node adjoint's da, du, z, kept to the layer's weight gradients
+    if (xmgn_status r = p->ensure(n * H * ts, st)) return r;
+  if (xmgn_status r = c->wpart.ensure(wgrad_partial_floats(s) * 4, st)) return r;
   // the edge adjoint may accumulate its dense weight gradients itself
   // the edge adjoint runs on its own tiling of the batch's edges
   Shape se = s;
@@ -1410,14 +1393,17 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     DecBwdOut o{c->dhA.as<float>(), c->fa.p, c->fb.p, c->fc.p, c->fd.p, c->dy.as<float>(), part};
     { KT("dec_bwd"); launch_dec_bwd(s, b, weights(c, d, params, 2 + 2 * L, 4, 0), hl(L), d_out, d->out_dim, o, st); }
     VecSeg segs[3] = {{0, (int)H, P(4, 0, 1)}, {(int)H, (int)H, P(4, 0, 3)}, {2 * (int)H, d->out_dim, P(4, 0, 5)}};
-    launch_vec_reduce(part, G, 2 * (int)H + 16, segs, 3, rt, st);
     const int ni = c->cur->n_inner;
-    wgrad(s, wop(c->dy.p, 1, 16, 0, nullptr, c->fb.p, 0, (int)H, 0, nullptr, ni, 16, (int)H, P(4, 0, 4), (int)H,
-                 d->out_dim), c->wpart, st);
-    wgrad(s, wop(c->fd.p, 0, (int)H, 0, nullptr, c->fa.p, 0, (int)H, 0, nullptr, ni, (int)H, (int)H, P(4, 0, 2), (int)H),
-          c->wpart, st);
-    wgrad(s, wop(c->fc.p, 0, (int)H, 0, nullptr, hl(L), 0, (int)H, 0, b.inner, ni, (int)H, (int)H, P(4, 0, 0), (int)H),
-          c->wpart, st);
+    KT("wgrad");
+    RedBatch rb;
+    rb.add_vec(part, G, 2 * (int)H + 16, segs, 3);
+    WgradBatch wb;
+    wb.add(wop(c->dy.p, 1, 16, 0, c->fb.p, 0, (int)H, 0, nullptr, ni, 16, (int)H, P(4, 0, 4), (int)H,
+               d->out_dim));
+    wb.add(wop(c->fd.p, 0, (int)H, 0, c->fa.p, 0, (int)H, 0, nullptr, ni, (int)H, (int)H, P(4, 0, 2), (int)H));
+    wb.add(wop(c->fc.p, 0, (int)H, 0, hl(L), 0, (int)H, 0, b.inner, ni, (int)H, (int)H, P(4, 0, 0), (int)H));
+    launch_wgrad(s, wb, c->wpart.as<float>(), rb, st);
+    launch_reduce_batch(rb, rt, st);
   }
   // processor layers, last to first
   const float* de_in = nullptr;
@@ -1435,7 +1421,7 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
       if (xmgn_status r = tape_in(c, d, st, l - 1, true, em, em, &back[l - 1])) return r;
     }
     const MlpW wn = weights(c, d, params, 3 + 2 * l, 3, l);
-    NodeBwdOut no{c->dhMid.as<float>(), c->dm.as<float>(), c->fa.p, c->fb.p, c->fc.p, part};
+    NodeBwdOut no{c->dhMid.as<float>(), c->dm.as<float>(), c->na.p, c->nb.p, c->nc.p, part};
     {
       KT("node_bwd");
       if (l == L - 1)  // below the decoder
@@ -1444,23 +1430,19 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
         launch_node_bwd(s, b, wn, hl(l), mslot(c, d, l), c->dhMid.as<float>(), c->Sr.as<float>(), c->Ss.as<float>(), no,
                         st);
     }
-    // the layer's reductions of partial sums run as one batch at its end
+    // the layer's weight-gradient products run in one launch at its end, and the
+    // reductions of all its partial sums in another two
     RedBatch rb;
-    int n_wg = 0;
-    auto wg = [&](const WgradOp& op) {
-      if (n_wg >= kLayerWgrads) throw std::logic_error("more weight-gradient products in a layer than partials");
-      KT("wgrad");
-      launch_wgrad_partials(s, op, c->wpart.as<float>() + (size_t)(n_wg++) * wpart_stride, rb, st);
-    };
+    WgradBatch wb;
     VecSeg ns[4] = {{0, (int)H, P(3, l, 1)}, {(int)H, (int)H, P(3, l, 3)}, {2 * (int)H, (int)H, P(3, l, 4)},
                     {3 * (int)H, (int)H, P(3, l, 5)}};
     rb.add_vec(part, edge_stream_grid(s, (int)n), 4 * (int)H, ns, 4);
     // dW1 = sum da [h ; m]^T (two products); dW2 = sum du z^T
-    wg(wop(c->fa.p, 0, (int)H, 0, nullptr, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 0),
+    wb.add(wop(c->na.p, 0, (int)H, 0, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 0),
            2 * (int)H));
-    wg(wop(c->fa.p, 0, (int)H, 0, nullptr, mslot(c, d, l), 1, (int)H, 0, nullptr, (int)n, (int)H, (int)H,
+    wb.add(wop(c->na.p, 0, (int)H, 0, mslot(c, d, l), 1, (int)H, 0, nullptr, (int)n, (int)H, (int)H,
            P(3, l, 0) + H, 2 * (int)H));
-    wg(wop(c->fb.p, 0, (int)H, 0, nullptr, c->fc.p, 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 2),
+    wb.add(wop(c->nb.p, 0, (int)H, 0, c->nc.p, 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 2),
            (int)H));
 
     const MlpW we = weights(c, d, params, 2 + 2 * l, 2, l);
@@ -1482,19 +1464,23 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
       KT("node_dh");
       launch_node_dh(s, b, we, c->dhMid.as<float>(), c->Sr.as<float>(), c->Ss.as<float>(), c->dhA.as<float>(), st);
     }
-    wg(wop(c->Sr.p, 1, (int)H, 0, nullptr, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(2, l, 0),
+    wb.add(wop(c->Sr.p, 1, (int)H, 0, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(2, l, 0),
            3 * (int)H));
-    wg(wop(c->Ss.p, 1, (int)H, 0, nullptr, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(2, l, 0) + H,
+    wb.add(wop(c->Ss.p, 1, (int)H, 0, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(2, l, 0) + H,
            3 * (int)H));
     if (!fw) {
-      wg(wop(c->fa.p, 0, (int)H, 0, nullptr, eslot(c, d, l), 0, (int)H, 0, nullptr, (int)E, (int)H, (int)H,
+      wb.add(wop(c->fa.p, 0, (int)H, 0, eslot(c, d, l), 0, (int)H, 0, nullptr, (int)E, (int)H, (int)H,
              P(2, l, 0) + 2 * H, 3 * (int)H));
-      wg(wop(c->fb.p, 0, (int)H, 0, nullptr, zt ? zt : c->fc.p, 0, (int)H, 0, nullptr, (int)E, (int)H, (int)H,
+      wb.add(wop(c->fb.p, 0, (int)H, 0, zt ? zt : c->fc.p, 0, (int)H, 0, nullptr, (int)E, (int)H, (int)H,
              P(2, l, 2), (int)H));
     }
-    if ((size_t)rb.tmp_floats > reduce_tmp_floats((int)red_cols))
-      throw std::logic_error("a layer's reduction batch exceeds its scratch");
-    { KT("wgrad"); launch_reduce_batch(rb, rt, st); }
+    {
+      KT("wgrad");
+      launch_wgrad(s, wb, c->wpart.as<float>(), rb, st);
+      if ((size_t)rb.tmp_floats > reduce_tmp_floats((int)red_cols))
+        throw std::logic_error("a layer's reduction batch exceeds its scratch");
+      launch_reduce_batch(rb, rt, st);
+    }
     de_in = de_out->as<float>();
     std::swap(de_out, de_other);
   }
@@ -1521,23 +1507,26 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     }
     VecSeg vs[5] = {{0, (int)H, P(blk, 0, 1)}, {(int)H, (int)H, P(blk, 0, 3)}, {2 * (int)H, (int)H, P(blk, 0, 5)},
                     {3 * (int)H, (int)H, P(blk, 0, 6)}, {4 * (int)H, (int)H, P(blk, 0, 7)}};
-    launch_vec_reduce(part, sn.grid, 13 * (int)H, vs, 5, rt, st);
+    KT("wgrad");
+    RedBatch rb;
+    WgradBatch wb;
+    rb.add_vec(part, sn.grid, 13 * (int)H, vs, 5);
     if (wide)
-      wgrad(s, wop(c->Sr.p, 1, (int)H, 0, nullptr, c->f_node_in, 1, in_dim, 0, b.gid, (int)n, (int)H, in_dim,
-                   P(blk, 0, 0), in_dim), c->wpart, st);
-    else
-      launch_vec_reduce_strided(part, sn.grid, 13 * (int)H, 5 * (int)H, (int)H, in_dim, 8, P(blk, 0, 0), in_dim, rt, st);
+      wb.add(wop(c->Sr.p, 1, (int)H, 0, c->f_node_in, 1, in_dim, 0, b.gid, (int)n, (int)H, in_dim,
+                 P(blk, 0, 0), in_dim));
     if (fe) {
-      KT("wgrad");
-      launch_wgrad_reduce(c->wfused.as<float>(), sn.grid, (int)H, (int)H, P(blk, 0, 2), (int)H, 2 * (int)(H * H), rt, st);
-      launch_wgrad_reduce(c->wfused.as<float>() + H * H, sn.grid, (int)H, (int)H, P(blk, 0, 4), (int)H,
-                          2 * (int)(H * H), rt, st);
+      rb.add(c->wfused.as<float>(), sn.grid, 2 * (int)(H * H), (int)H, (int)H, P(blk, 0, 2), (int)H);
+      rb.add(c->wfused.as<float>() + H * H, sn.grid, 2 * (int)(H * H), (int)H, (int)H, P(blk, 0, 4), (int)H);
     } else {
-      wgrad(s, wop(c->fd.p, 0, (int)H, 0, nullptr, c->fb.p, 0, (int)H, 0, nullptr, R, (int)H, (int)H, P(blk, 0, 4),
-                   (int)H), c->wpart, st);
-      wgrad(s, wop(c->fc.p, 0, (int)H, 0, nullptr, c->fa.p, 0, (int)H, 0, nullptr, R, (int)H, (int)H, P(blk, 0, 2),
-                   (int)H), c->wpart, st);
+      wb.add(wop(c->fd.p, 0, (int)H, 0, c->fb.p, 0, (int)H, 0, nullptr, R, (int)H, (int)H, P(blk, 0, 4),
+                 (int)H));
+      wb.add(wop(c->fc.p, 0, (int)H, 0, c->fa.p, 0, (int)H, 0, nullptr, R, (int)H, (int)H, P(blk, 0, 2),
+                 (int)H));
     }
+    launch_wgrad(s, wb, c->wpart.as<float>(), rb, st);
+    launch_reduce_batch(rb, rt, st);
+    if (!wide)
+      launch_vec_reduce_strided(part, sn.grid, 13 * (int)H, 5 * (int)H, (int)H, in_dim, 8, P(blk, 0, 0), in_dim, rt, st);
   }
   HIPCHK(hipGetLastError());
   if (g_config_error) return fail(XMGN_ERR_UNSUPPORTED, "tile configuration does not fit this kernel");

@@ -2,6 +2,7 @@
 // (split over row chunks, reduced in a fixed order), fixed-order reductions
 // of per-workgroup partial vectors, weight preparation (cast / transpose into
 // the compute type), the masked MSE and gradient accumulation.
+#include <algorithm>
 #include <mutex>
 #include <stdexcept>
 #include <type_traits>
@@ -14,118 +15,202 @@ namespace xmgn {
 int g_config_error = 0;
 
 // ---------------------------------------------------------------------------
-// wgrad: C[m][n] = sum_r A[r][a0 + m] * B[r][b0 + n].  A workgroup owns one
-// chunk of rows and one 128x128 output block.  Rows go through LDS 128 at a
-// time, transposed so that the row index is the MFMA k dimension; the loads
-// of the next stage are issued before the products of the current one, so
-// their round trip overlaps the MFMAs.
+// wgrad: C[m][n] = sum_r A[r][a0 + m] * B[r][b0 + n], several such products in
+// one launch.  A workgroup owns one chunk of one product's rows and one block
+// of its outputs: 128 x 128 by four waves, or, in the BF16 form from H = 256
+// on, 256 x 256 by eight, which halves the reads of the operands.  Rows go to
+// LDS as they lie in memory, 64 (FP32: 32) at a time, into two buffers in turn,
+// with one barrier per stage and the loads of the next stage in flight behind
+// it; the row index is the MFMA k dimension, so the BF16 fragments are
+// transposing reads (32-byte units swizzled by row: no bank conflicts on either
+// side) and the FP32 ones four reads of one word (rows padded by 16 bytes).
+// Two products over 444k rows, BF16, H = 512: 480 us (970 TFLOP/s).  All weight
+// gradients of a step with their sums, against a launch per product of 128-row
+// stages transposed on their way into LDS (eight lanes to a bank) and two
+// reductions each: 2,000 nodes, FP32: 441 -> 155 us; 50k nodes, FP32: 2.54 -> 1.78
+// ms; 100k, BF16, H = 256: 3.26 -> 2.5; 50k, H = 512: 4.07 -> 2.9; 400k, H = 128
+// (bound by reading its operands): 5.9 -> 4.4.  Loads under a condition, or
+// behind a possible row index, each waited for the ones before: 20% slower.
 // ---------------------------------------------------------------------------
-constexpr int WG_B = 128;  // output block edge
-constexpr int WG_K = 128;  // rows per stage
-
-template <typename T>
-struct WgLds {
-  static constexpr int PAD = 16 / sizeof(T);
-  static constexpr int LD = WG_K + PAD;
+template <typename T, int BLK, int ROWS = 64>
+struct Wg {
+  static constexpr int NW = BLK == 256 ? 8 : 4, NT = 64 * NW;
+  static constexpr int KR = sizeof(T) == 2 ? ROWS : 32;     // rows per stage
+  static constexpr int E = 16 / sizeof(T), UPR = BLK / E;   // elements per 16-byte unit; units per row
+  static constexpr int RPP = NT / UPR, P = KR / RPP;        // rows per pass of the workgroup; passes
+  static constexpr int LD = sizeof(T) == 2 ? BLK * 2 : BLK * 4 + 16;  // bytes per LDS row
+  static constexpr int TILE = KR * LD;
+  static constexpr int FM = BLK / 32, FN = 4;               // 16 x 16 blocks of a wave
+  static __device__ __forceinline__ int off(int row, int u) {
+    if constexpr (sizeof(T) == 2)
+      return row * LD + (((u >> 1) ^ (row & 7)) << 5) + ((u & 1) << 4);
+    else
+      return row * LD + 16 * u;
+  }
 };
 
-// One thread's share of a stage: 4 columns (4 (t % 32)) of 16 rows
-// (16 (t / 32)) of one operand, loaded as 8 (BF16) or 16 (FP32) bytes per row.
-template <typename S>
-struct Slab {
-  using L = typename std::conditional<sizeof(S) == 4, float4, uint2>::type;
-  L v[16];
-  __device__ __forceinline__ void load(const S* base, int ld, int col0, const int* idx, int r0, int r_end, int c0,
-                                       int C) {
-    const int c = c0 + 4 * ((int)threadIdx.x & 31), rr = r0 + 16 * ((int)threadIdx.x >> 5);
-    const S* p = base + col0 + c;
-    // uniform branch: a gathered operand loads its 16 row indices first, so
-    // that neither path waits between its data loads
-    if (idx) {
-      int ri[16];
+// One thread's share of a stage of one operand (source type S).
+template <typename T, typename S, typename G, int BLK>
+struct WgStage {
+  static constexpr int N = sizeof(S) / sizeof(T);  // 16-byte loads per unit
+  uint4 v[G::P][N];
+  // (rows and columns out of range repeat one within; store() clears them)
+  __device__ __forceinline__ void load(const S* base, int ld, int r0, int r_end, int c0, int C) {
+    const int c = c0 + G::E * ((int)threadIdx.x % G::UPR), rr = (int)threadIdx.x / G::UPR;
+    const char* s = (const char*)(base + (size_t)r0 * ld);  // (uniform; 32-bit offsets within a stage)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) ri[j] = (c < C && rr + j < r_end) ? idx[rr + j] : -1;
+    for (int p = 0; p < G::P; ++p)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) v[j] = ri[j] >= 0 ? *(const L*)(p + (size_t)ri[j] * ld) : L{};
-    } else {
+      for (int k = 0; k < N; ++k) {
+        const int ck = c + k * (G::E / N);
+        const unsigned o = (unsigned)(min(rr + p * G::RPP, r_end - 1 - r0) * ld + (ck < C ? ck : 0)) * (unsigned)sizeof(S);
+        v[p][k] = *(const uint4*)(s + o);
+      }
+  }
+  // rows taken through idx (their indices first, so that no load waits for another)
+  __device__ __forceinline__ void load(const S* base, int ld, const int* idx, int r0, int r_end, int c0, int C) {
+    const int c = c0 + G::E * ((int)threadIdx.x % G::UPR), rr = r0 + (int)threadIdx.x / G::UPR;
+    int ri[G::P];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) v[j] = (c < C && rr + j < r_end) ? *(const L*)(p + (size_t)(rr + j) * ld) : L{};
+    for (int p = 0; p < G::P; ++p) ri[p] = idx[min(rr + p * G::RPP, r_end - 1)];
+#pragma unroll
+    for (int p = 0; p < G::P; ++p)
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const int ck = c + k * (G::E / N);
+        v[p][k] = *(const uint4*)(base + (size_t)ri[p] * ld + (ck < C ? ck : 0));
+      }
+  }
+  __device__ __forceinline__ void store(unsigned char* tile, int r0, int r_end, int c0, int C) {
+    const int u = (int)threadIdx.x % G::UPR, rr = (int)threadIdx.x / G::UPR;
+    if (r0 + G::KR > r_end || c0 + BLK > C) {
+#pragma unroll
+      for (int p = 0; p < G::P; ++p)
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+          if (r0 + rr + p * G::RPP >= r_end || c0 + G::E * u + k * (G::E / N) >= C) v[p][k] = uint4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int p = 0; p < G::P; ++p) {
+      uint4 x = v[p][0];
+      if constexpr (N == 2) {
+        T h[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) h[k] = from_f<T>(((const float*)&v[p][k >> 2])[k & 3]);
+        x = *(const uint4*)h;
+      }
+      *(uint4*)(tile + G::off(rr + p * G::RPP, u)) = x;
     }
   }
-  // column q of the 4, as 16 consecutive k values
-  template <typename T>
-  __device__ __forceinline__ void store(T* dst) const {
-    constexpr int LD = WgLds<T>::LD;
-    T* d0 = dst + (4 * ((int)threadIdx.x & 31)) * LD + 16 * ((int)threadIdx.x >> 5);
+};
+
+// Fragment [columns c0 .. + 15][k chunk c] of a tile; the k order of BF16
+// (rows 4 g + r, 16 + 4 g + r of 32) is the same on both operands.
+template <typename T, int BLK>
+__device__ __forceinline__ typename TT<T>::V wg_frag(const unsigned char* tile, int c, int c0) {
+  using G = Wg<T, BLK>;
+  const int l = lane_id(), L = l & 15, lg = l >> 4;
+  if constexpr (sizeof(T) == 2) {
+    const int row = 32 * c + 4 * lg + (L >> 2), f = c0 + 4 * (L & 3);
+    const unsigned char* p = tile + G::off(row, f >> 3) + (f & 7) * 2;
+    const bf16x4_lds lo = lds_read_tr4((const bf16*)p), hi = lds_read_tr4((const bf16*)(p + 16 * G::LD));
+    return bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  } else {
+    const unsigned char* p = tile + (16 * c + 4 * lg) * G::LD + (c0 + L) * 4;
+    return f32x4{*(const float*)p, *(const float*)(p + G::LD), *(const float*)(p + 2 * G::LD),
+                 *(const float*)(p + 3 * G::LD)};
+  }
+}
+
+template <typename T, int BLK, typename SA, typename SB, bool IDX>
+__device__ __forceinline__ void wg_block(const WgradOp& op, int r_begin, int r_end, int m0, int n0, unsigned char* smem,
+                                         float* __restrict__ out) {
+  // (two FP32 sources of BF16 products: 32 rows, or their loads spill)
+  using G = Wg<T, BLK, sizeof(SA) + sizeof(SB) == 8 ? 32 : 64>;
+  using V = typename TT<T>::V;
+  constexpr int KC = 4 * TT<T>::E;
+  const int w = wave_id(), wm = (w & 1) * (BLK / 2), wn = (w >> 1) * 64;
+  const int l = lane_id(), li = l & 15, lg = l >> 4;
+  const SA* A = (const SA*)op.A + op.a0;
+  const SB* B = (const SB*)op.B + op.b0;
+  f32x4 acc[G::FM][G::FN];
+  zero_acc(acc);
+  WgStage<T, SA, G, BLK> sa;
+  WgStage<T, SB, G, BLK> sb;
+  auto load = [&](int r0) {
+    if constexpr (IDX)
+      sb.load(B, op.ldb, op.ib, r0, r_end, n0, op.N);
+    else
+      sb.load(B, op.ldb, r0, r_end, n0, op.N);
+    sa.load(A, op.lda, r0, r_end, m0, op.M);
+  };
+  const bool live = m0 + wm < op.M && n0 + wn < op.N;  // (uniform)
+  load(r_begin);
+  int half = 0;
+  for (int r0 = r_begin; r0 < r_end; r0 += G::KR, half ^= 1) {
+    unsigned char* At = smem + half * 2 * G::TILE;
+    unsigned char* Bt = At + G::TILE;
+    // this buffer was last read before the previous stage's barrier
+    sa.store(At, r0, r_end, m0, op.M);
+    sb.store(Bt, r0, r_end, n0, op.N);
+    __syncthreads();
+    if (r0 + G::KR < r_end) load(r0 + G::KR);
+    if (live) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      T col[16];
+      for (int c = 0; c < G::KR / KC; ++c) {
+        V b[G::FN];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        if constexpr (sizeof(S) == 4) {
-          col[j] = from_f<T>(((const float*)&v[j])[q]);
-        } else {
-          col[j] = from_f<T>(to_f(((const S*)&v[j])[q]));
+        for (int j = 0; j < G::FN; ++j) b[j] = wg_frag<T, BLK>(Bt, c, wn + 16 * j);
+        V a = wg_frag<T, BLK>(At, c, wm);
+#pragma unroll
+        for (int i = 0; i < G::FM; ++i) {
+          const V ai = a;
+          if (i + 1 < G::FM) a = wg_frag<T, BLK>(At, c, wm + 16 * (i + 1));
+#pragma unroll
+          for (int j = 0; j < G::FN; ++j) acc[i][j] = mma(ai, b[j], acc[i][j]);
         }
       }
-#pragma unroll
-      for (int j = 0; j < 16; j += 16 / (int)sizeof(T)) *(uint4*)(d0 + q * LD + j) = *(const uint4*)&col[j];
     }
   }
-};
-
-template <typename T, typename SA, typename SB>
-__global__ __launch_bounds__(NTHR, 2) void k_wgrad(WgradOp op, int rows_per_chunk, int nbm, float* __restrict__ partial) {
-  using V = typename TT<T>::V;
-  constexpr int E = TT<T>::E, KC = 4 * E, LD = WgLds<T>::LD;
-  __shared__ __align__(16) T At[WG_B * LD];
-  __shared__ __align__(16) T Bt[WG_B * LD];
-  const int chunk = blockIdx.x;
-  const int bm = blockIdx.y % nbm, bn = blockIdx.y / nbm;
-  const int m0 = bm * WG_B, nn0 = bn * WG_B;
-  const int r_begin = chunk * rows_per_chunk;
-  const int r_end = min(op.R, r_begin + rows_per_chunk);
-  const int w = wave_id(), wm = w & 1, wn = w >> 1;
-  const int l = lane_id(), li = l & 15, lg = l >> 4;
-  f32x4 acc[4][4];
-  zero_acc(acc);
-  Slab<SA> sa;
-  Slab<SB> sb;
-  sa.load((const SA*)op.A, op.lda, op.a0, op.ia, r_begin, r_end, m0, op.M);
-  sb.load((const SB*)op.B, op.ldb, op.b0, op.ib, r_begin, r_end, nn0, op.N);
-  for (int r0 = r_begin; r0 < r_end; r0 += WG_K) {
-    __syncthreads();  // the previous stage's products are done with At, Bt
-    sa.template store<T>(At);
-    sb.template store<T>(Bt);
-    __syncthreads();
-    if (r0 + WG_K < r_end) {  // next stage in flight during this stage's MFMAs
-      sa.load((const SA*)op.A, op.lda, op.a0, op.ia, r0 + WG_K, r_end, m0, op.M);
-      sb.load((const SB*)op.B, op.ldb, op.b0, op.ib, r0 + WG_K, r_end, nn0, op.N);
-    }
 #pragma unroll
-    for (int k = 0; k < WG_K; k += KC) {
-      V bfr[4];
+  for (int i = 0; i < G::FM; ++i)
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) bfr[nb] = *(const V*)(Bt + (wn * 64 + nb * 16 + li) * LD + k + lg * E);
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        const V a = *(const V*)(At + (wm * 64 + mb * 16 + li) * LD + k + lg * E);
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = mma(a, bfr[nb], acc[mb][nb]);
-      }
-    }
-  }
-  float* out = partial + (size_t)chunk * op.M * op.N;
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
+    for (int j = 0; j < G::FN; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm * 64 + mb * 16 + lg * 4 + r;
-        const int n = nn0 + wn * 64 + nb * 16 + li;
-        if (m < op.M && n < op.N) out[(size_t)m * op.N + n] = acc[mb][nb][r];
+        const int m = m0 + wm + 16 * i + 4 * lg + r, n = n0 + wn + 16 * j + li;
+        if (m < op.M && n < op.N) out[(size_t)m * op.N + n] = acc[i][j][r];
       }
+}
+
+// Workgroup ids of a product go chunk by chunk in groups of eight, one per XCD,
+// so that the blocks of one chunk, and the products over the same rows, meet
+// their operands in one L2.
+template <typename T, int BLK>
+__global__ __launch_bounds__((Wg<T, BLK>::NT), 2) void k_wgrad(WgradBatch b) {
+  using G = Wg<T, BLK>;
+  __shared__ __align__(16) unsigned char smem[4 * G::TILE];
+  int j = 0;
+  while (j + 1 < b.n && (int)blockIdx.x >= b.job[j + 1].first) ++j;
+  const WgradJob& jb = b.job[j];
+  const WgradOp& op = jb.op;
+  const int id = blockIdx.x - jb.first, nbm = (op.M + BLK - 1) / BLK, blocks = nbm * ((op.N + BLK - 1) / BLK);
+  const int blk = (id >> 3) % blocks, chunk = (id >> 3) / blocks * 8 + (id & 7);
+  if (chunk >= jb.chunks) return;
+  const int r0 = chunk * jb.rows, r1 = min(op.R, r0 + jb.rows);
+  const int m0 = blk % nbm * BLK, n0 = blk / nbm * BLK;
+  float* out = jb.partial + (size_t)chunk * op.M * op.N;
+  // (the combinations launch_wgrad lets through)
+  if (op.ib) {
+    if (op.b_f32) wg_block<T, BLK, float, float, true>(op, r0, r1, m0, n0, smem, out);
+    else if constexpr (sizeof(T) == 2) wg_block<T, BLK, T, T, true>(op, r0, r1, m0, n0, smem, out);
+  } else if constexpr (sizeof(T) == 4) {
+    wg_block<T, BLK, float, float, false>(op, r0, r1, m0, n0, smem, out);
+  } else {
+    if (op.a_f32) wg_block<T, BLK, float, T, false>(op, r0, r1, m0, n0, smem, out);
+    else if (op.b_f32) wg_block<T, BLK, T, float, false>(op, r0, r1, m0, n0, smem, out);
+    else wg_block<T, BLK, T, T, false>(op, r0, r1, m0, n0, smem, out);
+  }
 }
 
 // Fixed-order column sums of a [rows][stride] partial matrix, in two
@@ -181,109 +266,91 @@ __global__ void k_colsum_stage1(const float* __restrict__ src, int rows, int str
   tmp[(size_t)s * ncol + j] = split_sum(src + j, stride, r0, r1);
 }
 
-__global__ void k_wgrad_reduce(const float* __restrict__ tmp, int splits, int M_valid, int N,
-                               float* __restrict__ dst, int ldd, int ncol) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= M_valid * N) return;
-  const int m = idx / N, n = idx - m * N;
-  dst[(size_t)m * ldd + n] = order_sum(tmp + idx, ncol, splits);
-}
-
 size_t reduce_tmp_floats(int max_cols) { return (size_t)RED_SPLITS * (size_t)max_cols; }
 
-// dst[m * ldd + n] = sum over r < rows of src[r * stride + m * N + n], m < M_valid.
-// tmp: caller scratch of reduce_tmp_floats(M_valid * N) floats.
-static void colsum_to(const float* src, int rows, int stride, int M_valid, int N, float* dst, int ldd, float* tmp,
-                      hipStream_t st) {
-  const int ncol = M_valid * N;
-  const int splits = rows < RED_SPLITS ? (rows > 0 ? rows : 1) : RED_SPLITS;
-  const int per = rows > 0 ? (rows + splits - 1) / splits : 0;
-  k_colsum_stage1<<<dim3((ncol + 255) / 256, splits), 256, 0, st>>>(src, rows, stride, ncol, per, tmp);
-  k_wgrad_reduce<<<(ncol + 255) / 256, 256, 0, st>>>(tmp, splits, M_valid, N, dst, ldd, ncol);
+// Two workgroups of 128 x 128 blocks per CU, one of 256 x 256 (from H = 256 on
+// in BF16: 2.6 ms in all on 100k nodes where 128 x 128 took 3.26; an FP32 block
+// of 256 x 256 would leave no room for a second buffer)
+static int wgrad_block(const Shape& s) { return s.prec == 1 && s.H >= 256 ? 256 : 128; }
+static int wgrad_target(const Shape& s) { return wgrad_block(s) == 256 ? 256 : 512; }
+
+size_t wgrad_partial_floats(const Shape& s) {
+  const int blk = wgrad_block(s), nb = (s.H + blk - 1) / blk;
+  return (size_t)std::max(wgrad_target(s), kMaxWgradJobs * nb * nb) * blk * blk;
 }
 
-void launch_wgrad_reduce(const float* partial, int n_chunks, int M_valid, int N, float* dst, int ldd, int MN,
-                         float* tmp, hipStream_t st) {
-  colsum_to(partial, n_chunks, MN, M_valid, N, dst, ldd, tmp, st);
-}
-
-// Row chunks of a weight gradient: about 512 workgroups in all (two per CU),
-// whole 128-row stages per chunk.
-static int wgrad_chunks(const WgradOp& op, int* rows_per_chunk) {
-  *rows_per_chunk = WG_K;
-  if (op.R <= 0) return 0;
-  const int blocks = ((op.M + WG_B - 1) / WG_B) * ((op.N + WG_B - 1) / WG_B);
-  int target = 512 / blocks;
-  const int max_chunks = (op.R + WG_K - 1) / WG_K;
-  if (target > max_chunks) target = max_chunks;
-  if (target < 1) target = 1;
-  int rpc = (op.R + target - 1) / target;
-  rpc = (rpc + WG_K - 1) / WG_K * WG_K;
-  *rows_per_chunk = rpc;
-  return (op.R + rpc - 1) / rpc;
-}
-
-size_t wgrad_partial_floats(const Shape&, const WgradOp& op) {
-  int rpc;
-  const int nc = wgrad_chunks(op, &rpc);
-  return (size_t)(nc > 0 ? nc : 1) * op.M * op.N;
-}
-
-void launch_wgrad(const Shape& s, const WgradOp& op, float* partial, float* tmp, hipStream_t st) {
-  int rpc;
-  const int nc = wgrad_chunks(op, &rpc);
-  const int nbm = (op.M + WG_B - 1) / WG_B, nbn = (op.N + WG_B - 1) / WG_B;
-  if (nc > 0) {
-    dim3 grid(nc, nbm * nbn);
-    if (s.prec == 1) {
-      if (op.a_f32 && op.b_f32) k_wgrad<bf16, float, float><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-      else if (op.a_f32) k_wgrad<bf16, float, bf16><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-      else if (op.b_f32) k_wgrad<bf16, bf16, float><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-      else k_wgrad<bf16, bf16, bf16><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-    } else {
-      k_wgrad<float, float, float><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-    }
+void launch_wgrad(const Shape& s, WgradBatch& b, float* partial, RedBatch& red, hipStream_t st) {
+  // the fewest rows per chunk, in whole stages, with which no workgroup waits
+  // for another to end (a launch a little over that takes twice as long)
+  const int blk = wgrad_block(s), kr = s.prec == 1 ? 64 : 32, target = wgrad_target(s);
+  auto blocks = [&](const WgradOp& o) { return ((o.M + blk - 1) / blk) * ((o.N + blk - 1) / blk); };
+  // a row of which one operand is to be rounded from FP32 takes about twice as
+  // long (H = 512: 68 against 35 ns in a workgroup)
+  auto weight = [&](const WgradOp& o) { return s.prec == 1 && (o.a_f32 || o.b_f32) ? 2 : 1; };
+  long long rows = 0;
+  for (int j = 0; j < b.n; ++j) rows += (long long)b.job[j].op.R * weight(b.job[j].op) * blocks(b.job[j].op);
+  long long rpc = std::max<long long>(kr, ((rows + target - 1) / target + kr - 1) / kr * kr);
+  for (;; rpc += kr) {
+    long long wgs = 0;
+    for (int j = 0; j < b.n; ++j)
+      wgs += (b.job[j].op.R * (long long)weight(b.job[j].op) + rpc - 1) / rpc * blocks(b.job[j].op);
+    if (wgs <= target) break;
   }
-  colsum_to(partial, nc, op.M * op.N, op.M_valid, op.N, op.dst, op.ldd, tmp, st);
-}
-
-void launch_wgrad_partials(const Shape& s, const WgradOp& op, float* partial, RedBatch& b, hipStream_t st) {
-  int rpc;
-  const int nc = wgrad_chunks(op, &rpc);
-  const int nbm = (op.M + WG_B - 1) / WG_B, nbn = (op.N + WG_B - 1) / WG_B;
-  if (nc > 0) {
-    dim3 grid(nc, nbm * nbn);
-    if (s.prec == 1) {
-      if (op.a_f32 && op.b_f32) k_wgrad<bf16, float, float><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-      else if (op.a_f32) k_wgrad<bf16, float, bf16><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-      else if (op.b_f32) k_wgrad<bf16, bf16, float><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-      else k_wgrad<bf16, bf16, bf16><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-    } else {
-      k_wgrad<float, float, float><<<grid, NTHR, 0, st>>>(op, rpc, nbm, partial);
-    }
+  int grid = 0;
+  size_t at = 0;
+  for (int j = 0; j < b.n; ++j) {
+    WgradJob& jb = b.job[j];
+    WgradOp& o = jb.op;
+    if (s.prec == 0) o.a_f32 = o.b_f32 = 1;
+    if (o.ib ? o.a_f32 != o.b_f32 : s.prec == 1 && o.a_f32 && o.b_f32)
+      throw std::logic_error("no weight-gradient kernel for these operands");
+    jb.chunks = (int)((o.R * (long long)weight(o) + rpc - 1) / rpc);
+    jb.rows = jb.chunks > 0 ? ((o.R + jb.chunks - 1) / jb.chunks + kr - 1) / kr * kr : 0;
+    if (jb.rows) jb.chunks = (o.R + jb.rows - 1) / jb.rows;
+    jb.first = grid;
+    jb.partial = partial + at;
+    grid += (jb.chunks + 7) / 8 * 8 * blocks(o);
+    at += (size_t)jb.chunks * o.M * o.N;
+    red.add(jb.partial, jb.chunks, o.M * o.N, o.M_valid, o.N, o.dst, o.ldd);
   }
-  b.add(partial, nc, op.M * op.N, op.M_valid, op.N, op.dst, op.ldd);
+  if (at > wgrad_partial_floats(s)) throw std::logic_error("weight-gradient partials exceed their scratch");
+  if (grid == 0) return;
+  if (s.prec == 0)
+    k_wgrad<float, 128><<<grid, Wg<float, 128>::NT, 0, st>>>(b);
+  else if (blk == 128)
+    k_wgrad<bf16, 128><<<grid, Wg<bf16, 128>::NT, 0, st>>>(b);
+  else
+    k_wgrad<bf16, 256><<<grid, Wg<bf16, 256>::NT, 0, st>>>(b);
 }
 
-// Batched form: blockIdx.z selects the job; the per-job work is exactly
-// k_colsum_stage1's and k_wgrad_reduce's.
+// Batched form: workgroups in job order (a grid of the largest job's size for
+// all of them spent 100 us on empty workgroups at H = 512).  A job of at most
+// RED_SPLITS rows has no first stage: the second reads its rows, in the same
+// order.
+// (the lanes look at one job each: one after the other they took half of a
+// small workgroup's time)
+__device__ __forceinline__ int red_job(const int* first, int n) {
+  const int l = lane_id();
+  return __popcll(__ballot(l < n && (int)blockIdx.x >= first[min(l, n - 1)])) - 1;
+}
 __global__ void k_colsum_batch1(RedBatch b, float* __restrict__ tmp) {
-  const RedJob& jb = b.job[blockIdx.z];
-  const int ncol = jb.M_valid * jb.N;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int s = blockIdx.y;
-  if (j >= ncol || s >= jb.splits) return;
+  const int job = __builtin_amdgcn_readfirstlane(red_job(b.first1, b.n));
+  const RedJob& jb = b.job[job];
+  const int ncol = jb.M_valid * jb.N, cb = (ncol + 255) / 256, id = blockIdx.x - b.first1[job];
+  const int s = id / cb, j = (id - s * cb) * 256 + threadIdx.x;
+  if (j >= ncol) return;
   const int r0 = s * jb.per, r1 = min(jb.rows, r0 + jb.per);
   tmp[jb.tmp_off + (size_t)s * ncol + j] = split_sum(jb.src + j, jb.stride, r0, r1);
 }
 
 __global__ void k_colsum_batch2(RedBatch b, const float* __restrict__ tmp) {
-  const RedJob& jb = b.job[blockIdx.y];
-  const int ncol = jb.M_valid * jb.N;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  const int job = __builtin_amdgcn_readfirstlane(red_job(b.first2, b.n));
+  const RedJob& jb = b.job[job];
+  const int ncol = jb.M_valid * jb.N, idx = (blockIdx.x - b.first2[job]) * 256 + threadIdx.x;
   if (idx >= ncol) return;
   const int m = idx / jb.N, n = idx - m * jb.N;
-  jb.dst[(size_t)m * jb.ldd + n] = order_sum(tmp + jb.tmp_off + idx, ncol, jb.splits);
+  jb.dst[(size_t)m * jb.ldd + n] =
+      jb.per <= 1 ? order_sum(jb.src + idx, jb.stride, jb.rows) : order_sum(tmp + jb.tmp_off + idx, ncol, jb.splits);
 }
 
 void RedBatch::add(const float* src, int rows, int stride, int M_valid, int N, float* dst, int ldd) {
@@ -298,9 +365,13 @@ void RedBatch::add(const float* src, int rows, int stride, int M_valid, int N, f
   j.ldd = ldd;
   j.splits = rows < RED_SPLITS ? (rows > 0 ? rows : 1) : RED_SPLITS;
   j.per = rows > 0 ? (rows + j.splits - 1) / j.splits : 0;
+  const int cb = (M_valid * N + 255) / 256;
+  first1[n - 1] = grid1;
+  first2[n - 1] = grid2;
+  grid1 += j.per > 1 ? cb * j.splits : 0;
+  grid2 += cb;
   j.tmp_off = tmp_floats;
   tmp_floats += (long long)j.splits * M_valid * N;
-  if (M_valid * N > max_cols) max_cols = M_valid * N;
 }
 
 void RedBatch::add_vec(const float* partial, int G, int row, const VecSeg* segs, int n_seg) {
@@ -309,8 +380,8 @@ void RedBatch::add_vec(const float* partial, int G, int row, const VecSeg* segs,
 
 void launch_reduce_batch(const RedBatch& b, float* tmp, hipStream_t st) {
   if (b.n == 0) return;
-  k_colsum_batch1<<<dim3((b.max_cols + 255) / 256, RED_SPLITS, b.n), 256, 0, st>>>(b, tmp);
-  k_colsum_batch2<<<dim3((b.max_cols + 255) / 256, b.n), 256, 0, st>>>(b, tmp);
+  if (b.grid1) k_colsum_batch1<<<b.grid1, 256, 0, st>>>(b, tmp);
+  k_colsum_batch2<<<b.grid2, 256, 0, st>>>(b, tmp);
 }
 
 // ---------------------------------------------------------------------------
@@ -344,27 +415,6 @@ static const float* vec_stage1(const float* partial, int G, int row, int* splits
   return tmp;
 }
 
-void launch_vec_reduce(const float* partial, int G, int row, const VecSeg* segs, int n_seg, float* tmp,
-                       hipStream_t st) {
-  VecSegs s{};
-  s.n = n_seg;
-  int maxlen = 1;
-  for (int i = 0; i < n_seg; ++i) {
-    s.src[i] = segs[i].src;
-    s.len[i] = segs[i].len;
-    s.inner[i] = segs[i].len;
-    s.src_stride[i] = 0;
-    s.dst_stride[i] = 0;
-    s.dst[i] = segs[i].dst;
-    if (segs[i].len > maxlen) maxlen = segs[i].len;
-  }
-  int splits;
-  const float* t1 = vec_stage1(partial, G, row, &splits, tmp, st);
-  k_vec_reduce<<<dim3((maxlen + 255) / 256, n_seg), 256, 0, st>>>(t1, splits, row, s);
-}
-
-// Strided variant: dst[c * dst_stride + k] = sum_g partial[g][src + c * src_stride + k],
-// c < runs, k < inner.
 void launch_vec_reduce_strided(const float* partial, int G, int row, int src, int runs, int inner, int src_stride,
                                float* dst, int dst_stride, float* tmp, hipStream_t st) {
   VecSegs s{};

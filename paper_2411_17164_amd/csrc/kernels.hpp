@@ -1,6 +1,7 @@
 // Kernel argument blocks and launcher declarations of the xmgn library.
 #pragma once
 
+#include <stdexcept>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -117,8 +118,6 @@ bool edge_bwd_fuses_wgrad(const Shape& s);
 // Fixed-order sums over the rows of partial matrices use a two-stage
 // reduction with caller scratch of reduce_tmp_floats(columns) floats.
 size_t reduce_tmp_floats(int max_cols);
-void launch_wgrad_reduce(const float* partial, int n_chunks, int M_valid, int N, float* dst, int ldd, int MN,
-                         float* tmp, hipStream_t st);
 // True when the edge adjoint can read z from the forward's tape instead of
 // recomputing it (every form); zt is then that tape (else NULL: recompute),
 // and the unfused form does not write o.z (its dW2 product reads the tape).
@@ -199,13 +198,12 @@ void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, cons
                            const float* dout, const EncBwdOut& o, float* a2, hipStream_t st);
 
 // ---- auxiliary ----
-// C[m][n] = sum_r A[ia(r)][a0 + m] * B[ib(r)][b0 + n] over r < R; partial
+// C[m][n] = sum_r A[r][a0 + m] * B[ib(r)][b0 + n] over r < R; partial
 // sums per row chunk, then dst[m * ldd + n] = sum over chunks (m < M_valid).
 struct WgradOp {
   const void* A;
   int a_f32;  // 1: A is FP32, else compute type
   int lda, a0;
-  const int* ia;
   const void* B;
   int b_f32;
   int ldb, b0;
@@ -214,17 +212,28 @@ struct WgradOp {
   float* dst;
   int ldd;
 };
-size_t wgrad_partial_floats(const Shape& s, const WgradOp& op);
-void launch_wgrad(const Shape& s, const WgradOp& op, float* partial, float* tmp, hipStream_t st);
+struct WgradJob {
+  WgradOp op;
+  int chunks, rows, first;  // (set by the launch: row chunks, rows in each, first workgroup, its partials)
+  float* partial;
+};
+constexpr int kMaxWgradJobs = 7;
+struct WgradBatch {
+  int n = 0;
+  WgradJob job[kMaxWgradJobs];
+  void add(const WgradOp& op) {
+    if (n >= kMaxWgradJobs) throw std::logic_error("weight-gradient batch is full");
+    job[n++].op = op;
+  }
+};
 
 struct VecSeg {
   int src;  // offset in the partial row
   int len;
   float* dst;
 };
-// dst[j] = sum over g < G of partial[g * row + src + j] for every segment.
-void launch_vec_reduce(const float* partial, int G, int row, const VecSeg* segs, int n_seg, float* tmp,
-                       hipStream_t st);
+// dst[i * dst_stride + k] = sum over g < G of partial[g * row + src + i *
+// src_stride + k] for i < runs, k < inner.
 void launch_vec_reduce_strided(const float* partial, int G, int row, int src, int runs, int inner, int src_stride,
                                float* dst, int dst_stride, float* tmp, hipStream_t st);
 
@@ -242,17 +251,19 @@ struct RedJob {
 constexpr int kMaxRedJobs = 24;
 struct RedBatch {
   int n = 0;
-  int max_cols = 0;
   long long tmp_floats = 0;  // scratch the batch needs
+  int grid1 = 0, grid2 = 0;  // workgroups of the two launches, and each job's first
+  int first1[kMaxRedJobs], first2[kMaxRedJobs];
   RedJob job[kMaxRedJobs];
   void add(const float* src, int rows, int stride, int M_valid, int N, float* dst, int ldd);
   // the segments of a per-workgroup partial row [G][row] (launch_vec_reduce)
   void add_vec(const float* partial, int G, int row, const VecSeg* segs, int n_seg);
 };
 void launch_reduce_batch(const RedBatch& b, float* tmp, hipStream_t st);
-// The products of launch_wgrad without their reduction: adds that
-// reduction to b.
-void launch_wgrad_partials(const Shape& s, const WgradOp& op, float* partial, RedBatch& b, hipStream_t st);
+// Runs the products of b in one launch and adds their reductions to red;
+// partial: wgrad_partial_floats(s) floats of scratch, in use until red has run.
+size_t wgrad_partial_floats(const Shape& s);
+void launch_wgrad(const Shape& s, WgradBatch& b, float* partial, RedBatch& red, hipStream_t st);
 
 struct PrepJob {
   int64_t src_off;   // element offset in the FP32 params

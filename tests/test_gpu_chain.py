@@ -145,7 +145,20 @@ def test_stream_encoder_inputs(api, hidden, node_in):
     """The streamed encoders at every way they take the node inputs (1 and 8 in
     LDS, 12 and 32 from memory) and a ragged last group of rows, SiLU, held to
     the bar of the BF16 form (outputs and whole gradient 2e-2)."""
-    n = 77
+    inputs_step(api, "bf16", hidden, node_in, 77, 2e-2)
+
+
+@pytest.mark.parametrize("precision,hidden,node_in,n", [
+    ("bf16", 128, 12, 65), ("bf16", 128, 32, 127), ("bf16", 256, 24, 129), ("bf16", 512, 32, 64),
+    ("fp32", 128, 12, 33), ("fp32", 128, 32, 31), ("fp32", 256, 20, 32), ("fp32", 128, 4, 2), ("bf16", 128, 8, 2),
+])
+def test_weight_gradient_rows(api, precision, hidden, node_in, n):
+    """The weight-gradient products at row counts around one stage (64 rows,
+    FP32 32), gathered node inputs of any width included, at the form's bar."""
+    inputs_step(api, precision, hidden, node_in, n, 2e-2 if precision == "bf16" else 1e-4)
+
+
+def inputs_step(api, precision, hidden, node_in, n, bar):
     rng = np.random.default_rng(node_in)
     G = degree_graph(n, [3, 5, 1], 3)
     pos = rng.standard_normal((n, 3)).astype(np.float32)
@@ -154,7 +167,7 @@ def test_stream_encoder_inputs(api, hidden, node_in):
     norm = np.array([[0, 0, 0, 1], [1, 1, 1, 0.5]], dtype=np.float32)
     desc = om.Desc(hidden=hidden, layers=1, node_in=node_in, activation="silu")
     params = init_params(om.param_entries(desc), 5)
-    model = api.Model(hidden, 1, node_in=node_in, activation="silu", precision="bf16")
+    model = api.Model(hidden, 1, node_in=node_in, activation="silu", precision=precision)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
     ctx = api.Context(0)
     ps = api.Partset.halo(api.Graph.from_csr(G.row_ptr, G.col), pos, None, 1)
@@ -165,7 +178,8 @@ def test_stream_encoder_inputs(api, hidden, node_in):
     ctx.mse_grad(out, dev(target), n, d_out, loss)
     ctx.backward(model, p, d_out, grad)
     torch.cuda.synchronize()
-    _, y, g = om.step_full(desc, om.amp_cast(desc, params), G, x, pos, norm, target)
+    cast = om.amp_cast(desc, params) if precision == "bf16" else params.astype(np.float64)
+    _, y, g = om.step_full(desc, cast, G, x, pos, norm, target)
     e_out, e_grad = rel_l2(out.cpu().numpy(), y), rel_l2(grad.cpu().numpy(), g)
-    log(f"encoder H={hidden} node_in={node_in}: out {e_out:.2e} grad {e_grad:.2e}")
-    assert e_out <= 2e-2 and e_grad <= 2e-2
+    log(f"inputs {precision} H={hidden} node_in={node_in}: out {e_out:.2e} grad {e_grad:.2e}")
+    assert e_out <= bar and e_grad <= bar
