@@ -897,8 +897,15 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
     }
     add_job(c, poff(d, b, 0, 2), H, 0, 0, H, H, w.W2);
     add_job(c, poff(d, b, 0, 4), H, 0, 0, H, H, w.W3);
-    add_job(c, poff(d, b, 0, 2), H, 0, 1, H, H, w.W2T);
-    add_job(c, poff(d, b, 0, 4), H, 0, 1, H, H, w.W3T);
+    if (b == 0) {
+      add_job(c, poff(d, b, 0, 2), H, 0, 1, H, H, w.W2T);
+      add_job(c, poff(d, b, 0, 4), H, 0, 1, H, H, w.W3T);
+    } else {  // the edge encoder's adjoint
+      w.BS = add_frag_job(c, poff(d, b, 0, 2), H, 0, 0, H, H);
+      add_frag_job(c, poff(d, b, 0, 4), H, 0, 0, H, H);
+      add_frag_job(c, poff(d, b, 0, 4), H, 0, 1, H, H);
+      add_frag_job(c, poff(d, b, 0, 2), H, 0, 1, H, H);
+    }
   }
   for (int l = 0; l < L; ++l) {
     BlockW& we = c->bw[2 + 2 * l];
@@ -1374,7 +1381,7 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
   const size_t ge = std::max(se.grid, edge_bwd_chain_grid(se, (int)E));
   if (c->tape_z) se.grid = edge_bwd_chain_grid(se, (int)E);
   if (enc_bwd_fuses_wgrad(s))  // encoders: [<=256][2][H][H]
-    if (xmgn_status r = c->wfused.ensure((size_t)std::min(s.grid, 256) * 2 * H * H * 4, st)) return r;
+    if (xmgn_status r = c->wfused.ensure((size_t)256 * 2 * H * H * 4, st)) return r;
   if (fw)  // edge adjoint: [se.grid][2][H][H]
     if (xmgn_status r = c->wfused_e.ensure(ge * 2 * H * H * 4, st)) return r;
   if (xmgn_status r = c->part_e.ensure(ge * 4 * H * 4, st)) return r;
@@ -1486,8 +1493,7 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
   }
   // encoders
   const bool fe = enc_bwd_fuses_wgrad(s);
-  Shape sn = s;  // encoders: with fused weight gradients, at most one workgroup per CU in flight
-  if (fe) sn.grid = std::min(s.grid, 256);
+  Shape sn = s;
   for (int blk = 1; blk >= 0; --blk) {
     const MlpW w = weights(c, d, params, blk, blk, 0);
     // more than 8 node inputs: the input layer's dW1 is a separate product
@@ -1496,7 +1502,8 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     EncBwdOut o{c->fa.p, c->fb.p, c->fc.p, c->fd.p, part, fe ? c->wfused.as<float>() : nullptr,
                 wide ? c->Sr.as<float>() : nullptr};
     const int R = blk == 1 ? (int)E : (int)n, in_dim = blk == 1 ? 4 : d->node_in;
-    if (enc_stream(s)) sn.grid = edge_stream_grid(s, R);
+    // (with fused weight gradients at most one workgroup per CU in flight)
+    sn.grid = enc_stream(s) || blk == 1 ? edge_stream_grid(s, R) : std::min(s.grid, 256);
     // (the streaming form's FP32 scratch: the adjoint buffers the layers are done with)
     if (blk == 1) {
       KT("enc_edge_bwd");

@@ -15,6 +15,7 @@
 
 #include "kernels.hpp"
 #include "stream.hpp"
+#include "tile.hpp"
 
 namespace xmgn {
 
@@ -423,6 +424,245 @@ __global__ __launch_bounds__((StreamDims<T, H, W>::NT), (StreamDims<T, H, W>::NW
         d[128 * q + 2 * lane_id() + 1] = cw[q][k][1];
       }
     });
+}
+
+// ---------------------------------------------------------------------------
+// Edge encoder adjoint, BF16, H = 128: one kernel.  xhat, the upstream gradient
+// and both hidden rows of 16 edges fit in a wave's registers there, so nothing
+// but the column sums and the weight gradients leaves it: dW3 = du3^T z2 and
+// dW2 = da2^T z1 are accumulated from 128-row tiles (tile.hpp).  The four
+// matrices are streamed: with the tiles they do not fit in LDS.  3.55M edges:
+// 3,556 -> 1,615 us against the workgroup-tile kernel with the same fusion,
+// which passed every intermediate through LDS behind a barrier; its floor is
+// reading dout (1.8 GB, 370 us).  Bound by LDS: the waves' reads of the weight
+// and tile fragments take about 5 of the 15 us of a 128-row step, the sums over
+// rows and the barriers between them most of the rest.
+// ---------------------------------------------------------------------------
+template <int ACT>
+__global__ __launch_bounds__(512, 2) void k_enc_edge_bwd_chain(int rows, MlpW w, const float* __restrict__ src,
+                                                               const float* __restrict__ dout, EncBwdOut o,
+                                                               float* __restrict__ a2_out, float eps) {
+  using T = bf16;
+  constexpr int H = 128, KIN = 4, SW = 32;
+  using L = StreamDims<T, H>;
+  using C = Chunk<T>;
+  constexpr int NW = L::NW, NT = L::NT, MBS = L::MBS, KC = L::KC, SP = L::SP;
+  static_assert(NW == 8, "tiles of eight waves");
+  constexpr size_t HEAD = L::RING + 5 * H * 4 + enc_w1_bytes<H, KIN>();
+  __shared__ __align__(16) unsigned char smem[HEAD + NW * kTileReg];
+  float* vec = (float*)(smem + L::RING);
+  unsigned char* regs = smem + HEAD;
+  unsigned char* reg = regs + wave_id() * kTileReg;
+  float* buf = (float*)reg;
+  const int wm = wave_id() & 3, wn = wave_id() >> 2;
+  const WStream<NW, 4 * SP, L::FR> ws{(const unsigned char*)w.BS, smem};
+  EncIn<H, KIN, 1> in{src, nullptr, w.W1f, nullptr, 4}, nx = in;
+  in.stage(vec + 5 * H, NT);
+  stage_vecs<H>(vec, w, NT);
+  const WaveRows wr(rows, NW);
+  const int last = max(wr.end - 1, 0);
+  if (wr.steps) nx.load(min(wr.begin + (lane_id() & 15), last));
+  ws.start();
+  lds_sync();
+  f32x4 accW3[2][4], accW2[2][4];
+  zero_acc(accW3);
+  zero_acc(accW2);
+  double cb1[2] = {}, cb2[2] = {}, cb3[2] = {}, cg[2] = {}, cbt[2] = {}, cw[KIN][2] = {};
+  for (int it = 0; it < wr.steps; ++it) {
+    const int l = opaque(lane_id()), li = l & 15, lg = l >> 4;
+    const int r0 = wr.begin + 16 * it;
+    const bool ok = r0 + li < wr.end;
+    const size_t row = (size_t)min(r0 + li, last) * H;
+    auto vget = [&](int v, int mb) { return *(const f32x4*)(vec + v * H + 16 * mb + 4 * lg); };
+#pragma unroll
+    for (int k = 0; k < KIN; ++k) in.x[k] = nx.x[k];
+    f32x4 x[MBS];
+    bf16x8 z1[KC], z2[KC], d[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      f32x4 a[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        a[k] = in.layer(vec, 2 * c + k, lg);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[k][r] = act_f<ACT>(a[k][r]);
+      }
+      z1[c] = C::of(a);
+    }
+    stream_product<T, H>(ws, 0, x, z1);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      f32x4 a[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        a[k] = x[2 * c + k] + vget(1, 2 * c + k);
+        if (ACT != 0 && ok) *(f32x4*)(a2_out + row + 16 * (2 * c + k) + 4 * lg) = a[k];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[k][r] = act_f<ACT>(a[k][r]);
+      }
+      z2[c] = C::of(a);
+    }
+    f32x4 g[MBS];  // dout, in flight during the product
+#pragma unroll
+    for (int mb = 0; mb < MBS; ++mb) g[mb] = *(const f32x4*)(dout + row + 16 * mb + 4 * lg);
+    stream_product<T, H>(ws, SP, x, z2);
+#pragma unroll
+    for (int mb = 0; mb < MBS; ++mb) x[mb] += vget(2, mb);
+    const float inv = ln_chain<H, SW>(x, eps);
+    float sg = 0.f, sgx = 0.f, sa[4], sd[4];
+#pragma unroll
+    for (int gr = 0; gr < 2; ++gr) {
+      f32x4 dv[4], t[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dv[k][r] = ok ? g[4 * gr + k][r] : 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) t[k] = dv[k] * x[4 * gr + k];
+      cg[gr] += (double)colsum64(t);
+      cbt[gr] += (double)colsum64(dv);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int mb = 4 * gr + k;
+        const f32x4 gm = vget(3, mb);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float p = dv[k][r] * gm[r];
+          sa[r] = mb % 2 ? __builtin_fmaf(dv[k][r], gm[r], sa[r]) : p;
+          sd[r] = mb % 2 ? __builtin_fmaf(x[mb][r], p, sd[r]) : x[mb][r] * p;
+          g[mb][r] = p;
+        }
+        if (mb % 2 == 1) {  // a span is whole
+          sg += add_xor32(add_xor16((sa[0] + sa[1]) + (sa[2] + sa[3])));
+          sgx += add_xor32(add_xor16((sd[0] + sd[1]) + (sd[2] + sd[3])));
+        }
+      }
+    }
+#pragma unroll
+    for (int gr = 0; gr < 2; ++gr) {
+      f32x4 t[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          t[k][r] = __builtin_fmaf(sgx * (-1.f / H), x[4 * gr + k][r], __builtin_fmaf(sg, -1.f / H, g[4 * gr + k][r])) * inv;
+      cb3[gr] += (double)colsum64(t);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) d[2 * gr + k] = C::of(*(const f32x4(*)[2])(t + 2 * k));
+    }
+    // (the last product's barriers: every wave is done with its buffer)
+    tile_put(reg, d, l);
+    tile_put(reg + kTileReg / 2, z2, l);
+    lds_sync();
+    tile_wgrad(accW3, regs, 0, kTileReg / 2, wm, wn, l);  // dW3 += du3^T z2
+    stream_product<T, H>(ws, 2 * SP, x, d);
+#pragma unroll
+    for (int gr = 0; gr < 2; ++gr) {
+      f32x4 t[4];
+      if constexpr (ACT == 0) {  // a2 > 0 exactly where z2 > 0
+#pragma unroll
+        for (int k = 0; k < 2; ++k) C::to(z2[2 * gr + k], *(f32x4(*)[2])(t + 2 * k));
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = *(const f32x4*)(a2_out + row + 64 * gr + 16 * k + 4 * lg);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) t[k][r] = x[4 * gr + k][r] * act_d<ACT>(t[k][r]);
+      cb2[gr] += (double)colsum64(t);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) d[2 * gr + k] = C::of(*(const f32x4(*)[2])(t + 2 * k));
+    }
+    // (that product's barriers: every wave is done with [du3 | z2])
+    tile_put(reg, d, l);
+    tile_put(reg + kTileReg / 2, z1, l);
+    lds_sync();
+    tile_wgrad(accW2, regs, 0, kTileReg / 2, wm, wn, l);  // dW2 += da2^T z1
+    if (it + 1 < wr.steps) nx.load(min(r0 + 16 + li, last));
+    stream_product<T, H>(ws, 3 * SP, x, d);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      f32x4 a[2];
+      if constexpr (ACT == 0)  // a1 > 0 exactly where z1 > 0
+        C::to(z1[c], a);
+      else {
+        a[0] = in.layer(vec, 2 * c, lg);
+        a[1] = in.layer(vec, 2 * c + 1, lg);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[2 * c + k][r] *= act_d<ACT>(a[k][r]);
+    }
+    // sums over the rows of da1 and da1 x^T, row by row through the wave's
+    // buffer (that product's barriers: every wave is done with [da2 | z1])
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) *(f32x4*)(buf + li * 128 + (((4 * k + lg) ^ li) << 2)) = x[k];
+    wave_sync();
+    float2 s = {0.f, 0.f}, sw[KIN];
+#pragma unroll
+    for (int k = 0; k < KIN; ++k) sw[k] = float2{0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float2 v = *(const float2*)(buf + i * 128 + ((((l >> 1) ^ i) << 2) | ((l & 1) << 1)));
+      s.x += v.x;
+      s.y += v.y;
+#pragma unroll
+      for (int k = 0; k < KIN; ++k) {
+        const float xi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, in.x[k]), i));
+        sw[k].x = __builtin_fmaf(v.x, xi, sw[k].x);
+        sw[k].y = __builtin_fmaf(v.y, xi, sw[k].y);
+      }
+    }
+    cb1[0] += (double)s.x;
+    cb1[1] += (double)s.y;
+#pragma unroll
+    for (int k = 0; k < KIN; ++k) {
+      cw[k][0] += (double)sw[k].x;
+      cw[k][1] += (double)sw[k].y;
+    }
+    wave_sync();
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no weights on their way into the ring)
+  float* p = o.partial + (size_t)blockIdx.x * 13 * H;
+  double* ds = (double*)smem;
+  auto two = [&](float* dst, int stride, const double (&v)[2]) {  // lane l: features 2 l, 2 l + 1
+    wg_colsum<H, NW>(ds, dst, stride, [&](double* q) {
+      q[2 * lane_id()] = v[0];
+      q[2 * lane_id() + 1] = v[1];
+    });
+  };
+  two(p, 1, cb1);
+  wg_colsum64<H, NW>(ds, p + H, cb2);
+  wg_colsum64<H, NW>(ds, p + 2 * H, cb3);
+  wg_colsum64<H, NW>(ds, p + 3 * H, cg);
+  wg_colsum64<H, NW>(ds, p + 4 * H, cbt);
+#pragma unroll
+  for (int k = 0; k < KIN; ++k) two(p + 5 * H + k, 8, cw[k]);
+  float* q2 = o.wpart + (size_t)blockIdx.x * 2 * H * H;
+  float* q3 = q2 + H * H;
+  const int li = lane_id() & 15, lg = lane_id() >> 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int at = (32 * wm + 16 * i + 4 * lg + r) * H + 64 * wn + 16 * j + li;
+        q2[at] = accW2[i][j][r];
+        q3[at] = accW3[i][j][r];
+      }
+}
+
+void launch_enc_edge_bwd_chain(const Shape& s, int R, const MlpW& w, const float* xe, const float* dout,
+                               const EncBwdOut& o, float* a2, hipStream_t st) {
+  const int grid = edge_stream_grid(s, R);
+  if (s.act)
+    k_enc_edge_bwd_chain<1><<<grid, 512, 0, st>>>(R, w, xe, dout, o, a2, s.eps);
+  else
+    k_enc_edge_bwd_chain<0><<<grid, 512, 0, st>>>(R, w, xe, dout, o, a2, s.eps);
 }
 
 // ---------------------------------------------------------------------------

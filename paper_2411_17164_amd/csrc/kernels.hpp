@@ -47,7 +47,7 @@ struct MlpW {
   // kernels with streamed weights (the node MLP's; edge_stream): MFMA fragment
   // order, k chunk by k chunk, as the kernels walk them
   const void* FS;   // forward: W1, W2 (edge, node MLP); W2, W3 (encoder)
-  const void* BS;   // adjoint: W2, W2^T, e-block of W1^T (edge MLP); W3^T, W2^T (encoder);
+  const void* BS;   // adjoint: W2, W2^T, e-block of W1^T (edge MLP); W3^T, W2^T (encoder; BF16 H = 128 edges: W2, W3 ahead);
                     // B_rs of the edge layer above (if any), W1, W2, W2^T, W1^T (node MLP)
 };
 
@@ -196,6 +196,12 @@ void launch_enc_fwd_stream(const Shape& s, int kind, int R, const int* gid, cons
                            void* out, hipStream_t st);
 void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
                            const float* dout, const EncBwdOut& o, float* a2, hipStream_t st);
+
+// The edge encoder's adjoint of the BF16 form at H = 128 (w.BS: W2, W3, W3^T,
+// W2^T): accumulates dW2 and dW3 itself; partials have edge_stream_grid(s, R)
+// rows; a2: FP32 [R][H] scratch (SiLU).
+void launch_enc_edge_bwd_chain(const Shape& s, int R, const MlpW& w, const float* xe, const float* dout,
+                               const EncBwdOut& o, float* a2, hipStream_t st);
 
 // ---- auxiliary ----
 // C[m][n] = sum_r A[r][a0 + m] * B[ib(r)][b0 + n] over r < R; partial

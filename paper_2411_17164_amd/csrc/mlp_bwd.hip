@@ -588,7 +588,7 @@ bool enc_bwd_fuses_wgrad(const Shape& s) { return s.prec == 1 && s.H == 128; }
 
 // KIN as for k_enc_fwd; with 32 input slots the input layer's dW1 is left to
 // a separate product over o.da1 (its FP32 adjoint, written here).
-template <typename T, int H, int MT, int ACT, int KIND, int KIN>
+template <typename T, int H, int MT, int ACT, int KIN>
 __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w, const float* __restrict__ src, int in_dim,
                                                   const float* __restrict__ dout, EncBwdOut o, float eps) {
   using D = BD<T, H>;
@@ -636,16 +636,8 @@ __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w,
         const int i = threadIdx.x;
         float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (i < nr) {
-          if constexpr (KIND == 0) {
-            const float* p = src + (size_t)b.gid[row0 + i] * in_dim;
-            for (int k = 0; k < in_dim; ++k) v[k] = p[k];
-          } else {
-            const float4 f = ((const float4*)src)[row0 + i];  // edge features (k_edge_feat)
-            v[0] = f.x;
-            v[1] = f.y;
-            v[2] = f.z;
-            v[3] = f.w;
-          }
+          const float* p = src + (size_t)b.gid[row0 + i] * in_dim;
+          for (int k = 0; k < in_dim; ++k) v[k] = p[k];
         }
 #pragma unroll
         for (int k = 0; k < 8; ++k) xin[i * 8 + k] = v[k];
@@ -986,9 +978,9 @@ void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, cons
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
     if constexpr (sizeof(T) == 2 && H == 128) {
       if (in_dim <= 8)
-        k_enc_bwd<T, H, MT, ACT, 0, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
+        k_enc_bwd<T, H, MT, ACT, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
       else if (o.da1)
-        k_enc_bwd<T, H, MT, ACT, 0, 32><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
+        k_enc_bwd<T, H, MT, ACT, 32><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
       else
         g_config_error = 1;
     } else {
@@ -999,16 +991,10 @@ void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, cons
 
 void launch_enc_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, const float* de0,
                          const EncBwdOut& o, float* a2, hipStream_t st) {
-  if (enc_stream(s)) {
+  if (enc_stream(s))
     launch_enc_bwd_stream(s, 1, b.E, nullptr, w, xe, 4, de0, o, a2, st);
-    return;
-  }
-  XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(enc_edge_rows(s), {
-    if constexpr (sizeof(T) == 2 && H == 128)
-      k_enc_bwd<T, H, MT, ACT, 1, 8><<<s.grid, NTHR, 0, st>>>(b.E, b, w, xe, 4, de0, o, s.eps);
-    else
-      g_config_error = 1;
-  }))));
+  else
+    launch_enc_edge_bwd_chain(s, b.E, w, xe, de0, o, a2, st);
 }
 
 }  // namespace xmgn
