@@ -895,14 +895,15 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
       add_frag_job(c, poff(d, b, 0, 2), H, 0, 1, H, H);
       continue;
     }
-    add_job(c, poff(d, b, 0, 2), H, 0, 0, H, H, w.W2);
-    add_job(c, poff(d, b, 0, 4), H, 0, 0, H, H, w.W3);
+    w.FS = add_frag_job(c, poff(d, b, 0, 2), H, 0, 0, H, H);
+    add_frag_job(c, poff(d, b, 0, 4), H, 0, 0, H, H);
     if (b == 0) {
+      add_job(c, poff(d, b, 0, 2), H, 0, 0, H, H, w.W2);
+      add_job(c, poff(d, b, 0, 4), H, 0, 0, H, H, w.W3);
       add_job(c, poff(d, b, 0, 2), H, 0, 1, H, H, w.W2T);
       add_job(c, poff(d, b, 0, 4), H, 0, 1, H, H, w.W3T);
-    } else {  // the edge encoder's adjoint
-      w.BS = add_frag_job(c, poff(d, b, 0, 2), H, 0, 0, H, H);
-      add_frag_job(c, poff(d, b, 0, 4), H, 0, 0, H, H);
+    } else {  // the edge encoder's adjoint takes all four in this order
+      w.BS = w.FS;
       add_frag_job(c, poff(d, b, 0, 4), H, 0, 1, H, H);
       add_frag_job(c, poff(d, b, 0, 2), H, 0, 1, H, H);
     }

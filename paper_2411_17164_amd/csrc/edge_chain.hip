@@ -98,9 +98,10 @@ struct Vecs128 {
 };
 
 // ---------------------------------------------------------------------------
-// Fused edge processor, forward, BF16 H = 128 (the gathered form): the MLP of
-// k_edge_fwd with each wave taking 16 edges of its own range at a time through
-// both products, the LayerNorm and the receiver sums, and the next 16 edges'
+// Fused edge processor, forward, BF16 H = 128 (the gathered form):
+//   x = [h_r ; h_s ; e],  v = LN(W2 act(W1 x + b1) + b2),  e' = e + v,
+//   m_r = sum over the edges into r of v (or of e'),
+// each wave taking 16 edges of its own range at a time through both products, the LayerNorm and the receiver sums, and the next 16 edges'
 // rows in flight meanwhile.  Both weights stay in LDS (128 KiB, one workgroup
 // of eight waves per CU), so nothing but edge data crosses the memory system
 // and no barrier follows the staging.  It is bound by HBM: on 3.55M edges and

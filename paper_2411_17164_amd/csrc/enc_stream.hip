@@ -21,7 +21,7 @@ namespace xmgn {
 
 template <typename T, int H, int W>
 struct EncStream : StreamDims<T, H, W> {
-  static constexpr int S = 2 * StreamDims<T, H>::SP;  // two H x H matrices
+  static constexpr int S = 2 * StreamDims<T, H>::SP;  // two H x H matrices (BF16 at H = 128: the ring holds both)
   static constexpr size_t VEC = 5 * H * 4;  // b1, b2, b3, gamma, beta
   static constexpr size_t BUF = 8192;       // per wave (second adjoint kernel): 16 rows x 128 FP32
   static constexpr int SW = H / 4;          // LayerNorm span: the sums of four waves
@@ -689,7 +689,9 @@ static void enc_dispatch(const Shape& s, int R, int kind, int in_dim, F f) {
       by(t, hh, ww, I0{});
   };
   if (s.prec == 1) {
-    if (s.H == 256)
+    if (s.H == 128)
+      by_act(bf16{}, integral_constant<int, 128>{}, I0{});
+    else if (s.H == 256)
       by_act(bf16{}, integral_constant<int, 256>{}, I0{});
     else
       by_act(bf16{}, integral_constant<int, 512>{}, I0{});
@@ -703,14 +705,30 @@ static void enc_dispatch(const Shape& s, int R, int kind, int in_dim, F f) {
   }
 }
 
-void launch_enc_fwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
+static void launch_enc_fwd(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
                            void* out, hipStream_t st) {
+  if (R == 0) return;
   enc_dispatch(s, R, kind, in_dim, [&](auto t, auto hh, auto ww, auto act, auto kin, auto kd) {
     using T = decltype(t);
     constexpr int H = decltype(hh)::value, W = decltype(ww)::value;
+    // BF16 at H = 128 runs two workgroups per CU (70 KiB of LDS, 16 waves of 86
+    // registers), its weights in LDS for good: 397 us for 3.55M edges (1.0 GB,
+    // 2.5 TB/s; bound by the LDS reads of the fragments) where the
+    // workgroup-tile kernel took 1,088
+    const int grid = s.prec == 1 && s.H == 128 ? std::max(1, std::min(512, (R + 47) / 48)) : edge_stream_grid(s, R);
     k_enc_fwd_stream<T, H, W, decltype(act)::value, decltype(kin)::value, decltype(kd)::value>
-        <<<edge_stream_grid(s, R), StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, (T*)out, s.eps);
+        <<<grid, StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, (T*)out, s.eps);
   });
+}
+
+void launch_enc_node_fwd(const Shape& s, const BatchView& b, const MlpW& w, const float* node_in, int in_dim,
+                         void* h0, hipStream_t st) {
+  launch_enc_fwd(s, 0, b.n, b.gid, w, node_in, in_dim, h0, st);
+}
+
+void launch_enc_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, void* e0,
+                         hipStream_t st) {
+  launch_enc_fwd(s, 1, b.E, nullptr, w, xe, 4, e0, st);
 }
 
 void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
@@ -719,10 +737,12 @@ void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, cons
     using T = decltype(t);
     constexpr int H = decltype(hh)::value, W = decltype(ww)::value, A = decltype(act)::value, KIN = decltype(kin)::value,
                   KD = decltype(kd)::value;
-    const int grid = edge_stream_grid(s, R);
-    k_enc_bwd1_stream<T, H, W, A, KIN, KD>
-        <<<grid, StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, dout, o, a2, s.eps);
-    k_enc_bwd2_stream<T, H, W, A, KIN, KD><<<grid, StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, o, a2);
+    if constexpr (sizeof(T) == 4 || H > 128) {  // (enc_stream)
+      const int grid = edge_stream_grid(s, R);
+      k_enc_bwd1_stream<T, H, W, A, KIN, KD>
+          <<<grid, StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, dout, o, a2, s.eps);
+      k_enc_bwd2_stream<T, H, W, A, KIN, KD><<<grid, StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, o, a2);
+    }
   });
 }
 

@@ -188,12 +188,10 @@ void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, cons
 void launch_enc_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, const float* de0,
                          const EncBwdOut& o, float* a2, hipStream_t st);
 
-// The encoders of the same forms stream their weights (w.FS, w.BS); kind 0:
+// Their encoder adjoints stream their weights (w.BS); kind 0:
 // node inputs src[gid[row]], 1: edge features src[row].  The adjoint's partials
 // have edge_stream_grid(s, R) rows; a2: FP32 [R][H] scratch (SiLU).
 bool enc_stream(const Shape& s);
-void launch_enc_fwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
-                           void* out, hipStream_t st);
 void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
                            const float* dout, const EncBwdOut& o, float* a2, hipStream_t st);
 

@@ -586,7 +586,7 @@ __global__ __launch_bounds__(NTHR, H == 128 ? 2 : 1) void k_dec_bwd(BatchView b,
 // ---------------------------------------------------------------------------
 bool enc_bwd_fuses_wgrad(const Shape& s) { return s.prec == 1 && s.H == 128; }
 
-// KIN as for k_enc_fwd; with 32 input slots the input layer's dW1 is left to
+// KIN: input slots per row, 8 or 32; with 32 input slots the input layer's dW1 is left to
 // a separate product over o.da1 (its FP32 adjoint, written here).
 template <typename T, int H, int MT, int ACT, int KIN>
 __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w, const float* __restrict__ src, int in_dim,

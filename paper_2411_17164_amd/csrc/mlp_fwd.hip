@@ -247,11 +247,6 @@ __global__ __launch_bounds__(NTHR, 2) void k_node_proj(int n, MlpW w, const T* _
   }
 }
 
-// ---------------------------------------------------------------------------
-// Encoders: in -> H -> H -> H, LN.  The first layer (in <= 8) is a plain FMA
-// product in the accumulator layout; the other two run on MFMA.
-// Node input: node_in[gid]; edge input: the edge features of k_edge_feat.
-// ---------------------------------------------------------------------------
 // Edge features ([x_s - x_r, |x_s - x_r|] - mu) / sd, one float4 per edge
 // (Sec. III.B), computed once per forward and read by both edge encoders.
 __global__ __launch_bounds__(256) void k_edge_feat(int E, BatchView b, const float* __restrict__ pos, EdgeNorm en,
@@ -269,131 +264,6 @@ __global__ __launch_bounds__(256) void k_edge_feat(int E, BatchView b, const flo
 void launch_edge_feat(const BatchView& b, const float* pos, EdgeNorm en, float* xe, hipStream_t st) {
   if (b.E == 0) return;
   k_edge_feat<<<(b.E + 255) / 256, 256, 0, st>>>(b.E, b, pos, en, (float4*)xe);
-}
-
-// KIN: input slots per row (8, or 32 for up to 32 inputs, whose first layer
-// reads its weights from global memory inside a runtime-length loop).
-template <typename T, int H, int MT, int ACT, int KIND, int KIN>
-__global__ __launch_bounds__(NTHR, H == 128 ? 2 : 1) void k_enc_fwd(int rows, BatchView b, MlpW w, const float* __restrict__ src,
-                                                  int in_dim, T* __restrict__ out, float eps) {
-  using D = Dims<T, H>;
-  constexpr int MB = MT / 16, NB = D::NB;
-  constexpr size_t ZS = (size_t)MT * D::LDH * sizeof(T);
-  __shared__ __align__(16) unsigned char smem[2 * ZS + MT * KIN * 4 + 2 * NWAVE * MT * 4];
-  T* zs = (T*)smem;
-  T* z2 = (T*)(smem + ZS);
-  float* xin = (float*)(smem + 2 * ZS);
-  float* red = xin + MT * KIN;  // [2][NWAVE][MT]
-  const T* W2 = (const T*)w.W2;
-  const T* W3 = (const T*)w.W3;
-  const int n0 = wave_id() * D::CPW;
-  const int n_tiles = (rows + MT - 1) / MT;
-
-  TileSched sch(n_tiles);
-  for (int t = sch.begin; t < sch.end; t += sch.step) {
-    const int row0 = t * MT, nr = min(MT, rows - row0);
-    if constexpr (KIN == 8) {
-      if (threadIdx.x < MT) {
-        const int i = threadIdx.x;
-        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (i < nr) {
-          if constexpr (KIND == 0) {
-            const float* p = src + (size_t)b.gid[row0 + i] * in_dim;
-            for (int k = 0; k < in_dim; ++k) v[k] = p[k];
-          } else {
-            const float4 f = ((const float4*)src)[row0 + i];  // edge features (k_edge_feat)
-            v[0] = f.x;
-            v[1] = f.y;
-            v[2] = f.z;
-            v[3] = f.w;
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) xin[i * 8 + k] = v[k];
-      }
-    } else {
-      for (int task = threadIdx.x; task < MT * KIN; task += NTHR) {
-        const int i = task / KIN, k = task - i * KIN;
-        xin[task] = (i < nr && k < in_dim) ? src[(size_t)b.gid[row0 + i] * in_dim + k] : 0.f;
-      }
-    }
-    lds_sync();
-    f32x4 acc[MB][NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int c = acc_col(n0, nb);
-      const float bb = w.b1[c];
-      if constexpr (KIN == 8) {
-        float wr[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) wr[k] = k < in_dim ? w.W1f[c * in_dim + k] : 0.f;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float* x = xin + acc_row(mb, r) * 8;
-            float a = bb;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) a += wr[k] * x[k];
-            acc[mb][nb][r] = act_f<ACT>(a);
-          }
-      } else {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[mb][nb][r] = bb;
-        for (int k = 0; k < in_dim; ++k) {
-          const float wk = w.W1f[c * in_dim + k];
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[mb][nb][r] += wk * xin[acc_row(mb, r) * KIN + k];
-        }
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[mb][nb][r] = act_f<ACT>(acc[mb][nb][r]);
-      }
-    }
-    acc_to_lds<T, MB, NB, D::LDH>(acc, zs, n0);
-    lds_sync();
-    zero_acc(acc);
-    wave_gemm<T, MB, NB, H, D::LDH>(acc, zs, W2, H, n0);
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const float bb = w.b2[acc_col(n0, nb)];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[mb][nb][r] = act_f<ACT>(acc[mb][nb][r] + bb);
-      }
-    acc_to_lds<T, MB, NB, D::LDH>(acc, z2, n0);
-    lds_sync();
-    zero_acc(acc);
-    wave_gemm<T, MB, NB, H, D::LDH>(acc, z2, W3, H, n0);
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const float bb = w.b3[acc_col(n0, nb)];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[mb][nb][r] += bb;
-      }
-    float inv[MB][4];
-    ln_normalize<MB, NB, MT, H>(acc, red, eps, inv);
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int c = acc_col(n0, nb);
-        const float g = w.gamma[c], be = w.beta[c];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) zs[acc_row(mb, r) * D::LDH + c] = from_f<T>(g * acc[mb][nb][r] + be);
-      }
-    lds_sync();
-    lds_rows_to_global<T, D::LDH>(zs, nr, H, out + (size_t)row0 * H, H, [](int i) { return i; });
-    lds_sync();
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -564,36 +434,6 @@ void launch_node_proj(const Shape& s, const BatchView& b, const MlpW& w, const v
     constexpr int MT = H == 512 ? 16 : 32;
     k_node_proj<T, H, MT><<<s.grid, NTHR, 0, st>>>(b.n, w, (const T*)h, pr, ps);
   }));
-}
-
-void launch_enc_node_fwd(const Shape& s, const BatchView& b, const MlpW& w, const float* node_in, int in_dim,
-                         void* h0, hipStream_t st) {
-  if (b.n == 0) return;
-  if (enc_stream(s)) {
-    launch_enc_fwd_stream(s, 0, b.n, b.gid, w, node_in, in_dim, h0, st);
-    return;
-  }
-  XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
-    if constexpr (sizeof(T) == 2 && H == 128) {
-      if (in_dim <= 8)
-        k_enc_fwd<T, H, MT, ACT, 0, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, (T*)h0, s.eps);
-      else
-        k_enc_fwd<T, H, MT, ACT, 0, 32><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, (T*)h0, s.eps);
-    }
-  }))));
-}
-
-void launch_enc_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, void* e0,
-                         hipStream_t st) {
-  if (b.E == 0) return;
-  if (enc_stream(s)) {
-    launch_enc_fwd_stream(s, 1, b.E, nullptr, w, xe, 4, e0, st);
-    return;
-  }
-  XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(enc_edge_rows(s), {
-    if constexpr (sizeof(T) == 2 && H == 128)
-      k_enc_fwd<T, H, MT, ACT, 1, 8><<<s.grid, NTHR, 0, st>>>(b.E, b, w, xe, 4, (T*)e0, s.eps);
-  }))));
 }
 
 void launch_dec_fwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, float* out, int out_dim,
