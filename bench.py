@@ -62,9 +62,8 @@ def kernel_bytes(name: str, n: int, E: int, H: int, s: int, fused: int = 0, de_i
                  ztape: bool = False, atape: bool = False, split: bool = False) -> float | None:
     """Algorithmic HBM bytes of one launch of a processor kernel: each input
     read once, each output written once (s = bytes per stored latent; FP32
-    adjoints are 4 bytes).  `fused`: the edge adjoint accumulates dW2 (1), or
-    dW2 and the e-block of dW1 (2), itself, so z and du are not written (and
-    with 1 the e-block is a separate product that reads da and e again).
+    adjoints are 4 bytes).  `fused`: the edge adjoint accumulates dW2 and the
+    e-block of dW1 itself (2; else 0), so z and du are not written.
     `de_in`: fraction of launches that read an incoming edge adjoint de' (all
     but the last layer).  `atape`: the forward also writes the
     pre-activation a (SiLU), which the adjoint reads too.  `ztape`: the
@@ -83,24 +82,20 @@ def kernel_bytes(name: str, n: int, E: int, H: int, s: int, fused: int = 0, de_i
         return E * (3 + (1 if ztape else 0) + (1 if atape else 0)) * H * s + n * (H * s + 4 * H)
     if name == "edge_bwd":
         # per edge: de' (FP32) read, de (FP32) and da written, and
-        #   both fused, z on the tape: z, e read
-        #   dW2 fused, z on the tape:  z read
+        #   fused, z on the tape:      z, e read
         #   fused, recompute:          h_s, e read
         #   unfused, z on the tape:    z read, du written
         #   unfused, recompute:        h_s, e read, z, du written
         # per receiver: h_r (not with ztape), dm (FP32) read, S_r (FP32) written
-        if ztape:
-            lat = 3 if fused == 2 else 2
-        else:
-            lat = 3 if fused else 5
+        lat = 3 if ztape or fused else 5
         per_edge = (lat + (1 if atape else 0)) * H * s + 4 * H * (1 + de_in)
         return E * per_edge + n * ((0 if ztape else H * s) + 8 * H)
     if name == "node_fwd":
         return n * (2 * H * s + 4 * H)
     if name == "node_bwd":
-        # h, m (FP32), dh' (FP32) read; dh_mid, dm (FP32) and da written (z and
-        # du too where dW2 is not fused: BF16 at H = 128 fuses it)
-        return n * (2 * H * s + 16 * H + (0 if (s == 2 and H == 128) else 2 * H * s))
+        # h, m and dh_mid of the layer above (FP32) read, on all but the last
+        # layer also S_r and S_s (FP32); dh_mid, dm (FP32), da, du, z written
+        return n * (4 * H * s + 16 * H + 8 * H * de_in)
     return None
 
 
@@ -113,12 +108,13 @@ def kernel_flops(name: str, n: int, E: int, H: int, fused: int = 0, ztape: bool 
         return n * 4.0 * H * H
     if name == "edge_bwd":
         # recompute (3H x H unless z is on the tape, H x H), W2^T du, W1e^T da;
-        # fused: du^T z (1), and da^T e (2)
+        # fused (2): du^T z and da^T e
         return E * (12.0 + 2.0 * fused - (6.0 if ztape else 0.0)) * H * H
     if name == "node_fwd":
         return n * 6.0 * H * H
     if name == "node_bwd":
-        return n * (14.0 if H == 128 else 12.0) * H * H
+        # recompute, adjoint, and the edge products of the layer above
+        return n * 16.0 * H * H
     return None
 
 
@@ -476,10 +472,8 @@ def main():
     # dominant kernel of the headline BF16 step and its roofline
     kern = bf["kernels"]
     ztape = bf["keep"]  # the edge adjoint reads z from the forward's tape (tape policy keep)
-    # the BF16 edge adjoint at H = 128 fuses its weight gradients: dW2 only on
-    # its 32-row tiles with the z tape, dW2 and the e-block of dW1 otherwise
-    adj_rows = (bf["tiles"][4] or bf["tiles"][0]) if bf["tiles"] else (args.adjoint_edge_rows or args.edge_rows or 64)
-    fused = 0 if H != 128 else (1 if (ztape and adj_rows == 32) else 2)
+    # the BF16 edge adjoint at H = 128 accumulates dW2 and the e-block of dW1
+    fused = 2 if H == 128 else 0
     atape = ztape and cfg.activation != "relu"  # ... and, under SiLU, a
     de_in = (L - 1) / L
     kb = lambda k, n_w, e_w: kernel_bytes(k, n_w, e_w, H, 2, fused, de_in, ztape, atape, bf["split"])  # noqa: E731

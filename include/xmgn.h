@@ -110,10 +110,10 @@ void xmgn_ctx_destroy(xmgn_ctx* ctx);
  * 64, 1024, 4; at H = 512 8 edge waves).  LDS fixes the rows at H = 128
  * (at most 64-row edge tiles), at H = 256 (32-row node tiles; 32-row edge
  * tiles unless, in the BF16 form, 64 are asked for) and at H = 512 (16-row
- * node tiles; 32-row edge tiles) whatever is asked.  The BF16 gathered edge
- * forward has one configuration at every width, whatever is asked; the rows
- * asked for still set the largest in-degree a batch may have.  Changing it
- * invalidates
+ * node tiles; 32-row edge tiles) whatever is asked.  The gathered edge
+ * forward, the node processor kernels and the forward encoders have one
+ * configuration, whatever is asked; the rows asked for still set the largest
+ * in-degree a batch may have.  Changing it invalidates
  * cached batch plans. */
 xmgn_status xmgn_ctx_set_tiles(xmgn_ctx* ctx, int32_t edge_rows, int32_t node_rows,
                                int32_t grid, int32_t edge_waves);
@@ -122,8 +122,7 @@ xmgn_status xmgn_ctx_set_tiles(xmgn_ctx* ctx, int32_t edge_rows, int32_t node_ro
  * receiver segments per tile).  edge_rows: 32 or 64 in the BF16 form at
  * H = 128 and 256, else the forward's; 0 = the forward's.  edge_waves: 4 or 8
  * waves per workgroup, any form; 0 = the forward's.  (With z on the tape the
- * BF16 adjoint at H = 128 has one configuration, whatever is asked.)
- * Invalidates the last forward. */
+ * adjoint has one configuration, whatever is asked.)  Invalidates the last forward. */
 xmgn_status xmgn_ctx_set_bwd_tiles(xmgn_ctx* ctx, int32_t edge_rows, int32_t edge_waves);
 xmgn_status xmgn_ctx_get_bwd_tiles(const xmgn_ctx* ctx, int32_t* edge_rows, int32_t* edge_waves);
 
