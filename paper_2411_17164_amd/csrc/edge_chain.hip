@@ -291,7 +291,7 @@ void launch_edge_fwd_chain(const Shape& s, const BatchView& b, const MlpW& w, co
 // e-block of W1^T stay in LDS (96 KiB); z comes a step ahead, de' and dm_r
 // during u and its statistics.  Column sums over edges (db2, dgamma, dbeta)
 // are taken across the 16 lanes of a DPP row; db1 is the total of the receiver
-// sums.  On 3.55M edges and 400k nodes 1,819 us (6.8 GB algorithmic, 3.7 TB/s;
+// sums.  On 3.55M edges and 400k nodes 1,730 us (6.8 GB algorithmic, 3.9 TB/s;
 // a large copy reaches 4.9); the 64-row workgroup-tile kernel it replaces took
 // 3,345 us, and its 32-row form 2,430 us plus a product of 300 us for the
 // e-block.  Bound by HBM and, between its barriers, by LDS reads of the weight
