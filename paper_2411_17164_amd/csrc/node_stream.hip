@@ -308,7 +308,11 @@ __global__ __launch_bounds__((StreamDims<T, H, W>::NT), (StreamDims<T, H, W>::NW
 #pragma unroll
       for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) t[k][r] = x[4 * gr + k][r] * act_d<ACT>(t[k][r]);
+        for (int r = 0; r < 4; ++r) {
+          t[k][r] = x[4 * gr + k][r] * act_d<ACT>(t[k][r]);
+          // (a wave without rows looks at another's, whose a may not be written yet)
+          if (ACT != 0 && !ok) t[k][r] = 0.f;
+        }
       cb1[gr] += (double)colsum64(t);
 #pragma unroll
       for (int k = 0; k < 4 / BLK; ++k) du[4 / BLK * gr + k] = C::of(*(const f32x4(*)[BLK])(t + BLK * k));
