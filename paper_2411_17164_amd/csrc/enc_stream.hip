@@ -569,7 +569,11 @@ __global__ __launch_bounds__(512, 2) void k_enc_edge_bwd_chain(int rows, MlpW w,
 #pragma unroll
       for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) t[k][r] = x[4 * gr + k][r] * act_d<ACT>(t[k][r]);
+        for (int r = 0; r < 4; ++r) {
+          t[k][r] = x[4 * gr + k][r] * act_d<ACT>(t[k][r]);
+          // (a wave without rows looks at another's, whose a2 may not be written yet)
+          if (ACT != 0 && !ok) t[k][r] = 0.f;
+        }
       cb2[gr] += (double)colsum64(t);
 #pragma unroll
       for (int k = 0; k < 2; ++k) d[2 * gr + k] = C::of(*(const f32x4(*)[2])(t + 2 * k));

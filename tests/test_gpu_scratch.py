@@ -78,3 +78,12 @@ def check(api, G, hidden, layers, precision, activation, agg="message"):
 @pytest.mark.parametrize("precision,hidden", [("bf16", 128), ("bf16", 256), ("bf16", 512), ("fp32", 128), ("fp32", 256)])
 def test_fewer_nodes_than_waves(api, precision, hidden, n, layers, activation):
     check(api, ring(n, lambda i: n - 1), hidden, layers, precision, activation)
+
+
+@pytest.mark.parametrize("activation", ["silu", "relu"])
+@pytest.mark.parametrize("edges", [1, 3, 7])
+@pytest.mark.parametrize("precision,hidden", [("bf16", 128), ("bf16", 256), ("bf16", 512), ("fp32", 128), ("fp32", 256)])
+def test_fewer_edges_than_waves(api, precision, hidden, edges, activation):
+    """(One layer: the buffer that takes the encoder's pre-activations is then
+    not written by the layers.)"""
+    check(api, ring(12, lambda i: int(i < edges)), hidden, 1, precision, activation)
