@@ -31,6 +31,13 @@ int g_config_error = 0;
 // ms; 100k, BF16, H = 256: 3.26 -> 2.5; 50k, H = 512: 4.07 -> 2.9; 400k, H = 128
 // (bound by reading its operands): 5.9 -> 4.4.  Loads under a condition, or
 // behind a possible row index, each waited for the ones before: 20% slower.
+// A chunk can be 20,000 rows, more than one running FP32 sum takes well: the
+// FP32 form adds up runs of 64 MFMA steps (256 rows) in a second set of
+// accumulators.  Gradient against 64 bits, 400k nodes, H = 128: 1.0e-7 (worst
+// tensor 1.4e-7) where one sum a chunk left 3.8e-7 (1.1e-6); the 50k-node step
+// takes 7.33 ms instead of 7.30.  Beside the rounding of BF16 operands the longer
+// sum does not show (worst tensor, 400k nodes and edges, H = 128, 256 and 512:
+// 1.85e-4, 1.39e-4 and 1.39e-4 here as with the shorter chunks of a launch per product).
 // ---------------------------------------------------------------------------
 template <typename T, int BLK, int ROWS = 64>
 struct Wg {
@@ -41,6 +48,7 @@ struct Wg {
   static constexpr int LD = sizeof(T) == 2 ? BLK * 2 : BLK * 4 + 16;  // bytes per LDS row
   static constexpr int TILE = KR * LD;
   static constexpr int FM = BLK / 32, FN = 4;               // 16 x 16 blocks of a wave
+  static constexpr int RUN = sizeof(T) == 4 ? 256 : 0;      // rows summed in one run (0: all)
   static __device__ __forceinline__ int off(int row, int u) {
     if constexpr (sizeof(T) == 2)
       return row * LD + (((u >> 1) ^ (row & 7)) << 5) + ((u & 1) << 4);
@@ -133,8 +141,9 @@ __device__ __forceinline__ void wg_block(const WgradOp& op, int r_begin, int r_e
   const int l = lane_id(), li = l & 15, lg = l >> 4;
   const SA* A = (const SA*)op.A + op.a0;
   const SB* B = (const SB*)op.B + op.b0;
-  f32x4 acc[G::FM][G::FN];
+  f32x4 acc[G::FM][G::FN], tot[G::RUN ? G::FM : 1][G::FN];
   zero_acc(acc);
+  zero_acc(tot);
   WgStage<T, SA, G, BLK> sa;
   WgStage<T, SB, G, BLK> sb;
   auto load = [&](int r0) {
@@ -146,7 +155,7 @@ __device__ __forceinline__ void wg_block(const WgradOp& op, int r_begin, int r_e
   };
   const bool live = m0 + wm < op.M && n0 + wn < op.N;  // (uniform)
   load(r_begin);
-  int half = 0;
+  int half = 0, run = 0;
   for (int r0 = r_begin; r0 < r_end; r0 += G::KR, half ^= 1) {
     unsigned char* At = smem + half * 2 * G::TILE;
     unsigned char* Bt = At + G::TILE;
@@ -171,6 +180,17 @@ __device__ __forceinline__ void wg_block(const WgradOp& op, int r_begin, int r_e
         }
       }
     }
+    if constexpr (G::RUN > 0) {
+      run += G::KR;
+      if (run == G::RUN || r0 + G::KR >= r_end) {
+        run = 0;
+#pragma unroll
+        for (int i = 0; i < G::FM; ++i)
+#pragma unroll
+          for (int j = 0; j < G::FN; ++j) tot[i][j] += acc[i][j];
+        zero_acc(acc);
+      }
+    }
   }
 #pragma unroll
   for (int i = 0; i < G::FM; ++i)
@@ -179,7 +199,7 @@ __device__ __forceinline__ void wg_block(const WgradOp& op, int r_begin, int r_e
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + wm + 16 * i + 4 * lg + r, n = n0 + wn + 16 * j + li;
-        if (m < op.M && n < op.N) out[(size_t)m * op.N + n] = acc[i][j][r];
+        if (m < op.M && n < op.N) out[(size_t)m * op.N + n] = (G::RUN ? tot : acc)[i][j][r];
       }
 }
 
