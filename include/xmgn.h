@@ -242,20 +242,22 @@ xmgn_status xmgn_backward(xmgn_ctx* ctx, const xmgn_model_desc* desc, const floa
 
 /*
  * Tile autotuner (batching).  Times forward + backward of the batch over
- * candidate configurations -- edge-tile rows {32, 64} x edge waves {4, 8} x
- * persistent grid {4, 8} workgroups per compute unit, then node-tile rows
- * {32, 64} for the best of those (64-row edge tiles at H = 128 and, BF16,
- * H = 256; 64-row node tiles at H = 128), then the edge adjoint's own
- * waves {4, 8} and (BF16, H = 128 and 256) its own tile rows {32, 64}
- * against each edge-tile height and wave count of the forward -- and keeps
- * the fastest in ctx (as xmgn_ctx_set_tiles and xmgn_ctx_set_bwd_tiles
- * would).
+ * candidate configurations -- where a kernel of that step takes edge tiles
+ * (the split edge forward; the edge adjoint when z is not on the tape):
+ * edge-tile rows {32, 64} x edge waves {4, 8} x persistent grid {4, 8}
+ * workgroups per compute unit, else the grid alone on the most rows; then
+ * node-tile rows {32, 64} for the best of those (64-row edge tiles at H = 128
+ * and, BF16, H = 256; 64-row node tiles at H = 128) -- and keeps the fastest
+ * in ctx (as xmgn_ctx_set_tiles would; the edge adjoint follows the
+ * forward's).
  * Arguments as for xmgn_forward / xmgn_backward; out and d_params are
  * overwritten, d_out is only read.  cache_path (host string or NULL): a text
  * file of configuration lines; a hit skips the timing,
  * a miss appends a line ("key edge_rows node_rows grid edge_waves
  * adjoint_edge_rows adjoint_edge_waves ms").  The key holds the device name, the model
- * description, the tape policy and the batch's node and edge counts.  The chosen
+ * description, whether the tape holds z, the edge forward's form and the
+ * batch's node and edge counts.  Of a line, settings that no kernel of the
+ * step takes are not used.  The chosen
  * configuration and its step time are returned (any output pointer may be
  * NULL).  Synchronises the stream.
  */

@@ -1659,7 +1659,7 @@ static std::string tune_key(const xmgn_ctx* c, const xmgn_model_desc* d) {
   if (hipGetDeviceProperties(&prop, c->device) == hipSuccess) arch = prop.gcnArchName;
   std::ostringstream k;
   k << arch.substr(0, arch.find(':')) << ":H" << d->hidden << ":L" << d->n_layers << ":p" << d->precision << ":a"
-    << d->activation << ":g" << d->aggregate << ":t" << (c->tape_hidden ? 1 : 0) << ":s" << (c->edge_split ? 1 : 0)
+    << d->activation << ":g" << d->aggregate << ":t" << (c->tape_z ? 1 : 0) << ":s" << (c->edge_split ? 1 : 0)
     << ":n" << c->cur->n << ":E"
     << c->cur->E;
   return k.str();
@@ -1684,6 +1684,13 @@ extern "C" xmgn_status xmgn_autotune(xmgn_ctx* c, const xmgn_model_desc* d, cons
   if (xmgn_status r = xmgn_forward(c, d, params, ps, part_ids, n_batch, node_in, pos, edge_norm, out, 1, stream))
     return r;
   const std::string key = tune_key(c, d);
+  // The split forward takes edge tiles, and the adjoint that recomputes z.  Where
+  // neither runs, edge rows and waves change no kernel, but the rows bound the
+  // in-degree a batch may have: they are not tried, and are set to the most.
+  const bool bwd_tiles = !c->tape_z, tiles = bwd_tiles || c->edge_split;
+  const std::vector<int> rows = d->hidden == 128 || (d->hidden == 256 && d->precision == 1) ? std::vector<int>{32, 64}
+                                                                                            : std::vector<int>{32};
+  const int any_rows = rows.back(), any_waves = d->hidden == 512 ? 8 : 4;
   int best[6] = {0, 0, 0, 0, 0, 0};  // edge rows, node rows, grid, edge waves, adjoint edge rows, adjoint waves
   float best_ms = -1.f;
   if (cache_path) {
@@ -1704,15 +1711,21 @@ extern "C" xmgn_status xmgn_autotune(xmgn_ctx* c, const xmgn_model_desc* d, cons
         best_ms = ms;
       }
     }
+    // (a line may be of a library whose kernels took more settings)
+    if (!tiles) {
+      best[0] = any_rows;
+      best[3] = any_waves;
+    }
+    if (!bwd_tiles) best[4] = best[5] = 0;
   }
   if (best_ms < 0.f) {
     hipEvent_t a, b;
     HIPCHK(hipEventCreate(&a));
     HIPCHK(hipEventCreate(&b));
     xmgn_status err = XMGN_OK;
-    auto trial = [&](int er, int nr, int g, int wv, int br, int bw) -> xmgn_status {
+    auto trial = [&](int er, int nr, int g, int wv) -> xmgn_status {
       if (xmgn_status r = xmgn_ctx_set_tiles(c, er, nr, g, wv)) return r;
-      if (xmgn_status r = xmgn_ctx_set_bwd_tiles(c, br, bw)) return r;
+      if (xmgn_status r = xmgn_ctx_set_bwd_tiles(c, 0, 0)) return r;
       auto step = [&]() -> xmgn_status {
         if (xmgn_status r = xmgn_forward(c, d, params, ps, part_ids, n_batch, node_in, pos, edge_norm, out, 1, stream))
           return r;
@@ -1733,35 +1746,17 @@ extern "C" xmgn_status xmgn_autotune(xmgn_ctx* c, const xmgn_model_desc* d, cons
         best[1] = nr;
         best[2] = g;
         best[3] = wv;
-        best[4] = br;
-        best[5] = bw;
       }
       return XMGN_OK;
     };
-    std::vector<int> rows = d->hidden == 128 || (d->hidden == 256 && d->precision == 1) ? std::vector<int>{32, 64}
-                                                                                         : std::vector<int>{32};
-    if (d->hidden == 256 && d->precision == 1 && !c->edge_split) rows.push_back(128);  // the wide forward
-    // stage 1: edge kernels (the bulk of the step), stage 2: node tiles
-    for (int er : rows)
-      for (int wv : {4, 8})
+    // stage 1: edge kernels and grid, stage 2: node tiles.  (An adjoint that
+    // takes tiles runs on the rows and waves tried here: no forward beside it
+    // takes any.)
+    for (int er : tiles ? rows : std::vector<int>{any_rows})
+      for (int wv : tiles ? std::vector<int>{4, 8} : std::vector<int>{any_waves})
         for (int wpc : {4, 8})
-          if (!err) err = trial(er, 32, ((cus * wpc + 7) / 8) * 8, wv, 0, 0);
-    if (!err && d->hidden == 128) err = trial(best[0], 64, best[2], best[3], 0, 0);
-    // stage 3: the edge adjoint on its own waves per workgroup and (BF16,
-    // H = 128 and 256) its own tile rows, against each forward tiling and
-    // wave count (stage 1 timed the adjoint on the forward's rows and waves
-    // only)
-    if (!err) {
-      const bool own_rows = (d->hidden == 128 || d->hidden == 256) && d->precision == 1;
-      const int nr = best[1], g = best[2];
-      const std::vector<int> ers = own_rows ? rows : std::vector<int>{best[0]};
-      const std::vector<int> brs = own_rows ? std::vector<int>{32, 64} : std::vector<int>{0};
-      for (int er : ers)
-        for (int wv : {4, 8})
-          for (int br : brs)
-            for (int bw : {4, 8})
-              if (!err && !((br == 0 || br == er) && bw == wv)) err = trial(er, nr, g, wv, br, bw);
-    }
+          if (!err) err = trial(er, 32, ((cus * wpc + 7) / 8) * 8, wv);
+    if (!err && d->hidden == 128) err = trial(best[0], 64, best[2], best[3]);
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     if (err) return err;
