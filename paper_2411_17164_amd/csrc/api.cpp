@@ -514,7 +514,7 @@ struct Batch {
 };
 
 struct BlockW {
-  int64_t W1 = -1, W2 = -1, W3 = -1, W1T = -1, W2T = -1, W3T = -1, Brs = -1, FS = -1, BS = -1;
+  int64_t W1 = -1, W2 = -1, W3 = -1, W1T = -1, W2T = -1, Brs = -1, FS = -1, BS = -1;
 };
 
 struct xmgn_ctx {
@@ -900,8 +900,6 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
     if (b == 0) {
       add_job(c, poff(d, b, 0, 2), H, 0, 0, H, H, w.W2);
       add_job(c, poff(d, b, 0, 4), H, 0, 0, H, H, w.W3);
-      add_job(c, poff(d, b, 0, 2), H, 0, 1, H, H, w.W2T);
-      add_job(c, poff(d, b, 0, 4), H, 0, 1, H, H, w.W3T);
     } else {  // the edge encoder's adjoint takes all four in this order
       w.BS = w.FS;
       add_frag_job(c, poff(d, b, 0, 4), H, 0, 1, H, H);
@@ -969,7 +967,6 @@ static MlpW weights(const xmgn_ctx* c, const xmgn_model_desc* d, const float* pa
   w.W3 = ptr(b.W3);
   w.W1T = ptr(b.W1T);
   w.W2T = ptr(b.W2T);
-  w.W3T = ptr(b.W3T);
   w.Brs = ptr(b.Brs);
   w.FS = ptr(b.FS);
   w.BS = ptr(b.BS);

@@ -305,7 +305,9 @@ void launch_wgrad(const Shape& s, WgradBatch& b, float* partial, RedBatch& red, 
   const int blk = wgrad_block(s), kr = s.prec == 1 ? 64 : 32, target = wgrad_target(s);
   auto blocks = [&](const WgradOp& o) { return ((o.M + blk - 1) / blk) * ((o.N + blk - 1) / blk); };
   // a row of which one operand is to be rounded from FP32 takes about twice as
-  // long (H = 512: 68 against 35 ns in a workgroup)
+  // long (H = 512: 68 against 35 ns in a workgroup).  With this weight against
+  // none, us a layer with its sums: H = 512, 50k nodes 667 / 712; H = 256, 100k
+  // 424 / 443; H = 128, 400k 165 / 182, 60k 48 / 47.
   auto weight = [&](const WgradOp& o) { return s.prec == 1 && (o.a_f32 || o.b_f32) ? 2 : 1; };
   long long rows = 0;
   for (int j = 0; j < b.n; ++j) rows += (long long)b.job[j].op.R * weight(b.job[j].op) * blocks(b.job[j].op);
@@ -407,47 +409,20 @@ void launch_reduce_batch(const RedBatch& b, float* tmp, hipStream_t st) {
 // ---------------------------------------------------------------------------
 // Fixed-order reduction of per-workgroup partial rows.
 // ---------------------------------------------------------------------------
-struct VecSegs {
-  int n;
-  int src[16];
-  int len[16];
-  int inner[16];       // elements per contiguous run
-  int src_stride[16];  // partial-row stride between runs
-  int dst_stride[16];
-  float* dst[16];
-};
-
-__global__ void k_vec_reduce(const float* __restrict__ tmp, int splits, int row, VecSegs s) {
-  const int seg = blockIdx.y;
-  if (seg >= s.n) return;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < s.len[seg]; j += gridDim.x * blockDim.x) {
-    const int run = j / s.inner[seg], k = j - run * s.inner[seg];
-    const int src = s.src[seg] + run * s.src_stride[seg] + k;
-    s.dst[seg][run * s.dst_stride[seg] + k] = order_sum(tmp + src, row, splits);
-  }
-}
-
-// stage 1 of the vector reductions: column sums of [G][row] in RED_SPLITS groups
-static const float* vec_stage1(const float* partial, int G, int row, int* splits, float* tmp, hipStream_t st) {
-  *splits = G < RED_SPLITS ? G : RED_SPLITS;
-  const int per = (G + *splits - 1) / *splits;
-  k_colsum_stage1<<<dim3((row + 255) / 256, *splits), 256, 0, st>>>(partial, G, row, row, per, tmp);
-  return tmp;
+__global__ void k_vec_reduce(const float* __restrict__ tmp, int splits, int row, int src, int len, int inner,
+                             int src_stride, float* __restrict__ dst, int dst_stride) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= len) return;
+  const int run = j / inner, k = j - run * inner;
+  dst[run * dst_stride + k] = order_sum(tmp + src + run * src_stride + k, row, splits);
 }
 
 void launch_vec_reduce_strided(const float* partial, int G, int row, int src, int runs, int inner, int src_stride,
                                float* dst, int dst_stride, float* tmp, hipStream_t st) {
-  VecSegs s{};
-  s.n = 1;
-  s.src[0] = src;
-  s.len[0] = runs * inner;
-  s.inner[0] = inner;
-  s.src_stride[0] = src_stride;
-  s.dst_stride[0] = dst_stride;
-  s.dst[0] = dst;
-  int splits;
-  const float* t1 = vec_stage1(partial, G, row, &splits, tmp, st);
-  k_vec_reduce<<<dim3((runs * inner + 255) / 256, 1), 256, 0, st>>>(t1, splits, row, s);
+  const int splits = G < RED_SPLITS ? G : RED_SPLITS, per = (G + splits - 1) / splits;
+  k_colsum_stage1<<<dim3((row + 255) / 256, splits), 256, 0, st>>>(partial, G, row, row, per, tmp);
+  k_vec_reduce<<<(runs * inner + 255) / 256, 256, 0, st>>>(tmp, splits, row, src, runs * inner, inner, src_stride, dst,
+                                                           dst_stride);
 }
 
 // ---------------------------------------------------------------------------

@@ -114,22 +114,24 @@ __device__ __forceinline__ void stage_frags(bf16x8* dst, const bf16* __restrict_
   }
 }
 
-// acc[t][mb] += W X^T over chunks [C0, C0 + NC) of the fragments F (KC chunks
-// per block): x[t][i] is chunk C0 + i of row group t, natural layout.
+template <int N>
+__device__ __forceinline__ void zero_blocks(f32x4 (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// acc[mb] += W X^T over the KC chunks of the fragments F (KC per block): x[c]
+// is chunk c of the rows, natural layout.
 // BOUND: keep the fragment reads of one chunk from being hoisted over the
 // chunk before (bounds their registers to 4 MBS).
-template <int ET, int MBS, int KC, int C0, int NC, int XN, bool BOUND = false>
-__device__ __forceinline__ void chain_gemm(f32x4 (&acc)[ET][MBS], const bf16x8* F, const bf16x8 (&x)[ET][XN], int x0) {
+template <bool BOUND = false, int MBS, int KC>
+__device__ __forceinline__ void chain_gemm(f32x4 (&acc)[MBS], const bf16x8* F, const bf16x8 (&x)[KC]) {
   const bf16x8* f = F + lane_id();
 #pragma unroll
-  for (int i = 0; i < NC; ++i) {
+  for (int c = 0; c < KC; ++c) {
     if constexpr (BOUND) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int mb = 0; mb < MBS; ++mb) {
-      const bf16x8 a = f[(mb * KC + C0 + i) * 64];
-#pragma unroll
-      for (int t = 0; t < ET; ++t) acc[t][mb] = mma(a, x[t][x0 + i], acc[t][mb]);
-    }
+    for (int mb = 0; mb < MBS; ++mb) acc[mb] = mma(f[(mb * KC + c) * 64], x[c], acc[mb]);
   }
   if constexpr (BOUND) __builtin_amdgcn_sched_barrier(0);
 }

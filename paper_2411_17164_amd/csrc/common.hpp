@@ -250,36 +250,6 @@ __device__ __forceinline__ float sum_groups(float s) {
   return s;
 }
 
-// Full-row sums of x over all columns of all NW waves.  red: LDS float
-// [NW][MT].  Returns out[mb][r] = sum over the row acc_row(mb, r), the wave
-// partials added in wave order.  Contains two barriers.
-template <int MB, int NB, int MT, int NW = NWAVE>
-__device__ __forceinline__ void row_sum(const f32x4 (&x)[MB][NB], float* red, float (&out)[MB][4]) {
-  const int w = wave_id(), l = lane_id();
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float s = 0.f;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) s += x[mb][nb][r];
-      s = sum16(s);
-      if ((l & 15) == 0) red[w * MT + acc_row(mb, r)] = s;
-    }
-  lds_sync();
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = acc_row(mb, r);
-      float t = 0.f;
-#pragma unroll
-      for (int k = 0; k < NW; k += 2) t += red[k * MT + row] + red[(k + 1) * MT + row];
-      out[mb][r] = t;
-    }
-  lds_sync();
-}
-
 // Two row sums (of x and of y) exchanged across the NW waves in one barrier
 // round.  red: LDS float [2][NW][MT].
 template <int MB, int NB, int MT, int NW = NWAVE>

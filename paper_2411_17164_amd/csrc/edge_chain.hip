@@ -118,13 +118,13 @@ struct EdgeFwdChain {
   static constexpr size_t bytes = W1S + W2S + NW * BUF;
 };
 
-template <int ACT, int AGG, int NW, int ET>
+template <int ACT, int AGG, int NW>
 __global__ __launch_bounds__(64 * NW, NW / 4) void k_edge_fwd_chain(BatchView b, MlpW w, const bf16* __restrict__ h,
                                                                     const bf16* __restrict__ e,
                                                                     bf16* __restrict__ e_out, float* __restrict__ m,
                                                                     bf16* __restrict__ z_out,
                                                                     bf16* __restrict__ a_out, float eps) {
-  constexpr int H = 128, MT = 16 * ET;
+  constexpr int H = 128;
   using L = EdgeFwdChain<NW>;
   __shared__ __align__(16) unsigned char smem[L::bytes];
   bf16x8* F1 = (bf16x8*)smem;
@@ -139,32 +139,26 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void k_edge_fwd_chain(BatchView b,
   vec.load(w.b1, w.b2, w.gamma, w.beta);
   const WaveEdges we(b, wv, nw);
 
-  // indices of a tile: this lane's edge of every 16-row group (clamped to the
-  // wave's last edge), its receiver, sender and the next edge's receiver
-  int rv[ET], cv[ET], rn[ET];
+  // indices of a tile: this lane's edge (clamped to the wave's last edge), its
+  // receiver, sender and the next edge's receiver
+  int rv = 0, cv = 0, rn = 0;
   auto load_idx = [&](int e0) {
-#pragma unroll
-    for (int t = 0; t < ET; ++t) {
-      const int k = min(e0 + 16 * t + li, we.end - 1);
-      rv[t] = b.recv[k];
-      cv[t] = b.col[k];
-      rn[t] = k + 1 < b.E ? b.recv[k + 1] : -1;
-    }
+    const int k = min(e0 + li, we.end - 1);
+    rv = b.recv[k];
+    cv = b.col[k];
+    rn = k + 1 < b.E ? b.recv[k + 1] : -1;
   };
-  bf16x8 x[ET][12];
+  bf16x8 x[12];
   auto load_rows = [&](int e0) {
+    const int k = min(e0 + li, we.end - 1);
+    const bf16* pr = h + (size_t)rv * H + 8 * lg;
+    const bf16* ps = h + (size_t)cv * H + 8 * lg;
+    const bf16* pe = e + (size_t)k * H + 8 * lg;
 #pragma unroll
-    for (int t = 0; t < ET; ++t) {
-      const int k = min(e0 + 16 * t + li, we.end - 1);
-      const bf16* pr = h + (size_t)rv[t] * H + 8 * lg;
-      const bf16* ps = h + (size_t)cv[t] * H + 8 * lg;
-      const bf16* pe = e + (size_t)k * H + 8 * lg;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        x[t][c] = *(const bf16x8*)(pr + 32 * c);
-        x[t][4 + c] = *(const bf16x8*)(ps + 32 * c);
-        x[t][8 + c] = *(const bf16x8*)(pe + 32 * c);
-      }
+    for (int c = 0; c < 4; ++c) {
+      x[c] = *(const bf16x8*)(pr + 32 * c);
+      x[4 + c] = *(const bf16x8*)(ps + 32 * c);
+      x[8 + c] = *(const bf16x8*)(pe + 32 * c);
     }
   };
   const bool any = we.begin < we.end;
@@ -174,89 +168,67 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void k_edge_fwd_chain(BatchView b,
   }
   __syncthreads();
   SegSum128 seg;
-  for (int e0 = we.begin; e0 < we.end; e0 += MT) {
-    const int ne = min(MT, we.end - e0);
-    int rc[ET];
-    unsigned ends[ET];
-#pragma unroll
-    for (int t = 0; t < ET; ++t) {
-      rc[t] = rv[t];
-      ends[t] = (unsigned)__ballot(rv[t] != rn[t]) & 0xffffu;
-    }
-    const bool more = e0 + MT < we.end;
-    if (more) load_idx(e0 + MT);
+  for (int e0 = we.begin; e0 < we.end; e0 += 16) {
+    const int ne = min(16, we.end - e0);
+    const bool ok = li < ne;
+    const size_t row = (size_t)(e0 + li) * H + 8 * lg;
+    const int rc = rv;
+    const unsigned ends = (unsigned)__ballot(rv != rn) & 0xffffu;
+    const bool more = e0 + 16 < we.end;
+    if (more) load_idx(e0 + 16);
     vec.put(buf);
-    f32x4 acc[ET][8];
-    zero_acc(acc);
-    chain_gemm<ET, 8, 12, 0, 12>(acc, F1, x, 0);
-    bf16x8 ec[ET][4];
+    f32x4 acc[8];
+    zero_blocks(acc);
+    chain_gemm(acc, F1, x);
+    bf16x8 ec[4];
 #pragma unroll
-    for (int t = 0; t < ET; ++t)
+    for (int c = 0; c < 4; ++c) ec[c] = x[8 + c];
+    if (more) load_rows(e0 + 16);  // the next tile's rows, in flight from here
+    bf16x8 z[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) ec[t][c] = x[t][8 + c];
-    if (more) load_rows(e0 + MT);  // the next tile's rows, in flight from here
-    bf16x8 z[ET][4];
-#pragma unroll
-    for (int mb = 0; mb < 8; ++mb) {
-      const f32x4 bb = Vecs128::get(buf, 0, mb);
-#pragma unroll
-      for (int t = 0; t < ET; ++t) acc[t][mb] += bb;
-    }
+    for (int mb = 0; mb < 8; ++mb) acc[mb] += Vecs128::get(buf, 0, mb);
     if (a_out) {
 #pragma unroll
-      for (int t = 0; t < ET; ++t)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const bf16x8 v = to_natural(acc[t][2 * c], acc[t][2 * c + 1]);
-          if (16 * t + li < ne) *(bf16x8*)(a_out + (size_t)(e0 + 16 * t + li) * H + 32 * c + 8 * lg) = v;
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < ET; ++t)
-#pragma unroll
       for (int c = 0; c < 4; ++c) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          acc[t][2 * c][r] = act_f<ACT>(acc[t][2 * c][r]);
-          acc[t][2 * c + 1][r] = act_f<ACT>(acc[t][2 * c + 1][r]);
-        }
-        z[t][c] = to_natural(acc[t][2 * c], acc[t][2 * c + 1]);
-        if (z_out && 16 * t + li < ne) *(bf16x8*)(z_out + (size_t)(e0 + 16 * t + li) * H + 32 * c + 8 * lg) = z[t][c];
+        const bf16x8 v = to_natural(acc[2 * c], acc[2 * c + 1]);
+        if (ok) *(bf16x8*)(a_out + row + 32 * c) = v;
       }
-    zero_acc(acc);
-    chain_gemm<ET, 8, 4, 0, 4>(acc, F2, z, 0);
-#pragma unroll
-    for (int mb = 0; mb < 8; ++mb) {
-      const f32x4 bb = Vecs128::get(buf, 1, mb);
-#pragma unroll
-      for (int t = 0; t < ET; ++t) acc[t][mb] += bb;
     }
 #pragma unroll
-    for (int t = 0; t < ET; ++t) ln128(acc[t], eps);
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        acc[2 * c][r] = act_f<ACT>(acc[2 * c][r]);
+        acc[2 * c + 1][r] = act_f<ACT>(acc[2 * c + 1][r]);
+      }
+      z[c] = to_natural(acc[2 * c], acc[2 * c + 1]);
+      if (z_out && ok) *(bf16x8*)(z_out + row + 32 * c) = z[c];
+    }
+    zero_blocks(acc);
+    chain_gemm(acc, F2, z);
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) acc[mb] += Vecs128::get(buf, 1, mb);
+    ln128(acc, eps);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const f32x4 g0 = Vecs128::get(buf, 2, 2 * c), g1 = Vecs128::get(buf, 2, 2 * c + 1);
       const f32x4 b0 = Vecs128::get(buf, 3, 2 * c), b1 = Vecs128::get(buf, 3, 2 * c + 1);
+      f32x4 e_lo, e_hi;
+      from_natural(ec[c], e_lo, e_hi);
 #pragma unroll
-      for (int t = 0; t < ET; ++t) {
-        f32x4 e_lo, e_hi;
-        from_natural(ec[t][c], e_lo, e_hi);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float v0 = g0[r] * acc[t][2 * c][r] + b0[r], v1 = g1[r] * acc[t][2 * c + 1][r] + b1[r];
-          e_lo[r] += v0;
-          e_hi[r] += v1;
-          acc[t][2 * c][r] = AGG ? e_lo[r] : v0;  // the summand of m
-          acc[t][2 * c + 1][r] = AGG ? e_hi[r] : v1;
-        }
-        if (e_out) {
-          const bf16x8 v = to_natural(e_lo, e_hi);
-          if (16 * t + li < ne) *(bf16x8*)(e_out + (size_t)(e0 + 16 * t + li) * H + 32 * c + 8 * lg) = v;
-        }
+      for (int r = 0; r < 4; ++r) {
+        const float v0 = g0[r] * acc[2 * c][r] + b0[r], v1 = g1[r] * acc[2 * c + 1][r] + b1[r];
+        e_lo[r] += v0;
+        e_hi[r] += v1;
+        acc[2 * c][r] = AGG ? e_lo[r] : v0;  // the summand of m
+        acc[2 * c + 1][r] = AGG ? e_hi[r] : v1;
+      }
+      if (e_out) {
+        const bf16x8 v = to_natural(e_lo, e_hi);
+        if (ok) *(bf16x8*)(e_out + row + 32 * c) = v;
       }
     }
-#pragma unroll
-    for (int t = 0; t < ET; ++t) seg.add(acc[t], ends[t], rc[t], ne - 16 * t, buf, m);
+    seg.add(acc, ends, rc, ne, buf, m);
   }
   zero_empty_rows(b, m, H, wv, nw);
 }
@@ -265,10 +237,10 @@ bool edge_fwd_chain(const Shape& s) { return s.prec == 1 && s.H == 128; }
 
 void launch_edge_fwd_chain(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e, void* e_out,
                            float* m, void* z_out, void* a_out, hipStream_t st) {
-  constexpr int NW = 8, ET = 1;
+  constexpr int NW = 8;
   const int grid = edge_bwd_chain_grid(s, b.E);
   auto go = [&](auto act, auto agg) {
-    k_edge_fwd_chain<decltype(act)::value, decltype(agg)::value, NW, ET><<<grid, 64 * NW, 0, st>>>(
+    k_edge_fwd_chain<decltype(act)::value, decltype(agg)::value, NW><<<grid, 64 * NW, 0, st>>>(
         b, w, (const bf16*)h, (const bf16*)e, (bf16*)e_out, m, (bf16*)z_out, (bf16*)a_out, s.eps);
   };
   using I0 = std::integral_constant<int, 0>;
@@ -408,18 +380,15 @@ __global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, 
     wave_sync();
     auto vget = [&](int v, int mb) { return *(const f32x4*)(fr + 128 * v + 16 * mb + 4 * lg); };
     // u = W2 z + b2, xhat
-    f32x4 x[1][8];
-    zero_acc(x);
-    {
-      const bf16x8 zz[1][4] = {{z[0], z[1], z[2], z[3]}};
-      chain_gemm<1, 8, 4, 0, 4, 4, true>(x, F2, zz, 0);
-    }
+    f32x4 x[8];
+    zero_blocks(x);
+    chain_gemm<true>(x, F2, z);
     f32x4 dvm[8];  // dm_r, in flight during the statistics
 #pragma unroll
     for (int mb = 0; mb < 8; ++mb) dvm[mb] = *(const f32x4*)(dm + (size_t)rc * H + 16 * mb + 4 * lg);
 #pragma unroll
-    for (int mb = 0; mb < 8; ++mb) x[0][mb] += vget(0, mb);
-    const float inv = ln128(x[0], eps);
+    for (int mb = 0; mb < 8; ++mb) x[mb] += vget(0, mb);
+    const float inv = ln128(x, eps);
     // dv = dm_r + de'
     f32x4 g[8];
 #pragma unroll
@@ -430,7 +399,7 @@ __global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, 
     {
       f32x4 t[8];
 #pragma unroll
-      for (int mb = 0; mb < 8; ++mb) t[mb] = g[mb] * x[0][mb];
+      for (int mb = 0; mb < 8; ++mb) t[mb] = g[mb] * x[mb];
       colsum16(t, cg);
     }
     colsum16(g, cbt);
@@ -439,7 +408,7 @@ __global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, 
     for (int q = 0; q < 4; ++q) {
       const f32x4 g0 = vget(1, 2 * q), g1 = vget(1, 2 * q + 1);
       f32x4 &lo = g[2 * q], &hi = g[2 * q + 1];
-      const f32x4 &xl = x[0][2 * q], &xu = x[0][2 * q + 1];
+      const f32x4 &xl = x[2 * q], &xu = x[2 * q + 1];
       float a[4], d[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -456,14 +425,14 @@ __global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, 
     for (int mb = 0; mb < 8; ++mb)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        g[mb][r] = __builtin_fmaf(sgx * (-1.f / H), x[0][mb][r], __builtin_fmaf(sg, -1.f / H, g[mb][r])) * inv;
+        g[mb][r] = __builtin_fmaf(sgx * (-1.f / H), x[mb][r], __builtin_fmaf(sg, -1.f / H, g[mb][r])) * inv;
     colsum16(g, cb2);
-    bf16x8 du[1][4];
+    bf16x8 du[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) du[0][c] = to_natural(g[2 * c], g[2 * c + 1]);
+    for (int c = 0; c < 4; ++c) du[c] = to_natural(g[2 * c], g[2 * c + 1]);
     // [du | z] of the 128 edges; act'(a) from z (ReLU: a > 0 exactly where z > 0) or a
     wave_sync();
-    tile_put(reg, du[0], l);
+    tile_put(reg, du, l);
     tile_put(reg + 4096, z, l);
     bf16x8 az[4];
 #pragma unroll
@@ -477,28 +446,28 @@ __global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, 
     lds_sync();
     tile_wgrad(accW2, regs, 0, 4096, wm, wn, l);  // dW2 += du^T z
     // dz = W2^T du ; da = dz * act'(a)
-    zero_acc(x);
-    chain_gemm<1, 8, 4, 0, 4, 4, true>(x, F2T, du, 0);
+    zero_blocks(x);
+    chain_gemm<true>(x, F2T, du);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       f32x4 lo, hi;
       from_natural(az[c], lo, hi);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        x[0][2 * c][r] *= act_d<ACT>(lo[r]);
-        x[0][2 * c + 1][r] *= act_d<ACT>(hi[r]);
+        x[2 * c][r] *= act_d<ACT>(lo[r]);
+        x[2 * c + 1][r] *= act_d<ACT>(hi[r]);
       }
     }
-    bf16x8 da[1][4];
+    bf16x8 da[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      da[0][c] = to_natural(x[0][2 * c], x[0][2 * c + 1]);
-      if (ok) *(bf16x8*)((bf16*)o.da + (size_t)(e0 + li) * H + 32 * c + 8 * lg) = da[0][c];
+      da[c] = to_natural(x[2 * c], x[2 * c + 1]);
+      if (ok) *(bf16x8*)((bf16*)o.da + (size_t)(e0 + li) * H + 32 * c + 8 * lg) = da[c];
     }
     lds_sync();  // every wave is done with [du | z]
     // S_r: receiver sums of da in edge order; their total is db1
 #pragma unroll
-    for (int mb = 0; mb < 8; ++mb) *(f32x4*)(fr + li * 128 + (((4 * mb + lg) ^ li) << 2)) = x[0][mb];
+    for (int mb = 0; mb < 8; ++mb) *(f32x4*)(fr + li * 128 + (((4 * mb + lg) ^ li) << 2)) = x[mb];
     wave_sync();
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -517,14 +486,14 @@ __global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, 
       }
     }
     wave_sync();
-    tile_put(reg, da[0], l);
+    tile_put(reg, da, l);
     tile_put(reg + 4096, er, l);
     if (more) load_rows(e0 + 16);  // the next step's rows, in flight from here
     lds_sync();
     tile_wgrad(accW1, regs, 0, 4096, wm, wn, l);  // dW1[:, 2H:3H] += da^T e
     // de = de' (+ dm_r) + (W1^T da)[2H:3H]
-    zero_acc(x);
-    chain_gemm<1, 8, 4, 0, 4, 4, true>(x, F1T, da, 0);
+    zero_blocks(x);
+    chain_gemm<true>(x, F1T, da);
     if (ok) {
       const size_t at_ = (size_t)(e0 + li) * H + 4 * lg;
       f32x4 v[8];
@@ -538,7 +507,7 @@ __global__ __launch_bounds__(512, 2) void k_edge_bwd_chain(BatchView b, MlpW w, 
 #pragma unroll
       for (int mb = 0; mb < 8; ++mb) {
         if (AGG) v[mb] += *(const f32x4*)(dm + (size_t)rc * H + 16 * mb + 4 * lg);
-        *(f32x4*)(o.de_out + at_ + 16 * mb) = x[0][mb] + v[mb];
+        *(f32x4*)(o.de_out + at_ + 16 * mb) = x[mb] + v[mb];
       }
     }
     lds_sync();  // every wave is done with [da | e]

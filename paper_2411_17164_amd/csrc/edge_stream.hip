@@ -160,8 +160,13 @@ bool edge_stream(const Shape& s) { return !(s.prec == 1 && s.H == 128); }
 
 // FP32 at H = 128 with at most 12 rows for each of 1024 waves: four waves per
 // workgroup.  One 16-row step is all there is to do then, and its FP32 MFMAs
-// take 14 us on a SIMD: two waves to a SIMD took 43 us over 12,000 edges where
-// one takes 30 (the workgroup-tile kernel 35).
+// take 14 us on a SIMD.  Four against eight waves, us a launch: edge forward on
+// 1,500 edges 26 / 40, on 9,000 28 / 42, on 12,000 30 / 43 where every node has
+// six in-edges, but 47 / 44 where in-degrees vary and some ranges of whole
+// segments take a second step, on 16,000 50 / 45.  Rows without segments gain up
+// to 16,000, but lie on either side of the line at little cost: node adjoint 48 /
+// 73 on 12,000 rows, 50 / 75 on 16,000, 87 / 78 on 24,000; edge encoder adjoint
+// 41 / 57 on 12,000, 67 / 59 on 20,000.
 bool stream_small(const Shape& s, int rows) { return s.prec == 0 && s.H == 128 && rows <= 1024 * 12; }
 
 // One workgroup per CU as soon as there are 6 rows for each of its waves: a

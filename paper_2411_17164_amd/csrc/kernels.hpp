@@ -36,7 +36,6 @@ struct MlpW {
   const void* W3;
   const void* W1T;  // edge: [H][H] block of W1^T for the e input; node/dec: full W1^T
   const void* W2T;
-  const void* W3T;
   const void* Brs;  // edge layers: [H][2H] = [W1_r^T | W1_s^T]
   const float* W1f; // FP32 first-layer weights (encoders) / last layer (decoder)
   const float* b1;
@@ -115,15 +114,14 @@ struct EdgeBwdOut {
 // True when the edge adjoint accumulates dW2 and the e-block of dW1 itself
 // (then du and z are not written and wpart must be given).
 bool edge_bwd_fuses_wgrad(const Shape& s);
-// Fixed-order sums over the rows of partial matrices use a two-stage
-// reduction with caller scratch of reduce_tmp_floats(columns) floats.
+// Scratch (floats) of the two-stage sums over the rows of partial matrices with
+// so many columns.
 size_t reduce_tmp_floats(int max_cols);
-// True when the edge adjoint can read z from the forward's tape instead of
-// recomputing it (every form); zt is then that tape (else NULL: recompute),
-// and the unfused form does not write o.z (its dW2 product reads the tape).
-// True when the forms that read z from the tape also need a (SiLU); at is
-// then the tape of pre-activations (else NULL).
+// True when the adjoint with z on the tape also needs a (SiLU).
 bool edge_a_tape(const Shape& s);
+// zt: z of every edge as the forward kept it, or NULL (recomputed; the unfused
+// form then writes it to o.z for its dW2 product); at: a likewise, where
+// edge_a_tape.
 void launch_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                      const void* zt, const void* at, const float* de_in, const float* dm, const EdgeBwdOut& o,
                      hipStream_t st);
@@ -177,9 +175,6 @@ struct EncBwdOut {
   float* wpart;    // fused weight gradients [grid][2][H][H] (dW2, dW3) or NULL
   float* da1;      // more than 8 inputs: adjoint of the input layer's output [rows][H] (FP32); dW1 not in partial
 };
-// Rows per tile of the edge encoder (no segment constraint): the edge tile
-// at H = 128, the node tile at H = 256 and 512 (whose LDS budget it shares).
-inline int enc_edge_rows(const Shape& s) { return s.H == 128 ? s.mt_edge : s.mt_node; }
 // True when the encoder adjoint accumulates dW2 and dW3 itself (then z1,
 // z2, da2 and du3 are not written and wpart must be given).
 bool enc_bwd_fuses_wgrad(const Shape& s);
@@ -188,9 +183,10 @@ void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, cons
 void launch_enc_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, const float* de0,
                          const EncBwdOut& o, float* a2, hipStream_t st);
 
-// Their encoder adjoints stream their weights (w.BS); kind 0:
-// node inputs src[gid[row]], 1: edge features src[row].  The adjoint's partials
-// have edge_stream_grid(s, R) rows; a2: FP32 [R][H] scratch (SiLU).
+// True for the forms whose encoder adjoints stream their weights (w.BS): all but
+// BF16 at H = 128.  kind 0: node inputs src[gid[row]], 1: edge features src[row].
+// The adjoint's partials have edge_stream_grid(s, R) rows; a2: FP32 [R][H]
+// scratch (SiLU).
 bool enc_stream(const Shape& s);
 void launch_enc_bwd_stream(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
                            const float* dout, const EncBwdOut& o, float* a2, hipStream_t st);
@@ -236,16 +232,16 @@ struct VecSeg {
   int len;
   float* dst;
 };
+// Fixed-order two-stage sums over the rows of partial matrices: 32 equal groups
+// of rows (fewer rows: one each), even and odd places of a group apart, then the
+// groups in order.  The result depends on the row count only.
 // dst[i * dst_stride + k] = sum over g < G of partial[g * row + src + i *
 // src_stride + k] for i < runs, k < inner.
 void launch_vec_reduce_strided(const float* partial, int G, int row, int src, int runs, int inner, int src_stride,
                                float* dst, int dst_stride, float* tmp, hipStream_t st);
 
-// A batch of the same fixed-order two-stage reductions, run as two launches
-// in all: job j sets dst[m * ldd + n] = sum over r < rows of
-// src[r * stride + m * N + n] (m < M_valid, n < N), with the split points
-// and summation order of the single reductions above, so each result is
-// bitwise the one a single reduction gives.
+// A batch of such sums in two launches in all: job j sets dst[m * ldd + n] =
+// sum over r < rows of src[r * stride + m * N + n] (m < M_valid, n < N).
 struct RedJob {
   const float* src;
   float* dst;
@@ -260,7 +256,7 @@ struct RedBatch {
   int first1[kMaxRedJobs], first2[kMaxRedJobs];
   RedJob job[kMaxRedJobs];
   void add(const float* src, int rows, int stride, int M_valid, int N, float* dst, int ldd);
-  // the segments of a per-workgroup partial row [G][row] (launch_vec_reduce)
+  // the segments of a per-workgroup partial row [G][row]
   void add_vec(const float* partial, int G, int row, const VecSeg* segs, int n_seg);
 };
 void launch_reduce_batch(const RedBatch& b, float* tmp, hipStream_t st);

@@ -1,7 +1,6 @@
-// Backward kernels: hand-written adjoints of the processor, encoders and
-// decoder.  Every layer is recomputed from its checkpoint (h^l, e^l, m^l)
-// inside the kernel (activation checkpointing), so only layer inputs are kept
-// between forward and backward.
+// Backward kernels on row tiles: the edge adjoint that recomputes its layer from
+// the checkpoint (h^l, e^l), the sender sums, the lowest layer's node products,
+// the decoder's adjoint and the BF16 H = 128 node encoder's.
 //
 // Edge adjoint, for v = LN(u), u = W2 z + b2, z = act(a), a = W1 x + b1,
 // x = [h_r ; h_s ; e]:
@@ -576,55 +575,50 @@ __global__ __launch_bounds__(NTHR, H == 128 ? 2 : 1) void k_dec_bwd(BatchView b,
 }
 
 // ---------------------------------------------------------------------------
-// Encoder adjoint: y = LN(W3 act(W2 act(W1 x + b1) + b2) + b3).  dW1
-// (H x in) is accumulated per workgroup since in <= 8.  dW3 and dW2 are
-// either accumulated per workgroup on MFMA as well (FE: BF16, H = 128 --
-// du3 and da2 straight from the accumulators, z2 and z1 read transposed from
-// their LDS tiles, W2 and W3 resident in LDS and read transposed for the
-// adjoint products; partials go to o.wpart), or du3, z2, da2, z1 are
-// written out for separate weight-gradient products.
+// Node encoder adjoint, BF16, H = 128: y = LN(W3 act(W2 act(W1 x + b1) + b2) + b3).
+// dW3 and dW2 are accumulated per workgroup on MFMA -- du3 and da2 straight
+// from the accumulators, z2 and z1 read transposed from their LDS tiles, W2 and
+// W3 resident in LDS and read transposed for the adjoint products; partials go
+// to o.wpart.  dW1 (H x in) too where in <= 8.
 // ---------------------------------------------------------------------------
 bool enc_bwd_fuses_wgrad(const Shape& s) { return s.prec == 1 && s.H == 128; }
 
 // KIN: input slots per row, 8 or 32; with 32 input slots the input layer's dW1 is left to
 // a separate product over o.da1 (its FP32 adjoint, written here).
-template <typename T, int H, int MT, int ACT, int KIN>
+template <int MT, int ACT, int KIN>
 __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w, const float* __restrict__ src, int in_dim,
                                                   const float* __restrict__ dout, EncBwdOut o, float eps) {
+  using T = bf16;
+  constexpr int H = 128;
   using D = BD<T, H>;
-  constexpr bool FE = sizeof(T) == 2 && H == 128;
   constexpr int MB = MT / 16, NB = D::NB;
   constexpr int LDW = H + 8;
   constexpr size_t ZS = (size_t)MT * D::LDH * sizeof(T);
   constexpr size_t FS = (size_t)MT * D::LDF * 4;
-  constexpr size_t WS = FE ? (size_t)H * LDW * 2 : 0;
-  static_assert(!FE || (MB % 2 == 0 && ZS <= FS), "fused weight gradients: k chunks of 32 rows, du3 over the FP32 tile");
+  constexpr size_t WS = (size_t)H * LDW * 2;
+  static_assert(MB % 2 == 0 && ZS <= FS, "k chunks of 32 rows, du3 over the FP32 tile");
   __shared__ __align__(16) unsigned char smem[2 * ZS + FS + MT * KIN * 4 + 2 * NWAVE * MT * 4 + 2 * WS];
   T* zs = (T*)smem;
   T* z2s = (T*)(smem + ZS);
   float* ft = (float*)(smem + 2 * ZS);
-  T* du3s = (T*)ft;  // FE: du3 once the FP32 tile is dead
+  T* du3s = (T*)ft;  // du3 once the FP32 tile is dead
   float* xin = (float*)(smem + 2 * ZS + FS);
   float* red = xin + MT * KIN;  // [2][NWAVE][MT]
-  bf16* W2s = (bf16*)(red + 2 * NWAVE * MT);  // FE: W2 [out][in]
-  bf16* W3s = W2s + (FE ? H * LDW : 0);       // FE: W3 [out][in]
+  bf16* W2s = (bf16*)(red + 2 * NWAVE * MT);  // W2 [out][in]
+  bf16* W3s = W2s + H * LDW;                  // W3 [out][in]
   const T* W2 = (const T*)w.W2;
   const T* W3 = (const T*)w.W3;
-  const T* W2T = (const T*)w.W2T;
-  const T* W3T = (const T*)w.W3T;
   const int n0 = wave_id() * D::CPW;
   const int li = lane_id() & 15, lg = lane_id() >> 4;
   double cb1[NB] = {}, cb2[NB] = {}, cb3[NB] = {}, cg[NB] = {}, cbt[NB] = {};
   double cw1[NB][KIN == 8 ? 8 : 1] = {};
   f32x4 accW2[NB][H / 16], accW3[NB][H / 16];
-  if constexpr (FE) {
-    zero_acc(accW2);
-    zero_acc(accW3);
-    for (int c = threadIdx.x; c < H * (H / 8); c += NTHR) {
-      const int r = c / (H / 8), q = c - r * (H / 8);
-      *(uint4*)(W2s + r * LDW + 8 * q) = *(const uint4*)(W2 + (size_t)r * H + 8 * q);
-      *(uint4*)(W3s + r * LDW + 8 * q) = *(const uint4*)(W3 + (size_t)r * H + 8 * q);
-    }
+  zero_acc(accW2);
+  zero_acc(accW3);
+  for (int c = threadIdx.x; c < H * (H / 8); c += NTHR) {
+    const int r = c / (H / 8), q = c - r * (H / 8);
+    *(uint4*)(W2s + r * LDW + 8 * q) = *(const uint4*)(W2 + (size_t)r * H + 8 * q);
+    *(uint4*)(W3s + r * LDW + 8 * q) = *(const uint4*)(W3 + (size_t)r * H + 8 * q);
   }
   const int n_tiles = (rows + MT - 1) / MT;
 
@@ -689,13 +683,9 @@ __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w,
     acc_to_lds<T, MB, NB, D::LDH>(x, zs, n0);
     lds_sync();
     zero_acc(a2);
-    if constexpr (FE) {
-      wave_gemm_lds<MB, NB, H, D::LDH>(a2, (const bf16*)zs, [&](int k, int nb) {
-        return *(const bf16x8*)(W2s + (n0 + 16 * nb + li) * LDW + k + 8 * lg);
-      });
-    } else {
-      wave_gemm<T, MB, NB, H, D::LDH>(a2, zs, W2, H, n0);
-    }
+    wave_gemm_lds<MB, NB, H, D::LDH>(a2, (const bf16*)zs, [&](int k, int nb) {
+      return *(const bf16x8*)(W2s + (n0 + 16 * nb + li) * LDW + k + 8 * lg);
+    });
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -710,13 +700,9 @@ __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w,
     acc_to_lds<T, MB, NB, D::LDH>(x, z2s, n0);
     lds_sync();
     zero_acc(x);
-    if constexpr (FE) {
-      wave_gemm_lds<MB, NB, H, D::LDH>(x, (const bf16*)z2s, [&](int k, int nb) {
-        return *(const bf16x8*)(W3s + (n0 + 16 * nb + li) * LDW + k + 8 * lg);
-      });
-    } else {
-      wave_gemm<T, MB, NB, H, D::LDH>(x, z2s, W3, H, n0);
-    }
+    wave_gemm_lds<MB, NB, H, D::LDH>(x, (const bf16*)z2s, [&](int k, int nb) {
+      return *(const bf16x8*)(W3s + (n0 + 16 * nb + li) * LDW + k + 8 * lg);
+    });
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -728,10 +714,6 @@ __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w,
     float inv[MB][4];
     ln_normalize<MB, NB, MT, H>(x, red, eps, inv);
     f32_rows_to_lds<H, D::LDF, MT>(ft, nr, [&](int i, int q) { return *(const float4*)(dout + (size_t)(row0 + i) * H + 4 * q); });
-    if constexpr (!FE) {
-      lds_rows_to_global<T, D::LDH>(zs, nr, H, (T*)o.z1 + (size_t)row0 * H, H, [](int i) { return i; });
-      lds_rows_to_global<T, D::LDH>(z2s, nr, H, (T*)o.z2 + (size_t)row0 * H, H, [](int i) { return i; });
-    }
     lds_sync();
     f32x4 g[MB][NB];
 #pragma unroll
@@ -743,19 +725,12 @@ __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w,
     ln_backward<MB, NB, MT, H>(x, g, inv, w.gamma, n0, red, cg, cbt);  // barriers inside: ft is dead after
     col_accumulate(g, cb3);
     zero_acc(x);
-    if constexpr (FE) {
-      wave_wgrad<MB, NB, H, D::LDH>(accW3, g, (const bf16*)z2s);  // dW3 += du3^T z2
-      acc_to_lds<T, MB, NB, D::LDH>(g, du3s, n0);
-      lds_sync();
-      wave_gemm_lds<MB, NB, H, D::LDH>(x, (const bf16*)du3s, [&](int k, int nb) {
-        return lds_bfrag_tr(W3s, LDW, k + 8 * lg, n0 + 16 * nb, 4);
-      });
-    } else {
-      acc_to_lds<T, MB, NB, D::LDH>(g, zs, n0);
-      lds_sync();
-      lds_rows_to_global<T, D::LDH>(zs, nr, H, (T*)o.du3 + (size_t)row0 * H, H, [](int i) { return i; });
-      wave_gemm<T, MB, NB, H, D::LDH>(x, zs, W3T, H, n0);
-    }
+    wave_wgrad<MB, NB, H, D::LDH>(accW3, g, (const bf16*)z2s);  // dW3 += du3^T z2
+    acc_to_lds<T, MB, NB, D::LDH>(g, du3s, n0);
+    lds_sync();
+    wave_gemm_lds<MB, NB, H, D::LDH>(x, (const bf16*)du3s, [&](int k, int nb) {
+      return lds_bfrag_tr(W3s, LDW, k + 8 * lg, n0 + 16 * nb, 4);
+    });
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -763,19 +738,14 @@ __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w,
 #pragma unroll
         for (int r = 0; r < 4; ++r) x[mb][nb][r] *= act_d<ACT>(a2[mb][nb][r]);
     col_accumulate(x, cb2);
-    if constexpr (FE) wave_wgrad<MB, NB, H, D::LDH>(accW2, x, (const bf16*)zs);  // dW2 += da2^T z1
+    wave_wgrad<MB, NB, H, D::LDH>(accW2, x, (const bf16*)zs);  // dW2 += da2^T z1
     lds_sync();
     acc_to_lds<T, MB, NB, D::LDH>(x, z2s, n0);
     lds_sync();
     zero_acc(x);
-    if constexpr (FE) {
-      wave_gemm_lds<MB, NB, H, D::LDH>(x, (const bf16*)z2s, [&](int k, int nb) {
-        return lds_bfrag_tr(W2s, LDW, k + 8 * lg, n0 + 16 * nb, 4);
-      });
-    } else {
-      lds_rows_to_global<T, D::LDH>(z2s, nr, H, (T*)o.da2 + (size_t)row0 * H, H, [](int i) { return i; });
-      wave_gemm<T, MB, NB, H, D::LDH>(x, z2s, W2T, H, n0);
-    }
+    wave_gemm_lds<MB, NB, H, D::LDH>(x, (const bf16*)z2s, [&](int k, int nb) {
+      return lds_bfrag_tr(W2s, LDW, k + 8 * lg, n0 + 16 * nb, 4);
+    });
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -820,20 +790,18 @@ __global__ __launch_bounds__(NTHR) void k_enc_bwd(int rows, BatchView b, MlpW w,
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int k = 0; k < 8; ++k) p[5 * H + acc_col(n0, nb) * 8 + k] = (float)cw1[nb][k];
-  if constexpr (FE) {
-    float* q2 = o.wpart + (size_t)blockIdx.x * 2 * H * H;
-    float* q3 = q2 + H * H;
+  float* q2 = o.wpart + (size_t)blockIdx.x * 2 * H * H;
+  float* q3 = q2 + H * H;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int jb = 0; jb < H / 16; ++jb)
+    for (int jb = 0; jb < H / 16; ++jb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = n0 + nb * 16 + lg * 4 + r, n = jb * 16 + li;
-          q2[m * H + n] = accW2[nb][jb][r];
-          q3[m * H + n] = accW3[nb][jb][r];
-        }
-  }
+      for (int r = 0; r < 4; ++r) {
+        const int m = n0 + nb * 16 + lg * 4 + r, n = jb * 16 + li;
+        q2[m * H + n] = accW2[nb][jb][r];
+        q3[m * H + n] = accW3[nb][jb][r];
+      }
 }
 
 // ---------------------------------------------------------------------------
@@ -975,18 +943,17 @@ void launch_enc_node_bwd(const Shape& s, const BatchView& b, const MlpW& w, cons
     launch_enc_bwd_stream(s, 0, b.n, b.gid, w, node_in, in_dim, dh0, o, a2, st);
     return;
   }
-  XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
-    if constexpr (sizeof(T) == 2 && H == 128) {
-      if (in_dim <= 8)
-        k_enc_bwd<T, H, MT, ACT, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
-      else if (o.da1)
-        k_enc_bwd<T, H, MT, ACT, 32><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
-      else
-        g_config_error = 1;
-    } else {
-      g_config_error = 1;
-    }
-  }))));
+  if (in_dim > 8 && !o.da1) {
+    g_config_error = 1;
+    return;
+  }
+  constexpr int H = 128;
+  XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT(s.mt_node, {
+    if (in_dim <= 8)
+      k_enc_bwd<MT, ACT, 8><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
+    else
+      k_enc_bwd<MT, ACT, 32><<<s.grid, NTHR, 0, st>>>(b.n, b, w, node_in, in_dim, dh0, o, s.eps);
+  }));
 }
 
 void launch_enc_edge_bwd(const Shape& s, const BatchView& b, const MlpW& w, const float* xe, const float* de0,

@@ -1,8 +1,8 @@
-// Forward kernels: node/edge encoders, the fused edge processor, the node
-// processor and the decoder.  All are persistent-grid kernels over row tiles
-// (see TileSched); each tile is staged in LDS, multiplied on MFMA with FP32
-// accumulation, and post-processed (bias, activation, LayerNorm, residual)
-// in registers before a coalesced write.
+// Forward kernels on row tiles: the split form of the edge processor with its
+// node projections, the edge features and the decoder.  Persistent grids (see
+// TileSched); each tile is staged in LDS, multiplied on MFMA with FP32
+// accumulation, and post-processed (bias, activation, LayerNorm, residual) in
+// registers before a coalesced write.
 #include <type_traits>
 
 #include "common.hpp"

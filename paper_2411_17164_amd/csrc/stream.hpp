@@ -154,11 +154,6 @@ __device__ __forceinline__ void stream_gemm(const WStream<NW, S, StreamDims<T, H
     ws.end(s + c, s0, s1);
   }
 }
-template <int N>
-__device__ __forceinline__ void zero_blocks(f32x4 (&x)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-}
 // a product of one operand: x = W xs, slabs [s0, s0 + SP)
 template <typename T, int H, int NW, int S, int SLOTS>
 __device__ __forceinline__ void stream_product(const WStream<NW, S, StreamDims<T, H>::FR, SLOTS>& ws, int s0,
