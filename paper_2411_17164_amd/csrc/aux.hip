@@ -29,7 +29,8 @@ int g_config_error = 0;
 // stages transposed on their way into LDS (eight lanes to a bank) and two
 // reductions each: 2,000 nodes, FP32: 441 -> 155 us; 50k nodes, FP32: 2.54 -> 1.78
 // ms; 100k, BF16, H = 256: 3.26 -> 2.5; 50k, H = 512: 4.07 -> 2.9; 400k, H = 128
-// (bound by reading its operands): 5.9 -> 4.4.  Loads under a condition, or
+// (bound by reading its operands, 5.5 TB/s): 5.9 -> 4.4.  In FP32 MFMA is busy for
+// 82% of the cycles that a CU is, but a launch's CUs end unevenly.  Loads under a condition, or
 // behind a possible row index, each waited for the ones before: 20% slower.
 // A chunk can be 20,000 rows, more than one running FP32 sum takes well: the
 // FP32 form adds up runs of 64 MFMA steps (256 rows) in a second set of

@@ -104,10 +104,10 @@ struct Vecs128 {
 // each wave taking 16 edges of its own range at a time through both products, the LayerNorm and the receiver sums, and the next 16 edges'
 // rows in flight meanwhile.  Both weights stay in LDS (128 KiB, one workgroup
 // of eight waves per CU), so nothing but edge data crosses the memory system
-// and no barrier follows the staging.  It is bound by HBM: on 3.55M edges and
-// 400k nodes (keeping z) 968 us, 3.9 GB algorithmic, 4.0 TB/s where a large
-// copy reaches 4.9; the workgroup-tile kernel it replaces took 1,818 us, most
-// of it waiting at seven barriers per 64 edges.  32 edges per step need 100
+// and no barrier follows the staging.  It is bound by HBM: on 3.54M edges and
+// 400k nodes (keeping z) 970 to 990 us, 3.96 GB by counters (3.93 algorithmic),
+// 4.0 TB/s where a large copy reaches 4.9; the workgroup-tile kernel it replaces
+// took 1,818 us, most of it waiting at seven barriers per 64 edges.  32 edges per step need 100
 // more registers than there are.  Every sum is taken in that kernel's order,
 // and the results are the same bits.
 // ---------------------------------------------------------------------------
@@ -263,11 +263,11 @@ void launch_edge_fwd_chain(const Shape& s, const BatchView& b, const MlpW& w, co
 // e-block of W1^T stay in LDS (96 KiB); z comes a step ahead, de' and dm_r
 // during u and its statistics.  Column sums over edges (db2, dgamma, dbeta)
 // are taken across the 16 lanes of a DPP row; db1 is the total of the receiver
-// sums.  On 3.55M edges and 400k nodes 1,730 us (6.8 GB algorithmic, 3.9 TB/s;
-// a large copy reaches 4.9); the 64-row workgroup-tile kernel it replaces took
-// 3,345 us, and its 32-row form 2,430 us plus a product of 300 us for the
-// e-block.  Bound by HBM and, between its barriers, by LDS reads of the weight
-// fragments (1 KiB per MFMA).  Sums keep that kernel's order: da, de and S_r
+// sums.  On 3.54M edges and 400k nodes 1,740 us; the 64-row workgroup-tile kernel
+// it replaces took 3,345 us, and its 32-row form 2,430 us plus a product of 300 us
+// for the e-block.  Bound by HBM: by counters it moves 8.5 GB at 4.9 TB/s, a large
+// copy's rate.  6.75 GB are algorithmic; de' is read twice (for dv and for de), as
+// it does not fit in the registers between.  Sums keep that kernel's order: da, de and S_r
 // are the same bits.
 struct EdgeBwdChain {
   static constexpr int NW = 8;

@@ -17,10 +17,12 @@ namespace xmgn {
 // kept in registers on their way to LDS (one slab ahead) gave 1,064 us, 400 us
 // of it waiting for them.  On 50k nodes, H = 512, SiLU, 444k edges: 1,844 us
 // (505 TFLOP/s) against 2,477 us in the 64-row K-sliced kernel.  FP32 at
-// H = 128 on 50k nodes, 443k edges: 590 us (98 TFLOP/s, an FP32 library
-// product here reaches 152) against 831 us.  What bounds the BF16 forms now is
-// the weight traffic: every 128 (64) rows read 0.5 (2) MB of fragments
-// from L2 into LDS and each wave reads all of it again from there.
+// H = 128 on 50k nodes, 443k edges: 590 to 610 us (98 TFLOP/s, an FP32 library
+// product here reaches 152) against 831 us.  Every 128 (64) rows bring 0.5 (2) MB
+// of fragments from L2 into LDS, and each wave reads all of it again from there.
+// By counters, of the cycles that a CU is busy: H = 256 30% MFMA, 37% LDS, its
+// waves waiting (slabs, rows, barriers) for 42% of theirs; H = 512 22%, 25% and
+// 41%, with one wave per SIMD to hide it; FP32 73% MFMA.
 // ---------------------------------------------------------------------------
 template <typename T, int H, int W>
 struct EdgeFwdStream : StreamDims<T, H, W> {
@@ -228,9 +230,12 @@ void launch_edge_fwd_stream(const Shape& s, const BatchView& b, const MlpW& w, c
 // groups of 64 features ahead of their use.  On 100k nodes, H = 256, 886k
 // edges: 1,165 us (3.9 GB, 3.3 TB/s) where the 32-row workgroup-tile kernel
 // took 2,717 us; on 50k nodes, H = 512, SiLU, 444k edges: 2,151 us (4.0 GB,
-// 1.9 TB/s) against 5,094 us; FP32, H = 128, 443k edges: 515 us against 789.  H = 256 is bound by HBM and the barriers around
-// its LayerNorm, H = 512 by the 1.5 MB of weight fragments that every 64 rows
-// read.  da, du, de and S_r are the same bits as that kernel's.
+// 1.9 TB/s) against 5,094 us; FP32, H = 128, 443k edges: 515 to 540 us against 789.
+// By counters H = 256 moves 4.9 GB (de' twice) at 4.35 TB/s, near a large copy's
+// 4.9: bound by HBM.  H = 512 moves 6.2 GB (de' twice, and spills of 544 bytes a
+// lane under SiLU) at 3.05 TB/s, its one wave per SIMD waiting for 35% of its
+// cycles; FP32 is busy with MFMA for 61%.  da, du, de and S_r are the same bits as
+// that kernel's.
 // ---------------------------------------------------------------------------
 template <typename T, int H, int W>
 struct EdgeBwdStream : StreamDims<T, H, W> {

@@ -434,9 +434,9 @@ __global__ __launch_bounds__((StreamDims<T, H, W>::NT), (StreamDims<T, H, W>::NW
 // matrices are streamed: with the tiles they do not fit in LDS.  3.55M edges:
 // 3,556 -> 1,615 us against the workgroup-tile kernel with the same fusion,
 // which passed every intermediate through LDS behind a barrier; its floor is
-// reading dout (1.8 GB, 370 us).  Bound by LDS: the waves' reads of the weight
-// and tile fragments take about 5 of the 15 us of a 128-row step, the sums over
-// rows and the barriers between them most of the rest.
+// reading dout (1.8 GB, 370 us).  Bound by issue and waits: by counters VALU and
+// MFMA instructions issue in 57% of a SIMD's cycles, LDS is active in 31%, and a
+// wave waits (slabs, barriers) for 35% of its own.
 // ---------------------------------------------------------------------------
 template <int ACT>
 __global__ __launch_bounds__(512, 2) void k_enc_edge_bwd_chain(int rows, MlpW w, const float* __restrict__ src,
@@ -717,8 +717,8 @@ static void launch_enc_fwd(const Shape& s, int kind, int R, const int* gid, cons
     constexpr int H = decltype(hh)::value, W = decltype(ww)::value;
     // BF16 at H = 128 runs two workgroups per CU (70 KiB of LDS, 16 waves of 86
     // registers), its weights in LDS for good: 397 us for 3.55M edges (1.0 GB,
-    // 2.5 TB/s; bound by the LDS reads of the fragments) where the
-    // workgroup-tile kernel took 1,088
+    // 2.5 TB/s; by counters LDS is active in 61% of a CU's cycles, and VALU and
+    // MFMA issue fill the SIMDs') where the workgroup-tile kernel took 1,088
     const int grid = s.prec == 1 && s.H == 128 ? std::max(1, std::min(512, (R + 47) / 48)) : edge_stream_grid(s, R);
     k_enc_fwd_stream<T, H, W, decltype(act)::value, decltype(kin)::value, decltype(kd)::value>
         <<<grid, StreamDims<T, H, W>::NT, 0, st>>>(R, gid, w, src, in_dim, (T*)out, s.eps);
