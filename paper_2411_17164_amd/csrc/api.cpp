@@ -548,7 +548,7 @@ struct xmgn_ctx {
   std::vector<hipEvent_t> sev;       // ordering events between st and cs
   size_t sev_used = 0;
   // backward workspace
-  DBuf dhA, dhMid, dm, Sr, Ss, deA, deB, fa, fb, fc, fd, na, nb, nc, dy, part, wpart, wfused, redtmp, lossp;
+  DBuf dhA, dhMid, dm, Sr, Ss, deA, deB, fa, fb, fc, fd, dy, part, wpart, wfused, redtmp, lossp;
   DBuf part_e, wfused_e;  // the edge adjoint's partials, reduced with the node adjoint's at the end of a layer
   DBuf xe;    // edge features of the forward [E][4]
   DBuf optp;  // optimizer: per-workgroup squared-norm partials (FP64)
@@ -757,7 +757,7 @@ extern "C" xmgn_status xmgn_ctx_memory(const xmgn_ctx* c, int64_t* bytes) {
   int64_t t = 0;
   for (const auto& P : c->plans) t += (int64_t)P->ints.bytes;
   const DBuf* bufs[] = {&c->jobs_dev, &c->blob, &c->h, &c->e, &c->m, &c->dhA, &c->dhMid,
-                        &c->dm, &c->Sr, &c->Ss, &c->deA, &c->deB, &c->fa, &c->fb, &c->fc, &c->fd, &c->na, &c->nb, &c->nc,
+                        &c->dm, &c->Sr, &c->Ss, &c->deA, &c->deB, &c->fa, &c->fb, &c->fc, &c->fd,
                         &c->dy, &c->part, &c->wpart, &c->wfused, &c->redtmp, &c->lossp, &c->xe, &c->zt,
                         &c->part_e, &c->wfused_e, &c->proj,
                         &c->at, &c->optp};
@@ -1361,12 +1361,14 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
     if (xmgn_status r = p->ensure(n * H * 4, st)) return r;
   for (DBuf* p : {&c->deA, &c->deB})
     if (xmgn_status r = p->ensure(E * H * 4, st)) return r;
-  for (DBuf* p : {&c->fa, &c->fb, &c->fc, &c->fd})
+  for (DBuf* p : {&c->fa, &c->fb, &c->fc})
     if (xmgn_status r = p->ensure(rows * H * ts, st)) return r;
+  // a layer's node adjoint keeps da, du and z to the layer's weight gradients in
+  // fd, which only the decoder and the encoders use besides
+  if (xmgn_status r = c->fd.ensure(std::max(rows, 3 * n) * H * ts, st)) return r;
+  char* const nf[3] = {c->fd.as<char>(), c->fd.as<char>() + n * H * ts, c->fd.as<char>() + 2 * n * H * ts};
   if (xmgn_status r = c->dy.ensure((size_t)c->cur->n_inner * 16 * 4, st)) return r;
   if (xmgn_status r = c->part.ensure((size_t)std::max(G, 256) * 13 * H * 4, st)) return r;
-  for (DBuf* p : {&c->na, &c->nb, &c->nc})  // the node adjoint's da, du, z, kept to the layer's weight gradients
-    if (xmgn_status r = p->ensure(n * H * ts, st)) return r;
   if (xmgn_status r = c->wpart.ensure(wgrad_partial_floats(s) * 4, st)) return r;
   // the edge adjoint may accumulate its dense weight gradients itself
   // the edge adjoint runs on its own tiling of the batch's edges
@@ -1426,7 +1428,7 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
       if (xmgn_status r = tape_in(c, d, st, l - 1, true, em, em, &back[l - 1])) return r;
     }
     const MlpW wn = weights(c, d, params, 3 + 2 * l, 3, l);
-    NodeBwdOut no{c->dhMid.as<float>(), c->dm.as<float>(), c->na.p, c->nb.p, c->nc.p, part};
+    NodeBwdOut no{c->dhMid.as<float>(), c->dm.as<float>(), nf[0], nf[1], nf[2], part};
     {
       KT("node_bwd");
       if (l == L - 1)  // below the decoder
@@ -1443,11 +1445,11 @@ extern "C" xmgn_status xmgn_backward(xmgn_ctx* c, const xmgn_model_desc* d, cons
                     {3 * (int)H, (int)H, P(3, l, 5)}};
     rb.add_vec(part, edge_stream_grid(s, (int)n), 4 * (int)H, ns, 4);
     // dW1 = sum da [h ; m]^T (two products); dW2 = sum du z^T
-    wb.add(wop(c->na.p, 0, (int)H, 0, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 0),
+    wb.add(wop(nf[0], 0, (int)H, 0, hl(l), 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 0),
            2 * (int)H));
-    wb.add(wop(c->na.p, 0, (int)H, 0, mslot(c, d, l), 1, (int)H, 0, nullptr, (int)n, (int)H, (int)H,
+    wb.add(wop(nf[0], 0, (int)H, 0, mslot(c, d, l), 1, (int)H, 0, nullptr, (int)n, (int)H, (int)H,
            P(3, l, 0) + H, 2 * (int)H));
-    wb.add(wop(c->nb.p, 0, (int)H, 0, c->nc.p, 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 2),
+    wb.add(wop(nf[1], 0, (int)H, 0, nf[2], 0, (int)H, 0, nullptr, (int)n, (int)H, (int)H, P(3, l, 2),
            (int)H));
 
     const MlpW we = weights(c, d, params, 2 + 2 * l, 2, l);
