@@ -112,8 +112,8 @@ void xmgn_ctx_destroy(xmgn_ctx* ctx);
  * tiles unless, in the BF16 form, 64 are asked for) and at H = 512 (16-row
  * node tiles; 32-row edge tiles) whatever is asked.  The gathered edge
  * forward, the node processor kernels and the forward encoders have one
- * configuration, whatever is asked; the rows asked for still set the largest
- * in-degree a batch may have.  Changing it invalidates
+ * configuration, whatever is asked (but edge forwards of few edges take the
+ * rows); the rows asked for still set the largest in-degree a batch may have.  Changing it invalidates
  * cached batch plans. */
 xmgn_status xmgn_ctx_set_tiles(xmgn_ctx* ctx, int32_t edge_rows, int32_t node_rows,
                                int32_t grid, int32_t edge_waves);

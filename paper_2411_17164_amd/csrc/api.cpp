@@ -885,6 +885,7 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
   c->blob_elems = 0;
   const int H = d->hidden, L = d->n_layers;
   const bool stream = edge_stream(make_shape(c, d));
+  const bool tiles = row_tiles(make_shape(c, d), 1);  // (their kernels take row-major matrices)
   c->bw.assign(3 + 2 * L, BlockW{});
   for (int b = 0; b < 2; ++b) {
     BlockW& w = c->bw[b];
@@ -893,6 +894,10 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
       add_frag_job(c, poff(d, b, 0, 4), H, 0, 0, H, H);
       w.BS = add_frag_job(c, poff(d, b, 0, 4), H, 0, 1, H, H);
       add_frag_job(c, poff(d, b, 0, 2), H, 0, 1, H, H);
+      if (tiles) {
+        add_job(c, poff(d, b, 0, 2), H, 0, 0, H, H, w.W2);
+        add_job(c, poff(d, b, 0, 4), H, 0, 0, H, H, w.W3);
+      }
       continue;
     }
     w.FS = add_frag_job(c, poff(d, b, 0, 2), H, 0, 0, H, H);
@@ -943,6 +948,10 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
     bs(W2n, H, 0, 1, H);
     bs(W1n, 2 * H, 0, 1, H);
     bs(W1n, 2 * H, H, 1, H);
+    if (tiles) {
+      add_job(c, W1n, 2 * H, 0, 0, H, 2 * H, wn.W1);
+      add_job(c, W2n, H, 0, 0, H, H, wn.W2);
+    }
   }
   BlockW& wd = c->bw[2 + 2 * L];
   add_job(c, poff(d, 4, 0, 0), H, 0, 0, H, H, wd.W1);
@@ -990,6 +999,19 @@ static MlpW weights(const xmgn_ctx* c, const xmgn_model_desc* d, const float* pa
     w.b3 = P(5);
   }
   return w;
+}
+
+// 16-row steps of the longest range of edges among the waves of the streaming
+// kernels (see WaveEdges): shares of the edges, moved on to the next segment start.
+static int wave_steps(const std::vector<int32_t>& row_ptr, int64_t n, int64_t E, int waves) {
+  const int64_t nw = (int64_t)stream_grid((int)E, waves) * waves;
+  int64_t longest = 0, begin = 0, r = 0;
+  for (int64_t w = 1; w <= nw; ++w) {
+    while (r < n && row_ptr[r] < E * w / nw) ++r;
+    longest = std::max(longest, row_ptr[r] - begin);
+    begin = row_ptr[r];
+  }
+  return (int)((longest + 15) / 16);
 }
 
 static xmgn_status ensure_batch(xmgn_ctx* c, const xmgn_partset* ps, const int32_t* part_ids, int32_t n_batch,
@@ -1098,6 +1120,8 @@ static xmgn_status ensure_batch(xmgn_ctx* c, const xmgn_partset* ps, const int32
   o += o & 1;  // the (receiver, edge) pairs are read as 8-byte loads
   V.etiles = up(etiles);
   V.n_etiles = (int)nt;
+  V.steps4 = E <= kMaxTiledEdges ? wave_steps(row_ptr, n, E, 4) : 0;
+  V.steps8 = E <= kMaxTiledEdges ? wave_steps(row_ptr, n, E, 8) : 0;
   V.inner = up(inner);
   V.n_inner = (int)ni;
   B.view_b = V;
@@ -1684,8 +1708,9 @@ extern "C" xmgn_status xmgn_autotune(xmgn_ctx* c, const xmgn_model_desc* d, cons
     return r;
   const std::string key = tune_key(c, d);
   // The split forward takes edge tiles, and the adjoint that recomputes z.  Where
-  // neither runs, edge rows and waves change no kernel, but the rows bound the
-  // in-degree a batch may have: they are not tried, and are set to the most.
+  // neither runs, edge rows and waves change no kernel (but the forward of few
+  // edges, on tiles of the most rows), and the rows bound the in-degree a batch may
+  // have: they are not tried, and are set to the most.
   const bool bwd_tiles = !c->tape_z, tiles = bwd_tiles || c->edge_split;
   const std::vector<int> rows = d->hidden == 128 || (d->hidden == 256 && d->precision == 1) ? std::vector<int>{32, 64}
                                                                                             : std::vector<int>{32};

@@ -175,9 +175,9 @@ bool stream_small(const Shape& s, int rows) { return s.prec == 0 && s.H == 128 &
 // wave's time goes by its 16-row steps, so a few rows on every CU beat full
 // steps on some, and ranges that end on whole segments stay within one step
 // (12,000 edges, FP32, H = 128: 78 us on 94 full workgroups).
+int stream_grid(int rows, int waves) { return std::max(1, std::min(256, (rows + 6 * waves - 1) / (6 * waves))); }
 int edge_stream_grid(const Shape& s, int rows) {
-  const int waves = s.H * (s.prec == 1 ? 2 : 4) <= 512 && !stream_small(s, rows) ? 8 : 4;
-  return std::max(1, std::min(256, (rows + 6 * waves - 1) / (6 * waves)));
+  return stream_grid(rows, s.H * (s.prec == 1 ? 2 : 4) <= 512 && !stream_small(s, rows) ? 8 : 4);
 }
 
 // f(T{}, H, W) with the form's type, width and waves for so many rows

@@ -712,6 +712,10 @@ static void enc_dispatch(const Shape& s, int R, int kind, int in_dim, F f) {
 static void launch_enc_fwd(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
                            void* out, hipStream_t st) {
   if (R == 0) return;
+  if (row_tiles(s, R)) {
+    launch_enc_fwd_tiles(s, kind, R, gid, w, src, in_dim, out, st);
+    return;
+  }
   enc_dispatch(s, R, kind, in_dim, [&](auto t, auto hh, auto ww, auto act, auto kin, auto kd) {
     using T = decltype(t);
     constexpr int H = decltype(hh)::value, W = decltype(ww)::value;

@@ -11,6 +11,8 @@ namespace xmgn {
 // hardware (LDS); the host turns it into XMGN_ERR_UNSUPPORTED.
 extern int g_config_error;
 
+constexpr int kMaxTiledEdges = 1 << 17;  // (see edge_tiles)
+
 // Device view of a batch (disjoint union of partitions).
 struct BatchView {
   int n;                 // nodes
@@ -23,6 +25,8 @@ struct BatchView {
   const int* csc_edge;   // [E] CSR edge of each sender slot
   const int* etiles;     // [n_etiles+1][2] (receiver, edge) bounds of edge tiles
   int n_etiles;
+  int steps4, steps8;    // up to kMaxTiledEdges edges: 16-row steps of the longest range that a wave of the
+                         // streaming kernels takes, with four and with eight waves per workgroup
   const int* inner;      // [n_inner] batch rows of inner nodes
   int n_inner;
 };
@@ -90,9 +94,18 @@ void launch_edge_fwd_chain(const Shape& s, const BatchView& b, const MlpW& w, co
 // Every other form streams its weights (w.FS) through LDS.
 bool edge_stream(const Shape& s);
 bool stream_small(const Shape& s, int rows);     // so few rows that it runs four waves per workgroup
+int stream_grid(int rows, int waves);            // workgroups of so many waves over so many rows
 int edge_stream_grid(const Shape& s, int rows);  // workgroups of a streaming kernel over so many rows
 void launch_edge_fwd_stream(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                             void* e_out, float* m, void* z_out, void* a_out, hipStream_t st);
+// Few rows run on tiles instead (why: at the definitions): the node processor and
+// the encoders (FP32, H = 256), and the gathered edge processor (FP32; BF16, H = 128).
+bool row_tiles(const Shape& s, int rows);
+bool edge_tiles(const Shape& s, const BatchView& b);
+void launch_node_fwd_tiles(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const float* m,
+                           void* h_out, hipStream_t st);
+void launch_enc_fwd_tiles(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
+                          void* out, hipStream_t st);
 // pr = W1_r h + b1, ps = W1_s h for every node (FP32 [n][H] each).
 void launch_node_proj(const Shape& s, const BatchView& b, const MlpW& w, const void* h, float* pr, float* ps,
                       hipStream_t st);

@@ -1,8 +1,9 @@
 // Forward kernels on row tiles: the split form of the edge processor with its
-// node projections, the edge features and the decoder.  Persistent grids (see
-// TileSched); each tile is staged in LDS, multiplied on MFMA with FP32
-// accumulation, and post-processed (bias, activation, LayerNorm, residual) in
-// registers before a coalesced write.
+// node projections, the edge features, the decoder, and the gathered edge processor
+// (BF16 H = 128, FP32), node processor and encoders (FP32 H = 256) of few rows (see
+// edge_tiles and row_tiles).  Persistent grids (see TileSched); each tile is staged in LDS,
+// multiplied on MFMA with FP32 accumulation, and post-processed (bias, activation,
+// LayerNorm, residual) in registers before a coalesced write.
 #include <type_traits>
 
 #include "common.hpp"
@@ -22,22 +23,23 @@ struct Dims {
 };
 
 // ---------------------------------------------------------------------------
-// Fused edge processor, forward (Eq. 1-2), split form:
+// Fused edge processor, forward (Eq. 1-2), on tiles:
 //   x = [h_r ; h_s ; e],  v = LN(W2 act(W1 x + b1) + b2),  e' = e + v,
-//   m_r = sum over the tile-local segment of r of v (or of e'),
-// with W1 x + b1 = W1_e e + (W1_r h_r + b1) + W1_s h_s, the last two read per
-// edge from the FP32 node projections pr and ps (k_node_proj): the value of
+//   m_r = sum over the tile-local segment of r of v (or of e').
+// SPLIT: with W1 x + b1 = W1_e e + (W1_r h_r + b1) + W1_s h_s, the last two read
+// per edge from the FP32 node projections pr and ps (k_node_proj): the value of
 // the gathered form up to the rounding order of the sum.
 // A tile holds whole receiver segments, so m_r is summed in one workgroup in
 // ascending sender order (the CSR order) -- deterministic, no atomics.
 // ---------------------------------------------------------------------------
 // NW waves per workgroup; each wave owns H / NW output columns of every GEMM.
-// The FP32 tile of the segment sums aliases the staging tile and holds one
-// half of the columns at a time.
-template <typename T, int H, int MT, int NW>
-struct EdgeSplitLds {
+// The FP32 tile of the segment sums aliases the staging tile; in the split form,
+// whose staging tile is H wide, it holds one half of the columns at a time.
+template <typename T, int H, int MT, int NW, int SPLIT>
+struct EdgeTileLds {
   using D = Dims<T, H, NW>;
-  static constexpr size_t GS = (size_t)MT * D::LDH * sizeof(T);  // e rows
+  static constexpr int LDX = SPLIT ? D::LDH : D::LD3;  // staged row: e, or [h_r | h_s | e]
+  static constexpr size_t GS = (size_t)MT * LDX * sizeof(T);
   static constexpr int NH = (size_t)MT * D::LDF * 4 > GS ? 2 : 1;
   static constexpr int LDFH = H / NH + 4;
   static constexpr size_t FS = (size_t)MT * LDFH * 4;
@@ -49,14 +51,14 @@ struct EdgeSplitLds {
 // z_out (or NULL): the hidden activation z = act(W1 x + b1) of every edge,
 // kept for the adjoint; a_out (or NULL): its pre-activation a = W1 x + b1
 // (SiLU's derivative needs a).
-template <typename T, int H, int MT, int ACT, int AGG, int NW>
-__global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeSplitLds<T, H, MT, NW>::bytes, NW)) void k_edge_fwd_split(
+template <typename T, int H, int MT, int ACT, int AGG, int NW, int SPLIT>
+__global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeTileLds<T, H, MT, NW, SPLIT>::bytes, NW)) void k_edge_fwd_tile(
     BatchView b, MlpW w, const T* __restrict__ h, const T* __restrict__ e, T* __restrict__ e_out,
     float* __restrict__ m, T* __restrict__ z_out, T* __restrict__ a_out, const float* __restrict__ pr,
     const float* __restrict__ ps, float eps) {
   using D = Dims<T, H, NW>;
-  using L = EdgeSplitLds<T, H, MT, NW>;
-  constexpr int LDX = D::LDH;
+  using L = EdgeTileLds<T, H, MT, NW, SPLIT>;
+  constexpr int LDX = L::LDX, EC = SPLIT ? 0 : 2 * H;  // column of e in a staged row
   constexpr int MB = MT / 16, NB = D::NB;
   constexpr size_t XS = L::XS, ZS = L::ZS;
   constexpr int NH = L::NH, HH = H / NH, LDFH = L::LDFH;
@@ -84,33 +86,44 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeSplitLds<T, H, MT, NW>:
     }
     lds_sync();
     f32x4 acc[MB][NB];
-    gather_tile<T, D::LDH, MT, 1, H, 64 * NW>(
-        xs, ne, [&](int, int i) { return e + (size_t)(e0 + i) * H; }, [](int, int, int, const uint4&) {});
-    // the node blocks of the first product, in the accumulator layout:
-    // acc = P_r[receiver] + P_s[sender], in flight during the barrier
-    f32x4 sv[MB][NB];
+    if constexpr (SPLIT) {
+      gather_tile<T, D::LDH, MT, 1, H, 64 * NW>(
+          xs, ne, [&](int, int i) { return e + (size_t)(e0 + i) * H; }, [](int, int, int, const uint4&) {});
+      // the node blocks of the first product, in the accumulator layout:
+      // acc = P_r[receiver] + P_s[sender], in flight during the barrier
+      f32x4 sv[MB][NB];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = acc_row(mb, r);
-        const float* prow = pr + (size_t)rs[row] * H + n0 + (lane_id() & 15);
-        const float* srow = ps + (size_t)ss[row] * H + n0 + (lane_id() & 15);
+        for (int r = 0; r < 4; ++r) {
+          const int row = acc_row(mb, r);
+          const float* prow = pr + (size_t)rs[row] * H + n0 + (lane_id() & 15);
+          const float* srow = ps + (size_t)ss[row] * H + n0 + (lane_id() & 15);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          acc[mb][nb][r] = prow[16 * nb];
-          sv[mb][nb][r] = srow[16 * nb];
+          for (int nb = 0; nb < NB; ++nb) {
+            acc[mb][nb][r] = prow[16 * nb];
+            sv[mb][nb][r] = srow[16 * nb];
+          }
         }
-      }
-    ip.advance(b, sch, t);  // next tile's indices and the bounds after, in flight from here
-    lds_sync();
+      ip.advance(b, sch, t);  // next tile's indices and the bounds after, in flight from here
+      lds_sync();
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[mb][nb][r] += sv[mb][nb][r];
-    wave_gemm<T, MB, NB, H, D::LDH>(acc, xs, W1 + 2 * H, 3 * H, n0);  // + W1_e e
+          for (int r = 0; r < 4; ++r) acc[mb][nb][r] += sv[mb][nb][r];
+      wave_gemm<T, MB, NB, H, D::LDH>(acc, xs, W1 + 2 * H, 3 * H, n0);  // + W1_e e
+    } else {
+      gather_tile<T, LDX, MT, 3, H, 64 * NW>(
+          xs, ne,
+          [&](int p, int i) { return p == 0 ? h + (size_t)rs[i] * H : p == 1 ? h + (size_t)ss[i] * H : e + (size_t)(e0 + i) * H; },
+          [](int, int, int, const uint4&) {});
+      ip.advance(b, sch, t);
+      lds_sync();
+      zero_acc(acc);
+      wave_gemm<T, MB, NB, 3 * H, LDX>(acc, xs, W1, 3 * H, n0);
+    }
     f32x4 ev[MB][NB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -118,7 +131,10 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeSplitLds<T, H, MT, NW>:
       for (int nb = 0; nb < NB; ++nb) {
         const int c = acc_col(n0, nb);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ev[mb][nb][r] = to_f(xs[acc_row(mb, r) * LDX + c]);  // (b1 is in P_r)
+        for (int r = 0; r < 4; ++r) {
+          if constexpr (!SPLIT) acc[mb][nb][r] += w.b1[c];  // (else in P_r)
+          ev[mb][nb][r] = to_f(xs[acc_row(mb, r) * LDX + EC + c]);
+        }
       }
     if (a_out) {  // uniform: the pre-activation goes out through zs first
       acc_to_lds<T, MB, NB, D::LDH>(acc, zs, n0);
@@ -267,6 +283,167 @@ void launch_edge_feat(const BatchView& b, const float* pos, EdgeNorm en, float* 
 }
 
 // ---------------------------------------------------------------------------
+// Node processor and encoders, forward, FP32 at H = 256, on 32-row tiles whose
+// columns are split over four waves: for few rows (see row_tiles).
+// ---------------------------------------------------------------------------
+template <int ACT>
+__global__ __launch_bounds__(NTHR, 1) void k_node_fwd_tile(int n, MlpW w, const float* __restrict__ h,
+                                                           const float* __restrict__ m, float* __restrict__ h_out,
+                                                           float eps) {
+  using T = float;
+  constexpr int H = 256, MT = 32;
+  using D = Dims<T, H>;
+  constexpr int MB = MT / 16, NB = D::NB;
+  constexpr size_t XS = (size_t)MT * D::LD2 * sizeof(T);
+  constexpr size_t ZS = (size_t)MT * D::LDH * sizeof(T);
+  __shared__ __align__(16) unsigned char smem[XS + ZS + 2 * NWAVE * MT * 4];
+  T* xs = (T*)smem;
+  T* zs = (T*)(smem + XS);
+  float* red = (float*)(smem + XS + ZS);
+  const int n0 = wave_id() * D::CPW;
+  TileSched sch((n + MT - 1) / MT);
+  for (int t = sch.begin; t < sch.end; t += sch.step) {
+    const int row0 = t * MT, nr = min(MT, n - row0);
+    global_rows_to_lds<T, D::LD2, MT, H>(xs, nr, 0, [&](int i) { return h + (size_t)(row0 + i) * H; });
+    global_f32_rows_to_lds<T, D::LD2, MT, H>(xs, nr, H, [&](int i) { return m + (size_t)(row0 + i) * H; });
+    lds_sync();
+    f32x4 acc[MB][NB], hv[MB][NB];
+    zero_acc(acc);
+    wave_gemm<T, MB, NB, 2 * H, D::LD2>(acc, xs, (const T*)w.W1, 2 * H, n0);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int c = acc_col(n0, nb);
+        const float bb = w.b1[c];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          acc[mb][nb][r] = act_f<ACT>(acc[mb][nb][r] + bb);
+          hv[mb][nb][r] = xs[acc_row(mb, r) * D::LD2 + c];
+        }
+      }
+    acc_to_lds<T, MB, NB, D::LDH>(acc, zs, n0);
+    lds_sync();
+    zero_acc(acc);
+    wave_gemm<T, MB, NB, H, D::LDH>(acc, zs, (const T*)w.W2, H, n0);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const float bb = w.b2[acc_col(n0, nb)];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mb][nb][r] += bb;
+      }
+    float inv[MB][4];
+    ln_normalize<MB, NB, MT, H>(acc, red, eps, inv);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int c = acc_col(n0, nb);
+        const float g = w.gamma[c], be = w.beta[c];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          zs[acc_row(mb, r) * D::LDH + c] = __builtin_fmaf(g, acc[mb][nb][r], hv[mb][nb][r]) + be;
+      }
+    lds_sync();
+    lds_rows_to_global<T, D::LDH>(zs, nr, H, h_out + (size_t)row0 * H, H, [](int i) { return i; });
+    lds_sync();
+  }
+}
+
+// KIND 0: node inputs src[gid[row]], 1: edge features src[row]; KIN: input slots
+// (8 or 32).
+template <int ACT, int KIND, int KIN>
+__global__ __launch_bounds__(NTHR, 1) void k_enc_fwd_tile(int rows, const int* __restrict__ gid, MlpW w,
+                                                          const float* __restrict__ src, int in_dim,
+                                                          float* __restrict__ out, float eps) {
+  using T = float;
+  constexpr int H = 256, MT = 32;
+  using D = Dims<T, H>;
+  constexpr int MB = MT / 16, NB = D::NB;
+  constexpr size_t ZS = (size_t)MT * D::LDH * sizeof(T);
+  __shared__ __align__(16) unsigned char smem[2 * ZS + MT * KIN * 4 + 2 * NWAVE * MT * 4];
+  T* zs = (T*)smem;
+  T* z2 = (T*)(smem + ZS);
+  float* xin = (float*)(smem + 2 * ZS);
+  float* red = xin + MT * KIN;  // [2][NWAVE][MT]
+  const int n0 = wave_id() * D::CPW;
+  TileSched sch((rows + MT - 1) / MT);
+  for (int t = sch.begin; t < sch.end; t += sch.step) {
+    const int row0 = t * MT, nr = min(MT, rows - row0);
+    for (int task = threadIdx.x; task < MT * KIN; task += NTHR) {
+      const int i = task / KIN, k = task - i * KIN;
+      float v = 0.f;
+      if (i < nr && k < in_dim) v = src[(size_t)(KIND == 0 ? gid[row0 + i] : row0 + i) * in_dim + k];
+      xin[task] = v;
+    }
+    lds_sync();
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int c = acc_col(n0, nb);
+      const float bb = w.b1[c];
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mb][nb][r] = bb;
+#pragma unroll 4
+      for (int k = 0; k < in_dim; ++k) {
+        const float wk = w.W1f[c * in_dim + k];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            acc[mb][nb][r] = __builtin_fmaf(wk, xin[acc_row(mb, r) * KIN + k], acc[mb][nb][r]);
+      }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mb][nb][r] = act_f<ACT>(acc[mb][nb][r]);
+    }
+    acc_to_lds<T, MB, NB, D::LDH>(acc, zs, n0);
+    lds_sync();
+    zero_acc(acc);
+    wave_gemm<T, MB, NB, H, D::LDH>(acc, zs, (const T*)w.W2, H, n0);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const float bb = w.b2[acc_col(n0, nb)];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mb][nb][r] = act_f<ACT>(acc[mb][nb][r] + bb);
+      }
+    acc_to_lds<T, MB, NB, D::LDH>(acc, z2, n0);
+    lds_sync();
+    zero_acc(acc);
+    wave_gemm<T, MB, NB, H, D::LDH>(acc, z2, (const T*)w.W3, H, n0);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const float bb = w.b3[acc_col(n0, nb)];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mb][nb][r] += bb;
+      }
+    float inv[MB][4];
+    ln_normalize<MB, NB, MT, H>(acc, red, eps, inv);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int c = acc_col(n0, nb);
+        const float g = w.gamma[c], be = w.beta[c];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) zs[acc_row(mb, r) * D::LDH + c] = __builtin_fmaf(g, acc[mb][nb][r], be);
+      }
+    lds_sync();
+    lds_rows_to_global<T, D::LDH>(zs, nr, H, out + (size_t)row0 * H, H, [](int i) { return i; });
+    lds_sync();
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Decoder: y = W3 act(W2 act(W1 h + b1) + b2) + b3 on the batch's inner rows,
 // written to out[gid][0:out_dim].  The last layer (out_dim <= 16) is FMA.
 // ---------------------------------------------------------------------------
@@ -389,22 +566,62 @@ constexpr bool edge_fits() {
              (size_t)MT * 4 * 8 <= 160 * 1024;
 }
 
+constexpr int kFewGrid = 1024;  // workgroups of the forms for few rows, whatever grid is asked for
+
 template <int NW>
-static void edge_split_nw(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e, void* e_out,
-                        float* m, void* z_out, void* a_out, const float* pr, const float* ps, hipStream_t st) {
+static void edge_tile_nw(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e, void* e_out,
+                         float* m, void* z_out, void* a_out, const float* pr, const float* ps, hipStream_t st) {
+  const int grid = pr ? s.grid : kFewGrid;
   XMGN_DISPATCH_T(s.prec, XMGN_DISPATCH_H(s.H, XMGN_DISPATCH_ACT(s.act, XMGN_DISPATCH_MT_EDGE(s.mt_edge, {
     if constexpr (edge_fits<T, H, MT>()) {
-      auto go = [&](auto agg) {
-        k_edge_fwd_split<T, H, MT, ACT, decltype(agg)::value, NW><<<s.grid, 64 * NW, 0, st>>>(
+      if (s.mt_edge != MT) {  // (the plan's tiles are the kernel's)
+        g_config_error = 1;
+        return;
+      }
+      auto go = [&](auto agg, auto split) {
+        k_edge_fwd_tile<T, H, MT, ACT, decltype(agg)::value, NW, decltype(split)::value><<<grid, 64 * NW, 0, st>>>(
             b, w, (const T*)h, (const T*)e, (T*)e_out, m, (T*)z_out, (T*)a_out, pr, ps, s.eps);
       };
       using I0 = std::integral_constant<int, 0>;
       using I1 = std::integral_constant<int, 1>;
-      if (s.agg) go(I1{}); else go(I0{});
+      if (pr) {
+        if (s.agg) go(I1{}, I1{}); else go(I0{}, I1{});
+      } else if constexpr (NW == 4 && (sizeof(T) == 4 || H == 128)) {  // (edge_tiles)
+        if (s.agg) go(I1{}, I0{}); else go(I0{}, I0{});
+      }
     } else {
       g_config_error = 1;
     }
   }))));
+}
+
+// The streaming kernels give a wave at least 16 whole rows, whose FP32 products
+// take 55 us at H = 256; a 32-row tile splits its columns over four waves.  So
+// while the tiles go round once (256 CUs), they are the faster: on 8,000 rows node
+// processor 43 against 59 us, node encoder 34 against 54, edge encoder (7,800) 33
+// against 45.  On 10,000 rows 74 against 60, 55 against 54 and (9,600) 54 against
+// 45.  The same bits either way.
+bool row_tiles(const Shape& s, int rows) { return s.prec == 0 && s.H == 256 && rows <= 8192; }
+
+// A wave of the chain or streaming kernel takes whole receiver segments, so where
+// in-degrees vary its longest range has a step or two more than its share of the
+// edges; tiles of segments go round all CUs.  In FP32 both times follow from the
+// plan (us, measured on 1- and 3-level graphs of 300 to 14,000 nodes): rounds of the
+// tiles against steps of the longest range.  3 levels, 8,800 edges: H = 128 31
+// against 52, H = 256 95 against 150; 17,700: 56 / 74 and 142 / 220; 124,000: 229 /
+// 182 and 841 / 665.  1 level: 12,000: 32 / 31 and 99 / 84; 30,000: 58 / 77 and 198
+// / 158.  Over kMaxTiledEdges the streaming kernel has been the faster throughout.
+// BF16 at H = 128: the tiles' one round, whose loads overlap two to a CU, takes 15 us
+// and saves staging 128 KiB of weights; the chain 16 to 17 on 1 level, 19 to 21 on 3.
+// Two rounds take 20, the chain 18 to 22.  (At H = 256 and 512 the streaming kernel
+// has been the faster from 100 nodes on.)  The same bits either way.
+bool edge_tiles(const Shape& s, const BatchView& b) {
+  if (b.E > kMaxTiledEdges || (s.prec == 1 && s.H != 128)) return false;
+  const int rows = 256 * (s.H == 128 ? 64 : 32);  // of one round
+  const int rounds = (int)(((long long)b.n_etiles * s.mt_edge + rows - 1) / rows);
+  if (s.prec == 1) return rounds <= 1;
+  if (s.H == 256) return 6 + 47 * rounds < 13 + 70 * b.steps4;
+  return 5 + 26 * rounds < (stream_small(s, b.E) ? 12 + 19 * b.steps4 : 10 + 33 * b.steps8);
 }
 
 void launch_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
@@ -414,17 +631,36 @@ void launch_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
   // gathered form: BF16 at H = 128 keeps both weights in LDS beside the waves'
   // buffers (at H = 256 W1 alone takes 384 KiB, in FP32 at H = 128 192), the
   // others stream them
-  if (!pr) {
+  if (!pr && !edge_tiles(s, b)) {
     if (edge_fwd_chain(s))
       launch_edge_fwd_chain(s, b, w, h, e, e_out, m, z_out, a_out, st);
     else
       launch_edge_fwd_stream(s, b, w, h, e, e_out, m, z_out, a_out, st);
     return;
   }
-  if (s.nw_edge == 8)
-    edge_split_nw<8>(s, b, w, h, e, e_out, m, z_out, a_out, pr, ps, st);
+  if (pr && s.nw_edge == 8)
+    edge_tile_nw<8>(s, b, w, h, e, e_out, m, z_out, a_out, pr, ps, st);
   else
-    edge_split_nw<4>(s, b, w, h, e, e_out, m, z_out, a_out, pr, ps, st);
+    edge_tile_nw<4>(s, b, w, h, e, e_out, m, z_out, a_out, pr, ps, st);
+}
+
+void launch_node_fwd_tiles(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const float* m,
+                           void* h_out, hipStream_t st) {
+  XMGN_DISPATCH_ACT(s.act, {
+    k_node_fwd_tile<ACT><<<kFewGrid, NTHR, 0, st>>>(b.n, w, (const float*)h, m, (float*)h_out, s.eps);
+  });
+}
+
+void launch_enc_fwd_tiles(const Shape& s, int kind, int R, const int* gid, const MlpW& w, const float* src, int in_dim,
+                          void* out, hipStream_t st) {
+  XMGN_DISPATCH_ACT(s.act, {
+    if (kind == 1)
+      k_enc_fwd_tile<ACT, 1, 8><<<kFewGrid, NTHR, 0, st>>>(R, gid, w, src, in_dim, (float*)out, s.eps);
+    else if (in_dim <= 8)
+      k_enc_fwd_tile<ACT, 0, 8><<<kFewGrid, NTHR, 0, st>>>(R, gid, w, src, in_dim, (float*)out, s.eps);
+    else
+      k_enc_fwd_tile<ACT, 0, 32><<<kFewGrid, NTHR, 0, st>>>(R, gid, w, src, in_dim, (float*)out, s.eps);
+  });
 }
 
 void launch_node_proj(const Shape& s, const BatchView& b, const MlpW& w, const void* h, float* pr, float* ps,

@@ -371,6 +371,10 @@ static void node_form(const Shape& s, int rows, F f) {
 void launch_node_fwd(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const float* m, void* h_out,
                      hipStream_t st) {
   if (b.n == 0) return;
+  if (row_tiles(s, b.n)) {
+    launch_node_fwd_tiles(s, b, w, h, m, h_out, st);
+    return;
+  }
   node_form(s, b.n, [&](auto t, auto hh, auto ww, auto act) {
     using T = decltype(t);
     constexpr int H = decltype(hh)::value, W = decltype(ww)::value;
