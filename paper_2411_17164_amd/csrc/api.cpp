@@ -885,7 +885,6 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
   c->blob_elems = 0;
   const int H = d->hidden, L = d->n_layers;
   const bool stream = edge_stream(make_shape(c, d));
-  const bool tiles = row_tiles(make_shape(c, d), 1);  // (their kernels take row-major matrices)
   c->bw.assign(3 + 2 * L, BlockW{});
   for (int b = 0; b < 2; ++b) {
     BlockW& w = c->bw[b];
@@ -894,10 +893,6 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
       add_frag_job(c, poff(d, b, 0, 4), H, 0, 0, H, H);
       w.BS = add_frag_job(c, poff(d, b, 0, 4), H, 0, 1, H, H);
       add_frag_job(c, poff(d, b, 0, 2), H, 0, 1, H, H);
-      if (tiles) {
-        add_job(c, poff(d, b, 0, 2), H, 0, 0, H, H, w.W2);
-        add_job(c, poff(d, b, 0, 4), H, 0, 0, H, H, w.W3);
-      }
       continue;
     }
     w.FS = add_frag_job(c, poff(d, b, 0, 2), H, 0, 0, H, H);
@@ -948,10 +943,6 @@ static xmgn_status ensure_wplan(xmgn_ctx* c, const xmgn_model_desc* d, hipStream
     bs(W2n, H, 0, 1, H);
     bs(W1n, 2 * H, 0, 1, H);
     bs(W1n, 2 * H, H, 1, H);
-    if (tiles) {
-      add_job(c, W1n, 2 * H, 0, 0, H, 2 * H, wn.W1);
-      add_job(c, W2n, H, 0, 0, H, H, wn.W2);
-    }
   }
   BlockW& wd = c->bw[2 + 2 * L];
   add_job(c, poff(d, 4, 0, 0), H, 0, 0, H, H, wd.W1);
@@ -987,11 +978,19 @@ static MlpW weights(const xmgn_ctx* c, const xmgn_model_desc* d, const float* pa
     w.b3 = P(5);
     w.gamma = P(6);
     w.beta = P(7);
+    if (row_tiles(make_shape(c, d), 1)) {  // row-major matrices in FP32: the parameters themselves
+      w.W2 = P(2);
+      w.W3 = P(4);
+    }
   } else if (block == 2 || block == 3) {
     w.b1 = P(1);
     w.b2 = P(3);
     w.gamma = P(4);
     w.beta = P(5);
+    if (block == 3 && row_tiles(make_shape(c, d), 1)) {
+      w.W1 = P(0);
+      w.W2 = P(2);
+    }
   } else {
     w.b1 = P(1);
     w.b2 = P(3);

@@ -99,7 +99,7 @@ int edge_stream_grid(const Shape& s, int rows);  // workgroups of a streaming ke
 void launch_edge_fwd_stream(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const void* e,
                             void* e_out, float* m, void* z_out, void* a_out, hipStream_t st);
 // Few rows run on tiles instead (why: at the definitions): the node processor and
-// the encoders (FP32, H = 256), and the gathered edge processor (FP32; BF16, H = 128).
+// the encoders (FP32, H = 256), and the gathered edge processor.
 bool row_tiles(const Shape& s, int rows);
 bool edge_tiles(const Shape& s, const BatchView& b);
 void launch_node_fwd_tiles(const Shape& s, const BatchView& b, const MlpW& w, const void* h, const float* m,

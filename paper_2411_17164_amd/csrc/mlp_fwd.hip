@@ -1,7 +1,7 @@
 // Forward kernels on row tiles: the split form of the edge processor with its
-// node projections, the edge features, the decoder, and the gathered edge processor
-// (BF16 H = 128, FP32), node processor and encoders (FP32 H = 256) of few rows (see
-// edge_tiles and row_tiles).  Persistent grids (see TileSched); each tile is staged in LDS,
+// node projections, the edge features, the decoder, and the gathered edge processor,
+// node processor and encoders (FP32, H = 256) of few rows (see edge_tiles and
+// row_tiles).  Persistent grids (see TileSched); each tile is staged in LDS,
 // multiplied on MFMA with FP32 accumulation, and post-processed (bias, activation,
 // LayerNorm, residual) in registers before a coalesced write.
 #include <type_traits>
@@ -211,6 +211,192 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(EdgeTileLds<T, H, MT, NW, S
     }
     if (e_out) lds_rows_to_global<T, D::LDH>(zs, ne, H, e_out + (size_t)e0 * H, H, [](int i) { return i; });
     lds_sync();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same, gathered, BF16 at H = 512: a 64-row tile of [h_r | h_s | e] does not fit in
+// LDS, so the first product goes over K slices of 64 columns, double-buffered: the
+// next slice's rows and weight fragments are in flight while the current slice's
+// MFMAs run.  After the second product e is staged in the z tile's place; the FP32
+// tile of the segment sums then takes that place, one half of the columns at a time.
+// ---------------------------------------------------------------------------
+struct EdgeFwdWide {
+  static constexpr int H = 512, MT = 64, NW = 8, NT = 64 * NW;
+  static constexpr int KS = 64, LDK = KS + 8;         // slice width, slice row stride
+  static constexpr int NS = 3 * H / KS;               // slices of [h_r ; h_s ; e]
+  static constexpr int LDH = H + 8;
+  static constexpr size_t SL = (size_t)MT * LDK * 2;  // one slice buffer
+  static constexpr size_t ZS = (size_t)MT * LDH * 2;  // z, then e and e', then the FP32 tile
+  static constexpr int FC = H / 2, LDF = FC + 4;      // FP32 tile: half of the columns
+  static_assert((size_t)MT * LDF * 4 <= ZS, "FP32 half tile fits in the z tile");
+  static constexpr size_t bytes = 2 * SL + ZS + 2 * NW * MT * 4 + 2 * MT * 4;
+};
+
+template <int ACT, int AGG>
+__global__ __launch_bounds__(512, 2) void k_edge_fwd_wide(BatchView b, MlpW w, const bf16* __restrict__ h,
+                                                          const bf16* __restrict__ e, bf16* __restrict__ e_out,
+                                                          float* __restrict__ m, bf16* __restrict__ z_out,
+                                                          bf16* __restrict__ a_out, float eps) {
+  using L = EdgeFwdWide;
+  constexpr int H = L::H, MT = L::MT, NW = L::NW, NT = L::NT, KS = L::KS, LDK = L::LDK, NS = L::NS, LDH = L::LDH;
+  constexpr int FC = L::FC, LDF = L::LDF;
+  constexpr int CPW = H / NW, NB = CPW / 16, MB = MT / 16;
+  static_assert(NS % 2 == 0, "slices go in pairs");
+  static_assert(CPW <= FC, "a wave's columns lie in one half");
+  constexpr int CPRS = KS / 8, SLT = MT * CPRS, SIT = SLT / NT;  // 16-byte chunks of a slice
+  static_assert(SLT % NT == 0, "whole steps of the workgroup");
+  __shared__ __align__(16) unsigned char smem[L::bytes];
+  bf16* sl0 = (bf16*)smem;
+  bf16* sl1 = (bf16*)(smem + L::SL);
+  bf16* zs = (bf16*)(smem + 2 * L::SL);
+  float* ft = (float*)zs;
+  float* red = (float*)(smem + 2 * L::SL + L::ZS);
+  int* rs = (int*)(red + 2 * NW * MT);
+  int* ss = rs + MT;
+  const bf16* W1 = (const bf16*)w.W1;
+  const bf16* W2 = (const bf16*)w.W2;
+  const int n0 = wave_id() * CPW;
+
+  TileSched sch(b.n_etiles);
+  EdgeTilePipe ip;
+  ip.start(b, sch);
+  for (int t = sch.begin; t < sch.end; t += sch.step) {
+    const EdgeTileIdx cur = ip.nx;
+    const int r0 = cur.r0, r1 = cur.r1, e0 = cur.e0, ne = cur.ne;
+    if (threadIdx.x < MT) {
+      rs[threadIdx.x] = cur.rv;
+      ss[threadIdx.x] = cur.cv;
+    }
+    lds_sync();
+    uint4 v[SIT];
+    auto load_slice = [&](int sl) {
+      const int p = sl / (H / KS), c0 = (sl % (H / KS)) * KS;
+#pragma unroll
+      for (int k = 0; k < SIT; ++k) {
+        const int c = (int)threadIdx.x + k * NT, i = c / CPRS, q = c - i * CPRS;
+        v[k] = uint4{0u, 0u, 0u, 0u};
+        if (i < ne) {
+          const bf16* row = p == 0 ? h + (size_t)rs[i] * H : p == 1 ? h + (size_t)ss[i] * H : e + (size_t)(e0 + i) * H;
+          v[k] = *(const uint4*)(row + c0 + q * 8);
+        }
+      }
+    };
+    auto store_slice = [&](bf16* buf) {
+#pragma unroll
+      for (int k = 0; k < SIT; ++k) {
+        const int c = (int)threadIdx.x + k * NT, i = c / CPRS, q = c - i * CPRS;
+        *(uint4*)(buf + i * LDK + q * 8) = v[k];
+      }
+    };
+    f32x4 acc[MB][NB];
+    zero_acc(acc);
+    WFrag<bf16, NB, KS> fa, fb;
+    load_slice(0);
+    fa.load(W1, 3 * H, n0);
+    store_slice(sl0);
+    ip.advance(b, sch, t);  // next tile's indices and the bounds after, in flight from here
+#pragma unroll 1
+    for (int sl = 0; sl < NS; sl += 2) {
+      // slice sl from sl0 with fa; slice sl + 1 and its weights in flight
+      load_slice(sl + 1);
+      fb.load(W1 + (sl + 1) * KS, 3 * H, n0);
+      lds_sync();  // slice sl stored by every wave; slice sl - 1's products done with sl1
+      wave_gemm<bf16, MB, NB, KS, LDK>(acc, sl0, fa);
+      store_slice(sl1);
+      // slice sl + 1 from sl1 with fb
+      if (sl + 2 < NS) {
+        load_slice(sl + 2);
+        fa.load(W1 + (sl + 2) * KS, 3 * H, n0);
+      }
+      lds_sync();
+      wave_gemm<bf16, MB, NB, KS, LDK>(acc, sl1, fb);
+      if (sl + 2 < NS) store_slice(sl0);
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const float bb = w.b1[acc_col(n0, nb)];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mb][nb][r] += bb;
+      }
+    if (a_out) {  // uniform: the pre-activation goes out through zs first
+      acc_to_lds<bf16, MB, NB, LDH>(acc, zs, n0);
+      lds_sync();
+      lds_rows_to_global<bf16, LDH>(zs, ne, H, a_out + (size_t)e0 * H, H, [](int i) { return i; });
+      lds_sync();
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mb][nb][r] = act_f<ACT>(acc[mb][nb][r]);
+    acc_to_lds<bf16, MB, NB, LDH>(acc, zs, n0);
+    lds_sync();
+    if (z_out) lds_rows_to_global<bf16, LDH>(zs, ne, H, z_out + (size_t)e0 * H, H, [](int i) { return i; });
+    zero_acc(acc);
+    wave_gemm<bf16, MB, NB, H, LDH>(acc, zs, W2, H, n0);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const float bb = w.b2[acc_col(n0, nb)];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mb][nb][r] += bb;
+      }
+    float inv[MB][4];
+    ln_normalize<MB, NB, MT, H, NW>(acc, red, eps, inv);  // barriers: every wave is done with z
+    // e of the tile's edges, in the z tile's place
+    gather_tile<bf16, LDH, MT, 1, H, NT>(
+        zs, ne, [&](int, int i) { return e + (size_t)(e0 + i) * H; }, [](int, int, int, const uint4&) {});
+    lds_sync();
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int c = acc_col(n0, nb);
+        const float g = w.gamma[c], be = w.beta[c];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = acc_row(mb, r);
+          const float vv = g * acc[mb][nb][r] + be;
+          const float en = to_f(zs[row * LDH + c]) + vv;
+          acc[mb][nb][r] = AGG ? en : vv;  // the summand of m
+          zs[row * LDH + c] = from_f<bf16>(en);
+        }
+      }
+    lds_sync();
+    if (e_out) lds_rows_to_global<bf16, LDH>(zs, ne, H, e_out + (size_t)e0 * H, H, [](int i) { return i; });
+    lds_sync();  // e' is out: the FP32 tile takes its place
+    // m_r: sequential sum over the receiver's edges (ascending sender id), one column half at a time
+    const int nr = r1 - r0;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      if (n0 / FC == hf)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ft[acc_row(mb, r) * LDF + acc_col(n0, nb) - hf * FC] = acc[mb][nb][r];
+      lds_sync();
+      for (int task = threadIdx.x; task < nr * (FC / 4); task += NT) {
+        const int rl = task / (FC / 4), q = task - rl * (FC / 4);
+        const int lo = b.row_ptr[r0 + rl] - e0, hi = b.row_ptr[r0 + rl + 1] - e0;
+        float4 sm = {0.f, 0.f, 0.f, 0.f};
+        for (int i = lo; i < hi; ++i) {
+          const float4 x = *(const float4*)(ft + i * LDF + 4 * q);
+          sm.x += x.x;
+          sm.y += x.y;
+          sm.z += x.z;
+          sm.w += x.w;
+        }
+        *(float4*)(m + (size_t)(r0 + rl) * H + hf * FC + 4 * q) = sm;
+      }
+      lds_sync();
+    }
   }
 }
 
@@ -586,7 +772,7 @@ static void edge_tile_nw(const Shape& s, const BatchView& b, const MlpW& w, cons
       using I1 = std::integral_constant<int, 1>;
       if (pr) {
         if (s.agg) go(I1{}, I1{}); else go(I0{}, I1{});
-      } else if constexpr (NW == 4 && (sizeof(T) == 4 || H == 128)) {  // (edge_tiles)
+      } else if constexpr (NW == 4 && H <= 256) {  // (edge_tiles)
         if (s.agg) go(I1{}, I0{}); else go(I0{}, I0{});
       }
     } else {
@@ -613,10 +799,13 @@ bool row_tiles(const Shape& s, int rows) { return s.prec == 0 && s.H == 256 && r
 // / 158.  Over kMaxTiledEdges the streaming kernel has been the faster throughout.
 // BF16 at H = 128: the tiles' one round, whose loads overlap two to a CU, takes 15 us
 // and saves staging 128 KiB of weights; the chain 16 to 17 on 1 level, 19 to 21 on 3.
-// Two rounds take 20, the chain 18 to 22.  (At H = 256 and 512 the streaming kernel
-// has been the faster from 100 nodes on.)  The same bits either way.
+// Two rounds take 20, the chain 18 to 22.  BF16 at H = 256: one round 24 us (64-row
+// tiles 33), one step of the streaming kernel 24 to 29, two 39 to 45.  At H = 512: one
+// round of 64-row tiles 75 to 79, one step 53 to 60, two 95 to 112.  The same bits either way.
 bool edge_tiles(const Shape& s, const BatchView& b) {
-  if (b.E > kMaxTiledEdges || (s.prec == 1 && s.H != 128)) return false;
+  if (b.E > kMaxTiledEdges) return false;
+  if (s.prec == 1 && s.H == 256) return s.mt_edge <= 64 && b.n_etiles <= 256 && b.steps8 > 1;
+  if (s.prec == 1 && s.H == 512) return s.mt_edge == 64 && b.n_etiles <= 256 && b.steps4 > 1;
   const int rows = 256 * (s.H == 128 ? 64 : 32);  // of one round
   const int rounds = (int)(((long long)b.n_etiles * s.mt_edge + rows - 1) / rows);
   if (s.prec == 1) return rounds <= 1;
@@ -636,6 +825,20 @@ void launch_edge_fwd(const Shape& s, const BatchView& b, const MlpW& w, const vo
       launch_edge_fwd_chain(s, b, w, h, e, e_out, m, z_out, a_out, st);
     else
       launch_edge_fwd_stream(s, b, w, h, e, e_out, m, z_out, a_out, st);
+    return;
+  }
+  if (!pr && s.H == 512) {
+    auto go = [&](auto act, auto agg) {
+      k_edge_fwd_wide<decltype(act)::value, decltype(agg)::value><<<kFewGrid, 512, 0, st>>>(
+          b, w, (const bf16*)h, (const bf16*)e, (bf16*)e_out, m, (bf16*)z_out, (bf16*)a_out, s.eps);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    if (s.act) {
+      if (s.agg) go(I1{}, I1{}); else go(I1{}, I0{});
+    } else {
+      if (s.agg) go(I0{}, I1{}); else go(I0{}, I0{});
+    }
     return;
   }
   if (pr && s.nw_edge == 8)

@@ -1,6 +1,5 @@
-"""Forwards of few rows run on tiles (FP32; BF16 edges at H = 128), larger ones as
-chains and streams: a row's result is the same bits either way, also at the line
-between the two."""
+"""Forwards of few rows run on tiles, larger ones as chains and streams: a row's
+result is the same bits either way, also at the line between the two."""
 from __future__ import annotations
 
 import numpy as np
@@ -44,7 +43,8 @@ def forward(api, recv, send, n, pos, x, hidden, activation, agg, precision="fp32
 
 @pytest.mark.parametrize("agg", ["message", "edge"])
 @pytest.mark.parametrize("activation", ["silu", "relu"])
-@pytest.mark.parametrize("precision,hidden,node_in", [("fp32", 128, 6), ("fp32", 256, 6), ("fp32", 256, 24), ("bf16", 128, 6)])
+@pytest.mark.parametrize("precision,hidden,node_in", [("fp32", 128, 6), ("fp32", 256, 6), ("fp32", 256, 24), ("bf16", 128, 6),
+                                                       ("bf16", 256, 6), ("bf16", 512, 6)])
 @pytest.mark.parametrize("degrees", [[1, 0, 2], [6], [24, 3, 9, 0, 6, 15], [31, 30]])
 def test_copies(api, precision, hidden, node_in, degrees, activation, agg):
     """A graph of 530 nodes alone and as so many disjoint copies (over 2^17 edges and
@@ -78,3 +78,35 @@ def test_line(api, n):
     a = forward(api, recv, send, n, pos[:n].copy(), x[:n].copy(), 256, "silu", "message")
     b = forward(api, recv, send, n + 1, pos, x, 256, "silu", "message")
     assert torch.isfinite(b).all() and torch.equal(a, b[:n])
+
+
+@pytest.mark.parametrize("precision,hidden", [("fp32", 256), ("fp32", 128), ("bf16", 128), ("bf16", 512)])
+@pytest.mark.parametrize("n", [40, 9000])
+def test_params_anywhere(api, precision, hidden, n):
+    """Parameters, inputs and results that begin at any element: the same bits."""
+    rng = np.random.default_rng(n)
+    recv = np.repeat(np.arange(n), 2)
+    send = (recv + rng.integers(1, n, len(recv))) % n
+    G = og.Graph(n, recv, send)
+    pos = rng.standard_normal((n, 3)).astype(np.float32)
+    desc = om.Desc(hidden=hidden, layers=1, node_in=6, activation="silu")
+    model = api.Model(hidden, 1, node_in=6, activation="silu", precision=precision)
+    norm = np.array([[0, 0, 0, 1], [1, 1, 1, 0.5]], dtype=np.float32)
+    params, x = init_params(om.param_entries(desc), 5), rng.standard_normal((n, 6)).astype(np.float32)
+    ps = api.Partset.halo(api.Graph.from_csr(G.row_ptr, G.col), pos, None, 1)
+    got = []
+    for off in (0, 1, 3):
+        def at(a):
+            room = torch.zeros(a.size + 8, device="cuda")
+            room[off:off + a.size] = torch.from_numpy(a.reshape(-1)).cuda()
+            return room[off:off + a.size].view(a.shape)
+        ctx = api.Context(0)
+        p, xd, pd = at(params), at(x), at(pos)
+        out, grad, d_out = at(np.zeros((n, 4), np.float32)), at(np.zeros_like(params)), at(np.full((n, 4), 1e-3, np.float32))
+        ctx.forward(model, p, ps, [0], xd, pd, norm, out)
+        ctx.backward(model, p, d_out, grad)
+        torch.cuda.synchronize()
+        got.append((out.clone(), grad.clone()))
+    assert torch.isfinite(got[0][1]).all()
+    for out, grad in got[1:]:
+        assert torch.equal(out, got[0][0]) and torch.equal(grad, got[0][1])
